@@ -69,7 +69,12 @@ extern "C" {
 #define WWBI_FP64                 0  /* FP64 matrix and matvecs                          */
 #define WWBI_FP32_REFINED         1  /* FP32 matrix/matvec (FP32 accumulation) inside
                                         FP64 iterative refinement                      */
-#define WWBI_MATVEC_AUTO          0  /* stored matrix                                    */
+#define WWBI_MATVEC_AUTO          0  /* the fastest: above 1024 unknowns, from a cold
+                                        start and where the grid has nodes to spare,
+                                        a two-grid iteration (a coarse subset of the
+                                        nodes, corrections and true residuals on all of
+                                        them with on-the-fly FP64 products); otherwise,
+                                        or from where that stops, the stored matrix   */
 #define WWBI_MATVEC_STORED        1  /* assemble once, stream the matrix per matvec      */
 #define WWBI_MATVEC_ON_THE_FLY    2  /* recompute entries inside every matvec            */
 #define WWBI_FLAG_PROFILE         1  /* time every launch of the dominant matvec kernel  */
@@ -116,7 +121,8 @@ typedef struct {
     double tol;          /* stop when ||b - A x||_2 <= tol ||b||_2 (true FP64 residual)   */
     double inner_tol;    /* FP32_REFINED: relative tolerance of each inner FP32 solve     */
     int32_t restart;     /* GMRES restart length, 1..WWBI_MAX_RESTART                      */
-    int32_t max_iter;    /* budget of Arnoldi steps (all cycles, all refinement steps)     */
+    int32_t max_iter;    /* budget of Arnoldi steps (all cycles, all refinement steps);
+                            below 200 no two-grid iteration is tried                      */
     int32_t precision;   /* WWBI_FP64 or WWBI_FP32_REFINED                                 */
     int32_t matvec;      /* WWBI_MATVEC_*                                                  */
     int32_t poll_every;  /* Arnoldi steps between host checks for the end of a cycle      */
@@ -132,9 +138,10 @@ typedef struct {
 
 typedef struct {
     int32_t status;
-    int32_t iters;         /* Arnoldi steps taken (all cycles and refinement steps)       */
-    int32_t restarts;      /* restart cycles                                              */
-    int32_t refine_steps;  /* FP32_REFINED: inner solves                                  */
+    int32_t iters;         /* Arnoldi steps taken (all cycles, refinement steps and
+                              coarse solves)                                              */
+    int32_t restarts;      /* restart cycles and two-grid passes                          */
+    int32_t refine_steps;  /* FP32_REFINED: inner solves and two-grid passes              */
     double rel_resid;      /* final ||b - A x|| / ||b|| with the FP64 operator            */
     double ms_prep, ms_assemble, ms_solve, ms_U, ms_total;   /* HIP-event phase times     */
     int32_t n_matvec;      /* launches of the dominant matvec kernel (FLAG_PROFILE)       */
@@ -152,12 +159,13 @@ typedef struct {
                            /* ||b - A x|| / ||b|| in the order measured: at the start of
                               every restart cycle of an FP64 GMRES solve (the true
                               residual) and after every step of an iterative refinement
-                              (the FP64 residual; the largest over the systems of a
-                              multi-RHS solve); the first WWBI_HIST_MAX values          */
+                              or two-grid pass (the FP64 residual; the largest over the
+                              systems of a multi-RHS solve); the first WWBI_HIST_MAX
+                              values                                                    */
 } wwbi_report;
 
 /* Fill *o with defaults: tol 1e-13, inner_tol 1e-7, restart 100, max_iter 2000,
- * FP64, stored matvec, poll every 2 steps, max_refine 8, band 16, no flags. */
+ * FP64, automatic matvec, poll every 2 steps, max_refine 8, band 16, no flags. */
 void wwbi_default_opts(wwbi_opts *o);
 
 /* Human-readable name of a status code (static string). */

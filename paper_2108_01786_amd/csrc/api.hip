@@ -82,7 +82,7 @@ int Ctx::ws_plan(int n, int restart, WsItem *it, bool recycle) {
     D(eIl, capeIl, nn);
     D(cell, capcell, 4 * (nn / kCellNodes) + 4);
     I(nlist, capnlist, (size_t)kNearStride * (nn / kCellNodes));
-    D(val, capval, 4 * kMaxB + 8 + kValidateBlocks);
+    D(val, capval, 5 * kMaxB + 8 + kValidateBlocks);
     return k;
 }
 
@@ -143,6 +143,12 @@ void Ctx::release() {
     F(pw);
     cappw = 0;
     F(hsum);
+    F(xch);
+    capxch = 0;
+    F(cA); F(cmap); F(cfac); F(ce);
+    capcA = capcmap = capcfac = capce = 0;
+    if (hsmall) hipHostFree(hsmall);
+    hsmall = dsmall = nullptr;
     F(V);
     F(v32);
     F(Urec);
@@ -213,7 +219,13 @@ int Ctx::setup(const wwbi_geom *g, const double *phi, int nphi, bool check) {
     val_blocks = validate_data_blocks(phi ? nphi : 0);
     launch_validate(L, N, phi, phi ? nphi : 0, val, stream);   // also zeroes val[4 nb + 1]
     launch_near_cells(N, nlist, val + 4 * L.nb + 1, stream);
-    if (hipMemcpyAsync(hst, val, sizeof(double) * (4 * L.nb + 2 + val_blocks),
+    have_strips = want_coarse && L.n > kSmallMax && !fixed_ws && !profiling;
+    want_coarse = false;     // set anew by each call that can use it
+    if (have_strips)
+        launch_strip(L, N, reinterpret_cast<unsigned long long *>(val + 4 * L.nb + 2 + val_blocks),
+                     stream);
+    if (hipMemcpyAsync(hst, val,
+                       sizeof(double) * (4 * L.nb + 2 + val_blocks + (have_strips ? L.nb : 0)),
                        hipMemcpyDeviceToHost, stream) != hipSuccess)
         return WWBI_EHIP;
     if (hipEventRecord(pollev[2], stream) != hipSuccess) return WWBI_EHIP;
@@ -233,6 +245,8 @@ int Ctx::setup_check() {
     for (int k = 0; k < L.nb; ++k)
         if (h[4 * k + 3] != 0.0) return WWBI_EINVAL_RANGE;
     N.near = h[4 * L.nb + 1] > 0.0 ? 1 : 0;
+    for (int k = 0; have_strips && k < L.nb; ++k)
+        strip[k] = std::sqrt(h[4 * L.nb + 2 + val_blocks + k]);
     near_pairs = (long)h[4 * L.nb + 1];
     for (int k = 0; k < L.nb; ++k) {
         if (k <= 1 && !(h[4 * k + 2] > 0.0)) return WWBI_EINVAL_ORIENTATION;
@@ -250,7 +264,7 @@ void Ctx::apply(const Op &op, const double *x, const float *x32, const double *c
     const long ld = op.ld;
     switch (op.kind) {
     case OP_A_S64:
-        launch_gemv64((const double *)A, ld, op.n, x, c, y, active, stream);
+        launch_gemv64((const double *)A, ld, op.n, x, c, y, op.flip, active, stream);
         break;
     case OP_A_S32:
     case OP_GT_S32:
@@ -260,37 +274,41 @@ void Ctx::apply(const Op &op, const double *x, const float *x32, const double *c
             launch_to_f32(x, v32, op.n, stream);
             x32 = v32;
         }
-        launch_gemv32((const float *)A, ld, op.n, x32, c, y, active, stream);
+        launch_gemv32((const float *)A, ld, op.n, x32, c, y, op.flip, active, stream);
         break;
     case OP_A_O64:
-        launch_otf_matvec(L, N, op.flags, 0, op.band, 0, x, c, y, part, active, stream);
+        launch_otf_matvec(L, N, op.flags, 0, op.band, 0, x, c, y, part, active, stream,
+                          op.flip);
         break;
     case OP_A_O32:
-        launch_otf_matvec(L, N, op.flags, 1, op.band, 0, x, c, y, part, active, stream);
+        launch_otf_matvec(L, N, op.flags, 1, op.band, 0, x, c, y, part, active, stream,
+                          op.flip);
         break;
     case OP_AT_O64:
-        launch_otf_matvec(L, N, op.flags, 0, op.band, 1, x, c, y, part, active, stream);
+        launch_otf_matvec(L, N, op.flags, 0, op.band, 1, x, c, y, part, active, stream,
+                          op.flip);
         break;
     case OP_AT_O32:
-        launch_otf_matvec(L, N, op.flags, 1, op.band, 1, x, c, y, part, active, stream);
+        launch_otf_matvec(L, N, op.flags, 1, op.band, 1, x, c, y, part, active, stream,
+                          op.flip);
         break;
     case OP_W_S64:
-        launch_gemv64((const double *)A, ld, op.n, x, c, y, active, stream);
+        launch_gemv64((const double *)A, ld, op.n, x, c, y, op.flip, active, stream);
         break;
     case OP_W_O64: {
         const int o1 = L.off[1], nw = L.n - o1;
         launch_rflavour(L, N, hrow, 3, 0, o1, nw, o1, nw, x, part, active, stream);
         launch_reduce_partials(nw, part, rflavour_nsplit(N, nw, nw, 0), c, 1.0, y, active,
-                               stream);
+                               stream, op.flip);
         break;
     }
     case OP_GT_S64:
-        launch_gemv64((const double *)A, ld, op.n, x, c, y, active, stream);
+        launch_gemv64((const double *)A, ld, op.n, x, c, y, op.flip, active, stream);
         break;
     case OP_GT_O64:
         launch_rflavour(L, N, hrow, 8, 0, 0, L.n, 0, L.n, x, part, active, stream);
         launch_reduce_partials(L.n, part, rflavour_nsplit(N, L.n, L.n, 0), c, 1.0, y, active,
-                               stream);
+                               stream, op.flip);
         break;
     }
 }
@@ -342,6 +360,17 @@ void Ctx::prof_end() {
     }
 }
 
+// The sign of the surface rows.  A's identity part is -1/2 on the surface and
+// +1/2 on the walls (+1/2 and -1/2 in the gamma_t system), so its spectrum
+// clusters at two points and a Krylov method spends two steps where one
+// cluster takes one.  Every solve therefore runs on S A x = S b, S negating
+// the surface rows (Op::flip, applied where a product is summed; the
+// right-hand sides are written with it): one cluster, and since S is
+// orthogonal the same residual norms.  With a stored matrix FP64 takes 23 steps
+// instead of 32 on the M = 10240 cell (3.79 ms a solve, 5.1 before); on the
+// near-overturning M = 40960 cell refined FP32 takes 30 instead of 62 (34.9 ms,
+// 62 before).
+//
 // Restarted GMRES on op: x <- solution of op x = b.  x must hold the initial
 // guess unless x_zero.  With verify, every cycle starts from the true residual
 // b - op x and convergence is declared only on it.  Without verify a single
@@ -445,11 +474,11 @@ int Ctx::gmres(const Op &op, const double *b, double *x, bool x_zero, double tol
                 const bool fuse64 = !single_pass && stored_fp64(op.kind) && j < 64;
                 prof_begin();
                 if (fuse32)
-                    launch_gemv32_dots((const float *)A, op.ld, n, x32, w, &gs->active, Cb, ldv,
-                                       kc + j, pw, pw + 64L * NB, stream);
+                    launch_gemv32_dots((const float *)A, op.ld, n, x32, w, op.flip, &gs->active,
+                                       Cb, ldv, kc + j, pw, pw + 64L * NB, stream);
                 else if (fuse64)
-                    launch_gemv64_dots((const double *)A, op.ld, n, vj, w, &gs->active, Vb, ldv,
-                                       j, pw, pw + 64L * NB, stream);
+                    launch_gemv64_dots((const double *)A, op.ld, n, vj, w, op.flip, &gs->active,
+                                       Vb, ldv, j, pw, pw + 64L * NB, stream);
                 else
                     apply(op, vj, x32, nullptr, w, &gs->active);
                 prof_end();
@@ -508,6 +537,214 @@ int Ctx::gmres(const Op &op, const double *b, double *x, bool x_zero, double tol
     if (!x_set) launch_fill(x, 0.0, n, stream);   // stopped before the first update
     return status;
 }
+
+bool Ctx::ensure_small(int nsys) {
+    // the abort tag sits in front of the exchange words
+    if (grow(xch, capxch, (size_t)nsys * small_exchange_words() + 8) != WWBI_OK) return false;
+    if (hsmall) return true;
+    if (hipHostMalloc((void **)&hsmall, kMaxMulti * sizeof(SmallRes),
+                      hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) {
+        hsmall = nullptr;
+        (void)hipGetLastError();
+        return false;
+    }
+    if (hipHostGetDevicePointer((void **)&dsmall, hsmall, 0) != hipSuccess) {
+        (void)hipGetLastError();
+        hipHostFree(hsmall);
+        hsmall = nullptr;
+        return false;
+    }
+    return true;
+}
+
+// The first of `need` tags for one launch; the words are cleared when the
+// counter would wrap.
+bool Ctx::take_tags(long need, unsigned &first) {
+    if (need > 0x40000000L) return false;
+    if (xtag > 0xffffffffu - (unsigned)need) {
+        if (hipStreamSynchronize(stream) != hipSuccess || hipMemset(xch, 0, capxch * 8) != hipSuccess)
+            return false;
+        xtag = 1;
+    }
+    first = xtag;
+    xtag += (unsigned)need;
+    return true;
+}
+
+// The most accurate grid whose one-launch solve keeps 24 steps or more in a
+// cycle (kSmallFullCycle nodes: the solve then ends in one, at M = 10240 512
+// nodes and 0.62 ms a solve where 1024 in cycles of 17 took 0.82), else the
+// most accurate that fits at all.  A coarser grid costs passes, a finer one
+// steps of the coarse solve: each pass takes two products over all nodes.
+bool Ctx::choose_coarse(int k0, Coarse &C) const {
+    if (!have_strips) return false;
+    const int total = L.n - L.off[k0];
+    struct { double eps; int most; } const tries[] = {
+        {1e-15, kSmallFullCycle}, {1e-13, kSmallFullCycle}, {1e-11, kSmallFullCycle},
+        {1e-13, kSmallCoarseMax}, {1e-10, kSmallCoarseMax}, {1e-7, kSmallCoarseMax},
+        {1e-4, kSmallCoarseMax}};
+    for (const auto &t : tries) {
+        C.nb = L.nb - k0;
+        C.off[0] = 0;
+        for (int k = k0; k < L.nb; ++k) {
+            const int M = L.off[k + 1] - L.off[k];
+            const double need = strip[k] > 0.0 ? std::log(1.0 / t.eps) / strip[k] : HUGE_VAL;
+            int c = 1;       // the largest step that leaves an even grid of enough nodes
+            for (int i = M / 32; i > 1; --i)
+                if (M % i == 0 && (M / i) % 2 == 0 && (double)(M / i) >= need) { c = i; break; }
+            C.c[k - k0] = c;
+            C.first[k - k0] = L.off[k];
+            C.off[k - k0 + 1] = C.off[k - k0] + M / c;
+        }
+        C.n = C.off[C.nb];
+        if (C.n <= t.most && 2 * C.n <= total) return true;
+    }
+    return false;
+}
+
+constexpr double kTwoGridMargin = 0.2;
+
+int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, const wwbi_opts &o,
+                  bool check_rough, SolveStats &st) {
+    Coarse C;
+    // a budget too small for the coarse solves is left to GMRES, which counts
+    // steps of the whole system
+    if (o.max_iter < 200 || !choose_coarse(k0, C) || !ensure_small(1)) return kTwoGridNone;
+    const int n = op.n, r0 = L.off[k0], nc = C.n;
+    const long ldc = round_up(nc, 64);
+    if (grow(cA, capcA, (size_t)nc * ldc) || grow(cmap, capcmap, (size_t)nc) ||
+        grow(cfac, capcfac, (size_t)nc) || grow(ce, capce, (size_t)nc))
+        return kTwoGridNone;
+    const int corr = (o.flags & WWBI_FLAG_NO_CORRECTION) ? 0 : 1;
+    const double inv_d = mode == kCoarseGt || mode == kCoarseWall ? -2.0 : 2.0;
+    const int G = gmres_nblocks(n);
+    double *r = vec[VRR], *Pn = norm_partials();    // 128 doubles
+    const double *h = (const double *)hst;
+    launch_coarse_map(C, cmap, cfac, stream);
+    launch_assemble_coarse(N, hrow, mode, cmap, cfac, nc, corr, cA, ldc, stream);
+    double bn = -1.0, prev = HUGE_VAL;
+    const double *rr = b;
+    bool have_x = false;
+    if (check_rough) {
+        launch_roughness(b, n, part, stream);
+        if (hipMemcpyAsync(hst, part, 128 * sizeof(double), hipMemcpyDeviceToHost, stream) !=
+                hipSuccess ||
+            hipStreamSynchronize(stream) != hipSuccess)
+            return WWBI_EHIP;
+        double s2 = 0.0, d2 = 0.0;
+        for (int i = 0; i < 64; ++i) { s2 += h[i]; d2 += h[64 + i]; }
+        if (!std::isfinite(s2) || s2 == 0.0) return kTwoGridNone;
+        bn = std::sqrt(s2);
+        if (d2 > 0.05 * s2) {
+            // no coarse grid sees it: the identity part first
+            launch_scale_copy(n, b, inv_d, x, stream);
+            apply(op, x, nullptr, b, r, nullptr);
+            rr = r;
+            have_x = true;
+        }
+    }
+    int status = kTwoGridPart;
+    for (int pass = 0; pass < 6; ++pass) {
+        SmallArgs a{};
+        if (!take_tags(1024, a.tag)) break;
+        a.A = cA;
+        a.ld = ldc;
+        a.n = nc;
+        // the sign of the surface rows (the coarse nodes of boundary 0)
+        a.flip = op.flip > 0 ? C.off[1] : 0;
+        a.b = rr - r0;
+        a.map = cmap;
+        a.scale = mode == kCoarseAT ? cfac : nullptr;
+        a.x = ce;
+        // ||r|| against the target; the first pass aims past it once
+        a.tol = pass == 0 || bn < 0.0 || !(prev < HUGE_VAL)
+                    ? 0.03 * o.tol
+                    : std::min(0.1, 0.1 * o.tol * bn / prev);
+        a.tol = std::max(a.tol, 5e-16);
+        a.steps = 1024;
+        a.max_iter = 512;
+        // one cycle without its true residual, which the whole system's
+        // replaces; where the LDS holds only a short cycle, several with it
+        a.verify = nc > kSmallMax ? 1 : 0;
+        a.max_cycles = a.verify ? 16 : 1;
+        a.xch = xch + 8;
+        a.abort_tag = reinterpret_cast<unsigned *>(xch);
+        a.out = dsmall;
+        hsmall->status = kSmallAborted;
+        if (launch_small_gmres(a, 1, stream) != WWBI_OK) return WWBI_EHIP;
+        launch_coarse_correct(N, hrow, mode, cmap, cfac, nc, corr, ce, 0, r0, n, op.flip, inv_d, rr,
+                              0, x, 0, have_x, part, 1, stream);
+        const bool had_x = have_x;
+        have_x = true;
+        apply(op, x, nullptr, b, r, nullptr);
+        launch_norm_partial(r, n, Pn, G, stream);
+        if (bn < 0.0) launch_norm_partial(b, n, Pn + 64, G, stream);
+        if (hipMemcpyAsync(hst, Pn, sizeof(double) * 128, hipMemcpyDeviceToHost, stream) !=
+                hipSuccess ||
+            hipStreamSynchronize(stream) != hipSuccess || hipGetLastError() != hipSuccess)
+            return WWBI_EHIP;
+        if (hsmall->status == kSmallAborted) return had_x ? kTwoGridPart : kTwoGridNone;
+        double s2 = 0.0;
+        for (int i = 0; i < G; ++i) s2 += h[i];
+        const double rn = std::sqrt(s2);
+        if (bn < 0.0) {
+            double t2 = 0.0;
+            for (int i = 0; i < G; ++i) t2 += h[64 + i];
+            bn = std::sqrt(t2);
+        }
+        if (!std::isfinite(rn)) return kTwoGridNone;
+        st.iters += hsmall->its;
+        st.cycles += 1;
+        if (o.precision == WWBI_FP32_REFINED) st.refine_steps += 1;
+        else if (pass == 0) note_resid(1.0);
+        st.rel_resid = bn > 0 ? rn / bn : 0.0;
+        note_resid(st.rel_resid);
+        if (trace)
+            std::fprintf(stderr, "wwbi: two-grid mode %d n %d coarse %d pass %d its %d rel_resid %.3e\n",
+                         mode, n, nc, pass, hsmall->its, st.rel_resid);
+        // what a coarse grid leaves is smooth, but holds more of the modes that U
+        // amplifies than what an Arnoldi cycle leaves: aim below the tolerance
+        // while the passes gain (several decades each, but for the first of a
+        // rough right-hand side)
+        status = rn <= o.tol * bn ? WWBI_OK : kTwoGridPart;
+        if (rn <= std::max(kTwoGridMargin * o.tol, 4e-16) * bn && status == WWBI_OK) break;
+        if (pass > 0 && !(rn < 0.05 * prev)) break;
+        prev = rn;
+        rr = r;
+    }
+    return status;
+}
+
+template <class Assemble>
+int Ctx::solve_system(int mode, Op op, int k0, const int (&kinds)[4], const double *b, double *x,
+                      bool x_zero, const wwbi_opts &o, bool check_rough, bool &assembled,
+                      Assemble assemble, SolveStats &st, double &bytes) {
+    const bool stored = o.matvec != WWBI_MATVEC_ON_THE_FLY;
+    const bool fp32 = o.precision == WWBI_FP32_REFINED && (stored || kinds[3] >= 0);
+    Op op64 = op, in = op;
+    op64.kind = kinds[2];
+    in.kind = stored ? (fp32 ? kinds[1] : kinds[0]) : (fp32 ? kinds[3] : kinds[2]);
+    bytes = op_bytes(in);
+    if (o.matvec == WWBI_MATVEC_AUTO && x_zero && have_strips && op.n > kSmallMax) {
+        const int s = two_grid(mode, op64, k0, b, x, o, check_rough, st);
+        if (s == WWBI_OK || s < 0) return s;
+        if (s == kTwoGridPart) x_zero = false;
+    }
+    if (stored && !assembled) {
+        const int rc = assemble(fp32);
+        if (rc) return rc;
+        assembled = true;
+    }
+    if (fp32) return refine(in, op64, b, x, x_zero, o, st);
+    return gmres(in, b, x, x_zero, o.tol, o.restart, o.max_iter, o.poll_every, true, st);
+}
+
+// Operator kinds of a system: stored FP64, stored FP32, on the fly in FP64 and
+// (or -1) in FP32.
+constexpr int kKindsA[4] = {OP_A_S64, OP_A_S32, OP_A_O64, OP_A_O32};
+constexpr int kKindsAT[4] = {OP_A_S64, OP_A_S32, OP_AT_O64, OP_AT_O32};   // A^T is stored itself
+constexpr int kKindsW[4] = {OP_W_S64, OP_W_S32, OP_W_O64, -1};
+constexpr int kKindsGt[4] = {OP_GT_S64, OP_GT_S32, OP_GT_O64, -1};
 
 // Tolerance of an inner FP32 solve: o.inner_tol (the contraction the FP32
 // operator supports: FP32 entries and vector, FP64 accumulation), loosened
@@ -757,14 +994,16 @@ void Ctx::apply_multi(int kind, int n, long ld, const double *X, const float *X3
                       const double *c, double *Y) {
     const long ldv = round_up(n, 64);
     if (kind == OP_A_S64) {
-        launch_mfma_multi64((const double *)A, ld, n, X, xs, nr, c, ldv, Y, ldv, mw.part, stream);
+        launch_mfma_multi64((const double *)A, ld, n, X, xs, nr, c, ldv, Y, ldv, mw.part,
+                            L.off[1], stream);
     } else {
         if (!X32) {
             launch_to_f32_batched(X, xs, mw.x32, ldv, n, nr, stream);
             X32 = mw.x32;
             xs = ldv;
         }
-        launch_mfma_multi32((const float *)A, ld, n, X32, xs, nr, c, ldv, Y, ldv, mw.part, stream);
+        launch_mfma_multi32((const float *)A, ld, n, X32, xs, nr, c, ldv, Y, ldv, mw.part,
+                            L.off[1], stream);
     }
 }
 
@@ -843,7 +1082,8 @@ int Ctx::gmres_multi(int kind, int n, long ld, const double *B, double *X, int n
                         : launch_mfma_parts32((const float *)A, ld, n, x32, ldv, nr, m.part,
                                               stream);
                 prof_end();
-                launch_cgs_dot(m.V, ldv, m.w, n, j, P1, P3, G, m.gs, stream, bt, m.part, ks, nr);
+                launch_cgs_dot(m.V, ldv, m.w, n, j, P1, P3, G, m.gs, stream, bt, m.part, ks, nr,
+                               L.off[1]);
                 if (x32) {
                     // FP32 inner solves: one Gram-Schmidt pass, as for one system
                     launch_cgs_final(m.V, ldv, m.w, n, j, P1, P3, G, x32, m.H, ldp, false, m.cs,
@@ -931,11 +1171,12 @@ int Ctx::refine_multi(int n, long ld, const double *B, double *X, int nr, const 
             rn = bnrm;
         } else {
             if (stored64)
-                launch_mfma_multi64(A64, ld, n, X, ldv, nr, B, ldv, m.rr, ldv, m.part, stream);
+                launch_mfma_multi64(A64, ld, n, X, ldv, nr, B, ldv, m.rr, ldv, m.part, L.off[1],
+                                    stream);
             else
                 for (int s = 0; s < nr; ++s)
                     launch_otf_matvec(L, N, o.flags, 0, o.band, 0, X + s * ldv, B + s * ldv,
-                                      m.rr + s * ldv, part, nullptr, stream);
+                                      m.rr + s * ldv, part, nullptr, stream, L.off[1]);
             rc = norms(m.rr, rn);
             if (rc) return rc;
         }
@@ -1108,13 +1349,15 @@ int solve_phi_impl(Ctx *c, const wwbi_geom *g, const double *phi, const wwbi_opt
     if (!rc) {
         c->restart_cap = std::max(c->restart_cap, o->restart);
         c->begin_report((o->flags & WWBI_FLAG_PROFILE) != 0);
+        c->want_coarse = o->matvec == WWBI_MATVEC_AUTO && !o->x0 &&
+                         !(o->flags & WWBI_FLAG_NO_CORRECTION);
         rc = c->setup(g, phi, g ? g->M[0] : 0, false);
     }
     if (rc) {
         if (rep) { std::memset(rep, 0, sizeof(*rep)); rep->status = rc; }
         return rc;
     }
-    const int n = c->L.n;
+    const int n = c->L.n, n0 = c->L.off[1];
     const long ld = round_up(n, 64);
     double *b = c->vec[VB], *x = c->vec[VX];
     // the right-hand side, circulant rows and matrix go into internal buffers
@@ -1124,14 +1367,20 @@ int solve_phi_impl(Ctx *c, const wwbi_geom *g, const double *phi, const wwbi_opt
     launch_circulant_rows(c->L, WWBI_OP_H, c->rowH, c->stream);
     hipEventRecord(c->ev[1], c->stream);
     const bool stored = o->matvec != WWBI_MATVEC_ON_THE_FLY;
-    const bool fp32 = o->precision == WWBI_FP32_REFINED;
-    if (stored) {
-        rc = c->ensure_matrix((size_t)n * ld * (fp32 ? 4 : 8));
-        if (rc) { c->finish_report(rep, rc, st, 0); return rc; }
-        if (fp32)
+    auto assemble = [&](bool f32) -> int {
+        const int e = c->ensure_matrix((size_t)n * ld * (f32 ? 4 : 8));
+        if (e) return e;
+        if (f32)
             launch_assemble32(c->L, c->N, o->flags, o->band, (float *)c->A, ld, c->stream);
         else
             launch_assemble64(c->L, c->N, o->flags, (double *)c->A, ld, c->stream);
+        return WWBI_OK;
+    };
+    c->a_ready = false;
+    if (stored && !c->have_strips) {
+        rc = assemble(o->precision == WWBI_FP32_REFINED);
+        if (rc) { c->finish_report(rep, rc, st, 0); return rc; }
+        c->a_ready = true;
     }
     hipEventRecord(c->ev[2], c->stream);
     rc = c->setup_check();
@@ -1141,18 +1390,10 @@ int solve_phi_impl(Ctx *c, const wwbi_geom *g, const double *phi, const wwbi_opt
     }
     const bool xz = o->x0 == nullptr;
     if (!xz) launch_copy(x, o->x0, n, c->stream);
-    Op op64{stored ? OP_A_S64 : OP_A_O64, n, ld, o->flags, o->band};
-    int status;
-    double bytes;
-    if (!fp32) {
-        status = c->gmres(op64, b, x, xz, o->tol, o->restart, o->max_iter, o->poll_every, true, st);
-        bytes = c->op_bytes(op64);
-    } else {
-        Op op32{stored ? OP_A_S32 : OP_A_O32, n, ld, o->flags, o->band};
-        Op opres{OP_A_O64, n, ld, o->flags, o->band};
-        status = c->refine(op32, opres, b, x, xz, *o, st);
-        bytes = c->op_bytes(op32);
-    }
+    const Op op{OP_A_O64, n, ld, o->flags, o->band, n0};
+    double bytes = 0.0;
+    int status = c->solve_system(kCoarseA, op, 0, kKindsA, b, x, xz, *o, false, c->a_ready,
+                                 assemble, st, bytes);
     hipEventRecord(c->ev[3], c->stream);
     if (status < 0) { c->finish_report(rep, status, st, bytes); return status; }
     double *gam = c->vec[VG];
@@ -1220,6 +1461,7 @@ int wwbi_solve_gamma(wwbi_ctx *ctx, const wwbi_geom *g, const double *gamma0, co
     if (!rc) {
         c->restart_cap = std::max(c->restart_cap, o->restart);
         c->begin_report((o->flags & WWBI_FLAG_PROFILE) != 0);
+        c->want_coarse = o->matvec == WWBI_MATVEC_AUTO && !o->x0;
         rc = c->setup(g, gamma0, g ? g->M[0] : 0);
     }
     if (rc) {
@@ -1238,36 +1480,31 @@ int wwbi_solve_gamma(wwbi_ctx *ctx, const wwbi_geom *g, const double *gamma0, co
     // the wall operator: GMRES in FP64 (stored or on the fly), or (stored,
     // FP32_REFINED) FP32 products inside FP64 refinement with on-the-fly FP64
     // residuals
-    const bool stored = o->matvec != WWBI_MATVEC_ON_THE_FLY;
-    const bool refined = stored && o->precision == WWBI_FP32_REFINED;
-    if (stored) {
-        rc = c->ensure_matrix((size_t)nw * ldw * (refined ? 4 : 8));
-        if (rc) { c->finish_report(rep, rc, st, 0); return rc; }
-        if (refined)
+    auto assemble = [&](bool f32) -> int {
+        const int e = c->ensure_matrix((size_t)nw * ldw * (f32 ? 4 : 8));
+        if (e) return e;
+        if (f32)
             launch_assemble_wall32(c->L, c->N, c->hrow, (float *)c->A, ldw, c->stream);
         else
             launch_assemble_wall64(c->L, c->N, c->hrow, (double *)c->A, ldw, c->stream);
-    }
+        return WWBI_OK;
+    };
     hipEventRecord(c->ev[2], c->stream);
     double *gw = gam + n0;
     const bool xz = o->x0 == nullptr;
     if (!xz) launch_copy(gw, o->x0, nw, c->stream);
-    Op op{refined ? OP_W_S32 : (stored ? OP_W_S64 : OP_W_O64), nw, ldw, o->flags, o->band};
-    int status;
-    if (refined) {
-        const Op op64{OP_W_O64, nw, ldw, o->flags, o->band};
-        status = c->refine(op, op64, rhs, gw, xz, *o, st);
-    } else {
-        status = c->gmres(op, rhs, gw, xz, o->tol, o->restart, o->max_iter, o->poll_every,
-                          true, st);
-    }
+    const Op op{OP_W_O64, nw, ldw, o->flags, o->band, 0};
+    bool assembled = false;
+    double bytes = 0.0;
+    const int status = c->solve_system(kCoarseWall, op, 1, kKindsW, rhs, gw, xz, *o, false,
+                                       assembled, assemble, st, bytes);
     hipEventRecord(c->ev[3], c->stream);
-    if (status < 0) { c->finish_report(rep, status, st, c->op_bytes(op)); return status; }
+    if (status < 0) { c->finish_report(rep, status, st, bytes); return status; }
     launch_copy(gam, gamma0, n0, c->stream);
     c->eval_U_from_gamma(gam, U);
     if (gamma_wall) launch_copy(gamma_wall, gw, nw, c->stream);
     hipEventRecord(c->ev[4], c->stream);
-    c->finish_report(rep, status, st, c->op_bytes(op));
+    c->finish_report(rep, status, st, bytes);
     if (hipGetLastError() != hipSuccess) return WWBI_EHIP;
     return status;
 }
@@ -1392,36 +1629,33 @@ int wwbi_solve_gamma_t(wwbi_ctx *ctx, const wwbi_geom *g, const double *phi, con
         launch_rflavour(L, c->N, c->hrow, 7, 0, n0, nw, 0, n0, fV, c->part, nullptr, sm);
         launch_reduce_partials(nw, c->part, nsw, e + n0, 1.0, e + n0, nullptr, sm);
     }
-    launch_circulant_apply(L, c->rowD, e, b, 1.0, 0.0, 0, L.nb - 1, sm);
+    // D e, the surface rows negated as the solve takes them
+    launch_circulant_apply2(L, c->rowD, e, b, -1.0, 1.0, 0.0, 0, L.nb - 1, sm);
     hipEventRecord(c->ev[1], sm);
     // 3. the gamma_t operator, stored or on the fly: GMRES in FP64, or (stored,
     // FP32_REFINED) FP32 products inside FP64 refinement with on-the-fly
     // FP64 residuals
-    const bool stored = o->matvec != WWBI_MATVEC_ON_THE_FLY;
-    const bool refined = stored && o->precision == WWBI_FP32_REFINED;
-    if (stored) {
-        rc = c->ensure_matrix((size_t)n * ld * (refined ? 4 : 8));
-        if (rc) { c->finish_report(rep, rc, st, 0); return rc; }
-        if (refined)
+    auto assemble = [&](bool f32) -> int {
+        const int e2 = c->ensure_matrix((size_t)n * ld * (f32 ? 4 : 8));
+        if (e2) return e2;
+        if (f32)
             launch_assemble_gt32(L, c->N, (float *)c->A, ld, sm);
         else
             launch_assemble_gt64(L, c->N, (double *)c->A, ld, sm);
-    }
+        return WWBI_OK;
+    };
     hipEventRecord(c->ev[2], sm);
-    Op op{refined ? OP_GT_S32 : (stored ? OP_GT_S64 : OP_GT_O64), n, ld, o->flags, o->band};
-    int status;
-    if (refined) {
-        const Op op64{OP_GT_O64, n, ld, o->flags, o->band};
-        status = c->refine(op, op64, b, x, true, *o, st);
-    } else {
-        status = c->gmres(op, b, x, true, o->tol, o->restart, o->max_iter, o->poll_every, true, st);
-    }
+    const Op op{OP_GT_O64, n, ld, o->flags, o->band, n0};
+    bool assembled = false;
+    double bytes = 0.0;
+    const int status = c->solve_system(kCoarseGt, op, 0, kKindsGt, b, x, true, *o, false,
+                                       assembled, assemble, st, bytes);
     hipEventRecord(c->ev[3], sm);
-    if (status < 0) { c->finish_report(rep, status, st, c->op_bytes(op)); return status; }
+    if (status < 0) { c->finish_report(rep, status, st, bytes); return status; }
     launch_copy(gamma_t, x, n, sm);
     if (U) launch_copy(U, u0, n0, sm);
     hipEventRecord(c->ev[4], sm);
-    c->finish_report(rep, status, st, c->op_bytes(op));
+    c->finish_report(rep, status, st, bytes);
     if (hipGetLastError() != hipSuccess) return WWBI_EHIP;
     return status != WWBI_OK ? status : s1;
 }
@@ -1760,18 +1994,19 @@ int wwbi_pressure(wwbi_ctx *ctx, const wwbi_geom *g, const double *phi, double t
     launch_fill(b, 0.0, n, sm);
     launch_pressure_data(n0, c->N, sds, sdn, tau, grav, b, sm);
     // 3. A omega_aux = b with the matrix of step 1
-    const bool stored = o->matvec != WWBI_MATVEC_ON_THE_FLY;
-    const bool fp32 = o->precision == WWBI_FP32_REFINED;
-    Op op64{stored ? OP_A_S64 : OP_A_O64, n, ld, o->flags, o->band};
-    int status;
-    if (!fp32) {
-        status = c->gmres(op64, b, x, true, o->tol, o->restart, o->max_iter, o->poll_every,
-                          true, st);
-    } else {
-        Op op32{stored ? OP_A_S32 : OP_A_O32, n, ld, o->flags, o->band};
-        Op opres{OP_A_O64, n, ld, o->flags, o->band};
-        status = c->refine(op32, opres, b, x, true, *o, st);
-    }
+    auto assemble = [&](bool f32) -> int {
+        const int e = c->ensure_matrix((size_t)n * ld * (f32 ? 4 : 8));
+        if (e) return e;
+        if (f32)
+            launch_assemble32(L, c->N, o->flags, o->band, (float *)c->A, ld, sm);
+        else
+            launch_assemble64(L, c->N, o->flags, (double *)c->A, ld, sm);
+        return WWBI_OK;
+    };
+    const Op op{OP_A_O64, n, ld, o->flags, o->band, n0};
+    double bytes = 0.0;
+    const int status = c->solve_system(kCoarseA, op, 0, kKindsA, b, x, true, *o, false, c->a_ready,
+                                       assemble, st, bytes);
     if (status < 0) {
         if (rep) { *rep = r1; rep->status = status; }
         return status;
@@ -1825,6 +2060,8 @@ int wwbi_adjoint_phi(wwbi_ctx *ctx, const wwbi_geom *g, const double *omega, con
     if (!rc) {
         c->restart_cap = std::max(c->restart_cap, o->restart);
         c->begin_report((o->flags & WWBI_FLAG_PROFILE) != 0);
+        c->want_coarse = o->matvec == WWBI_MATVEC_AUTO && !o->x0 &&
+                         !(o->flags & WWBI_FLAG_NO_CORRECTION);
         rc = c->setup(g, dJdU, g ? g->M[0] : 0, false);
     }
     const int n = rc ? 0 : c->L.n, n0 = rc ? 0 : c->L.off[1];
@@ -1847,15 +2084,20 @@ int wwbi_adjoint_phi(wwbi_ctx *ctx, const wwbi_geom *g, const double *omega, con
     // so that its products stream rows (the forward matvec, about 6% faster at
     // large n than the column-split transpose product).  The matrix goes into
     // internal memory only, so it is queued before the input checks are read.
-    const bool stored = o->matvec != WWBI_MATVEC_ON_THE_FLY;
-    const bool fp32 = o->precision == WWBI_FP32_REFINED;
-    if (stored) {
-        rc = c->ensure_matrix((size_t)n * ld * (fp32 ? 4 : 8));
-        if (rc) { c->finish_report(rep, rc, st, 0); return rc; }
-        if (fp32)
+    auto assemble = [&](bool f32) -> int {
+        const int e = c->ensure_matrix((size_t)n * ld * (f32 ? 4 : 8));
+        if (e) return e;
+        if (f32)
             launch_assemble32_T(c->L, c->N, o->flags, o->band, (float *)c->A, ld, sm);
         else
             launch_assemble64_T(c->L, c->N, o->flags, (double *)c->A, ld, sm);
+        return WWBI_OK;
+    };
+    bool assembled = false;
+    if (o->matvec != WWBI_MATVEC_ON_THE_FLY && !c->have_strips) {
+        rc = assemble(o->precision == WWBI_FP32_REFINED);
+        if (rc) { c->finish_report(rep, rc, st, 0); return rc; }
+        assembled = true;
     }
     hipEventRecord(c->ev[2], sm);
     rc = c->setup_check();
@@ -1872,23 +2114,14 @@ int wwbi_adjoint_phi(wwbi_ctx *ctx, const wwbi_geom *g, const double *omega, con
     launch_reduce_partials(n, c->part, rflavour_nsplit(c->N, n0, n, 1), nullptr, 1.0, gbar,
                            nullptr, sm);
     launch_circulant_apply(c->L, c->rowH, cv, gbar, -0.5, 1.0, 0, 0, sm);
-    launch_circulant_apply2(c->L, c->rowD, gbar, mu, 1.0, -1.0, 0.0, 0, c->L.nb - 1, sm);
-    int status;
-    double bytes;
+    // (its surface rows negated, as the solve takes them)
+    launch_circulant_apply(c->L, c->rowD, gbar, mu, -1.0, 0.0, 0, c->L.nb - 1, sm);
     const bool xz = o->x0 == nullptr;
     if (!xz) launch_copy(lam, o->x0, n, sm);
-    if (!fp32) {
-        // the stored operator is A^T itself: the forward product applies it
-        Op op{stored ? OP_A_S64 : OP_AT_O64, n, ld, o->flags, o->band};
-        status = c->gmres(op, mu, lam, xz, o->tol, o->restart, o->max_iter, o->poll_every,
-                          true, st);
-        bytes = c->op_bytes(op);
-    } else {
-        Op op32{stored ? OP_A_S32 : OP_AT_O32, n, ld, o->flags, o->band};
-        Op op64{OP_AT_O64, n, ld, o->flags, o->band};
-        status = c->refine(op32, op64, mu, lam, xz, *o, st);
-        bytes = c->op_bytes(op32);
-    }
+    const Op op{OP_AT_O64, n, ld, o->flags, o->band, n0};
+    double bytes = 0.0;
+    const int status = c->solve_system(kCoarseAT, op, 0, kKindsAT, mu, lam, xz, *o, true, assembled,
+                                       assemble, st, bytes);
     hipEventRecord(c->ev[3], sm);
     if (status < 0) { c->finish_report(rep, status, st, bytes); return status; }
     // derivative contractions and the final combination
@@ -2051,7 +2284,7 @@ int wwbi_solve_phi_multi(wwbi_ctx *ctx, const wwbi_geom *g, const double *rhs, i
     const int n = c->L.n;
     const long ld = round_up(n, 64), ldv = ld;
     const bool fp32 = o->precision == WWBI_FP32_REFINED;
-    launch_copy_strided(rhs, n, c->mw.b, ldv, n, nr, sm);
+    launch_copy_strided(rhs, n, c->mw.b, ldv, n, nr, sm, c->L.off[1]);
     hipEventRecord(c->ev[1], sm);
     rc = c->ensure_matrix((size_t)n * ld * (fp32 ? 4 : 8));
     if (rc) { c->finish_report(rep, rc, st, 0); return rc; }
@@ -2228,7 +2461,7 @@ int wwbi_matvec(wwbi_ctx *ctx, const wwbi_geom *g, const double *x, double *y, i
         kind = fp32 ? OP_A_S32 : OP_A_S64;
     else
         kind = transpose ? (fp32 ? OP_AT_O32 : OP_AT_O64) : (fp32 ? OP_A_O32 : OP_A_O64);
-    Op op{kind, n, ld, 0, band};
+    Op op{kind, n, ld, 0, band, 0};
     c->prof_begin();
     c->apply(op, xw, nullptr, nullptr, yw, nullptr);
     c->prof_end();

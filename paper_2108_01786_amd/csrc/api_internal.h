@@ -44,6 +44,7 @@ struct Op {
     long ld;        // leading dimension of the stored matrix
     int flags;
     int band;
+    int flip;       // rows [0, flip) of the operator are negated (Ctx::gmres)
 };
 
 struct SolveStats {
@@ -63,6 +64,7 @@ constexpr int kStateSlotBytes = 8192;    // bytes per slot (up to kMaxMulti stat
 constexpr int kTailOffset = 24576;       // byte offset of the Fourier-tail energies in hst
 constexpr int kHostStaging = 32768;      // pinned host staging bytes
 constexpr int kMaxMulti = 32;            // right-hand sides per multi solve
+constexpr int kTwoGridPart = 100, kTwoGridNone = 101;   // Ctx::two_grid
 
 double inner_tolerance(const wwbi_opts &o, double bnorm, double rnorm);
 
@@ -119,6 +121,21 @@ struct Ctx {
     double *part = nullptr; size_t cappart = 0;
     double *pw = nullptr;   size_t cappw = 0;     // partials of the fused Arnoldi product
     double *hsum = nullptr; size_t caphsum = 0;   // their row sums
+    // one-launch solves of small systems: exchange words and the abort tag
+    // (device), results (host-mapped), and the next launch's first tag
+    unsigned long long *xch = nullptr; size_t capxch = 0;
+    SmallRes *hsmall = nullptr, *dsmall = nullptr;
+    unsigned xtag = 1;
+    // two-grid iteration: the coarse matrix, the coarse nodes' fine indices and
+    // weight factors, and the coarse solution
+    double *cA = nullptr;   size_t capcA = 0;
+    int *cmap = nullptr;    size_t capcmap = 0;
+    double *cfac = nullptr; size_t capcfac = 0;
+    double *ce = nullptr;   size_t capce = 0;
+    bool want_coarse = false;   // setup() measures the strips for choose_coarse()
+    bool have_strips = false;
+    bool a_ready = false;       // A holds the matrix of the last potential solve
+    double strip[kMaxB] = {};   // strip half-width of each boundary's nodes
     int *bid = nullptr;     size_t capbid = 0;
     int *loc = nullptr;     size_t caploc = 0;
     int *Mk = nullptr;      size_t capMk = 0;
@@ -211,6 +228,25 @@ struct Ctx {
     // cycle, no verification, x = the solution from zero)
     int gmres(const Op &op, const double *b, double *x, bool x_zero, double tol, int restart,
               int max_iter, int poll, bool verify, SolveStats &st, int kc = 0);
+    // words and results for nsys one-launch solves; false when out of memory
+    bool ensure_small(int nsys);
+    bool take_tags(long need, unsigned &first);
+    // Coarse grid for boundaries k0.. of the current geometry, resolving its
+    // strips to the best of a few accuracies that fits; false when none does or the grid is no coarser than half the nodes
+    bool choose_coarse(int k0, Coarse &C) const;
+    // Two-grid iteration (kernels_coarse.hip) for the operator of `mode`, op
+    // its on-the-fly FP64 form, from a zero start: kTwoGridNone when it does
+    // not apply (x untouched), kTwoGridPart when x holds an unconverged
+    // iterate, WWBI_OK when ||b - op x|| <= tol ||b||, or an error (< 0)
+    int two_grid(int mode, const Op &op, int k0, const double *b, double *x, const wwbi_opts &o,
+                 bool check_rough, SolveStats &st);
+    // Solve one second-kind system: two-grid, then (or instead) GMRES or
+    // refinement on the stored matrix, which `assemble(fp32)` forms when
+    // `assembled` is not yet set
+    template <class Assemble>
+    int solve_system(int mode, Op op, int k0, const int (&kinds)[4], const double *b, double *x,
+                     bool x_zero, const wwbi_opts &o, bool check_rough, bool &assembled,
+                     Assemble assemble, SolveStats &st, double &bytes);
     double device_norm(const double *v, int n);
     int refine(const Op &op32, const Op &op64, const double *b, double *x, bool x_zero,
                const wwbi_opts &o, SolveStats &st);

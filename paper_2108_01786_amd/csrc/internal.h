@@ -288,27 +288,28 @@ void launch_assemble_wall32(const Layout &L, const Nodes &N, const double *hrow,
 // the normal-velocity map T (surface rows, all columns), FP64
 void launch_assemble_T64(const Layout &L, const Nodes &N, const double *hrow, double *T, long ld,
                          hipStream_t st);
-// y = c - A x, or y = A x when c is null, accumulated in FP64 for either
-// matrix type (FP32 entries and x widened one by one)
+// y = c - S A x, or y = S A x when c is null, S negating rows [0, flip);
+// accumulated in FP64 for either matrix type (FP32 entries and x widened one
+// by one)
 void launch_gemv64(const double *A, long ld, int n, const double *x, const double *c, double *y,
-                   const int *active, hipStream_t st);
+                   int flip, const int *active, hipStream_t st);
 void launch_gemv32(const float *A, long ld, int n, const float *x, const double *c, double *y,
-                   const int *active, hipStream_t st);
+                   int flip, const int *active, hipStream_t st);
 // Number of per-block partials of the fused Arnoldi product below.
 int gemv_partials(int n);
-// y = A x (FP32 matrix and x, FP64 accumulation) fused with the first
+// y = S A x (FP32 matrix and x, FP64 accumulation) fused with the first
 // Gram-Schmidt dots: P[i * gemv_partials(n) + b] (i <= j < 64) and the squared
 // norm partials P3[b] of y, per block b, summed later in a fixed order.
 void launch_gemv32_dots(const float *A, long ld, int n, const float *x, double *y,
-                        const int *active, const double *V, long ldv, int j, double *P,
+                        int flip, const int *active, const double *V, long ldv, int j, double *P,
                         double *P3, hipStream_t st);
 // the same for an FP64 matrix
 void launch_gemv64_dots(const double *A, long ld, int n, const double *x, double *y,
-                        const int *active, const double *V, long ldv, int j, double *P,
+                        int flip, const int *active, const double *V, long ldv, int j, double *P,
                         double *P3, hipStream_t st);
 void launch_otf_matvec(const Layout &L, const Nodes &N, int flags, int fp32, int band,
                        int transpose, const double *x, const double *c, double *y, double *part,
-                       const int *active, hipStream_t st);
+                       const int *active, hipStream_t st, int flip = 0);
 // target-flavour products over rows [r0, r0+nr) and columns [c0, c0+nc):
 // mode 2 = T (normal-velocity map / G^dagger), mode 3 = wall operator T - I/2,
 // mode 4 = stream-function map P (surface rows), mode 5 = tangential map Q.
@@ -321,7 +322,7 @@ void launch_rflavour(const Layout &L, const Nodes &N, const double *hrow, int mo
 // (forward) or nc (transposed)
 int rflavour_nsplit(const Nodes &N, int nr, int nc, int transpose);
 void launch_reduce_partials(int n, const double *part, int nsplit, const double *c, double scale,
-                            double *y, const int *active, hipStream_t st);
+                            double *y, const int *active, hipStream_t st, int flip = 0);
 int otf_chunk(int n);
 int otf_nsplit(int n);
 
@@ -354,18 +355,87 @@ void launch_adj_finalize(const Nodes &N, const Flow &F, int n0, const double *Ub
                          int nsc, double *g_phi, double *g_x, double *g_y, double *g_dx,
                          double *g_dy, double *g_ddx, double *g_ddy, hipStream_t st);
 
+// ---- kernels_small.hip -------------------------------------------------------
+// Restarted GMRES of a small system in one launch: whole systems of up to
+// kSmallMax unknowns, whose basis the LDS holds for 17 steps or more, and
+// coarse systems of up to kSmallCoarseMax, in shorter cycles.
+constexpr int kSmallMax = 1024;
+constexpr int kSmallCoarseMax = 2048;
+constexpr int kSmallFullCycle = 640;   // the basis of 27 steps fits
+constexpr int kSmallAborted = -100;    // the blocks did not run together: solve otherwise
+struct SmallRes {
+    int status;            // WWBI_OK, WWBI_NOT_CONVERGED, WWBI_STAGNATED or kSmallAborted
+    int its, cycles;       // Arnoldi steps and cycles
+    int nhist;
+    double bnorm, resid;   // ||b|| and the last residual norm (an estimate without verify)
+    double hist[WWBI_HIST_MAX];   // true residual over ||b|| at every cycle start
+};
+struct SmallArgs {
+    const double *A;       // n x n, row-major, leading dimension ld
+    long ld;
+    int n, flip;           // rows [0, flip) are negated
+    const double *b;       // right-hand side: b[map[i]] * scale[i] (either may be null)
+    long bs;               // stride between systems
+    const int *map;
+    const double *scale;
+    double *x;             // solution
+    const double *x0;      // start, or null for zero
+    long xs;               // stride of both between systems
+    double tol;
+    int steps;             // Arnoldi steps per cycle (cut to what the LDS holds)
+    int max_iter, max_cycles;
+    int verify;            // 0: one cycle, no true residual
+    unsigned long long *xch;   // small_exchange_words() per system, zero at first
+    long xchs;
+    unsigned tag;          // first tag of this launch (each exchange takes the next)
+    unsigned *abort_tag;   // tag of the last launch that gave up
+    SmallRes *out;         // one per system
+};
+long small_exchange_words();
+// nsys systems with the same matrix; WWBI_OK when queued
+int launch_small_gmres(SmallArgs a, int nsys, hipStream_t st);
+
+// ---- kernels_coarse.hip ------------------------------------------------------
+// A coarse subset of the nodes: every c[k]-th node of boundary k from node
+// first[k] on, at off[k] .. off[k+1] of the coarse vectors.
+struct Coarse {
+    int nb, n;
+    int off[kMaxB + 1];
+    int first[kMaxB];
+    int c[kMaxB];
+};
+enum { kCoarseA = 0, kCoarseAT, kCoarseGt, kCoarseWall };
+// out[k]: bits of the squared strip half-width of boundary k (see k_strip)
+void launch_strip(const Layout &L, const Nodes &N, unsigned long long *out, hipStream_t st);
+void launch_coarse_map(const Coarse &C, int *map, double *fac, hipStream_t st);
+void launch_assemble_coarse(const Nodes &N, const double *hrow, int mode, const int *map,
+                            const double *fac, int n, int corr, double *out, long ld,
+                            hipStream_t st);
+// x (+)= (r - S K_hH e) / d on nodes r0 .. r0 + nr for nsys systems (strides
+// es, rs, xs); part: nsys * coarse_slices(nr, n) * nr doubles
+int coarse_slices(int nr, int n);
+void launch_coarse_correct(const Nodes &N, const double *hrow, int mode, const int *map,
+                           const double *fac, int n, int corr, const double *e, long es, int r0,
+                           int nr, int flip, double inv_d, const double *r, long rs, double *x,
+                           long xs, bool add, double *part, int nsys, hipStream_t st);
+void launch_scale_copy(int n, const double *b, double a, double *x, hipStream_t st);
+// out[0..63] and out[64..127]: partial sums of b^2 and of its squared differences
+void launch_roughness(const double *b, int n, double *out, hipStream_t st);
+
 // ---- kernels_multi.hip -------------------------------------------------------
-// Y_s = c_s - A X_s (or A X_s when c is null) for s < nr on the matrix cores.
+// Y_s = c_s - S A X_s (or S A X_s when c is null), S negating rows [0, flip),
+// for s < nr on the matrix cores.
 void launch_mfma_multi64(const double *A, long ld, int n, const double *X, long xs, int nr,
-                         const double *c, long cs, double *y, long ys, double *part,
+                         const double *c, long cs, double *y, long ys, double *part, int flip,
                          hipStream_t st);
 void launch_mfma_multi32(const float *A, long ld, int n, const float *X, long xs, int nr,
-                         const double *c, long cs, double *y, long ys, double *part,
+                         const double *c, long cs, double *y, long ys, double *part, int flip,
                          hipStream_t st);
 void launch_to_f32_batched(const double *src, long ss, float *dst, long ds, int n, int nr,
                            hipStream_t st);
+// dst_s = src_s, the entries [0, flip) negated
 void launch_copy_strided(const double *src, long ss, double *dst, long ds, int n, int nr,
-                         hipStream_t st);
+                         hipStream_t st, int flip = 0);
 int multi_part_size(int n, int nr);
 // the product alone: system s of slice k at part + (k * nr + s) * n, for the
 // caller to sum in slice order; returns the slice count
@@ -396,7 +466,7 @@ void launch_cycle_start(const double *r, int n, const double *P, int G, double *
 // first written as their sum in slice order.
 void launch_cgs_dot(const double *V, long ldv, double *w, int n, int j, double *P,
                     double *P3, int G, const GState *gs, hipStream_t st, const Bat &bt = kSingle,
-                    const double *part = nullptr, int ks = 0, int nr = 0);
+                    const double *part = nullptr, int ks = 0, int nr = 0, int flip = 0);
 // first Gram-Schmidt pass (w -= V h; dots of V with w into P2, |w|^2 into P3)
 // GP: the number of partials in P1 (0: G, the chunk count)
 // hred (may be null): the coefficients already summed (launch_reduce_rows)

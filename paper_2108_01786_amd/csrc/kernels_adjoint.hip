@@ -413,8 +413,8 @@ __global__ __launch_bounds__(256) void k_tlm_cols(Nodes N, int n0, int n, int nd
     }
 }
 
-// Right-hand sides of the nd tangent systems (rhs, system i at i * ldb) and
-// the surface terms of dU (um, direction i at i * n0):
+// Right-hand sides of the nd tangent systems (rhs, system i at i * ldb, the
+// surface rows negated as the solves take them) and the surface terms of dU (um, direction i at i * n0):
 //   rhs_i = [p on the surface] (dphi~_i - row terms of dA omega) - colA_i,
 //   um_i = d u_mv + row terms of dT gamma + colT_i - U ds,
 // the row terms being the adjoint's row sums times the direction at the node
@@ -450,7 +450,7 @@ __global__ void k_tlm_rhs(Nodes N, Flow F, int n0, int n, int nd, const double *
     double ux, uy, udx, udy;
     umv_derivs(F, x, y, dx, dy, ux, uy, udx, udy);
     const double dArow = R[0] * d[0] + R[1] * d[1] + w * omega[r] * dL.im;
-    rhs[i * ldb + r] = d[6] - dArow - colA;
+    rhs[i * ldb + r] = -(d[6] - dArow - colA);
     const double dumv = ux * d[0] + uy * d[1] + udx * d[2] + udy * d[3];
     const double dTrow = R[2] * d[0] + R[3] * d[1] + R[4] * d[2] + R[5] * d[3] + w * gamma[r] * dL.re;
     const double ds = (dx * d[2] + dy * d[3]) / s;

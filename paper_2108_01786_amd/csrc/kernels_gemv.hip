@@ -59,7 +59,7 @@ struct GemvDots {
     double *P, *P3;
 };
 
-// y = c - A x (or A x): each wave owns R rows and walks them in steps of
+// y = c - S A x (or S A x), S negating rows [0, flip): each wave owns R rows and walks them in steps of
 // 64 lanes x 16 bytes, U steps in flight, every product accumulated in TACC.
 // An FP32 matrix (and FP32 x) accumulates in FP64: the accumulation then adds
 // no error that grows with the row length, and a product's error is set by
@@ -68,8 +68,8 @@ template <typename TA, typename TX, typename TACC, int R, int U, bool DOTS = fal
 __global__ __launch_bounds__(64 * WPB) void k_gemv(const TA *__restrict__ A, long ld, int n,
                                               const TX *__restrict__ x,
                                               const double *__restrict__ c,
-                                              double *__restrict__ y, const int *active,
-                                              GemvDots d = GemvDots{}) {
+                                              double *__restrict__ y, int flip,
+                                              const int *active, GemvDots d = GemvDots{}) {
     if (active && *active == 0) return;     // uniform over the grid
     using V = typename Vec16<TA>::type;
     constexpr int VW = Vec16<TA>::n;
@@ -133,7 +133,7 @@ __global__ __launch_bounds__(64 * WPB) void k_gemv(const TA *__restrict__ A, lon
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         const TACC s = wave_sum(acc[r]);
-        const double v = (double)s;
+        const double v = r0 + r < flip ? -(double)s : (double)s;
         if (!DOTS) {
             if (lane == 0 && r0 + r < n) y[r0 + r] = c ? c[r0 + r] - v : v;
         } else if (r0 + r < n) {
@@ -171,9 +171,10 @@ constexpr int kGemvR = 2;   // rows per wave
 constexpr int kGemvU = 4;   // 16-byte steps in flight per row
 
 void launch_gemv64(const double *A, long ld, int n, const double *x, const double *c, double *y,
-                   const int *active, hipStream_t st) {
+                   int flip, const int *active, hipStream_t st) {
     hipLaunchKernelGGL((k_gemv<double, double, double, kGemvR, kGemvU>),
-                       dim3(gemv_blocks(n, kGemvR)), dim3(256), 0, st, A, ld, n, x, c, y, active);
+                       dim3(gemv_blocks(n, kGemvR)), dim3(256), 0, st, A, ld, n, x, c, y, flip,
+                       active);
 }
 
 // waves per block of the fused product (8, with half the partials, streamed
@@ -183,25 +184,26 @@ constexpr int kDotsWaves = 4;
 int gemv_partials(int n) { return cdiv(cdiv(n, kGemvR), kDotsWaves); }
 
 void launch_gemv32_dots(const float *A, long ld, int n, const float *x, double *y,
-                        const int *active, const double *V, long ldv, int j, double *P,
+                        int flip, const int *active, const double *V, long ldv, int j, double *P,
                         double *P3, hipStream_t st) {
     hipLaunchKernelGGL((k_gemv<float, float, double, kGemvR, kGemvU, true, kDotsWaves>),
                        dim3(gemv_partials(n)), dim3(64 * kDotsWaves), 0, st, A, ld, n, x, nullptr,
-                       y, active, GemvDots{V, ldv, j, P, P3});
+                       y, flip, active, GemvDots{V, ldv, j, P, P3});
 }
 
 void launch_gemv64_dots(const double *A, long ld, int n, const double *x, double *y,
-                        const int *active, const double *V, long ldv, int j, double *P,
+                        int flip, const int *active, const double *V, long ldv, int j, double *P,
                         double *P3, hipStream_t st) {
     hipLaunchKernelGGL((k_gemv<double, double, double, kGemvR, kGemvU, true, kDotsWaves>),
                        dim3(gemv_partials(n)), dim3(64 * kDotsWaves), 0, st, A, ld, n, x,
-                       nullptr, y, active, GemvDots{V, ldv, j, P, P3});
+                       nullptr, y, flip, active, GemvDots{V, ldv, j, P, P3});
 }
 
 void launch_gemv32(const float *A, long ld, int n, const float *x, const double *c, double *y,
-                   const int *active, hipStream_t st) {
+                   int flip, const int *active, hipStream_t st) {
     hipLaunchKernelGGL((k_gemv<float, float, double, kGemvR, kGemvU>),
-                       dim3(gemv_blocks(n, kGemvR)), dim3(256), 0, st, A, ld, n, x, c, y, active);
+                       dim3(gemv_blocks(n, kGemvR)), dim3(256), 0, st, A, ld, n, x, c, y, flip,
+                       active);
 }
 
 

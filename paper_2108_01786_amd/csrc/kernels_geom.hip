@@ -118,13 +118,14 @@ __device__ __forceinline__ double psi_mv(const Flow &F, double x, double y) {
     return v;
 }
 
-// b_0 = phi~ on the surface, b_k = psi_wall - psi_mv(zeta_k) on the walls (Sec. 3.2).
+// S b of Sec. 3.2: b_0 = phi~ on the surface, negated as the solves take the
+// surface rows, and b_k = psi_wall - psi_mv(zeta_k) on the walls.
 __global__ void k_rhs_phi(Layout L, Nodes N, Flow F, const double *phi, const double *psi_wall,
                           double *b) {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= L.n) return;
     if (p < L.off[1]) {
-        b[p] = phi[p];
+        b[p] = -phi[p];
         return;
     }
     const double g = psi_wall ? psi_wall[p - L.off[1]] : 0.0;

@@ -259,7 +259,7 @@ __global__ __launch_bounds__(kT) void k_reduce_rows(const double *P, int GP, con
 __global__ __launch_bounds__(kT) void k_cgs_dot(const double *V, long ldv, double *w, int n,
                                                 int j, double *P, double *P3, int G,
                                                 const GState *gs, Bat bt, const double *part,
-                                                int ks, int nr) {
+                                                int ks, int nr, int flip) {
     const int s = sys();
     gs += s;
     if (gs->active == 0) return;
@@ -273,10 +273,11 @@ __global__ __launch_bounds__(kT) void k_cgs_dot(const double *V, long ldv, doubl
     double nn = 0.0;
     if (part) {
         // w = the product's slices summed in order, on this block's chunk
+        // (negated in rows [0, flip))
         for (int m = c0 + threadIdx.x; m < c1; m += kT) {
             double a = 0.0;
             for (int k = 0; k < ks; ++k) a += part[((long)k * nr + s) * n + m];
-            w[m] = a;
+            w[m] = m < flip ? -a : a;
             nn += a * a;
         }
         __syncthreads();    // the chunk's w, written by this block, read below
@@ -675,9 +676,9 @@ void launch_cycle_start(const double *r, int n, const double *P, int G, double *
 }
 void launch_cgs_dot(const double *V, long ldv, double *w, int n, int j, double *P,
                     double *P3, int G, const GState *gs, hipStream_t st, const Bat &bt,
-                    const double *part, int ks, int nr) {
+                    const double *part, int ks, int nr, int flip) {
     hipLaunchKernelGGL(k_cgs_dot, dim3(G, bt.nsys), dim3(kT), 0, st, V, ldv, w, n, j, P, P3, G,
-                       gs, bt, part, ks, nr);
+                       gs, bt, part, ks, nr, flip);
 }
 void launch_cgs_first(const double *V, long ldv, double *w, int n, int j, const double *P1,
                       double *P2, double *P3, int G, double *H, int ldh, const GState *gs,

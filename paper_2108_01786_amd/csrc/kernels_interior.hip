@@ -163,7 +163,8 @@ __global__ __launch_bounds__(64 * kSliceWaves) void k_normal_finalize(
     out[p] = umv[p] + loc + acc;
 }
 
-// Dirichlet data of phi_t - C on the surface (Sec. 5.1, Laplace-Young):
+// Dirichlet data of phi_t - C on the surface (Sec. 5.1, Laplace-Young), negated
+// as the solves take the surface rows: -b with b =
 // tau kappa - |grad phi|^2 / 2 - g eta, kappa = Im(zeta''/zeta')/s = 2 Im L / s
 __global__ void k_pressure_data(int n0, Nodes N, const double *sds, const double *sdn,
                                 double tau, double grav, double *b) {
@@ -171,11 +172,11 @@ __global__ void k_pressure_data(int n0, Nodes N, const double *sds, const double
     if (m >= n0) return;
     const double s = N.s[m];
     const double a = sds[m] / s, c = sdn[m] / s;
-    b[m] = tau * 2.0 * N.lim[m] / s - 0.5 * (a * a + c * c) - grav * N.y[m];
+    b[m] = -(tau * 2.0 * N.lim[m] / s - 0.5 * (a * a + c * c) - grav * N.y[m]);
 }
 
 // Fluid-side boundary values of the auxiliary Cauchy integrals:
-// surface Re = the data, Im = P omega + H(omega_0)/2; wall k Re = KS omega_0 +
+// surface Re = the data (given negated), Im = P omega + H(omega_0)/2; wall k Re = KS omega_0 +
 // GS omega_w - H(omega_k)/2, Im = psi|_k (mean of omega_k for k >= 2, 0 on
 // the bottom).
 __global__ void k_phi_aux_values(int n, int n0, const double *data, const double *ps,
@@ -184,7 +185,7 @@ __global__ void k_phi_aux_values(int n, int n0, const double *data, const double
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= n) return;
     if (p < n0) {
-        fr[p] = data[p];
+        fr[p] = -data[p];
         fi[p] = ps[p] + 0.5 * hw[p];
     } else {
         const int k = bid[p];

@@ -1224,7 +1224,7 @@ static int near_width(int band) { return band > kNearBand ? band : kNearBand; }
 
 void launch_otf_matvec(const Layout &L, const Nodes &N, int flags, int fp32, int band,
                        int transpose, const double *x, const double *c, double *y, double *part,
-                       const int *active, hipStream_t st) {
+                       const int *active, hipStream_t st, int flip) {
     const double *hrow = nullptr;
     const int n = L.n;
     const int chunk = transpose ? cols_chunk(n, n) : rows_chunk(n, n);
@@ -1270,7 +1270,8 @@ void launch_otf_matvec(const Layout &L, const Nodes &N, int flags, int fp32, int
     }
     // FP64: far chunks, near band and the near-pair fix when there are near
     // pairs; FP32 takes no fix (the quotient's error is far below FP32 rounding)
-    launch_reduce_partials(n, part, (fp32 || !N.near) ? ns + 1 : ns + 2, c, 1.0, y, active, st);
+    launch_reduce_partials(n, part, (fp32 || !N.near) ? ns + 1 : ns + 2, c, 1.0, y, active, st,
+                           flip);
 }
 
 

@@ -327,22 +327,25 @@ __global__ __launch_bounds__(256) void k_mfma_multi_shared(const T *__restrict__
         }
 }
 
-// y_s = c_s - sum_k part[k][s] (or the plain sum when c is null), m rows
+// y_s = c_s - sum_k part[k][s] (or the plain sum when c is null), m rows; the
+// sums of rows [0, flip) are negated
 __global__ void k_reduce_multi(int m, int nr, const double *__restrict__ part, int ks,
                                const double *__restrict__ c, long cs, double *__restrict__ y,
-                               long ys) {
+                               long ys, int flip) {
     const int r = blockIdx.x * blockDim.x + threadIdx.x;
     const int s = blockIdx.y;
     if (r >= m || s >= nr) return;
     double acc = 0.0;
     for (int k = 0; k < ks; ++k) acc += part[((long)k * nr + s) * m + r];
+    if (r < flip) acc = -acc;
     y[(long)s * ys + r] = c ? c[(long)s * cs + r] - acc : acc;
 }
 
-__global__ void k_copy_strided(const double *src, long ss, double *dst, long ds, int n) {
+__global__ void k_copy_strided(const double *src, long ss, double *dst, long ds, int n,
+                               int flip) {
     const int m = blockIdx.x * blockDim.x + threadIdx.x;
     const long s = blockIdx.y;
-    if (m < n) dst[s * ds + m] = src[s * ss + m];
+    if (m < n) dst[s * ds + m] = m < flip ? -src[s * ss + m] : src[s * ss + m];
 }
 
 __global__ void k_to_f32_batched(const double *src, long ss, float *dst, long ds, int n) {
@@ -372,7 +375,8 @@ template <typename T, int ST> MultiGrid multi_grid_for(int m, int n) {
 // returns the slice count
 template <typename T, int ST>
 int launch_mfma_st(const T *A, long ld, int m, int n, const T *X, long xs, int nr,
-                   const double *c, long cs, double *y, long ys, double *part, hipStream_t st) {
+                   const double *c, long cs, double *y, long ys, double *part, int flip,
+                   hipStream_t st) {
     const MultiGrid g = multi_grid_for<T, ST>(m, n);
     const dim3 grid(cdiv(m, 4 * 16 * MultiShape<T, ST>::RT), g.ksn);
     if (ST == 2)
@@ -383,45 +387,48 @@ int launch_mfma_st(const T *A, long ld, int m, int n, const T *X, long xs, int n
                            g.kchunk, part);
     if (y)
         hipLaunchKernelGGL(k_reduce_multi, dim3(cdiv(m, 256), nr), dim3(256), 0, st, m, nr, part,
-                           g.ksn, c, cs, y, ys);
+                           g.ksn, c, cs, y, ys, flip);
     return g.ksn;
 }
 
 template <typename T>
 int launch_mfma_multi(const T *A, long ld, int m, int n, const T *X, long xs, int nr,
-                      const double *c, long cs, double *y, long ys, double *part,
+                      const double *c, long cs, double *y, long ys, double *part, int flip,
                       hipStream_t st) {
-    if (nr > 16) return launch_mfma_st<T, 2>(A, ld, m, n, X, xs, nr, c, cs, y, ys, part, st);
-    return launch_mfma_st<T, 1>(A, ld, m, n, X, xs, nr, c, cs, y, ys, part, st);
+    if (nr > 16)
+        return launch_mfma_st<T, 2>(A, ld, m, n, X, xs, nr, c, cs, y, ys, part, flip, st);
+    return launch_mfma_st<T, 1>(A, ld, m, n, X, xs, nr, c, cs, y, ys, part, flip, st);
 }
 
 }  // namespace
 
 void launch_mfma_multi64(const double *A, long ld, int n, const double *X, long xs, int nr,
-                         const double *c, long cs, double *y, long ys, double *part,
+                         const double *c, long cs, double *y, long ys, double *part, int flip,
                          hipStream_t st) {
-    launch_mfma_multi<double>(A, ld, n, n, X, xs, nr, c, cs, y, ys, part, st);
+    launch_mfma_multi<double>(A, ld, n, n, X, xs, nr, c, cs, y, ys, part, flip, st);
 }
 
 void launch_mfma_multi32(const float *A, long ld, int n, const float *X, long xs, int nr,
-                         const double *c, long cs, double *y, long ys, double *part,
+                         const double *c, long cs, double *y, long ys, double *part, int flip,
                          hipStream_t st) {
-    launch_mfma_multi<float>(A, ld, n, n, X, xs, nr, c, cs, y, ys, part, st);
+    launch_mfma_multi<float>(A, ld, n, n, X, xs, nr, c, cs, y, ys, part, flip, st);
 }
 
 int launch_mfma_parts64(const double *A, long ld, int n, const double *X, long xs, int nr,
                         double *part, hipStream_t st) {
-    return launch_mfma_multi<double>(A, ld, n, n, X, xs, nr, nullptr, 0, nullptr, 0, part, st);
+    return launch_mfma_multi<double>(A, ld, n, n, X, xs, nr, nullptr, 0, nullptr, 0, part, 0,
+                                     st);
 }
 
 int launch_mfma_parts32(const float *A, long ld, int n, const float *X, long xs, int nr,
                         double *part, hipStream_t st) {
-    return launch_mfma_multi<float>(A, ld, n, n, X, xs, nr, nullptr, 0, nullptr, 0, part, st);
+    return launch_mfma_multi<float>(A, ld, n, n, X, xs, nr, nullptr, 0, nullptr, 0, part, 0,
+                                     st);
 }
 
 void launch_mfma_rect64(const double *A, long ld, int m, int n, const double *X, long xs, int nr,
                         double *y, long ys, double *part, hipStream_t st) {
-    launch_mfma_multi<double>(A, ld, m, n, X, xs, nr, nullptr, 0, y, ys, part, st);
+    launch_mfma_multi<double>(A, ld, m, n, X, xs, nr, nullptr, 0, y, ys, part, 0, st);
 }
 
 void launch_to_f32_batched(const double *src, long ss, float *dst, long ds, int n, int nr,
@@ -431,9 +438,9 @@ void launch_to_f32_batched(const double *src, long ss, float *dst, long ds, int 
 }
 
 void launch_copy_strided(const double *src, long ss, double *dst, long ds, int n, int nr,
-                         hipStream_t st) {
+                         hipStream_t st, int flip) {
     hipLaunchKernelGGL(k_copy_strided, dim3(cdiv(n, 256), nr), dim3(256), 0, st, src, ss, dst, ds,
-                       n);
+                       n, flip);
 }
 
 // the largest partial-sum buffer any shape and precision needs for nr systems

@@ -1,0 +1,105 @@
+"""The two-grid iteration against the stored-matrix path, over grids that coarsen,
+grids that do not, and right-hand sides without smoothness."""
+import warnings
+
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from synth.geometry import Geometry, ellipse, fourier_surface, graph_bottom, trig_potential
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def ww():
+    from paper_2108_01786_amd import wwbi
+    warnings.simplefilter("ignore", RuntimeWarning)      # tiny grids are under-resolved
+    return wwbi
+
+
+@pytest.fixture(scope="module")
+def ctx(ww):
+    c = ww.Context(0)
+    yield c
+    c.close()
+
+
+def cell(M0, M1, Mo=(), gap=0.35, seed=0):
+    """Surface, bottom and a row of ellipses whose tops lie `gap` below y = 0."""
+    rng = np.random.default_rng(seed)
+    c = 0.01 * np.exp(-np.arange(2, 8) / 3.0) * (rng.standard_normal(6) + 1j * rng.standard_normal(6))
+    curves = [fourier_surface(M0, 0.08, c), graph_bottom(M1, -1.1, [(1, 0.05)])]
+    centres = [(2 * j + 1) * np.pi / max(1, len(Mo)) - 1j * (gap + 0.14) for j in range(len(Mo))]
+    curves += [ellipse(m, z.real, z.imag, 0.22, 0.14, 0.0) for m, z in zip(Mo, centres)]
+    geom = Geometry(curves, np.array(centres), rng.uniform(-1, 1, len(Mo)), 1.0)
+    return geom, trig_potential(M0, 0.1 * rng.standard_normal(3), 0.1 * rng.standard_normal(3))
+
+
+def rel(a, b):
+    a, b = np.asarray(a.cpu() if torch.is_tensor(a) else a), np.asarray(b.cpu() if torch.is_tensor(b) else b)
+    return float(np.abs(a - b).max() / np.abs(b).max())
+
+
+# coarsened by 2-power, odd and per-boundary factors; half sizes that are
+# prime (a boundary that stays whole); an ellipse close to the surface; n just
+# past the one-launch limit
+GRIDS = [(1024, 256, (128, 128), 0.35), (810, 450, (250,), 0.35), (1250, 626, (250,), 0.35),
+         (2018, 288, (96, 96), 0.35), (1440, 96, (96,), 0.35), (2048, 512, (768,), 0.06),
+         (768, 130, (130,), 0.35)]
+
+
+@pytest.mark.parametrize("M0,M1,Mo,gap", GRIDS)
+@pytest.mark.parametrize("prec", ["fp64", "refined"])
+def test_two_grid_matches_stored(ww, ctx, M0, M1, Mo, gap, prec):
+    """The default path against MATVEC_STORED for every system it solves."""
+    geom, phi = cell(M0, M1, Mo, gap, seed=M0)
+    n = geom.Mtot
+    print(f"case two-grid n={n} gap={gap} {prec}", flush=True)
+    fp64 = prec == "fp64"
+    kw = dict(precision=ww.FP64 if fp64 else ww.FP32_REFINED, tol=1e-15 if fp64 else 1e-14,
+              check=False)
+    st = dict(kw, matvec=ww.MATVEC_STORED)
+    dg = ww.DeviceGeometry.from_synth(geom, DEV)
+    p = torch.as_tensor(phi, device=DEV)
+    bar = 1e-11 if fp64 else 1e-10
+    U, om, psi, r = ctx.solve_phi(dg, p, **kw)
+    Us, oms, psis, rs = ctx.solve_phi(dg, p, **st)
+    assert r.rel_resid <= kw["tol"] and rs.rel_resid <= kw["tol"]
+    assert rel(om, oms) <= bar and rel(U, Us) <= bar
+    assert r.n_hist > 0 and r.history()[-1] == r.rel_resid
+    assert (r.refine_steps > 0) == (not fp64)
+    # the transpose, with weights that are noise
+    gU = torch.as_tensor(np.random.default_rng(1).uniform(0, 1, M0), device=DEV) * U
+    g, ra = ctx.adjoint_phi(dg, om, gU, **kw)
+    gs, _ = ctx.adjoint_phi(dg, om, gU, **st)
+    assert ra.rel_resid <= kw["tol"]
+    for k in g:
+        assert rel(g[k], gs[k]) <= 10 * bar, k
+    # the wall system
+    g0 = torch.as_tensor(trig_potential(M0, [0.2, 0.1], [0.1, -0.1]), device=DEV)
+    Uw, gw, rw = ctx.solve_gamma(dg, g0, **kw)
+    Uv, gv, _ = ctx.solve_gamma(dg, g0, **st)
+    assert rw.rel_resid <= kw["tol"] and rel(gw, gv) <= bar and rel(Uw, Uv) <= bar
+    # gamma_t, whose data and result each take a derivative more
+    V = torch.as_tensor(trig_potential(M0, [0.1, 0.05], [0.0, 0.1]), device=DEV)
+    gt, _, _, rt = ctx.solve_gamma_t(dg, p, V, tau=0.1, **kw)
+    gts, _, _, _ = ctx.solve_gamma_t(dg, p, V, tau=0.1, **st)
+    assert rt.rel_resid <= kw["tol"] and rel(gt, gts) <= 1e-9
+    # two solves and the interior rule
+    z = torch.as_tensor([0.3 - 0.2j, 1.0 - 0.9j], device=DEV)
+    pr, _ = ctx.pressure(dg, p, z, tau=0.1, **kw)
+    prs, _ = ctx.pressure(dg, p, z, tau=0.1, **st)
+    assert rel(pr, prs) <= bar
+
+
+def test_two_grid_is_deterministic(ww, ctx):
+    geom, phi = cell(1024, 256, (128, 128))
+    print("case two-grid determinism", flush=True)
+    dg = ww.DeviceGeometry.from_synth(geom, DEV)
+    p = torch.as_tensor(phi, device=DEV)
+    runs = [ctx.solve_phi(dg, p, poll_every=k)[:2] for k in (1, 2, 7)]
+    for U, om in runs[1:]:
+        assert torch.equal(U, runs[0][0]) and torch.equal(om, runs[0][1])
