@@ -67,8 +67,10 @@ extern "C" {
 
 /* ---- option values ----------------------------------------------------- */
 #define WWBI_FP64                 0  /* FP64 matrix and matvecs                          */
-#define WWBI_FP32_REFINED         1  /* FP32 matrix/matvec (FP32 accumulation) inside
-                                        FP64 iterative refinement                      */
+#define WWBI_FP32_REFINED         1  /* FP32 matrix/matvec (FP64 accumulation) inside
+                                        FP64 iterative refinement.  A system of at most
+                                        1024 unknowns is solved in FP64 either way, in
+                                        one launch (its cycles count as the steps)     */
 #define WWBI_MATVEC_AUTO          0  /* the fastest: above 1024 unknowns, from a cold
                                         start and where the grid has nodes to spare,
                                         a two-grid iteration (a coarse subset of the

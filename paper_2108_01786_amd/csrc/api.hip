@@ -388,6 +388,10 @@ void Ctx::prof_end() {
 int Ctx::gmres(const Op &op, const double *b, double *x, bool x_zero, double tol, int restart,
                int max_iter, int poll, bool verify, SolveStats &st, int kc) {
     const int n = op.n;
+    if (verify && n <= kSmallMax && stored_fp64(op.kind) && !fixed_ws && !profiling) {
+        int status;
+        if (gmres_small(op, b, x, x_zero, tol, restart, max_iter, st, status)) return status;
+    }
     const int G = gmres_nblocks(n);
     const int ldp = restart + 1 + vpre;    // rows of Gram-Schmidt partials (recycled ones too)
     const long ldv = round_up(n, 64);
@@ -538,6 +542,11 @@ int Ctx::gmres(const Op &op, const double *b, double *x, bool x_zero, double tol
     return status;
 }
 
+bool Ctx::small_system(int n, const wwbi_opts &o) {
+    cycle_cap = o.precision == WWBI_FP32_REFINED ? o.max_refine : INT_MAX;
+    return n <= kSmallMax && o.matvec != WWBI_MATVEC_ON_THE_FLY && !fixed_ws && !profiling;
+}
+
 bool Ctx::ensure_small(int nsys) {
     // the abort tag sits in front of the exchange words
     if (grow(xch, capxch, (size_t)nsys * small_exchange_words() + 8) != WWBI_OK) return false;
@@ -568,6 +577,43 @@ bool Ctx::take_tags(long need, unsigned &first) {
     }
     first = xtag;
     xtag += (unsigned)need;
+    return true;
+}
+
+bool Ctx::gmres_small(const Op &op, const double *b, double *x, bool x_zero, double tol,
+                      int restart, int max_iter, SolveStats &st, int &status) {
+    if (!ensure_small(1)) return false;
+    // an exchange takes a tag: one a step and one a cycle
+    SmallArgs a{};
+    if (!take_tags(2L * max_iter + 8, a.tag)) return false;
+    a.A = (const double *)A;
+    a.ld = op.ld;
+    a.n = op.n;
+    a.flip = op.flip;
+    a.b = b;
+    a.x = x;
+    a.x0 = x_zero ? nullptr : x;
+    a.tol = tol;
+    a.steps = restart;
+    a.max_iter = max_iter;
+    a.max_cycles = cycle_cap;
+    a.verify = 1;
+    a.xch = xch + 8;
+    a.abort_tag = reinterpret_cast<unsigned *>(xch);
+    a.out = dsmall;
+    hsmall->status = kSmallAborted;
+    if (launch_small_gmres(a, 1, stream) != WWBI_OK || hipGetLastError() != hipSuccess ||
+        hipStreamSynchronize(stream) != hipSuccess) {
+        status = WWBI_EHIP;
+        return true;
+    }
+    const SmallRes &r = *hsmall;
+    if (r.status == kSmallAborted) return false;
+    st.iters += r.its;
+    st.cycles += r.cycles;
+    for (int i = 0; i < r.nhist; ++i) note_resid(r.hist[i]);
+    st.rel_resid = r.bnorm > 0 ? r.resid / r.bnorm : 0.0;
+    status = r.status;
     return true;
 }
 
@@ -720,12 +766,14 @@ int Ctx::solve_system(int mode, Op op, int k0, const int (&kinds)[4], const doub
                       bool x_zero, const wwbi_opts &o, bool check_rough, bool &assembled,
                       Assemble assemble, SolveStats &st, double &bytes) {
     const bool stored = o.matvec != WWBI_MATVEC_ON_THE_FLY;
-    const bool fp32 = o.precision == WWBI_FP32_REFINED && (stored || kinds[3] >= 0);
+    const bool small = small_system(op.n, o);
+    const bool fp32 =
+        o.precision == WWBI_FP32_REFINED && !small && (stored || kinds[3] >= 0);
     Op op64 = op, in = op;
     op64.kind = kinds[2];
     in.kind = stored ? (fp32 ? kinds[1] : kinds[0]) : (fp32 ? kinds[3] : kinds[2]);
     bytes = op_bytes(in);
-    if (o.matvec == WWBI_MATVEC_AUTO && x_zero && have_strips && op.n > kSmallMax) {
+    if (o.matvec == WWBI_MATVEC_AUTO && x_zero && have_strips && !small) {
         const int s = two_grid(mode, op64, k0, b, x, o, check_rough, st);
         if (s == WWBI_OK || s < 0) return s;
         if (s == kTwoGridPart) x_zero = false;
@@ -736,7 +784,15 @@ int Ctx::solve_system(int mode, Op op, int k0, const int (&kinds)[4], const doub
         assembled = true;
     }
     if (fp32) return refine(in, op64, b, x, x_zero, o, st);
-    return gmres(in, b, x, x_zero, o.tol, o.restart, o.max_iter, o.poll_every, true, st);
+    const int status =
+        gmres(in, b, x, x_zero, o.tol, o.restart, o.max_iter, o.poll_every, true, st);
+    if (small && o.precision == WWBI_FP32_REFINED) as_refined(x_zero, st);
+    return status;
+}
+
+void Ctx::as_refined(bool x_zero, SolveStats &st) {
+    st.refine_steps = st.cycles;
+    if (x_zero && !hist.empty()) hist.erase(hist.begin());
 }
 
 // Operator kinds of a system: stored FP64, stored FP32, on the fly in FP64 and
@@ -1378,7 +1434,7 @@ int solve_phi_impl(Ctx *c, const wwbi_geom *g, const double *phi, const wwbi_opt
     };
     c->a_ready = false;
     if (stored && !c->have_strips) {
-        rc = assemble(o->precision == WWBI_FP32_REFINED);
+        rc = assemble(o->precision == WWBI_FP32_REFINED && !c->small_system(n, *o));
         if (rc) { c->finish_report(rep, rc, st, 0); return rc; }
         c->a_ready = true;
     }
@@ -2095,7 +2151,7 @@ int wwbi_adjoint_phi(wwbi_ctx *ctx, const wwbi_geom *g, const double *omega, con
     };
     bool assembled = false;
     if (o->matvec != WWBI_MATVEC_ON_THE_FLY && !c->have_strips) {
-        rc = assemble(o->precision == WWBI_FP32_REFINED);
+        rc = assemble(o->precision == WWBI_FP32_REFINED && !c->small_system(n, *o));
         if (rc) { c->finish_report(rep, rc, st, 0); return rc; }
         assembled = true;
     }

@@ -126,6 +126,7 @@ struct Ctx {
     unsigned long long *xch = nullptr; size_t capxch = 0;
     SmallRes *hsmall = nullptr, *dsmall = nullptr;
     unsigned xtag = 1;
+    int cycle_cap = 0;
     // two-grid iteration: the coarse matrix, the coarse nodes' fine indices and
     // weight factors, and the coarse solution
     double *cA = nullptr;   size_t capcA = 0;
@@ -228,6 +229,13 @@ struct Ctx {
     // cycle, no verification, x = the solution from zero)
     int gmres(const Op &op, const double *b, double *x, bool x_zero, double tol, int restart,
               int max_iter, int poll, bool verify, SolveStats &st, int kc = 0);
+    // whether a system of n unknowns is solved in one launch (in FP64, whichever
+    // precision was asked for); not for profiled calls, which time the products.
+    // Sets the cycle budget of such a solve: max_refine when FP32 was asked for.
+    bool small_system(int n, const wwbi_opts &o);
+    // one-launch solve; false when it could not run (solve by gmres())
+    bool gmres_small(const Op &op, const double *b, double *x, bool x_zero, double tol,
+                     int restart, int max_iter, SolveStats &st, int &status);
     // words and results for nsys one-launch solves; false when out of memory
     bool ensure_small(int nsys);
     bool take_tags(long need, unsigned &first);
@@ -247,6 +255,9 @@ struct Ctx {
     int solve_system(int mode, Op op, int k0, const int (&kinds)[4], const double *b, double *x,
                      bool x_zero, const wwbi_opts &o, bool check_rough, bool &assembled,
                      Assemble assemble, SolveStats &st, double &bytes);
+    // the report of a small FP64 solve that was asked for in refined FP32: its
+    // cycles are the refinement steps
+    void as_refined(bool x_zero, SolveStats &st);
     double device_norm(const double *v, int n);
     int refine(const Op &op32, const Op &op64, const double *b, double *x, bool x_zero,
                const wwbi_opts &o, SolveStats &st);

@@ -10,7 +10,17 @@ namespace wwbi {
 
 namespace {
 
-constexpr int kRowsPerAsmBlock = 32;
+constexpr int kRowsPerAsmBlock = 32;       // at most
+
+// Rows per block of the FP64 assemblies: 32 share one load of the columns'
+// node data, fewer where 32 would leave most of the chip idle (at n = 580, 57
+// blocks took 29 us; 4 rows per block, 8 us).
+inline int asm_rows(int rows, long ld) {
+    const long blocks = ((ld + 255) / 256) * rows;      // at one row per block
+    int r = kRowsPerAsmBlock;
+    while (r > 4 && blocks / r < 2048) r /= 2;
+    return r;
+}
 
 // Kinds of a far entry of A when the target and source boundaries are
 // uniform: the real part of the source-flavour term (surface row and wall
@@ -27,11 +37,11 @@ enum { kFastReNeg = 0, kFastRePos = 1, kFastIm = 2 };
 template <int WALL, typename OutT = double>
 __global__ __launch_bounds__(256) void k_assemble(Nodes N, const double *hrow, int r0, int nr,
                                                   int c0, int nc, int corr, OutT *out,
-                                                  long ld) {
+                                                  long ld, int rows) {
     __shared__ Tgt tg[kRowsPerAsmBlock];
     const int col = blockIdx.x * 256 + threadIdx.x;           // column within the output
-    const int rbase = blockIdx.y * kRowsPerAsmBlock;
-    if (threadIdx.x < kRowsPerAsmBlock) {
+    const int rbase = blockIdx.y * rows;
+    if ((int)threadIdx.x < rows) {
         const int r = rbase + threadIdx.x;
         if (r < nr) tg[threadIdx.x] = load_tgt(N, r0 + r);
     }
@@ -40,7 +50,7 @@ __global__ __launch_bounds__(256) void k_assemble(Nodes N, const double *hrow, i
     const bool live = col < nc;
     Src s;
     if (live) s = load_src(N, c0 + col);
-    const int rend = min(kRowsPerAsmBlock, nr - rbase);
+    const int rend = min(rows, nr - rbase);
     for (int i = 0; i < rend; ++i) {
         double v = 0.0;
         if (live) {
@@ -62,11 +72,11 @@ __global__ __launch_bounds__(256) void k_assemble(Nodes N, const double *hrow, i
 // FP64 assembly of the transpose A^T (row q = source q, column p = target p):
 // the staged rows hold sources, each thread one target.
 __global__ __launch_bounds__(256) void k_assemble64T(Nodes N, int n, int corr, double *out,
-                                                     long ld) {
+                                                     long ld, int rows) {
     __shared__ Src ss[kRowsPerAsmBlock];
     const int col = blockIdx.x * 256 + threadIdx.x;
-    const int rbase = blockIdx.y * kRowsPerAsmBlock;
-    if (threadIdx.x < kRowsPerAsmBlock) {
+    const int rbase = blockIdx.y * rows;
+    if ((int)threadIdx.x < rows) {
         const int r = rbase + threadIdx.x;
         if (r < n) ss[threadIdx.x] = load_src(N, r);
     }
@@ -74,7 +84,7 @@ __global__ __launch_bounds__(256) void k_assemble64T(Nodes N, int n, int corr, d
     if (col >= ld) return;
     const bool live = col < n;
     const Tgt t = load_tgt(N, live ? col : 0);
-    const int rend = min(kRowsPerAsmBlock, n - rbase);
+    const int rend = min(rows, n - rbase);
     for (int i = 0; i < rend; ++i)
         __builtin_nontemporal_store(live ? a_val64(N, t, ss[i], corr != 0) : 0.0,
                                     out + (long)(rbase + i) * ld + col);
@@ -435,8 +445,7 @@ __device__ __forceinline__ bool cells_far(const Nodes &N, int pa, int pb, int qa
     return true;
 }
 
-// FP64 assembly of A.  One column per thread and kRowsPerAsm64 rows per
-// block, as in the FP32 far pass.  A wave whose live columns lie on one
+// FP64 assembly of A.  One column per thread and asm_rows() rows per block, as in the FP32 far pass.  A wave whose live columns lie on one
 // boundary, in a block whose rows lie on one boundary, clear of the
 // same-boundary band and, by the 64-node cells' E discs, of every near pair,
 // takes the E quotient with one entry formula for the whole tile: the source
@@ -444,8 +453,6 @@ __device__ __forceinline__ bool cells_far(const Nodes &N, int pa, int pb, int qa
 // the FP32 estimate refined twice, and E's trailing parts only where the
 // discs come within |E| / 4 (cells_far).  Every other wave takes a_val64,
 // the full entry (band, near pairs, diagonal limits).
-constexpr int kRowsPerAsm64 = 32;
-
 template <int KIND, bool LO>
 __device__ __forceinline__ double a_fast64(const Tgt &t, const Src &s, double fa, double fb,
                                            double ec) {
@@ -469,12 +476,12 @@ __device__ __forceinline__ void asm64_tile(const Tgt *tg, int rend, const Src &s
 }
 
 __global__ __launch_bounds__(256) void k_assemble64(Nodes N, int n, int corr, double *out,
-                                                    long ld) {
-    __shared__ Tgt tg[kRowsPerAsm64];
+                                                    long ld, int rows) {
+    __shared__ Tgt tg[kRowsPerAsmBlock];
     const int wb = wave_base();
     const int col = blockIdx.x * 256 + threadIdx.x;
-    const int rbase = blockIdx.y * kRowsPerAsm64;
-    if (threadIdx.x < kRowsPerAsm64) {
+    const int rbase = blockIdx.y * rows;
+    if ((int)threadIdx.x < rows) {
         const int r = rbase + threadIdx.x;
         if (r < n) tg[threadIdx.x] = load_tgt(N, r);
     }
@@ -482,7 +489,7 @@ __global__ __launch_bounds__(256) void k_assemble64(Nodes N, int n, int corr, do
     if (col >= ld) return;
     const bool live = col < n;
     const Src s = load_src(N, live ? col : 0);
-    const int rend = min(kRowsPerAsm64, n - rbase);
+    const int rend = min(rows, n - rbase);
     double *o = out + (long)rbase * ld + col;
     // the wave's live columns [ca, cb] and the block's rows, each on one
     // boundary, clear of the band and of near pairs (wave-uniform tests)
@@ -1150,9 +1157,10 @@ static int fix_blocks(int o, int n) { return (o + n - 1) / kCellNodes - o / kCel
 void launch_assemble64(const Layout &L, const Nodes &N, int flags, double *A, long ld,
                        hipStream_t st) {
     const int n = L.n;
-    dim3 grid(cdiv(ld, 256), cdiv(n, kRowsPerAsm64));
+    const int rows = asm_rows(n, ld);
+    dim3 grid(cdiv(ld, 256), cdiv(n, rows));
     const int corr = (flags & WWBI_FLAG_NO_CORRECTION) ? 0 : 1;
-    hipLaunchKernelGGL(k_assemble64, grid, dim3(256), 0, st, N, n, corr, A, ld);
+    hipLaunchKernelGGL(k_assemble64, grid, dim3(256), 0, st, N, n, corr, A, ld, rows);
 }
 
 void launch_assemble32(const Layout &L, const Nodes &N, int flags, int band, float *A, long ld,
@@ -1181,43 +1189,52 @@ void launch_assemble64_T(const Layout &L, const Nodes &N, int flags, double *AT,
                          hipStream_t st) {
     const int n = L.n;
     const int corr = (flags & WWBI_FLAG_NO_CORRECTION) ? 0 : 1;
-    dim3 grid(cdiv(ld, 256), cdiv(n, kRowsPerAsmBlock));
-    hipLaunchKernelGGL(k_assemble64T, grid, dim3(256), 0, st, N, n, corr, AT, ld);
+    const int rows = asm_rows(n, ld);
+    dim3 grid(cdiv(ld, 256), cdiv(n, rows));
+    hipLaunchKernelGGL(k_assemble64T, grid, dim3(256), 0, st, N, n, corr, AT, ld, rows);
 }
 
 void launch_assemble_gt64(const Layout &L, const Nodes &N, double *B, long ld, hipStream_t st) {
     const int n = L.n;
-    dim3 grid(cdiv(ld, 256), cdiv(n, kRowsPerAsmBlock));
-    hipLaunchKernelGGL(k_assemble<2>, grid, dim3(256), 0, st, N, nullptr, 0, n, 0, n, 1, B, ld);
+    const int rows = asm_rows(n, ld);
+    dim3 grid(cdiv(ld, 256), cdiv(n, rows));
+    hipLaunchKernelGGL(k_assemble<2>, grid, dim3(256), 0, st, N, nullptr, 0, n, 0, n, 1, B, ld,
+                       rows);
 }
 
 void launch_assemble_gt32(const Layout &L, const Nodes &N, float *B, long ld, hipStream_t st) {
     const int n = L.n;
-    dim3 grid(cdiv(ld, 256), cdiv(n, kRowsPerAsmBlock));
+    const int rows = asm_rows(n, ld);
+    dim3 grid(cdiv(ld, 256), cdiv(n, rows));
     hipLaunchKernelGGL((k_assemble<2, float>), grid, dim3(256), 0, st, N, nullptr, 0, n, 0, n, 1,
-                       B, ld);
+                       B, ld, rows);
 }
 
 void launch_assemble_T64(const Layout &L, const Nodes &N, const double *hrow, double *T, long ld,
                          hipStream_t st) {
     const int n = L.n, n0 = L.off[1];
-    dim3 grid(cdiv(ld, 256), cdiv(n0, kRowsPerAsmBlock));
-    hipLaunchKernelGGL(k_assemble<3>, grid, dim3(256), 0, st, N, hrow, 0, n0, 0, n, 1, T, ld);
+    const int rows = asm_rows(n0, ld);
+    dim3 grid(cdiv(ld, 256), cdiv(n0, rows));
+    hipLaunchKernelGGL(k_assemble<3>, grid, dim3(256), 0, st, N, hrow, 0, n0, 0, n, 1, T, ld,
+                       rows);
 }
 
 void launch_assemble_wall64(const Layout &L, const Nodes &N, const double *hrow, double *W, long ld,
                             hipStream_t st) {
     const int c0 = L.off[1], nw = L.n - L.off[1];
-    dim3 grid(cdiv(ld, 256), cdiv(nw, kRowsPerAsmBlock));
-    hipLaunchKernelGGL(k_assemble<1>, grid, dim3(256), 0, st, N, hrow, c0, nw, c0, nw, 1, W, ld);
+    const int rows = asm_rows(nw, ld);
+    dim3 grid(cdiv(ld, 256), cdiv(nw, rows));
+    hipLaunchKernelGGL(k_assemble<1>, grid, dim3(256), 0, st, N, hrow, c0, nw, c0, nw, 1, W, ld,
+                       rows);
 }
 
 void launch_assemble_wall32(const Layout &L, const Nodes &N, const double *hrow, float *W, long ld,
                             hipStream_t st) {
     const int c0 = L.off[1], nw = L.n - L.off[1];
-    dim3 grid(cdiv(ld, 256), cdiv(nw, kRowsPerAsmBlock));
+    const int rows = asm_rows(nw, ld);
+    dim3 grid(cdiv(ld, 256), cdiv(nw, rows));
     hipLaunchKernelGGL((k_assemble<1, float>), grid, dim3(256), 0, st, N, hrow, c0, nw, c0, nw, 1,
-                       W, ld);
+                       W, ld, rows);
 }
 
 static int near_width(int band) { return band > kNearBand ? band : kNearBand; }

@@ -1,4 +1,5 @@
-"""The two-grid iteration against the stored-matrix path, over grids that coarsen,
+"""The one-launch solve of small systems at the edges of its shapes, and the
+two-grid iteration against the stored-matrix path, over grids that coarsen,
 grids that do not, and right-hand sides without smoothness."""
 import warnings
 
@@ -41,6 +42,36 @@ def cell(M0, M1, Mo=(), gap=0.35, seed=0):
 def rel(a, b):
     a, b = np.asarray(a.cpu() if torch.is_tensor(a) else a), np.asarray(b.cpu() if torch.is_tensor(b) else b)
     return float(np.abs(a - b).max() / np.abs(b).max())
+
+
+# n at both sides of every column count the kernel is built for (a multiple of
+# 128), one unknown pair past a wave's, a block's and the largest size's rows
+SMALL = [(8, 8, ()), (32, 32, ()), (48, 34, (48,)), (64, 32, (32,)), (126, 66, (64,)),
+         (192, 66, (126,)), (256, 128, (128,)), (258, 128, (128,)), (320, 192, (128,)),
+         (322, 192, (128,)), (384, 256, (128,)), (386, 254, (130,)), (448, 320, (128,)),
+         (512, 258, (128,)), (510, 256, (128, 128)), (514, 256, (128, 128)), (66, 958, ())]
+
+
+@pytest.mark.parametrize("M0,M1,Mo", SMALL)
+@pytest.mark.parametrize("prec", ["fp64", "refined"])
+def test_small_solve_matches_dense(ww, ctx, M0, M1, Mo, prec):
+    geom, phi = cell(M0, M1, Mo)
+    print(f"case small n={geom.Mtot} {prec}", flush=True)
+    ref = O.solve_phi(O.OGeom.from_synth(geom), torch.as_tensor(phi))
+    dg = ww.DeviceGeometry.from_synth(geom, DEV)
+    kw = dict(precision=ww.FP64 if prec == "fp64" else ww.FP32_REFINED,
+              tol=1e-13 if prec == "fp64" else 1e-14)
+    U, om, _, rep = ctx.solve_phi(dg, torch.as_tensor(phi, device=DEV), **kw)
+    assert rep.status in (ww.OK, ww.WARN_UNDERRESOLVED) and rep.rel_resid <= kw["tol"]
+    assert (rep.refine_steps > 0) == (prec == "refined")
+    assert rel(om, ref["omega"]) <= 1e-12 and rel(U, ref["U"]) <= 1e-11
+    # short cycles: the restarts, their history and a warm start
+    U5, om5, _, r5 = ctx.solve_phi(dg, torch.as_tensor(phi, device=DEV), restart=5, max_refine=60, **kw)
+    assert r5.rel_resid <= kw["tol"] and rel(om5, om) <= 1e-12
+    h = r5.history()
+    assert h[-1] == r5.rel_resid and all(b < a for a, b in zip(h, h[1:]))
+    _, omw, _, rw = ctx.solve_phi(dg, torch.as_tensor(phi, device=DEV), x0=om.clone(), **kw)
+    assert rw.iters == 0 and torch.equal(omw, om)
 
 
 # coarsened by 2-power, odd and per-boundary factors; half sizes that are
