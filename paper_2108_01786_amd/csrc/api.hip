@@ -602,13 +602,14 @@ bool Ctx::gmres_small(const Op &op, const double *b, double *x, bool x_zero, dou
     a.abort_tag = reinterpret_cast<unsigned *>(xch);
     a.out = dsmall;
     hsmall->status = kSmallAborted;
+    hsmall->aborted = 0;
     if (launch_small_gmres(a, 1, stream) != WWBI_OK || hipGetLastError() != hipSuccess ||
         hipStreamSynchronize(stream) != hipSuccess) {
         status = WWBI_EHIP;
         return true;
     }
     const SmallRes &r = *hsmall;
-    if (r.status == kSmallAborted) return false;
+    if (r.status == kSmallAborted || r.aborted) return false;
     st.iters += r.its;
     st.cycles += r.cycles;
     for (int i = 0; i < r.nhist; ++i) note_resid(r.hist[i]);
@@ -617,7 +618,7 @@ bool Ctx::gmres_small(const Op &op, const double *b, double *x, bool x_zero, dou
     return true;
 }
 
-// The most accurate grid whose one-launch solve keeps 24 steps or more in a
+// The most accurate grid whose one-launch solve keeps 27 steps in a
 // cycle (kSmallFullCycle nodes: the solve then ends in one, at M = 10240 512
 // nodes and 0.62 ms a solve where 1024 in cycles of 17 took 0.82), else the
 // most accurate that fits at all.  A coarser grid costs passes, a finer one
@@ -648,6 +649,17 @@ bool Ctx::choose_coarse(int k0, Coarse &C) const {
     return false;
 }
 
+// Buffers of the coarse systems of an n-unknown problem, at the largest size
+// any of its geometries takes (a solve of a seen size allocates nothing).
+int Ctx::ensure_coarse(int n, int nsys) {
+    const size_t nc = (size_t)round_up(std::min(kSmallCoarseMax, n / 2), 64);
+    int rc = grow(cA, capcA, nc * nc);
+    if (!rc) rc = grow(cmap, capcmap, nc);
+    if (!rc) rc = grow(cfac, capcfac, nc);
+    if (!rc) rc = grow(ce, capce, nc * nsys);
+    return rc;
+}
+
 constexpr double kTwoGridMargin = 0.2;
 
 int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, const wwbi_opts &o,
@@ -658,9 +670,7 @@ int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, co
     if (o.max_iter < 200 || !choose_coarse(k0, C) || !ensure_small(1)) return kTwoGridNone;
     const int n = op.n, r0 = L.off[k0], nc = C.n;
     const long ldc = round_up(nc, 64);
-    if (grow(cA, capcA, (size_t)nc * ldc) || grow(cmap, capcmap, (size_t)nc) ||
-        grow(cfac, capcfac, (size_t)nc) || grow(ce, capce, (size_t)nc))
-        return kTwoGridNone;
+    if (ensure_coarse(L.n)) return kTwoGridNone;
     const int corr = (o.flags & WWBI_FLAG_NO_CORRECTION) ? 0 : 1;
     const double inv_d = mode == kCoarseGt || mode == kCoarseWall ? -2.0 : 2.0;
     const int G = gmres_nblocks(n);
@@ -672,7 +682,7 @@ int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, co
     const double *rr = b;
     bool have_x = false;
     if (check_rough) {
-        launch_roughness(b, n, part, stream);
+        launch_roughness(b, 0, n, 1, part, stream);
         if (hipMemcpyAsync(hst, part, 128 * sizeof(double), hipMemcpyDeviceToHost, stream) !=
                 hipSuccess ||
             hipStreamSynchronize(stream) != hipSuccess)
@@ -717,9 +727,10 @@ int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, co
         a.abort_tag = reinterpret_cast<unsigned *>(xch);
         a.out = dsmall;
         hsmall->status = kSmallAborted;
+        hsmall->aborted = 0;
         if (launch_small_gmres(a, 1, stream) != WWBI_OK) return WWBI_EHIP;
-        launch_coarse_correct(N, hrow, mode, cmap, cfac, nc, corr, ce, 0, r0, n, op.flip, inv_d, rr,
-                              0, x, 0, have_x, part, 1, stream);
+        launch_coarse_correct(N, hrow, mode, cmap, cfac, nc, corr, ce, r0, n, op.flip, inv_d, rr, x,
+                              have_x, part, stream);
         const bool had_x = have_x;
         have_x = true;
         apply(op, x, nullptr, b, r, nullptr);
@@ -729,7 +740,8 @@ int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, co
                 hipSuccess ||
             hipStreamSynchronize(stream) != hipSuccess || hipGetLastError() != hipSuccess)
             return WWBI_EHIP;
-        if (hsmall->status == kSmallAborted) return had_x ? kTwoGridPart : kTwoGridNone;
+        if (hsmall->status == kSmallAborted || hsmall->aborted)
+            return had_x ? kTwoGridPart : kTwoGridNone;
         double s2 = 0.0;
         for (int i = 0; i < G; ++i) s2 += h[i];
         const double rn = std::sqrt(s2);
@@ -757,6 +769,118 @@ int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, co
         if (pass > 0 && !(rn < 0.05 * prev)) break;
         prev = rn;
         rr = r;
+    }
+    return status;
+}
+
+// The right-hand sides share the coarse matrix (one launch solves all their
+// coarse systems), K_hH and A64, each read once a pass on the matrix cores.
+int Ctx::two_grid_multi(const double *A64, long ld, double *K, size_t kcap, const double *B,
+                        double *X, int nr, const wwbi_opts &o, SolveStats &st) {
+    Coarse C;
+    if (o.max_iter < 200 || !choose_coarse(0, C) || !ensure_small(nr)) return kTwoGridNone;
+    const int n = L.n, n0 = L.off[1], nc = C.n;
+    const long ldc = round_up(nc, 64), ldv = round_up(n, 64);
+    if ((size_t)n * ldc > kcap || ensure_coarse(n, nr) ||
+        grow(mw.part, mw.cpart, (size_t)multi_part_size_rect64(n, nc, nr) + 64))
+        return kTwoGridNone;
+    const int G = gmres_nblocks(n);
+    MultiWS &m = mw;
+    const Bat bt{nr, 0, 0, ldv, 64, 0, 0};
+    const double *h = (const double *)hst;
+    static_assert(kMaxMulti * 128 * sizeof(double) <= kHostStaging, "host staging");
+    launch_coarse_map(C, cmap, cfac, stream);
+    launch_assemble_coarse(N, hrow, kCoarseA, cmap, cfac, nc, 1, cA, ldc, stream);
+    launch_assemble_interp(N, cmap, cfac, nc, 1, K, ldc, stream);
+    launch_roughness(B, ldv, n, nr, m.part, stream);
+    if (hipMemcpyAsync(hst, m.part, (size_t)nr * 128 * sizeof(double), hipMemcpyDeviceToHost,
+                       stream) != hipSuccess ||
+        hipStreamSynchronize(stream) != hipSuccess)
+        return WWBI_EHIP;
+    std::vector<double> bn(nr), rn(nr);
+    bool rough = false;
+    for (int s = 0; s < nr; ++s) {
+        double s2 = 0.0, d2 = 0.0;
+        for (int i = 0; i < 64; ++i) { s2 += h[s * 128 + i]; d2 += h[s * 128 + 64 + i]; }
+        if (!std::isfinite(s2)) return kTwoGridNone;
+        bn[s] = std::sqrt(s2);
+        rough = rough || d2 > 0.05 * s2;
+    }
+    auto residual = [&]() {
+        launch_mfma_multi64(A64, ld, n, X, ldv, nr, B, ldv, m.rr, ldv, m.part, n0, stream);
+    };
+    const double *R = B;
+    if (rough) {
+        launch_scale_copy((int)(nr * ldv), B, 2.0, X, stream);
+        residual();
+        R = m.rr;
+    }
+    int status = kTwoGridPart;
+    double gain = 0.03 * o.tol, prev = HUGE_VAL;
+    for (int pass = 0; pass < 6; ++pass) {
+        SmallArgs a{};
+        if (!take_tags(1024, a.tag)) break;
+        a.A = cA;
+        a.ld = ldc;
+        a.n = nc;
+        a.flip = C.off[1];
+        a.b = R;
+        a.bs = ldv;
+        a.map = cmap;
+        a.x = ce;
+        a.xs = ldc;
+        a.tol = std::max(gain, 5e-16);
+        a.steps = 1024;
+        a.max_iter = 512;
+        a.verify = nc > kSmallMax ? 1 : 0;
+        a.max_cycles = a.verify ? 16 : 1;
+        a.xch = xch + 8;
+        a.xchs = small_exchange_words();
+        a.abort_tag = reinterpret_cast<unsigned *>(xch);
+        a.out = dsmall;
+        for (int s = 0; s < nr; ++s) { hsmall[s].status = kSmallAborted; hsmall[s].aborted = 0; }
+        if (launch_small_gmres(a, nr, stream) != WWBI_OK) return WWBI_EHIP;
+        // x (+)= 2 (r - S K e)
+        launch_mfma_rect64(K, ldc, n, nc, ce, ldc, nr, m.d, ldv, m.part, stream, R, ldv, n0);
+        if (R == B)
+            launch_scale_copy((int)(nr * ldv), m.d, 2.0, X, stream);
+        else
+            launch_axpy(X, m.d, (int)(nr * ldv), 2.0, stream);
+        residual();
+        R = m.rr;
+        launch_norm_partial(m.rr, n, m.nrm, G, stream, bt);
+        if (hipMemcpyAsync(hst, m.nrm, sizeof(double) * 64 * nr, hipMemcpyDeviceToHost, stream) !=
+                hipSuccess ||
+            hipStreamSynchronize(stream) != hipSuccess || hipGetLastError() != hipSuccess)
+            return WWBI_EHIP;
+        double worst = 0.0;
+        int its = 0;
+        gain = 0.1;
+        for (int s = 0; s < nr; ++s) {
+            if (hsmall[s].status == kSmallAborted || hsmall[s].aborted) return kTwoGridNone;
+            double s2 = 0.0;
+            for (int i = 0; i < G; ++i) s2 += h[s * 64 + i];
+            rn[s] = std::sqrt(s2);
+            if (!std::isfinite(rn[s])) return kTwoGridNone;
+            if (bn[s] > 0.0) worst = std::max(worst, rn[s] / bn[s]);
+            if (rn[s] > 0.0) gain = std::min(gain, 0.1 * o.tol * bn[s] / rn[s]);
+            its = std::max(its, hsmall[s].its);
+        }
+        st.iters += its;
+        st.cycles += 1;
+        if (o.precision == WWBI_FP32_REFINED) {
+            st.refine_steps += 1;
+            if (pass == 0) note_resid(1.0);
+            note_resid(worst);
+        }
+        st.rel_resid = worst;
+        if (trace)
+            std::fprintf(stderr, "wwbi: two-grid %d systems n %d coarse %d pass %d its %d rel_resid %.3e\n",
+                         nr, n, nc, pass, its, worst);
+        status = worst <= o.tol ? WWBI_OK : kTwoGridPart;
+        if (status == WWBI_OK && worst <= std::max(kTwoGridMargin * o.tol, 4e-16)) break;
+        if (pass > 0 && !(worst < 0.05 * prev)) break;
+        prev = worst;
     }
     return status;
 }
@@ -1192,6 +1316,43 @@ int Ctx::gmres_multi(int kind, int n, long ld, const double *B, double *X, int n
     return status;
 }
 
+// The matrices of a multi-vector solve, but for the FP32 one where the
+// two-grid iteration may do without it.
+void Ctx::assemble_multi(int n, long ld, const wwbi_opts &o, bool stored64) {
+    const bool fp32 = o.precision == WWBI_FP32_REFINED;
+    if (fp32 && !(stored64 && have_strips))
+        launch_assemble32(L, N, o.flags, o.band, (float *)A, ld, stream);
+    if (!fp32) launch_assemble64(L, N, o.flags, (double *)A, ld, stream);
+    else if (stored64) launch_assemble64(L, N, o.flags, A64, ld, stream);
+}
+
+// mw.x from mw.b: two-grid where it applies, else batched GMRES.  K_hH goes
+// where the FP32 matrix would be, or to the buffer of the FP64 copy.
+int Ctx::solve_multi(int n, long ld, int nr, const wwbi_opts &o, bool stored64, SolveStats &st) {
+    const bool fp32 = o.precision == WWBI_FP32_REFINED;
+    if (have_strips && (!fp32 || stored64)) {
+        const size_t kw = (size_t)n * round_up(std::min(kSmallCoarseMax, n / 2), 64);
+        const int rc = fp32 ? ensure_matrix(kw * 8) : ensure_matrix64(kw * 8);
+        int s = kTwoGridNone;
+        if (rc == WWBI_OK)
+            s = fp32 ? two_grid_multi(A64, ld, (double *)A, kw, mw.b, mw.x, nr, o, st)
+                     : two_grid_multi((const double *)A, ld, A64, kw, mw.b, mw.x, nr, o, st);
+        if (s == WWBI_OK || s < 0) return s;
+        st = SolveStats{};
+        hist.clear();
+        if (fp32) {
+            if (rc != WWBI_OK) {      // the FP32 matrix went with the failed allocation
+                const int e = ensure_matrix((size_t)n * ld * 4);
+                if (e) return e;
+            }
+            launch_assemble32(L, N, o.flags, o.band, (float *)A, ld, stream);
+        }
+    }
+    if (fp32) return refine_multi(n, ld, mw.b, mw.x, nr, o, stored64, st);
+    return gmres_multi(OP_A_S64, n, ld, mw.b, mw.x, nr, o.tol, o.restart, o.max_iter,
+                       o.poll_every, true, st);
+}
+
 // FP64 refinement of nr systems around batched FP32 inner solves.  With
 // stored64 the FP64 residuals of all systems come from one matrix-core pass
 // over the FP64 copy A64; otherwise each is formed on the fly.
@@ -1389,6 +1550,11 @@ int wwbi_reserve(wwbi_ctx *ctx, int64_t max_unknowns, int32_t max_restart, int32
         const size_t ld = round_up((long)max_unknowns, 64);
         const size_t es = precision == WWBI_FP64 ? 8 : 4;
         rc = c->ensure_matrix((size_t)max_unknowns * ld * es);
+        // the one-launch solves and the coarse systems of the default path
+        if (!rc) rc = c->ensure_small(1) ? c->ensure_coarse((int)max_unknowns) : WWBI_ECAPACITY;
+        // small systems are stored in FP64 whichever precision is asked for
+        const size_t ns = (size_t)std::min<int64_t>(max_unknowns, kSmallMax);
+        if (!rc) rc = c->ensure_matrix(ns * round_up((long)ns, 64) * 8);
     }
     return rc;
 }
@@ -2209,6 +2375,7 @@ int wwbi_tangent_phi(wwbi_ctx *ctx, const wwbi_geom *g, const double *omega, int
     if (!rc) {
         c->restart_cap = std::max(c->restart_cap, o->restart);
         c->begin_report((o->flags & WWBI_FLAG_PROFILE) != 0);
+        c->want_coarse = o->matvec == WWBI_MATVEC_AUTO && !(o->flags & WWBI_FLAG_NO_CORRECTION);
         // the directions are checked for finite values with the geometry
         rc = c->setup(g, dirs, (int)(7L * nd * g->M[0]), false);
     }
@@ -2242,12 +2409,7 @@ int wwbi_tangent_phi(wwbi_ctx *ctx, const wwbi_geom *g, const double *omega, int
     rc = c->ensure_matrix((size_t)n * ld * (fp32 ? 4 : 8));
     if (rc) { c->finish_report(rep, rc, st, 0); return rc; }
     const bool stored64 = fp32 && c->ensure_matrix64((size_t)n * ld * 8) == WWBI_OK;
-    if (fp32) {
-        launch_assemble32(c->L, c->N, o->flags, o->band, (float *)c->A, ld, sm);
-        if (stored64) launch_assemble64(c->L, c->N, o->flags, c->A64, ld, sm);
-    } else {
-        launch_assemble64(c->L, c->N, o->flags, (double *)c->A, ld, sm);
-    }
+    c->assemble_multi(n, ld, *o, stored64);
     hipEventRecord(c->ev[2], sm);
     rc = c->setup_check();
     if (rc) {
@@ -2263,12 +2425,7 @@ int wwbi_tangent_phi(wwbi_ctx *ctx, const wwbi_geom *g, const double *omega, int
     launch_tlm_cols(c->N, n0, n, nd, dirs, omega, gam, wts, pA, pT, sm);
     launch_tlm_rhs(c->N, c->F, n0, n, nd, dirs, omega, gam, U, prow, pA, pT, c->mw.b, ldv, um,
                    sm);
-    int status;
-    if (!fp32)
-        status = c->gmres_multi(OP_A_S64, n, ld, c->mw.b, c->mw.x, nd, o->tol, o->restart,
-                                o->max_iter, o->poll_every, true, st);
-    else
-        status = c->refine_multi(n, ld, c->mw.b, c->mw.x, nd, *o, stored64, st);
+    const int status = c->solve_multi(n, ld, nd, *o, stored64, st);
     hipEventRecord(c->ev[3], sm);
     if (status >= 0) {
         // dU_i = (um_i + H d gamma_0,i / 2 + T d gamma_i) / s, d gamma_i = Gamma d omega_i,
@@ -2328,6 +2485,8 @@ int wwbi_solve_phi_multi(wwbi_ctx *ctx, const wwbi_geom *g, const double *rhs, i
         if (!rc) {
             c->restart_cap = std::max(c->restart_cap, o->restart);
             c->begin_report((o->flags & WWBI_FLAG_PROFILE) != 0);
+            c->want_coarse =
+                o->matvec == WWBI_MATVEC_AUTO && !(o->flags & WWBI_FLAG_NO_CORRECTION);
             rc = c->setup(g, rhs, (int)(ntot * nr));
         }
     }
@@ -2347,19 +2506,9 @@ int wwbi_solve_phi_multi(wwbi_ctx *ctx, const wwbi_geom *g, const double *rhs, i
     // the refined path also keeps an FP64 copy for the residuals of all
     // systems in one pass; without room for it they are formed on the fly
     const bool stored64 = fp32 && c->ensure_matrix64((size_t)n * ld * 8) == WWBI_OK;
-    if (fp32) {
-        launch_assemble32(c->L, c->N, o->flags, o->band, (float *)c->A, ld, sm);
-        if (stored64) launch_assemble64(c->L, c->N, o->flags, c->A64, ld, sm);
-    } else {
-        launch_assemble64(c->L, c->N, o->flags, (double *)c->A, ld, sm);
-    }
+    c->assemble_multi(n, ld, *o, stored64);
     hipEventRecord(c->ev[2], sm);
-    int status;
-    if (!fp32)
-        status = c->gmres_multi(OP_A_S64, n, ld, c->mw.b, c->mw.x, nr, o->tol, o->restart,
-                                o->max_iter, o->poll_every, true, st);
-    else
-        status = c->refine_multi(n, ld, c->mw.b, c->mw.x, nr, *o, stored64, st);
+    const int status = c->solve_multi(n, ld, nr, *o, stored64, st);
     hipEventRecord(c->ev[3], sm);
     if (status >= 0) launch_copy_strided(c->mw.x, ldv, omega, n, n, nr, sm);
     hipEventRecord(c->ev[4], sm);

@@ -238,9 +238,11 @@ struct Ctx {
                      int restart, int max_iter, SolveStats &st, int &status);
     // words and results for nsys one-launch solves; false when out of memory
     bool ensure_small(int nsys);
+    int ensure_coarse(int n, int nsys = 1);
     bool take_tags(long need, unsigned &first);
     // Coarse grid for boundaries k0.. of the current geometry, resolving its
-    // strips to the best of a few accuracies that fits; false when none does or the grid is no coarser than half the nodes
+    // strips to the best of a few accuracies that fits; false when none does
+    // or the grid would be no coarser than half the nodes
     bool choose_coarse(int k0, Coarse &C) const;
     // Two-grid iteration (kernels_coarse.hip) for the operator of `mode`, op
     // its on-the-fly FP64 form, from a zero start: kTwoGridNone when it does
@@ -248,6 +250,12 @@ struct Ctx {
     // iterate, WWBI_OK when ||b - op x|| <= tol ||b||, or an error (< 0)
     int two_grid(int mode, const Op &op, int k0, const double *b, double *x, const wwbi_opts &o,
                  bool check_rough, SolveStats &st);
+    // The same for nr systems with A and stored matrices: A64 (row stride ld)
+    // for the residuals, K (n x coarse unknowns) for the corrections
+    int two_grid_multi(const double *A64, long ld, double *K, size_t kcap, const double *B,
+                       double *X, int nr, const wwbi_opts &o, SolveStats &st);
+    void assemble_multi(int n, long ld, const wwbi_opts &o, bool stored64);
+    int solve_multi(int n, long ld, int nr, const wwbi_opts &o, bool stored64, SolveStats &st);
     // Solve one second-kind system: two-grid, then (or instead) GMRES or
     // refinement on the stored matrix, which `assemble(fp32)` forms when
     // `assembled` is not yet set

@@ -362,11 +362,12 @@ void launch_adj_finalize(const Nodes &N, const Flow &F, int n0, const double *Ub
 constexpr int kSmallMax = 1024;
 constexpr int kSmallCoarseMax = 2048;
 constexpr int kSmallFullCycle = 640;   // the basis of 27 steps fits
-constexpr int kSmallAborted = -100;    // the blocks did not run together: solve otherwise
+constexpr int kSmallAborted = -100;
 struct SmallRes {
     int status;            // WWBI_OK, WWBI_NOT_CONVERGED, WWBI_STAGNATED or kSmallAborted
     int its, cycles;       // Arnoldi steps and cycles
     int nhist;
+    int aborted;           // the blocks did not run together: solve otherwise
     double bnorm, resid;   // ||b|| and the last residual norm (an estimate without verify)
     double hist[WWBI_HIST_MAX];   // true residual over ||b|| at every cycle start
 };
@@ -411,16 +412,20 @@ void launch_coarse_map(const Coarse &C, int *map, double *fac, hipStream_t st);
 void launch_assemble_coarse(const Nodes &N, const double *hrow, int mode, const int *map,
                             const double *fac, int n, int corr, double *out, long ld,
                             hipStream_t st);
-// x (+)= (r - S K_hH e) / d on nodes r0 .. r0 + nr for nsys systems (strides
-// es, rs, xs); part: nsys * coarse_slices(nr, n) * nr doubles
+// K_hH of A for all nodes: N.n x n, its padding columns zero
+void launch_assemble_interp(const Nodes &N, const int *map, const double *fac, int n, int corr,
+                            double *out, long ld, hipStream_t st);
+// x (+)= (r - S K_hH e) / d on nodes r0 .. r0 + nr; part: coarse_slices(nr, n)
+// * nr doubles
 int coarse_slices(int nr, int n);
 void launch_coarse_correct(const Nodes &N, const double *hrow, int mode, const int *map,
-                           const double *fac, int n, int corr, const double *e, long es, int r0,
-                           int nr, int flip, double inv_d, const double *r, long rs, double *x,
-                           long xs, bool add, double *part, int nsys, hipStream_t st);
+                           const double *fac, int n, int corr, const double *e, int r0, int nr,
+                           int flip, double inv_d, const double *r, double *x, bool add,
+                           double *part, hipStream_t st);
 void launch_scale_copy(int n, const double *b, double a, double *x, hipStream_t st);
-// out[0..63] and out[64..127]: partial sums of b^2 and of its squared differences
-void launch_roughness(const double *b, int n, double *out, hipStream_t st);
+// out[0..63] and out[64..127]: partial sums of b^2 and of its squared
+// differences; 128 per system, the right-hand sides bs apart
+void launch_roughness(const double *b, long bs, int n, int nsys, double *out, hipStream_t st);
 
 // ---- kernels_multi.hip -------------------------------------------------------
 // Y_s = c_s - S A X_s (or S A X_s when c is null), S negating rows [0, flip),
@@ -443,10 +448,12 @@ int launch_mfma_parts64(const double *A, long ld, int n, const double *X, long x
                         double *part, hipStream_t st);
 int launch_mfma_parts32(const float *A, long ld, int n, const float *X, long xs, int nr,
                         double *part, hipStream_t st);
-// y_s = T X_s, s < nr, for an FP64 m x n matrix T (row stride ld, a multiple
-// of 64 columns readable past n); part needs multi_part_size_rect64(m, n, nr).
+// y_s = T X_s, or c_s - S T X_s, s < nr, for an FP64 m x n matrix T (row stride
+// ld, a multiple of 64 columns readable past n); part needs
+// multi_part_size_rect64(m, n, nr).
 void launch_mfma_rect64(const double *A, long ld, int m, int n, const double *X, long xs, int nr,
-                        double *y, long ys, double *part, hipStream_t st);
+                        double *y, long ys, double *part, hipStream_t st,
+                        const double *c = nullptr, long cs = 0, int flip = 0);
 int multi_part_size_rect64(int m, int n, int nr);
 
 // ---- kernels_gmres.hip -------------------------------------------------------

@@ -135,6 +135,25 @@ __global__ __launch_bounds__(256) void k_assemble_coarse(Nodes N, const double *
     out[(long)i * ld + j] = v;
 }
 
+// K_hH of A for many right-hand sides: rows of all n0 nodes, the coarse nodes'
+// columns, a column per lane and kInterpRows rows per wave.
+constexpr int kInterpRows = 16;
+
+__global__ __launch_bounds__(256) void k_assemble_interp(Nodes N, const int *map,
+                                                         const double *fac, int rows, int n,
+                                                         int corr, double *out, long ld) {
+    const int j = blockIdx.x * 64 + (threadIdx.x & 63);
+    const int i0 = (blockIdx.y * 4 + (threadIdx.x >> 6)) * kInterpRows;
+    if (j >= ld) return;
+    Src s = load_src(N, map[j < n ? j : 0]);
+    s.w *= fac[j < n ? j : 0];
+    for (int i = i0; i < min(rows, i0 + kInterpRows); ++i) {
+        const Tgt t = load_tgt(N, i);
+        const double v = k_entry<kCoarseA>(N, t, s, corr != 0, nullptr);
+        out[(long)i * ld + j] = j < n ? v : 0.0;
+    }
+}
+
 // K_hH e_H: one output node per thread (rows r0 .. r0 + nr), the coarse
 // nodes of chunk blockIdx.y staged in LDS; slice blockIdx.y of `part`.  For
 // the transpose the outputs are sources and the coarse nodes targets.
@@ -144,14 +163,11 @@ template <int MODE>
 __global__ __launch_bounds__(256) void k_coarse_product(Nodes N, const double *hrow,
                                                         const int *map, const double *fac, int n,
                                                         int r0, int nr, int chunk, int corr,
-                                                        const double *e, long es, double *part,
-                                                        long ps) {
+                                                        const double *e, double *part) {
     constexpr bool T = MODE == kCoarseAT;
     __shared__ Src ss[T ? 1 : kCoarseStage];
     __shared__ Tgt ts[T ? kCoarseStage : 1];
     __shared__ double se[kCoarseStage];
-    e += blockIdx.z * es;
-    part += blockIdx.z * ps;
     const int r = blockIdx.x * 256 + threadIdx.x;
     const bool live = r < nr;
     const int me = r0 + (live ? r : 0);
@@ -184,14 +200,10 @@ __global__ __launch_bounds__(256) void k_coarse_product(Nodes N, const double *h
 // x (+)= (r - S K_hH e_H) / d on every node: the slices summed in order, the
 // sums of rows [0, flip) negated.
 __global__ __launch_bounds__(64 * kSliceWaves) void k_coarse_finish(int nr, const double *part,
-                                                                    long ps, int ns, int flip,
+                                                                    int ns, int flip,
                                                                     double inv_d, const double *r,
-                                                                    long rs, double *x, long xs,
-                                                                    int add) {
+                                                                    double *x, int add) {
     __shared__ double red[kSliceWaves][64];
-    part += blockIdx.y * ps;
-    r += blockIdx.y * rs;
-    x += blockIdx.y * xs;
     const int i = blockIdx.x * 64 + (threadIdx.x & 63);
     double s = sum_slices_waves<kSliceWaves>(part, ns, nr, i, i < nr, red);
     if (threadIdx.x >= 64 || i >= nr) return;
@@ -206,10 +218,13 @@ __global__ void k_scale_copy(int n, const double *b, double a, double *x) {
     if (i < n) x[i] = a * b[i];
 }
 
-// out[0..63]: partial sums of b^2, out[64..127]: of (b_{i+1} - b_i)^2 scaled
-// to tell a sampled smooth function (far below b^2) from noise (about 2 b^2)
-__global__ __launch_bounds__(256) void k_roughness(const double *b, int n, double *out) {
+// Per system out[0..63]: partial sums of b^2, out[64..127]: of
+// (b_{i+1} - b_i)^2, to tell a sampled smooth function (far below b^2) from noise (about 2 b^2)
+__global__ __launch_bounds__(256) void k_roughness(const double *b, long bs, int n,
+                                                   double *out) {
     __shared__ double sh[8];
+    b += blockIdx.y * bs;
+    out += blockIdx.y * 128;
     double s = 0.0, d = 0.0;
     for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) {
         const double v = b[i], w = i + 1 < n ? b[i + 1] - v : 0.0;
@@ -262,31 +277,36 @@ void launch_assemble_coarse(const Nodes &N, const double *hrow, int mode, const 
     }
 }
 
+void launch_assemble_interp(const Nodes &N, const int *map, const double *fac, int n, int corr,
+                            double *out, long ld, hipStream_t st) {
+    hipLaunchKernelGGL(k_assemble_interp, dim3(cdiv(ld, 64), cdiv(N.n, 4 * kInterpRows)),
+                       dim3(256), 0, st, N, map, fac, N.n, n, corr, out, ld);
+}
+
 int coarse_slices(int nr, int n) { return cdiv(n, product_chunk(nr, n)); }
 
 void launch_coarse_correct(const Nodes &N, const double *hrow, int mode, const int *map,
-                           const double *fac, int n, int corr, const double *e, long es, int r0,
-                           int nr, int flip, double inv_d, const double *r, long rs, double *x,
-                           long xs, bool add, double *part, int nsys, hipStream_t st) {
+                           const double *fac, int n, int corr, const double *e, int r0, int nr,
+                           int flip, double inv_d, const double *r, double *x, bool add,
+                           double *part, hipStream_t st) {
     const int chunk = product_chunk(nr, n), ns = cdiv(n, chunk);
-    const long ps = (long)ns * nr;
-    const dim3 grid(cdiv(nr, 256), ns, nsys);
+    const dim3 grid(cdiv(nr, 256), ns);
     switch (mode) {
-    case kCoarseA: hipLaunchKernelGGL(k_coarse_product<kCoarseA>, grid, dim3(256), 0, st, N, hrow, map, fac, n, r0, nr, chunk, corr, e, es, part, ps); break;
-    case kCoarseAT: hipLaunchKernelGGL(k_coarse_product<kCoarseAT>, grid, dim3(256), 0, st, N, hrow, map, fac, n, r0, nr, chunk, corr, e, es, part, ps); break;
-    case kCoarseGt: hipLaunchKernelGGL(k_coarse_product<kCoarseGt>, grid, dim3(256), 0, st, N, hrow, map, fac, n, r0, nr, chunk, corr, e, es, part, ps); break;
-    default: hipLaunchKernelGGL(k_coarse_product<kCoarseWall>, grid, dim3(256), 0, st, N, hrow, map, fac, n, r0, nr, chunk, corr, e, es, part, ps); break;
+    case kCoarseA: hipLaunchKernelGGL(k_coarse_product<kCoarseA>, grid, dim3(256), 0, st, N, hrow, map, fac, n, r0, nr, chunk, corr, e, part); break;
+    case kCoarseAT: hipLaunchKernelGGL(k_coarse_product<kCoarseAT>, grid, dim3(256), 0, st, N, hrow, map, fac, n, r0, nr, chunk, corr, e, part); break;
+    case kCoarseGt: hipLaunchKernelGGL(k_coarse_product<kCoarseGt>, grid, dim3(256), 0, st, N, hrow, map, fac, n, r0, nr, chunk, corr, e, part); break;
+    default: hipLaunchKernelGGL(k_coarse_product<kCoarseWall>, grid, dim3(256), 0, st, N, hrow, map, fac, n, r0, nr, chunk, corr, e, part); break;
     }
-    hipLaunchKernelGGL(k_coarse_finish, dim3(cdiv(nr, 64), nsys), dim3(64 * kSliceWaves), 0, st,
-                       nr, part, ps, ns, flip, inv_d, r, rs, x, xs, add ? 1 : 0);
+    hipLaunchKernelGGL(k_coarse_finish, dim3(cdiv(nr, 64)), dim3(64 * kSliceWaves), 0, st, nr,
+                       part, ns, flip, inv_d, r, x, add ? 1 : 0);
 }
 
 void launch_scale_copy(int n, const double *b, double a, double *x, hipStream_t st) {
     hipLaunchKernelGGL(k_scale_copy, dim3(cdiv(n, 256)), dim3(256), 0, st, n, b, a, x);
 }
 
-void launch_roughness(const double *b, int n, double *out, hipStream_t st) {
-    hipLaunchKernelGGL(k_roughness, dim3(64), dim3(256), 0, st, b, n, out);
+void launch_roughness(const double *b, long bs, int n, int nsys, double *out, hipStream_t st) {
+    hipLaunchKernelGGL(k_roughness, dim3(64, nsys), dim3(256), 0, st, b, bs, n, out);
 }
 
 }  // namespace wwbi

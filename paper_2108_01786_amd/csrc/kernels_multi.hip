@@ -427,8 +427,9 @@ int launch_mfma_parts32(const float *A, long ld, int n, const float *X, long xs,
 }
 
 void launch_mfma_rect64(const double *A, long ld, int m, int n, const double *X, long xs, int nr,
-                        double *y, long ys, double *part, hipStream_t st) {
-    launch_mfma_multi<double>(A, ld, m, n, X, xs, nr, nullptr, 0, y, ys, part, 0, st);
+                        double *y, long ys, double *part, hipStream_t st, const double *c, long cs,
+                        int flip) {
+    launch_mfma_multi<double>(A, ld, m, n, X, xs, nr, c, cs, y, ys, part, flip, st);
 }
 
 void launch_to_f32_batched(const double *src, long ss, float *dst, long ds, int n, int nr,

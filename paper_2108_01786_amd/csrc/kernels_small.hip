@@ -21,7 +21,7 @@
 // caller's counter), so nothing has to be cleared.
 //
 // A poll gives up after kSpinTicks of the constant-rate clock or when another
-// block has given up; the kernel then ends with kSmallAborted and the caller
+// block has given up; the result is then marked as aborted and the caller
 // solves by the multi-kernel loop.  That can only happen when the blocks of
 // one launch are kept from running together for that long, by other work
 // filling the device.
@@ -152,6 +152,7 @@ __global__ __launch_bounds__(kTS, 2) void k_small_gmres(SmallArgs a) {
         }
         if (quit) {
             stop = 2;
+            a.out[sys].aborted = 1;        // whatever block 0 reports
             __hip_atomic_store(a.abort_tag, a.tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         ++tag;
@@ -387,6 +388,18 @@ int launch_small_gmres(SmallArgs a, int nsys, hipStream_t st) {
     // within 144 registers a lane and a launch within 32 blocks (of whole
     // systems; 128 at the largest coarse one)
     const int cpl = (cdiv(a.n, 64) + 1) / 2 * 2;
+    // A block's basis fills the LDS of its CU.  Where many systems would not
+    // all be resident, more rows per wave run more of them at once (32 of 512
+    // unknowns: 8 blocks each, one round of 256 blocks instead of four).
+    if (nsys > 1 && cpl <= 10 && (long)nsys * cdiv(a.n, 2 * kWS) > 256) {
+        switch (cpl) {
+        case 2: return launch_cpl<2, 8>(a, nsys, st);
+        case 4: return launch_cpl<4, 8>(a, nsys, st);
+        case 6: return launch_cpl<6, 8>(a, nsys, st);
+        case 8: return launch_cpl<8, 8>(a, nsys, st);
+        default: return launch_cpl<10, 10>(a, nsys, st);
+        }
+    }
     switch (cpl) {
     case 2: return launch_cpl<2, 2>(a, nsys, st);
     case 4: return launch_cpl<4, 2>(a, nsys, st);

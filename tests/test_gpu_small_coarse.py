@@ -134,3 +134,42 @@ def test_two_grid_is_deterministic(ww, ctx):
     runs = [ctx.solve_phi(dg, p, poll_every=k)[:2] for k in (1, 2, 7)]
     for U, om in runs[1:]:
         assert torch.equal(U, runs[0][0]) and torch.equal(om, runs[0][1])
+
+
+# one system tile, its edge, past it, and both sides of the counts that change
+# the rows per wave of the coarse solves
+@pytest.mark.parametrize("M0,M1,Mo,gap", GRIDS)
+@pytest.mark.parametrize("prec", ["fp64", "refined"])
+@pytest.mark.parametrize("nr", [1, 7, 17, 32])
+def test_two_grid_many_matches_stored(ww, ctx, M0, M1, Mo, gap, prec, nr):
+    geom, phi = cell(M0, M1, Mo, gap, seed=M0)
+    n = geom.Mtot
+    print(f"case two-grid n={n} gap={gap} {prec} systems={nr}", flush=True)
+    fp64 = prec == "fp64"
+    kw = dict(precision=ww.FP64 if fp64 else ww.FP32_REFINED, tol=1e-14, check=False)
+    st = dict(kw, matvec=ww.MATVEC_STORED)
+    bar = 1e-11 if fp64 else 1e-10
+    dg = ww.DeviceGeometry.from_synth(geom, DEV)
+    rng = np.random.default_rng(nr)
+    # smooth right-hand sides, then one that is noise, one that is zero
+    t = 2 * np.pi * np.arange(n) / n
+    rhs = np.stack([np.exp(np.sin(t + j)) * np.cos((j % 5 + 1) * t) for j in range(nr)])
+    for part in ("smooth", "mixed"):
+        if part == "mixed":
+            rhs[-1] = rng.standard_normal(n)
+            rhs[0] *= 0.0 if nr > 1 else 1.0
+        b = torch.as_tensor(rhs, device=DEV)
+        om, r = ctx.solve_phi_multi(dg, b, **kw)
+        oms, rs = ctx.solve_phi_multi(dg, b, **st)
+        assert r.status == ww.OK and r.rel_resid <= kw["tol"]
+        for a, c in zip(om, oms):
+            assert float((a - c).abs().max()) <= bar * max(1e-300, float(c.abs().max()))
+    p = torch.as_tensor(phi, device=DEV)
+    _, omega, _, _ = ctx.solve_phi(dg, p, **kw)
+    a0 = 2 * np.pi * np.arange(M0) / M0
+    dirs = np.stack([[np.sin((j + k % 3 + 1) * a0 + k) for j in range(nr)] for k in range(7)])
+    d = torch.as_tensor(dirs, device=DEV)
+    dU, dom, rt = ctx.tangent_phi(dg, omega, d, want_omega=True, **kw)
+    dUs, doms, _ = ctx.tangent_phi(dg, omega, d, want_omega=True, **st)
+    assert rt.rel_resid <= kw["tol"]
+    assert rel(dom, doms) <= bar and rel(dU, dUs) <= 10 * bar
