@@ -211,19 +211,16 @@ int Ctx::setup(const wwbi_geom *g, const double *phi, int nphi, bool check) {
     N.ex = eR; N.ey = eI; N.exl = eRl; N.eyl = eIl; N.cell = cell; N.nlist = nlist;
     N.n = L.n;
     psi_wall = g->psi_wall;
-    launch_prep_nodes(L, g->x, g->y, g->dx, g->dy, g->ddx, g->ddy, bid, loc, Mk, wq, s, lre, lim,
-                      eR, eI, eRl, eIl, stream);
-    launch_cells(N, cell, stream);
-    launch_circulant_rows(L, kOpHalfCot, hrow, stream);
     N.near = 0;
     val_blocks = validate_data_blocks(phi ? nphi : 0);
-    launch_validate(L, N, phi, phi ? nphi : 0, val, stream);   // also zeroes val[4 nb + 1]
-    launch_near_cells(N, nlist, val + 4 * L.nb + 1, stream);
     have_strips = want_coarse && L.n > kSmallMax && !fixed_ws && !profiling;
     want_coarse = false;     // set anew by each call that can use it
-    if (have_strips)
-        launch_strip(L, N, reinterpret_cast<unsigned long long *>(val + 4 * L.nb + 2 + val_blocks),
-                     stream);
+    unsigned long long *strips =
+        have_strips ? reinterpret_cast<unsigned long long *>(val + 4 * L.nb + 2 + val_blocks)
+                    : nullptr;
+    const SetupOut so{bid, loc, Mk, wq, s, lre, lim, eR, eI, eRl, eIl, rowD, rowH, hrow, cell};
+    launch_setup(L, N, so, phi, phi ? nphi : 0, val, strips, stream);
+    launch_near_cells(L, N, nlist, val + 4 * L.nb + 1, strips, stream);
     if (hipMemcpyAsync(hst, val,
                        sizeof(double) * (4 * L.nb + 2 + val_blocks + (have_strips ? L.nb : 0)),
                        hipMemcpyDeviceToHost, stream) != hipSuccess)
@@ -1585,8 +1582,6 @@ int solve_phi_impl(Ctx *c, const wwbi_geom *g, const double *phi, const wwbi_opt
     // the right-hand side, circulant rows and matrix go into internal buffers
     // only, so they are queued before the input checks are read back
     launch_rhs_phi(c->L, c->N, c->F, phi, c->psi_wall, b, c->stream);
-    launch_circulant_rows(c->L, WWBI_OP_D, c->rowD, c->stream);
-    launch_circulant_rows(c->L, WWBI_OP_H, c->rowH, c->stream);
     hipEventRecord(c->ev[1], c->stream);
     const bool stored = o->matvec != WWBI_MATVEC_ON_THE_FLY;
     auto assemble = [&](bool f32) -> int {
@@ -1693,7 +1688,6 @@ int wwbi_solve_gamma(wwbi_ctx *ctx, const wwbi_geom *g, const double *gamma0, co
     const int n = c->L.n, n0 = c->L.off[1], nw = n - n0;
     const long ldw = round_up(nw, 64);
     double *gam = c->vec[VG], *rhs = c->vec[VB], *um = c->vec[VUM];
-    launch_circulant_rows(c->L, WWBI_OP_H, c->rowH, c->stream);
     // wall right-hand side: -G_0k^dagger gamma_0 - s dphi_mv/dn on every wall
     launch_umv(c->N, c->F, n0, nw, um, c->stream);
     launch_rflavour(c->L, c->N, c->hrow, 2, 0, n0, nw, 0, n0, gamma0, c->part, nullptr, c->stream);
@@ -1751,8 +1745,6 @@ int wwbi_tangential_energy(wwbi_ctx *ctx, const wwbi_geom *g, const double *phi,
     hipStream_t sm = c->stream;
     const int n = c->L.n, n0 = c->L.off[1];
     double *gam = c->vec[VG], *tm = c->vec[VUM], *hg = c->vec[VHG];
-    launch_circulant_rows(c->L, WWBI_OP_D, c->rowD, sm);
-    launch_circulant_rows(c->L, WWBI_OP_H, c->rowH, sm);
     launch_tmv(c->N, c->F, 0, n, tm, sm);
     hipEventRecord(c->ev[1], sm);
     hipEventRecord(c->ev[2], sm);
@@ -2075,8 +2067,6 @@ static void boundary_derivs(Ctx *c, const double *omega, double *sds, double *sd
     const Layout &L = c->L;
     const int n = L.n, n0 = L.off[1];
     double *gam = c->vec[VG], *hg = c->vec[VHG], *tm = c->vec[VTM], *um = c->vec[VUM];
-    launch_circulant_rows(L, WWBI_OP_D, c->rowD, sm);
-    launch_circulant_rows(L, WWBI_OP_H, c->rowH, sm);
     c->gamma_from_omega(omega, gam);
     launch_circulant_apply(L, c->rowH, gam, hg, 1.0, 0.0, 0, L.nb - 1, sm);
     launch_tmv(c->N, c->F, 0, n, tm, sm);
@@ -2299,8 +2289,6 @@ int wwbi_adjoint_phi(wwbi_ctx *ctx, const wwbi_geom *g, const double *omega, con
     const long ld = round_up(n, 64);
     double *gam = c->vec[VG], *U = c->vec[VTMP2], *cv = c->vec[VC], *gbar = c->vec[VTMP];
     double *mu = c->vec[VMU], *lam = c->vec[VLAM];
-    launch_circulant_rows(c->L, WWBI_OP_D, c->rowD, sm);
-    launch_circulant_rows(c->L, WWBI_OP_H, c->rowH, sm);
     hipEventRecord(c->ev[1], sm);
     // the transpose solve A^T lambda = mu; the stored path assembles A^T itself,
     // so that its products stream rows (the forward matvec, about 6% faster at
@@ -2399,8 +2387,6 @@ int wwbi_tangent_phi(wwbi_ctx *ctx, const wwbi_geom *g, const double *omega, int
     double *prow = c->apart, *pA = prow + (size_t)6 * nsr * n0, *pT = pA + (size_t)nsc * nd * n;
     double *um = pT + (size_t)nsc * nd * n0, *hgs = um + (size_t)nd * n0;
     double *tgs = hgs + (size_t)nd * n0, *wts = tgs + (size_t)nd * n0;
-    launch_circulant_rows(c->L, WWBI_OP_D, c->rowD, sm);
-    launch_circulant_rows(c->L, WWBI_OP_H, c->rowH, sm);
     hipEventRecord(c->ev[1], sm);
     // the nd systems share A: one multi-RHS solve (matrix read once per step).
     // The matrix goes into internal memory only, so it is queued before the

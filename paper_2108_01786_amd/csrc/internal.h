@@ -46,7 +46,7 @@ struct Nodes {
     const double *lre;     // Re{zeta''/(2 zeta')}
     const double *lim;     // Im{zeta''/(2 zeta')}
     // per cell of kCellNodes consecutive nodes: centre (2), radius of a disc
-    // holding their E values, and the largest |E| (k_cells)
+    // holding their E values, and the largest |E| (k_setup)
     const double *cell;
     const int *nlist;      // per cell: its near-pair list (kNearStride ints)
     int n;
@@ -135,20 +135,27 @@ constexpr int kOpHalfCot = 100;
 struct Ctx;   // host context (api.hip)
 
 // ---- kernels_geom.hip --------------------------------------------------------
-void launch_prep_nodes(const Layout &L, const double *x, const double *y, const double *dx,
-                       const double *dy, const double *ddx, const double *ddy, int *bid,
-                       int *loc, int *Mk, double *w, double *s, double *lre, double *lim,
-                       double *ex, double *ey, double *exl, double *eyl, hipStream_t st);
-void launch_cells(const Nodes &N, double *cell, hipStream_t st);
-void launch_near_cells(const Nodes &N, int *lists, double *count, hipStream_t st);
-// Input checks: per boundary k, out[4k..4k+3] = (non-finite samples, signed
-// area, mean x', samples beyond the height limit); out[4 nb + 1] = 0 (the
-// near-pair count, added by launch_near_cells); out[4 nb + 2 + b] for
+// Where the set-up's results go: the per-node data (see Nodes), the circulant
+// rows of D, H and (1/2) cot (a boundary's row laid out like its nodes), and
+// the cells' discs.
+struct SetupOut {
+    int *bid, *loc, *Mk;
+    double *w, *s, *lre, *lim, *eR, *eI, *eRl, *eIl, *rowD, *rowH, *hrow, *cell;
+};
+// The data derived from the samples N.x .. N.ddy, and the input checks in val:
+// per boundary k, val[4k..4k+3] = (non-finite samples, signed area, mean x',
+// samples beyond the height limit); val[4 nb + 1] = 0 (the near-pair count,
+// added by launch_near_cells); val[4 nb + 2 + b] for
 // b < validate_data_blocks(nphi): non-finite entries of the data array.
+// strips (may be null): nb words, set for launch_near_cells to lower.
 constexpr int kValidateBlocks = 64;
 int validate_data_blocks(int nphi);
-void launch_validate(const Layout &L, const Nodes &N, const double *phi, int nphi,
-                     double *out, hipStream_t st);
+void launch_setup(const Layout &L, const Nodes &N, const SetupOut &o, const double *phi, int nphi,
+                  double *val, unsigned long long *strips, hipStream_t st);
+// The cells' near-pair lists and count and, with strips, per boundary the bits
+// of the squared half-width of its nodes' strip of analyticity.
+void launch_near_cells(const Layout &L, const Nodes &N, int *lists, double *count,
+                       unsigned long long *strips, hipStream_t st);
 void launch_rhs_phi(const Layout &L, const Nodes &N, const Flow &F, const double *phi,
                     const double *psi_wall, double *b, hipStream_t st);
 void launch_umv(const Nodes &N, const Flow &F, int first, int count, double *out,
@@ -171,8 +178,6 @@ void launch_gt_surface(int n0, const Nodes &N, double tau, double grav, const do
 void launch_energy(int n0, const Nodes &N, const Flow &F, double tau, double grav,
                    const double *hw, const double *part, int nsplit, const double *dphi,
                    const double *tmv, const double *psi_k, double *e, double *E, hipStream_t st);
-// op: WWBI_OP_D, WWBI_OP_H or kOpHalfCot, one row per boundary laid out like the nodes
-void launch_circulant_rows(const Layout &L, int op, double *rows, hipStream_t st);
 // Fourier-tail measure of f on every boundary (Sec. 7.1's resolution test):
 // out[2k] = energy in the modes ceil(3 M_k / 8) .. M_k / 2 (both signs),
 // out[2k+1] = total energy; modes holds tail_modes_total(L) doubles.
@@ -406,8 +411,6 @@ struct Coarse {
     int c[kMaxB];
 };
 enum { kCoarseA = 0, kCoarseAT, kCoarseGt, kCoarseWall };
-// out[k]: bits of the squared strip half-width of boundary k (see k_strip)
-void launch_strip(const Layout &L, const Nodes &N, unsigned long long *out, hipStream_t st);
 void launch_coarse_map(const Coarse &C, int *map, double *fac, hipStream_t st);
 void launch_assemble_coarse(const Nodes &N, const double *hrow, int mode, const int *map,
                             const double *fac, int n, int corr, double *out, long ld,

@@ -21,7 +21,7 @@
 // L = zeta'' / (2 zeta'), alpha and 2 alpha_0 - alpha have the same zeta, so the
 // self kernel's nearest pole is about 1 / |L| away (on an ellipse of semi-axes
 // q > b exactly 2 atanh(b / q)).
-// k_strip takes the least of both over sampled nodes of every boundary; the
+// strip_block takes the least of both over sampled nodes of every boundary; the
 // host keeps m >= ln(1 / eps) / delta nodes of it (Ctx::choose_coarse).
 #include <algorithm>
 
@@ -33,55 +33,6 @@ namespace wwbi {
 namespace {
 
 inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
-
-constexpr int kStripSamples = 2048;      // sampled nodes, about
-
-// Node of sample s: sample counts per boundary are ceil(M_k / stride).
-__device__ __forceinline__ int sample_node(const Layout &L, int stride, int s) {
-    for (int k = 0; k < L.nb; ++k) {
-        const int M = L.off[k + 1] - L.off[k], cnt = (M + stride - 1) / stride;
-        if (s < cnt) return L.off[k] + s * stride;
-        s -= cnt;
-    }
-    return -1;
-}
-
-// One wave per sampled source q: the square of its strip estimate, the least
-// over the sampled targets on other boundaries, or half a radian or more
-// along its own, and the nodal term, into out[k] (bits of a positive double,
-// whose order is that of the integers; set to infinity by the caller).
-// |E_q - E_p|^2 / (|E_q| |E_p|) = |2 sin((zeta_q - zeta_p) / 2)|^2 is the
-// squared distance across the period.
-__global__ __launch_bounds__(256) void k_strip(Layout L, Nodes N, int stride, int count,
-                                               unsigned long long *out) {
-    const int lane = threadIdx.x & 63;
-    const int sq = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (sq >= count) return;
-    const int q = sample_node(L, stride, sq);
-    const double ex = N.ex[q], ey = N.ey[q], aq = ex * ex + ey * ey;
-    const int kq = N.bid[q], lq = N.loc[q], mq = N.Mk[q];
-    double best = HUGE_VAL;
-    for (int sp = lane; sp < count; sp += 64) {
-        const int p = sample_node(L, stride, sp);
-        if (N.bid[p] == kq && cyc_dist(N.loc[p], lq, mq) * 12 < mq) continue;
-        const double px = N.ex[p], py = N.ey[p];
-        const double dx = px - ex, dy = py - ey;
-        const double d2 = (dx * dx + dy * dy) / sqrt(aq * (px * px + py * py));
-        best = min(best, d2);
-    }
-    for (int o = 32; o > 0; o >>= 1) best = min(best, __shfl_xor(best, o, 64));
-    if (lane == 0) {
-        const double s = N.s[q], a = N.lre[q], b = N.lim[q];
-        best = min(best / (s * s), 1.0 / (a * a + b * b));
-        if (!(best > 0.0)) best = 0.0;      // also for a NaN
-        atomicMin(out + kq, (unsigned long long)__double_as_longlong(best));
-    }
-}
-
-__global__ void k_strip_init(int nb, unsigned long long *out) {
-    if ((int)threadIdx.x < nb)
-        out[threadIdx.x] = (unsigned long long)__double_as_longlong(HUGE_VAL);
-}
 
 // Fine node and weight factor of every coarse node.
 __global__ void k_coarse_map(Coarse C, int *map, double *fac) {
@@ -252,14 +203,6 @@ int product_chunk(int nr, int n) {
 }
 
 }  // namespace
-
-void launch_strip(const Layout &L, const Nodes &N, unsigned long long *out, hipStream_t st) {
-    const int stride = std::max(1, cdiv(L.n, kStripSamples));
-    int count = 0;
-    for (int k = 0; k < L.nb; ++k) count += cdiv(L.off[k + 1] - L.off[k], stride);
-    hipLaunchKernelGGL(k_strip_init, dim3(1), dim3(kMaxB), 0, st, L.nb, out);
-    hipLaunchKernelGGL(k_strip, dim3(cdiv(count, 4)), dim3(256), 0, st, L, N, stride, count, out);
-}
 
 void launch_coarse_map(const Coarse &C, int *map, double *fac, hipStream_t st) {
     hipLaunchKernelGGL(k_coarse_map, dim3(cdiv(C.n, 256)), dim3(256), 0, st, C, map, fac);

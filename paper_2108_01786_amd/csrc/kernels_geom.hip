@@ -18,34 +18,67 @@ __device__ __forceinline__ int find_block(const Layout &L, int p) {
     return k;
 }
 
-// Per-node data derived once per call: boundary index, local index, M_k,
-// weight 1/M_k, s = |zeta'| and the self limit zeta''/(2 zeta').
-__global__ void k_prep_nodes(Layout L, const double *x, const double *y, const double *dx,
-                             const double *dy, const double *ddx, const double *ddy, int *bid,
-                             int *loc, int *Mk, double *w, double *s, double *lre, double *lim,
-                             double *eR, double *eI, double *eRl, double *eIl) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= L.n) return;
-    const int k = find_block(L, p);
-    const int M = L.off[k + 1] - L.off[k];
-    bid[p] = k;
-    loc[p] = p - L.off[k];
-    Mk[p] = M;
-    w[p] = 1.0 / (double)M;
-    const double a = dx[p], b = dy[p], ex = ddx[p], ey = ddy[p];
-    const double d2 = a * a + b * b;
-    s[p] = sqrt(d2);
-    // zeta''/(2 zeta') = (ex + i ey)(a - i b) / (2 |zeta'|^2)
-    lre[p] = (ex * a + ey * b) / (2.0 * d2);
-    lim[p] = (ey * a - ex * b) / (2.0 * d2);
-    // E = e^{i zeta} = e^{-y} (cos x + i sin x) as a double-double, so that
-    // differences of E between nodes keep their relative accuracy
-    DD er, ei;
-    dd_expi(x[p], y[p], er, ei);
-    eR[p] = er.hi;
-    eI[p] = ei.hi;
-    eRl[p] = er.lo;
-    eIl[p] = ei.lo;
+// What k_setup derives from the samples: per node its boundary, index there,
+// M_k, weight 1/M_k, s = |zeta'|, the self limit zeta''/(2 zeta') and E, the
+// circulant rows, and the discs of the 64-node cells.
+__device__ void prep_node(const Layout &L, const SetupOut &o, const Nodes &N, int p) {
+    const bool live = p < L.n;
+    double er1 = 0.0, ei1 = 0.0;
+    if (live) {
+        const int k = find_block(L, p);
+        const int M = L.off[k + 1] - L.off[k];
+        o.bid[p] = k;
+        o.loc[p] = p - L.off[k];
+        o.Mk[p] = M;
+        o.w[p] = 1.0 / (double)M;
+        const double a = N.dx[p], b = N.dy[p], ex = N.ddx[p], ey = N.ddy[p];
+        const double d2 = a * a + b * b;
+        o.s[p] = sqrt(d2);
+        // zeta''/(2 zeta') = (ex + i ey)(a - i b) / (2 |zeta'|^2)
+        o.lre[p] = (ex * a + ey * b) / (2.0 * d2);
+        o.lim[p] = (ey * a - ex * b) / (2.0 * d2);
+        // E = e^{i zeta} = e^{-y} (cos x + i sin x) as a double-double, so that
+        // differences of E between nodes keep their relative accuracy
+        DD er, ei;
+        dd_expi(N.x[p], N.y[p], er, ei);
+        o.eR[p] = er1 = er.hi;
+        o.eI[p] = ei1 = ei.hi;
+        o.eRl[p] = er.lo;
+        o.eIl[p] = ei.lo;
+    }
+    // Disc of the E values of the cell, which is this wave's 64 nodes: the
+    // centre and half-diagonal of their bounding box, and the largest |E|.
+    double xlo = live ? er1 : HUGE_VAL, xhi = live ? er1 : -HUGE_VAL;
+    double ylo = live ? ei1 : HUGE_VAL, yhi = live ? ei1 : -HUGE_VAL;
+    double amax = er1 * er1 + ei1 * ei1;
+    for (int i = 32; i > 0; i >>= 1) {
+        xlo = min(xlo, __shfl_xor(xlo, i, 64));
+        xhi = max(xhi, __shfl_xor(xhi, i, 64));
+        ylo = min(ylo, __shfl_xor(ylo, i, 64));
+        yhi = max(yhi, __shfl_xor(yhi, i, 64));
+        amax = max(amax, __shfl_xor(amax, i, 64));
+    }
+    if (live && p % kCellNodes == 0) {
+        double *c = o.cell + 4 * (p / kCellNodes);
+        c[0] = 0.5 * (xlo + xhi);
+        c[1] = 0.5 * (ylo + yhi);
+        c[2] = 0.5 * sqrt((xhi - xlo) * (xhi - xlo) + (yhi - ylo) * (yhi - ylo));
+        c[3] = sqrt(amax);
+    }
+}
+
+// Circulant rows on each boundary's grid (Sec. 3.4 symbols, Nyquist zeroed):
+//   D: c(n) = (1/2)(-1)^n cot(pi n / M), c(0) = 0
+//   H: c(n) = (2/M) cot(pi n / M) for odd n, 0 for even n
+//   h (the Hilbert regulariser of the kernels): c(n) = (1/2) cot(pi n / M)
+__device__ __forceinline__ void circ_entry(int nn, int M, double &d, double &h, double &half) {
+    d = h = half = 0.0;
+    if (nn == 0) return;
+    const double th = (double)nn / (double)M;
+    const double ct = cospi(th) / sinpi(th);
+    half = 0.5 * ct;
+    d = (nn & 1) ? -0.5 * ct : 0.5 * ct;
+    if (nn & 1) h = 2.0 * ct / (double)M;
 }
 
 __device__ __forceinline__ double block_sum(double v, double *sh) {
@@ -59,13 +92,13 @@ __device__ __forceinline__ double block_sum(double v, double *sh) {
     return t;
 }
 
-// One block per boundary: count of non-finite samples, signed area
-// (1/2) sum (x y' - y x') 2pi/M (negative = clockwise) and the mean of x'.
-// Block nb checks the potential.
-__global__ __launch_bounds__(1024) void k_validate(Layout L, Nodes N, const double *phi,
-                                                  int nphi, int pb, double *out) {
+// Checks of the input: block k < nb counts the non-finite samples of boundary
+// k and its far nodes, and forms its signed area (1/2) sum (x y' - y x') 2pi/M
+// (negative = clockwise) and the mean of x'; block nb + b checks share b of
+// the data.
+__device__ void validate_block(const Layout &L, const Nodes &N, const double *phi, int nphi,
+                               int pb, int k, double *out) {
     __shared__ double sh[16];
-    const int k = blockIdx.x;
     if (k >= L.nb) {
         // the data array: block b of pb counts its share (grid-stride) into
         // out[4 nb + 2 + b], for the host to add
@@ -102,6 +135,42 @@ __global__ __launch_bounds__(1024) void k_validate(Layout L, Nodes N, const doub
         out[4 * k + 2] = mdx;
         out[4 * k + 3] = far;
     }
+}
+
+// Everything a call derives from its samples alone, one launch: the checks,
+// the nodes' data with the cells' discs, the circulant rows, and the strips'
+// start value.  Each part is a few blocks that wait on memory or on one chain
+// of FP64 arithmetic, 2 to 10 us on their own; together they take as long as
+// the longest: 11 us at 580 nodes and 12 at 10240, where six launches took 27
+// and 33.
+// The checks read a boundary in rounds of a whole block; the nodes' chain of
+// double-double arithmetic is bound by the FP64 rate of its SIMD, so it is
+// spread thinly: kSetupNodes of a block's threads take a node (all 512: 17 us
+// for 11 at 580 nodes).
+constexpr int kSetupThreads = 512;
+constexpr int kSetupNodes = 128;
+
+__global__ __launch_bounds__(kSetupThreads) void k_setup(Layout L, Nodes N, SetupOut o,
+                                                         const double *phi, int nphi, int pb,
+                                                         double *val, unsigned long long *strips) {
+    int b = blockIdx.x;
+    if (b == 0 && strips && (int)threadIdx.x < L.nb)
+        strips[threadIdx.x] = (unsigned long long)__double_as_longlong(HUGE_VAL);
+    if (b < L.nb + pb) {
+        validate_block(L, N, phi, nphi, pb, b, val);
+        return;
+    }
+    b -= L.nb + pb;
+    if ((int)threadIdx.x >= kSetupNodes) return;
+    const int nodes = (L.n + kSetupNodes - 1) / kSetupNodes;
+    if (b < nodes) {
+        prep_node(L, o, N, b * kSetupNodes + threadIdx.x);
+        return;
+    }
+    const int p = (b - nodes) * kSetupNodes + threadIdx.x;
+    if (p >= L.n) return;
+    const int k = find_block(L, p);
+    circ_entry(p - L.off[k], L.off[k + 1] - L.off[k], o.rowD[p], o.rowH[p], o.hrow[p]);
 }
 
 // ln|1 - e^{i w}| with |1 - e^{iw}|^2 = expm1(-v)^2 + 4 e^{-v} sin^2(u/2)
@@ -149,45 +218,12 @@ __global__ void k_umv(Nodes N, Flow F, int first, int count, double *out) {
     out[i] = v;
 }
 
-// Circulant rows on each boundary's grid (Sec. 3.4 symbols, Nyquist zeroed):
-//   D: c(n) = (1/2)(-1)^n cot(pi n / M), c(0) = 0
-//   H: c(n) = (2/M) cot(pi n / M) for odd n, 0 for even n
-//   h (the Hilbert regulariser of the kernels): c(n) = (1/2) cot(pi n / M)
-__global__ void k_circ_rows(Layout L, int op, double *rows) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= L.n) return;
-    const int k = find_block(L, p);
-    const int M = L.off[k + 1] - L.off[k];
-    const int nn = p - L.off[k];
-    double v = 0.0;
-    if (nn != 0) {
-        const double th = (double)nn / (double)M;
-        const double ct = cospi(th) / sinpi(th);
-        if (op == kOpHalfCot)
-            v = 0.5 * ct;
-        else if (op == WWBI_OP_D)
-            v = (nn & 1) ? -0.5 * ct : 0.5 * ct;
-        else if (nn & 1)
-            v = 2.0 * ct / (double)M;
-    }
-    rows[p] = v;
-}
-
 __global__ void k_circ_row1(int M, int op, double *row) {
     const int nn = blockIdx.x * blockDim.x + threadIdx.x;
     if (nn >= M) return;
-    double v = 0.0;
-    if (nn != 0) {
-        const double th = (double)nn / (double)M;
-        const double ct = cospi(th) / sinpi(th);
-        if (op == kOpHalfCot)
-            v = 0.5 * ct;
-        else if (op == WWBI_OP_D)
-            v = (nn & 1) ? -0.5 * ct : 0.5 * ct;
-        else if (nn & 1)
-            v = 2.0 * ct / (double)M;
-    }
-    row[nn] = v;
+    double d, h, half;
+    circ_entry(nn, M, d, h, half);
+    row[nn] = op == kOpHalfCot ? half : op == WWBI_OP_D ? d : h;
 }
 
 // Circulant product on one periodic grid of M points:
@@ -518,24 +554,15 @@ __global__ void k_add_scalar(int n, double *v, double c) {
 
 }  // namespace
 
-void launch_prep_nodes(const Layout &L, const double *x, const double *y, const double *dx,
-                       const double *dy, const double *ddx, const double *ddy, int *bid,
-                       int *loc, int *Mk, double *w, double *s, double *lre, double *lim,
-                       double *ex, double *ey, double *exl, double *eyl, hipStream_t st) {
-    hipLaunchKernelGGL(k_prep_nodes, dim3(cdiv(L.n, 256)), dim3(256), 0, st, L, x, y, dx, dy, ddx,
-                       ddy, bid, loc, Mk, w, s, lre, lim, ex, ey, exl, eyl);
-}
-
 int validate_data_blocks(int nphi) {
     return std::max(1, std::min(kValidateBlocks, cdiv(nphi, 8192)));
 }
 
-void launch_validate(const Layout &L, const Nodes &N, const double *phi, int nphi, double *out,
-                     hipStream_t st) {
+void launch_setup(const Layout &L, const Nodes &N, const SetupOut &o, const double *phi, int nphi,
+                  double *val, unsigned long long *strips, hipStream_t st) {
     const int pb = validate_data_blocks(nphi);
-    // 1024 threads: a block walks its boundary (or share of the data) in few
-    // rounds of loads (12 -> 9 us at M = 10240 against 256 threads)
-    hipLaunchKernelGGL(k_validate, dim3(L.nb + pb), dim3(1024), 0, st, L, N, phi, nphi, pb, out);
+    hipLaunchKernelGGL(k_setup, dim3(L.nb + pb + 2 * cdiv(L.n, kSetupNodes)),
+                       dim3(kSetupThreads), 0, st, L, N, o, phi, nphi, pb, val, strips);
 }
 
 void launch_rhs_phi(const Layout &L, const Nodes &N, const Flow &F, const double *phi,
@@ -583,10 +610,6 @@ void launch_energy(int n0, const Nodes &N, const Flow &F, double tau, double gra
     hipLaunchKernelGGL(k_energy_terms, dim3(cdiv(n0, 64)), dim3(64 * kSliceWaves), 0, st, n0, N,
                        F, tau, grav, hw, part, nsplit, dphi, tmv, e);
     hipLaunchKernelGGL(k_energy_final, dim3(1), dim3(1024), 0, st, n0, e, F, psi_k, E);
-}
-
-void launch_circulant_rows(const Layout &L, int op, double *rows, hipStream_t st) {
-    hipLaunchKernelGGL(k_circ_rows, dim3(cdiv(L.n, 256)), dim3(256), 0, st, L, op, rows);
 }
 
 void launch_circulant_batched(const Layout &L, const double *rows, const double *f, long fs,

@@ -539,6 +539,14 @@ __global__ __launch_bounds__(256) void k_assemble64(Nodes N, int n, int corr, do
 // (k_near_fix), visiting only the listed cells.
 constexpr int kMaxScanCells = 1024;        // cells tested per pass of the full scan
 
+// v of lane jj (the same jj in every lane)
+__device__ __forceinline__ double lane_bcast(double v, int jj) {
+    const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+    const int lo = __builtin_amdgcn_readlane((int)(u & 0xffffffffu), jj);
+    const int hi = __builtin_amdgcn_readlane((int)(u >> 32), jj);
+    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+
 // The pair test shared by the list build and the fix: outside the band of
 // `nb` steps (by index: me's boundary starts at mbase, has mM nodes, me is
 // node mloc of it) and inside the near cut.
@@ -554,12 +562,13 @@ __device__ __forceinline__ bool near_pair(int q, int mbase, int mloc, int mM, in
 
 // Ordered list, in LDS, of the cells of [c0, c0 + cn) whose discs come within
 // the near cut of disc `d` (cn <= kMaxScanCells); returns its length.  Every
-// thread of the block calls it.
+// thread of the block of W waves calls it.
+template <int W>
 __device__ int list_disc_cells(const Nodes &N, const double *d, int c0, int cn, int *list,
                                int *wcnt) {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     int nl = 0;
-    for (int j0 = 0; j0 < cn; j0 += 256) {
+    for (int j0 = 0; j0 < cn; j0 += 64 * W) {
         const int j = j0 + (int)threadIdx.x;
         const bool f = j < cn && discs_may_be_near(N.cell + 4 * (long)(c0 + j), d);
         const unsigned long long bal = __ballot(f);
@@ -568,7 +577,7 @@ __device__ int list_disc_cells(const Nodes &N, const double *d, int c0, int cn, 
         int before = nl;
         for (int w = 0; w < wv; ++w) before += wcnt[w];
         if (f) list[before + __popcll(bal & ((1ull << lane) - 1ull))] = c0 + j;
-        nl += wcnt[0] + wcnt[1] + wcnt[2] + wcnt[3];
+        for (int w = 0; w < W; ++w) nl += wcnt[w];
         __syncthreads();
     }
     return nl;
@@ -588,14 +597,97 @@ __device__ __forceinline__ void stage_cell(const Nodes &N, int b, double (*se)[k
     __syncthreads();
 }
 
-// One block per cell a: its list, and the number of near pairs (p in a, any
-// q) added into *count.
-__global__ __launch_bounds__(256) void k_near_cells(Nodes N, int nb, int *lists, double *count) {
-    __shared__ int list[kMaxScanCells];
-    __shared__ int wcnt[4];
-    __shared__ int hit;
-    __shared__ double se[4][kCellNodes];
-    __shared__ double red[4];
+// Half-width of the strip of analyticity, per boundary (the grid rule of the
+// two-grid iteration): a block takes a sampled source per thread
+// and one chunk of the sampled targets on other boundaries, or half a
+// radian or more along its own, and lowers out[k] (bits of a positive double,
+// whose order is that of the integers) to the square of the least estimate.
+// |E_q - E_p|^2 / (|E_q| |E_p|) = |2 sin((zeta_q - zeta_p) / 2)|^2 is the
+// squared distance across the period.
+constexpr int kStripSamples = 2048;      // sampled nodes, about
+constexpr int kStripTargets = 32;        // of a block
+constexpr int kNearWaves = 8;            // of a block of k_near_cells
+
+// Node of sample s: sample counts per boundary are ceil(M_k / stride).
+__device__ __forceinline__ int sample_node(const Layout &L, int stride, int s) {
+    for (int k = 0; k < L.nb; ++k) {
+        const int M = L.off[k + 1] - L.off[k], cnt = (M + stride - 1) / stride;
+        if (s < cnt) return L.off[k] + s * stride;
+        s -= cnt;
+    }
+    return -1;
+}
+
+__device__ void strip_block(const Layout &L, const Nodes &N, int stride, int count, int blk,
+                            unsigned long long *out) {
+    __shared__ double px[kStripTargets], py[kStripTargets], ir[kStripTargets];
+    __shared__ int pk[kStripTargets], pl[kStripTargets];
+    __shared__ unsigned long long least[kMaxB];
+    const int t = threadIdx.x, nsb = (count + 64 * kNearWaves - 1) / (64 * kNearWaves);
+    const int sq = blk % nsb * (64 * kNearWaves) + t, p0 = blk / nsb * kStripTargets;
+    const int np = min(kStripTargets, count - p0);
+    if (t < np) {
+        const int p = sample_node(L, stride, p0 + t);
+        const double a = N.ex[p], b = N.ey[p];
+        px[t] = a;
+        py[t] = b;
+        ir[t] = 1.0 / sqrt(a * a + b * b);
+        pk[t] = N.bid[p];
+        pl[t] = N.loc[p];
+    }
+    if (t < L.nb) least[t] = (unsigned long long)__double_as_longlong(HUGE_VAL);
+    __syncthreads();
+    if (sq < count) {
+        const int q = sample_node(L, stride, sq);
+        const double ex = N.ex[q], ey = N.ey[q];
+        const int kq = N.bid[q], lq = N.loc[q], mq = N.Mk[q];
+        double best = HUGE_VAL;
+        for (int i = 0; i < np; ++i) {
+            const double dx = px[i] - ex, dy = py[i] - ey;
+            const double d2 = (dx * dx + dy * dy) * ir[i];
+            const bool own = pk[i] == kq && cyc_dist(pl[i], lq, mq) * 12 < mq;
+            best = own ? best : min(best, d2);
+        }
+        const double s = N.s[q], a = N.lre[q], b = N.lim[q];
+        best = min(best / (sqrt(ex * ex + ey * ey) * (s * s)), 1.0 / (a * a + b * b));
+        if (!(best > 0.0)) best = 0.0;      // also for a NaN
+        // one atomic for a wave on one boundary
+        if (__all(kq == __shfl(kq, 0, 64)) && __popcll(__ballot(true)) == 64) {
+            for (int o = 32; o > 0; o >>= 1) best = min(best, __shfl_xor(best, o, 64));
+            if ((t & 63) == 0)
+                atomicMin(&least[kq], (unsigned long long)__double_as_longlong(best));
+        } else {
+            atomicMin(&least[kq], (unsigned long long)__double_as_longlong(best));
+        }
+    }
+    __syncthreads();
+    if (t < L.nb && least[t] < (unsigned long long)__double_as_longlong(HUGE_VAL))
+        atomicMin(out + t, least[t]);
+}
+
+// Blocks [0, cells): one per 64-node cell a, its list, and the number of near
+// pairs (p in a, any q) added into *count.  A cell that straddles two
+// boundaries has a disc that meets nearly every other: testing all pairs of
+// up to 80 cells, one cell after the other, took 32 us at 580 nodes, 105 at
+// 2208 and 144 at 5002.  So the listed cells are first cut down, one per
+// thread, to those whose disc comes near a node of a, and then only the nodes
+// of either cell that come near the other's disc are tested, in shares of the
+// block's waves, the next cell's nodes in flight: 16, 16 and 17 us.
+// The blocks after them measure the strips (12 us for both at 10240 nodes; the
+// strips alone took 56 with a wave per source and a square root and a
+// division per pair, which are now one of each per node).
+__global__ __launch_bounds__(64 * kNearWaves) void k_near_cells(Layout L, Nodes N, int nb, int *lists,
+                                                    double *count, int stride, int samples,
+                                                    unsigned long long *strips) {
+    const int ncell = (N.n + kCellNodes - 1) / kCellNodes;
+    if ((int)blockIdx.x >= ncell) {
+        strip_block(L, N, stride, samples, blockIdx.x - ncell, strips);
+        return;
+    }
+    __shared__ int list[kMaxScanCells], found[kMaxScanCells];
+    __shared__ int wcnt[kNearWaves];
+    __shared__ double sx[kCellNodes], sy[kCellNodes], sr[kCellNodes];
+    __shared__ double red[kNearWaves];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
     const int a = blockIdx.x;
     const int p = a * kCellNodes + lane;
@@ -604,47 +696,110 @@ __global__ __launch_bounds__(256) void k_near_cells(Nodes N, int nb, int *lists,
     const double ex = N.ex[me], ey = N.ey[me], exl = N.exl[me], eyl = N.eyl[me];
     const int mloc = N.loc[me], mM = N.Mk[me], mbase = me - mloc;
     const double *da = N.cell + 4 * a;
-    const int ncell = (N.n + kCellNodes - 1) / kCellNodes;
+    const double er = sqrt(ex * ex + ey * ey);
+    // every kNearWaves-th node of a cell
+    const unsigned long long share = 0x0101010101010101ull << wv;
+    static_assert(kNearWaves == 8, "shares");
+    if (wv == 0) {
+        sx[lane] = ex;
+        sy[lane] = ey;
+        sr[lane] = er;
+    }
+    // discs_within for a node (radius 0) and a disc, squared
+    auto node_near = [](double x, double y, double r, const double *d) {
+        const double gx = x - d[0], gy = y - d[1];
+        const double reach = d[2] + 1.001 / kNearCut * max(r, d[3]);
+        return gx * gx + gy * gy < 1.0001 * (reach * reach);
+    };
     int nfound = 0;
-    bool full = false;
     double pairs = 0.0;
     for (int c0 = 0; c0 < ncell; c0 += kMaxScanCells) {
         __syncthreads();
-        const int nl = list_disc_cells(N, da, c0, min(kMaxScanCells, ncell - c0), list, wcnt);
-        for (int li = 0; li < nl; ++li) {
-            const int b = list[li];
-            if (threadIdx.x == 0) hit = 0;
-            stage_cell(N, b, se);
-            int mine = 0;
-            if (live) {
-                for (int jj = 16 * wv; jj < 16 * wv + 16; ++jj) {
-                    const int q = b * kCellNodes + jj;
-                    if (q >= N.n) break;
-                    mine += near_pair(q, mbase, mloc, mM, nb, ex, ey, exl, eyl, se[0][jj],
-                                      se[1][jj], se[2][jj], se[3][jj]) ? 1 : 0;
+        int nl = list_disc_cells<kNearWaves>(N, da, c0, min(kMaxScanCells, ncell - c0), list, wcnt);
+        if (nl > 8) {
+            // in place: a round writes at most as far as it has read
+            int kept = 0;
+            for (int j0 = 0; j0 < nl; j0 += 64 * kNearWaves) {
+                const int j = j0 + (int)threadIdx.x, b = j < nl ? list[j] : 0;
+                bool f = false;
+                if (j < nl) {
+                    const double d[4] = {N.cell[4 * b], N.cell[4 * b + 1], N.cell[4 * b + 2],
+                                         N.cell[4 * b + 3]};
+                    for (int i = 0; i < kCellNodes; ++i) f = f || node_near(sx[i], sy[i], sr[i], d);
                 }
+                const unsigned long long bal = __ballot(f);
+                if (lane == 0) wcnt[wv] = __popcll(bal);
+                __syncthreads();
+                int before = kept;
+                for (int w = 0; w < wv; ++w) before += wcnt[w];
+                if (f) list[before + __popcll(bal & ((1ull << lane) - 1ull))] = b;
+                for (int w = 0; w < kNearWaves; ++w) kept += wcnt[w];
+                __syncthreads();
             }
-            if (mine) atomicOr(&hit, 1);
-            pairs += (double)mine;
-            __syncthreads();
-            const bool h = hit != 0;
-            __syncthreads();                // every thread has read hit before it is reset
-            if (h) {
-                if (nfound < kNearList) {
-                    if (threadIdx.x == 0) lists[(long)a * kNearStride + 1 + nfound] = b;
-                    ++nfound;
-                } else {
-                    full = true;
-                }
-            }
+            nl = kept;
         }
+        for (int li = threadIdx.x; li < nl; li += 64 * kNearWaves) found[li] = 0;
+        __syncthreads();
+        // the next cell's nodes are fetched while this one's are tested
+        double nx = 0.0, ny = 0.0, nxl = 0.0, nyl = 0.0;
+        auto fetch = [&](int li) {
+            const int q = min(list[li] * kCellNodes + lane, N.n - 1);
+            nx = N.ex[q];
+            ny = N.ey[q];
+            nxl = N.exl[q];
+            nyl = N.eyl[q];
+        };
+        if (nl > 0) fetch(0);
+        for (int li = 0; li < nl; ++li) {
+            const int q0 = list[li] * kCellNodes;
+            const double qx = nx, qy = ny, qxl = nxl, qyl = nyl;
+            if (li + 1 < nl) fetch(li + 1);
+            // the nodes of either cell that come near the other's disc; this
+            // wave loops over its share of the fewer, its lanes hold the other's
+            const bool qlive = q0 + lane < N.n;
+            const double *db = N.cell + 4 * list[li];
+            unsigned long long qs = __ballot(qlive && node_near(qx, qy, sqrt(qx * qx + qy * qy), da));
+            unsigned long long ps = __ballot(live && node_near(ex, ey, er, db));
+            int mine = 0;
+            if (__popcll(qs) <= __popcll(ps)) {
+                for (qs &= share; qs; qs &= qs - 1) {
+                    const int jj = __builtin_ctzll(qs);
+                    mine += near_pair(q0 + jj, mbase, mloc, mM, nb, ex, ey, exl, eyl,
+                                      lane_bcast(qx, jj), lane_bcast(qy, jj), lane_bcast(qxl, jj),
+                                      lane_bcast(qyl, jj)) ? 1 : 0;
+                }
+                if (!live) mine = 0;
+            } else {
+                for (ps &= share; ps; ps &= ps - 1) {
+                    const int jj = __builtin_ctzll(ps);
+                    mine += near_pair(q0 + lane, __builtin_amdgcn_readlane(mbase, jj),
+                                      __builtin_amdgcn_readlane(mloc, jj),
+                                      __builtin_amdgcn_readlane(mM, jj), nb, lane_bcast(ex, jj),
+                                      lane_bcast(ey, jj), lane_bcast(exl, jj), lane_bcast(eyl, jj),
+                                      qx, qy, qxl, qyl) ? 1 : 0;
+                }
+                if (!qlive) mine = 0;
+            }
+            if (__ballot(mine != 0) && lane == 0) found[li] = 1;
+            pairs += (double)mine;
+        }
+        __syncthreads();
+        if (wv == 0)
+            for (int j0 = 0; j0 < nl; j0 += 64) {
+                const bool f = j0 + lane < nl && found[j0 + lane];
+                const unsigned long long bal = __ballot(f);
+                const int at = nfound + __popcll(bal & ((1ull << lane) - 1ull));
+                if (f && at < kNearList) lists[(long)a * kNearStride + 1 + at] = list[j0 + lane];
+                nfound += __popcll(bal);
+            }
     }
     for (int o = 32; o > 0; o >>= 1) pairs += __shfl_xor(pairs, o, 64);
     if (lane == 0) red[wv] = pairs;
     __syncthreads();
     if (threadIdx.x == 0) {
-        lists[(long)a * kNearStride] = full ? -1 : nfound;
-        const double tot = ((red[0] + red[1]) + red[2]) + red[3];
+        lists[(long)a * kNearStride] = nfound > kNearList ? -1 : nfound;
+        double tot = 0.0;
+        for (int w = 0; w < kNearWaves; ++w) tot += red[w];
         if (tot > 0.0) atomicAdd(count, tot);       // integer counts: exact in any order
     }
 }
@@ -708,7 +863,7 @@ __global__ __launch_bounds__(256) void k_near_fix(Nodes N, const int *lists, con
         const int *cells;
         if (cnt < 0) {
             __syncthreads();
-            nl = list_disc_cells(N, N.cell + 4 * a, cs, min(kMaxScanCells, clast - cs + 1), list,
+            nl = list_disc_cells<4>(N, N.cell + 4 * a, cs, min(kMaxScanCells, clast - cs + 1), list,
                                  wcnt);
             cells = list;
         } else {
@@ -1081,31 +1236,6 @@ __global__ __launch_bounds__(256) void k_otf_cols(Nodes N, const double *hrow, i
     if (live) part[(long)blockIdx.y * nc + q] = ACC32 ? (double)acc32 : acc;
 }
 
-// Disc of the E values of every cell of kCellNodes consecutive nodes: the
-// centre and half-diagonal of their bounding box, and the largest |E|; one
-// wave per cell.
-__global__ __launch_bounds__(256) void k_cells(Nodes N, double *cell) {
-    const int c = blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int a = c * kCellNodes;
-    if (a >= N.n) return;
-    const int q = min(a + (int)(threadIdx.x & 63), N.n - 1);
-    const double ex = N.ex[q], ey = N.ey[q];
-    double xlo = ex, xhi = ex, ylo = ey, yhi = ey, amax = ex * ex + ey * ey;
-    for (int o = 32; o > 0; o >>= 1) {
-        xlo = min(xlo, __shfl_xor(xlo, o, 64));
-        xhi = max(xhi, __shfl_xor(xhi, o, 64));
-        ylo = min(ylo, __shfl_xor(ylo, o, 64));
-        yhi = max(yhi, __shfl_xor(yhi, o, 64));
-        amax = max(amax, __shfl_xor(amax, o, 64));
-    }
-    if ((threadIdx.x & 63) == 0) {
-        cell[4 * c] = 0.5 * (xlo + xhi);
-        cell[4 * c + 1] = 0.5 * (ylo + yhi);
-        cell[4 * c + 2] = 0.5 * sqrt((xhi - xlo) * (xhi - xlo) + (yhi - ylo) * (yhi - ylo));
-        cell[4 * c + 3] = sqrt(amax);
-    }
-}
-
 inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
 
 }  // namespace
@@ -1139,16 +1269,17 @@ int rflavour_nsplit(const Nodes &N, int nr, int nc, int transpose) {
     return transpose ? cdiv(nr, cols_chunk(nr, nc)) + fix : cdiv(nc, rows_chunk(nr, nc)) + fix;
 }
 
-void launch_cells(const Nodes &N, double *cell, hipStream_t st) {
-    hipLaunchKernelGGL(k_cells, dim3(cdiv(cdiv(N.n, kCellNodes), 4)), dim3(256), 0, st, N, cell);
-}
-
 // Lists of the cells holding near pairs outside the kNearBand band, and their
 // pair count added into *count (the products launch their fix kernels only
 // when there are any).
-void launch_near_cells(const Nodes &N, int *lists, double *count, hipStream_t st) {
-    hipLaunchKernelGGL(k_near_cells, dim3(cdiv(N.n, kCellNodes)), dim3(256), 0, st, N, kNearBand,
-                       lists, count);
+void launch_near_cells(const Layout &L, const Nodes &N, int *lists, double *count,
+                       unsigned long long *strips, hipStream_t st) {
+    const int stride = std::max(1, cdiv(L.n, kStripSamples));
+    int samples = 0;
+    for (int k = 0; k < L.nb; ++k) samples += cdiv(L.off[k + 1] - L.off[k], stride);
+    const int sb = strips ? cdiv(samples, 64 * kNearWaves) * cdiv(samples, kStripTargets) : 0;
+    hipLaunchKernelGGL(k_near_cells, dim3(cdiv(N.n, kCellNodes) + sb), dim3(64 * kNearWaves), 0, st,
+                       L, N, kNearBand, lists, count, stride, samples, strips);
 }
 
 // Blocks of the fix kernel: the 64-node cells overlapping [o, o + n).

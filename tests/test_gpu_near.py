@@ -109,3 +109,32 @@ def test_near_surface_obstacle(ww, ctx, gap, mode, prec):
     assert rep.status == ww.OK
     bar = 1e-11 if prec == "fp64" else 1e-10
     assert eU <= max(bar, 4.0 * sU) and eo <= max(bar, 4.0 * so)
+
+
+# boundaries whose ends share a 64-node cell, and enough of them that the cell's
+# disc meets more than eight others
+@pytest.mark.parametrize("M0,M1,M2,others", [(1026, 258, 514, 0), (1022, 130, 510, 1),
+                                             (1090, 34, 578, 4), (1024, 256, 512, 3)])
+def test_near_pairs_across_shared_cells(ww, ctx, M0, M1, M2, others):
+    gap, b = 0.01, 0.15
+    curves = [clustered_flat_surface(M0, np.pi, 0.9), graph_bottom(M1, -1.0),
+              clustered_ellipse(M2, np.pi, -gap - b, 0.3, b, 1.5 * np.pi, 0.9)]
+    centres = [np.pi - (gap + b) * 1j]
+    for j in range(others):
+        c = 0.3 + 0.35 * j + (2.4 if j > 1 else 0.0) - 0.65j
+        curves.append(clustered_ellipse(98 + 2 * j, c.real, c.imag, 0.1, 0.08, 0.0, 0.0))
+        centres.append(c)
+    geom = Geometry(curves, np.array(centres), 0.5 * np.ones(len(centres)), 1.0)
+    say(f"case shared cells n={geom.Mtot} boundaries={2 + len(centres)}")
+    dg = ww.DeviceGeometry.from_synth(geom, DEV)
+    phi = torch.as_tensor(0.1 * np.cos(2 * np.pi * np.arange(M0) / M0), device=DEV)
+    # the stored entries take every pair's own formula; the products look the
+    # near pairs up in the lists
+    Us, oms, _, _ = ctx.solve_phi(dg, phi, tol=1e-15, check=False, matvec=ww.MATVEC_STORED)
+    for mode in (ww.MATVEC_ON_THE_FLY, ww.MATVEC_AUTO):
+        U, om, _, _ = ctx.solve_phi(dg, phi, tol=1e-15, check=False, matvec=mode)
+        eU, eo = rel(U.cpu(), Us.cpu()), rel(om.cpu(), oms.cpu())
+        say(f"  U {eU:.2e} omega {eo:.2e}")
+        # each side within the bar of the test above (1e-11, or the spread it
+        # measures, at most 2.2e-11)
+        assert eU <= 4.4e-11 and eo <= 2e-11
