@@ -726,7 +726,7 @@ int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, co
         hsmall->status = kSmallAborted;
         hsmall->aborted = 0;
         if (launch_small_gmres(a, 1, stream) != WWBI_OK) return WWBI_EHIP;
-        launch_coarse_correct(N, hrow, mode, cmap, cfac, nc, corr, ce, r0, n, op.flip, inv_d, rr, x,
+        launch_coarse_correct(N, C, hrow, mode, cmap, cfac, corr, ce, r0, n, op.flip, inv_d, rr, x,
                               have_x, part, stream);
         const bool had_x = have_x;
         have_x = true;

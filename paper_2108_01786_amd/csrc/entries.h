@@ -349,6 +349,62 @@ __device__ __forceinline__ int wave_base() {
     return __builtin_amdgcn_readfirstlane(threadIdx.x) & ~63;
 }
 
+// Smallest distance between two discs of E values (centre, radius) against
+// the cut |E| / f of the larger |E| (a relative margin covers the rounding of
+// the discs): false when no pair of the two cells is closer than the cut.
+__device__ __forceinline__ bool discs_within(const double *a, const double *b, double f) {
+    const double gx = a[0] - b[0], gy = a[1] - b[1];
+    return (sqrt(gx * gx + gy * gy) - a[2] - b[2]) * f < 1.001 * max(a[3], b[3]);
+}
+__device__ __forceinline__ bool discs_may_be_near(const double *a, const double *b) {
+    return discs_within(a, b, kNearCut);
+}
+
+// Kinds of a far entry of A when the target and source boundaries are
+// uniform: the real part of the source-flavour term (surface row and wall
+// column), its negative (wall row and surface column), or the imaginary part.
+enum { kFastReNeg = 0, kFastRePos = 1, kFastIm = 2 };
+
+// The entry of such a pair in a far tile of FP64: the source data pre-scaled
+// (fa = w dx / 2, fb = w dy / 2), the E quotient with the reciprocal of |D|^2
+// from the FP32 estimate, the trailing parts of E with LO.
+template <int KIND, bool LO>
+__device__ __forceinline__ double a_fast64(const Tgt &t, const Src &s, double fa, double fb,
+                                           double ec) {
+    const double dr = LO ? (s.ex - t.ex) + (s.exl - t.exl) : s.ex - t.ex;
+    const double di = LO ? (s.ey - t.ey) + (s.eyl - t.eyl) : s.ey - t.ey;
+    const double nr = s.ex + t.ex, ni = s.ey + t.ey;
+    const double inv = recip64_from32(dr * dr + di * di);
+    const double pr = nr * dr + ni * di;
+    const double pi = ni * dr - nr * di;
+    if (KIND == kFastReNeg) return -(fa * pi + fb * pr) * inv;
+    if (KIND == kFastRePos) return (fa * pi + fb * pr) * inv;
+    return (fa * pr - fb * pi) * inv - ec;
+}
+
+// How a wave may take the pairs of target nodes [pa, pb] and source nodes
+// [qa, qb]: kTileFull, each by its full entry (band, near pairs and diagonal
+// limits among them, or boundary ends inside a range); kTileLo and kTileFar,
+// by the E quotient with one formula for all, the latter without E's trailing
+// parts (every pair |E| / 4 or more apart).  Groups of LANES lanes take a tile
+// each; every lane of the wave calls it.
+enum { kTileFull = 0, kTileLo, kTileFar };
+template <int LANES>
+__device__ __forceinline__ int tile_kind(const Nodes &N, int pa, int pb, int qa, int qb) {
+    const int lane = threadIdx.x & 63, first = lane / LANES * LANES;
+    const int a0 = pa / kCellNodes, na = pb / kCellNodes - a0 + 1;
+    const int b0 = qa / kCellNodes, tests = (qb / kCellNodes - b0 + 1) * na;
+    bool near = !ranges_apart(N, pa, pb, qa, qb, kNearBand), mid = false;
+    for (int i = lane - first; i < tests; i += LANES) {
+        const double *a = N.cell + 4 * (a0 + i % na), *b = N.cell + 4 * (b0 + i / na);
+        near = near || discs_may_be_near(a, b);
+        mid = mid || discs_within(a, b, 4.0);
+    }
+    const unsigned long long group = (~0ull >> (64 - LANES)) << first;
+    if (__ballot(near) & group) return kTileFull;
+    return (__ballot(mid) & group) ? kTileLo : kTileFar;
+}
+
 // Whether a wave's outputs [o0, o0 + 64) (clipped to [0, nout)) are clear of
 // the near band of the summed nodes [q0, q0 + m); output node = obase +
 // output, and COLS says the outputs are sources.  Vacuously true for a wave

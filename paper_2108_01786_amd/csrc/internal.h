@@ -418,12 +418,10 @@ void launch_assemble_coarse(const Nodes &N, const double *hrow, int mode, const 
 // K_hH of A for all nodes: N.n x n, its padding columns zero
 void launch_assemble_interp(const Nodes &N, const int *map, const double *fac, int n, int corr,
                             double *out, long ld, hipStream_t st);
-// x (+)= (r - S K_hH e) / d on nodes r0 .. r0 + nr; part: coarse_slices(nr, n)
-// * nr doubles
-int coarse_slices(int nr, int n);
-void launch_coarse_correct(const Nodes &N, const double *hrow, int mode, const int *map,
-                           const double *fac, int n, int corr, const double *e, int r0, int nr,
-                           int flip, double inv_d, const double *r, double *x, bool add,
+// x (+)= (r - S K_hH e) / d on nodes r0 .. r0 + nr; part: up to 137 nr doubles
+void launch_coarse_correct(const Nodes &N, const Coarse &C, const double *hrow, int mode,
+                           const int *map, const double *fac, int corr, const double *e, int r0,
+                           int nr, int flip, double inv_d, const double *r, double *x, bool add,
                            double *part, hipStream_t st);
 void launch_scale_copy(int n, const double *b, double a, double *x, hipStream_t st);
 // out[0..63] and out[64..127]: partial sums of b^2 and of its squared

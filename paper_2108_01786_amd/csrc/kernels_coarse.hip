@@ -65,25 +65,83 @@ __device__ __forceinline__ double identity_part(int k) {
     return k == 0 ? -0.5 : 0.5;
 }
 
-// The coarse matrix, one entry per thread (rows in the unsigned form: the
-// solver negates the first rows itself).
+// Where the pairs of a tile allow it (tile_kind: all but the tiles around the
+// diagonal and where boundaries come close), the far form of an entry serves:
+// the E quotient without the near, band and diagonal tests, 20 instructions a
+// pair.  Products with every pair by its full entry took 29 us at 10240 x 640
+// nodes, 23 at 4608 x 448, 43 at 5002 x 1792 and 208 at 40960 x 1792; now 19,
+// 13, 24 and 89.  The small ones are bound by the latency of a block: its own
+// node, the staged ones, the tests, 16 to 64 pairs.
+
+// Far entries of A, a column per lane, target after target: f(i) loads row i's
+// target, put(i, v) takes the value.
+template <int KIND, bool LO, class Row, class Put>
+__device__ __forceinline__ void far_rows(int rows, const Src &s, double fa, double fb, double ec,
+                                         Row row, Put put) {
+    for (int i = 0; i < rows; ++i) put(i, a_fast64<KIND, LO>(row(i), s, fa, fb, ec));
+}
+
+// Rows [0, rows) of K (targets row(i), node indices [pa, pb]) against the
+// wave's columns: lane l holds coarse source j0 + l of n.
+template <class Row, class Put>
+__device__ __forceinline__ void interp_tile(const Nodes &N, const int *map, const double *fac,
+                                            int n, int j0, int corr, int pa, int pb, int rows,
+                                            Row row, Put put) {
+    const int j = min(j0 + (int)(threadIdx.x & 63), n - 1);
+    Src s = load_src(N, map[j]);
+    s.w *= fac[j];
+    const int qa = map[min(j0, n - 1)], qb = map[min(j0 + 63, n - 1)];
+    const int kind = tile_kind<64>(N, pa, pb, qa, qb);
+    if (kind == kTileFull) {
+        for (int i = 0; i < rows; ++i)
+            put(i, k_entry<kCoarseA>(N, row(i), s, corr != 0, nullptr));
+        return;
+    }
+    const int kp = N.bid[pa], kq = N.bid[qa];
+    const double fa = 0.5 * s.w * s.dx, fb = 0.5 * s.w * s.dy;
+    const double ec = (corr && kp == kq && kp >= 2) ? s.w : 0.0;
+    const bool lo = kind == kTileLo;
+    if ((kp == 0) == (kq == 0)) {
+        if (lo) far_rows<kFastIm, true>(rows, s, fa, fb, ec, row, put);
+        else far_rows<kFastIm, false>(rows, s, fa, fb, ec, row, put);
+    } else if (kp == 0) {
+        if (lo) far_rows<kFastReNeg, true>(rows, s, fa, fb, 0.0, row, put);
+        else far_rows<kFastReNeg, false>(rows, s, fa, fb, 0.0, row, put);
+    } else {
+        if (lo) far_rows<kFastRePos, true>(rows, s, fa, fb, 0.0, row, put);
+        else far_rows<kFastRePos, false>(rows, s, fa, fb, 0.0, row, put);
+    }
+}
+
+// The coarse matrix, kCoarseRows rows of 64 columns a wave (rows in the
+// unsigned form: the solver negates the first rows itself).
+constexpr int kCoarseRows = 4;
+
 template <int MODE>
 __global__ __launch_bounds__(256) void k_assemble_coarse(Nodes N, const double *hrow,
                                                          const int *map, const double *fac, int n,
                                                          int corr, double *out, long ld) {
-    const int j = blockIdx.x * 64 + (threadIdx.x & 63);
-    const int i = blockIdx.y * 4 + (threadIdx.x >> 6);
-    if (i >= n || j >= ld) return;
-    double v = 0.0;
-    if (j < n) {
-        const int ti = MODE == kCoarseAT ? j : i, si = MODE == kCoarseAT ? i : j;
+    const int j0 = blockIdx.x * 64, j = j0 + (threadIdx.x & 63);
+    const int i0 = (blockIdx.y * 4 + (threadIdx.x >> 6)) * kCoarseRows;
+    const int rows = min(kCoarseRows, n - i0);
+    if (rows <= 0) return;
+    auto put = [&](int i, double v) {
+        if (i0 + i == j) v += identity_part<MODE>(N.bid[map[j]]);
+        if (j < ld) out[(long)(i0 + i) * ld + j] = j < n ? v : 0.0;
+    };
+    if (MODE == kCoarseA) {
+        interp_tile(N, map, fac, n, j0, corr, map[i0], map[i0 + rows - 1], rows,
+                    [&](int i) { return load_tgt(N, map[i0 + i]); }, put);
+        return;
+    }
+    const int jc = min(j, n - 1);
+    for (int i = 0; i < rows; ++i) {
+        const int ti = MODE == kCoarseAT ? jc : i0 + i, si = MODE == kCoarseAT ? i0 + i : jc;
         const Tgt t = load_tgt(N, map[ti]);
         Src s = load_src(N, map[si]);
         s.w *= fac[si];
-        v = k_entry<MODE>(N, t, s, corr != 0, hrow);
-        if (i == j) v += identity_part<MODE>(t.k);
+        put(i, k_entry<MODE>(N, t, s, corr != 0, hrow));
     }
-    out[(long)i * ld + j] = v;
 }
 
 // K_hH of A for many right-hand sides: rows of all n0 nodes, the coarse nodes'
@@ -91,58 +149,191 @@ __global__ __launch_bounds__(256) void k_assemble_coarse(Nodes N, const double *
 constexpr int kInterpRows = 16;
 
 __global__ __launch_bounds__(256) void k_assemble_interp(Nodes N, const int *map,
-                                                         const double *fac, int rows, int n,
+                                                         const double *fac, int nodes, int n,
                                                          int corr, double *out, long ld) {
-    const int j = blockIdx.x * 64 + (threadIdx.x & 63);
+    const int j0 = blockIdx.x * 64, j = j0 + (threadIdx.x & 63);
     const int i0 = (blockIdx.y * 4 + (threadIdx.x >> 6)) * kInterpRows;
-    if (j >= ld) return;
-    Src s = load_src(N, map[j < n ? j : 0]);
-    s.w *= fac[j < n ? j : 0];
-    for (int i = i0; i < min(rows, i0 + kInterpRows); ++i) {
-        const Tgt t = load_tgt(N, i);
-        const double v = k_entry<kCoarseA>(N, t, s, corr != 0, nullptr);
-        out[(long)i * ld + j] = j < n ? v : 0.0;
-    }
+    const int rows = min(kInterpRows, nodes - i0);
+    if (rows <= 0) return;
+    interp_tile(N, map, fac, n, j0, corr, i0, i0 + rows - 1, rows,
+                [&](int i) { return load_tgt(N, i0 + i); },
+                [&](int i, double v) {
+                    if (j < ld) out[(long)(i0 + i) * ld + j] = j < n ? v : 0.0;
+                });
 }
 
 // K_hH e_H: one output node per thread (rows r0 .. r0 + nr), the coarse
 // nodes of chunk blockIdx.y staged in LDS; slice blockIdx.y of `part`.  For
-// the transpose the outputs are sources and the coarse nodes targets.
-constexpr int kCoarseStage = 32;
+// the transpose the outputs are sources and the coarse nodes targets.  The
+// same-boundary pairs within kNearBand steps, whose entry is a transcendental
+// formula, are the last `bands` slices: a lane visits its own few there, where in the
+// other slices a wave would take that formula for every coarse node that any
+// of its 64 lanes has near.
+constexpr int kCoarseStage = 64;
+constexpr int kCoarseTile = 16;          // coarse nodes per tile_kind test
+constexpr int kTileLanes = 64 / (kCoarseStage / kCoarseTile);
+
+// A staged coarse node for the far form: E and, for A, its source data times
+// e (a = w dx e / 2, b = w dy e / 2), else a = its weight times e.
+struct FarNode {
+    double ex, ey, exl, eyl, a, b;
+};
+
+// Sums over m staged nodes for one output node (E = ox, oy, oxl, oyl): for A
+// of the entries themselves into p; else of e pr / |D|^2 into p and e pi /
+// |D|^2 into q, D = E_source - E_target.
+template <int MODE, int KIND, bool LO>
+__device__ __forceinline__ void far_sums(const FarNode *f, int m, double ox, double oy,
+                                         double oxl, double oyl, double &p, double &q) {
+    for (int i = 0; i < m; ++i) {
+        const FarNode &c = f[i];
+        double dr = c.ex - ox, di = c.ey - oy;
+        if (LO) {
+            dr += c.exl - oxl;
+            di += c.eyl - oyl;
+        }
+        if (MODE == kCoarseAT) {
+            dr = -dr;
+            di = -di;
+        }
+        const double nr = c.ex + ox, ni = c.ey + oy;
+        const double inv = recip64_from32(dr * dr + di * di);
+        const double pr = nr * dr + ni * di, pi = ni * dr - nr * di;
+        if (MODE != kCoarseA) {
+            const double g = c.a * inv;
+            p += g * pr;
+            q += g * pi;
+        } else if (KIND == kFastIm) {
+            p += (c.a * pr - c.b * pi) * inv;
+        } else if (KIND == kFastReNeg) {
+            p -= (c.a * pi + c.b * pr) * inv;
+        } else {
+            p += (c.a * pi + c.b * pr) * inv;
+        }
+    }
+}
 
 template <int MODE>
-__global__ __launch_bounds__(256) void k_coarse_product(Nodes N, const double *hrow,
-                                                        const int *map, const double *fac, int n,
-                                                        int r0, int nr, int chunk, int corr,
+__global__ __launch_bounds__(256) void k_coarse_product(Nodes N, Coarse C, const double *hrow,
+                                                        const int *map, const double *fac, int r0,
+                                                        int nr, int chunk, int bands, int corr,
                                                         const double *e, double *part) {
     constexpr bool T = MODE == kCoarseAT;
     __shared__ Src ss[T ? 1 : kCoarseStage];
     __shared__ Tgt ts[T ? kCoarseStage : 1];
     __shared__ double se[kCoarseStage];
+    __shared__ FarNode sf[kCoarseStage];
+    const int n = C.n, lane = threadIdx.x & 63;
     const int r = blockIdx.x * 256 + threadIdx.x;
     const bool live = r < nr;
-    const int me = r0 + (live ? r : 0);
+    const int me = r0 + (live ? r : nr - 1);
     Tgt t;
     Src s;
     if (T) s = load_src(N, me);
     else t = load_tgt(N, me);
-    const int jb = blockIdx.y * chunk, je = min(n, jb + chunk);
+    const int loc = T ? s.loc : t.loc, M = T ? s.M : t.M, kme = T ? s.k : t.k;
     double acc = 0.0;
-    for (int jj = jb; jj < je; jj += kCoarseStage) {
-        const int j = jj + threadIdx.x;
-        if ((int)threadIdx.x < kCoarseStage && j < je) {
+    const int band = (int)blockIdx.y - ((int)gridDim.y - bands);
+    if (band >= 0) {
+        // the band: coarse nodes [lo, hi] of this boundary, cyclically
+        const int k = kme - N.bid[C.first[0]], c = C.c[k], mc = M / c;
+        int lo = (loc - kNearBand + 64 * c) / c - 64;
+        if (lo * c < loc - kNearBand) ++lo;
+        int hi = (loc + kNearBand) / c;
+        if (hi - lo + 1 >= mc) {
+            lo = 0;
+            hi = mc - 1;
+        }
+        for (int l = lo + band; l <= hi; l += bands) {
+            const int jl = l < 0 ? l + mc : l >= mc ? l - mc : l, j = C.off[k] + jl;
+            const int node = C.first[k] + jl * c;
             if (T) {
-                ts[threadIdx.x] = load_tgt(N, map[j]);
-                se[threadIdx.x] = e[j];
+                t = load_tgt(N, node);
+                if (in_band(t, s, kNearBand)) acc += k_entry<MODE>(N, t, s, corr != 0, hrow) * e[j];
             } else {
-                ss[threadIdx.x] = load_src(N, map[j]);
-                se[threadIdx.x] = fac[j] * e[j];
+                s = load_src(N, node);
+                if (in_band(t, s, kNearBand))
+                    acc += k_entry<MODE>(N, t, s, corr != 0, hrow) * ((double)c * e[j]);
             }
         }
+        if (live) part[(long)blockIdx.y * nr + r] = acc;
+        return;
+    }
+    // the wave's output nodes
+    const int oa = r0 + min(blockIdx.x * 256 + wave_base(), nr - 1);
+    const int ob = min(oa + 63, r0 + nr - 1), ko = N.bid[oa];
+    const double ox = T ? s.ex : t.ex, oy = T ? s.ey : t.ey;
+    const double oxl = T ? s.exl : t.exl, oyl = T ? s.eyl : t.eyl;
+    const int jb = blockIdx.y * chunk, je = min(n, jb + chunk);
+    for (int jj = jb; jj < je; jj += kCoarseStage) {
+        const int j = jj + threadIdx.x, js = min(je, jj + kCoarseStage);
+        if (j < js) {
+            if (T) {
+                const Tgt c = load_tgt(N, map[j]);
+                ts[threadIdx.x] = c;
+                se[threadIdx.x] = e[j];
+                sf[threadIdx.x] = FarNode{c.ex, c.ey, c.exl, c.eyl, e[j], 0.0};
+            } else {
+                const Src c = load_src(N, map[j]);
+                const double we = fac[j] * e[j];
+                ss[threadIdx.x] = c;
+                se[threadIdx.x] = we;
+                const double h = MODE == kCoarseA ? 0.5 * c.w * we : c.w * we;
+                sf[threadIdx.x] = FarNode{c.ex, c.ey, c.exl, c.eyl,
+                                          MODE == kCoarseA ? h * c.dx : h, h * c.dy};
+            }
+        }
+        // lanes kTileLanes i ..: how to take tile i, and its boundary
+        const int ta = min(jj + lane / kTileLanes * kCoarseTile, js - 1);
+        const int ca = map[ta], cb = map[min(ta + kCoarseTile, js) - 1], kcs = N.bid[ca];
+        const int kinds = T ? tile_kind<kTileLanes>(N, ca, cb, oa, ob)
+                            : tile_kind<kTileLanes>(N, oa, ob, ca, cb);
         __syncthreads();
-        const int m = min(kCoarseStage, je - jj);
-        for (int i = 0; i < m; ++i)
-            acc += k_entry<MODE>(N, T ? ts[i] : t, T ? s : ss[i], corr != 0, hrow) * se[i];
+        for (int i0 = 0; i0 < js - jj; i0 += kCoarseTile) {
+            const int m = min(kCoarseTile, js - jj - i0);
+            const int kind = __builtin_amdgcn_readlane(kinds, i0 / kCoarseTile * kTileLanes);
+            if (kind == kTileFull) {
+                for (int i = i0; i < i0 + m; ++i) {
+                    const Tgt &ti = T ? ts[i] : t;
+                    const Src &si = T ? s : ss[i];
+                    if (!in_band(ti, si, kNearBand))
+                        acc += k_entry<MODE>(N, ti, si, corr != 0, hrow) * se[i];
+                }
+                continue;
+            }
+            const FarNode *f = sf + i0;
+            const bool lo = kind == kTileLo;
+            const int kc = __builtin_amdgcn_readlane(kcs, i0 / kCoarseTile * kTileLanes);
+            const int kt = T ? kc : ko, ks = T ? ko : kc;
+            const bool im = (kt == 0) == (ks == 0);
+            double p = 0.0, q = 0.0;
+            if (MODE != kCoarseA || im) {
+                if (lo) far_sums<MODE, kFastIm, true>(f, m, ox, oy, oxl, oyl, p, q);
+                else far_sums<MODE, kFastIm, false>(f, m, ox, oy, oxl, oyl, p, q);
+            } else if (kt == 0) {
+                if (lo) far_sums<MODE, kFastReNeg, true>(f, m, ox, oy, oxl, oyl, p, q);
+                else far_sums<MODE, kFastReNeg, false>(f, m, ox, oy, oxl, oyl, p, q);
+            } else {
+                if (lo) far_sums<MODE, kFastRePos, true>(f, m, ox, oy, oxl, oyl, p, q);
+                else far_sums<MODE, kFastRePos, false>(f, m, ox, oy, oxl, oyl, p, q);
+            }
+            if (MODE == kCoarseA) {
+                acc += p;
+            } else if (T) {
+                const double fa = 0.5 * s.w * s.dx, fb = 0.5 * s.w * s.dy;
+                acc += im ? fa * p - fb * q : kt == 0 ? -(fa * q + fb * p) : fa * q + fb * p;
+            } else {
+                // R's real part on pairs of the surface and a wall, its
+                // imaginary part on the others
+                const double re = 0.5 * (t.dx * q + t.dy * p);
+                acc += im ? -0.5 * (t.dx * p - t.dy * q) : kt == 0 ? -re : re;
+            }
+            if (MODE <= kCoarseAT && corr && kt == ks && kt >= 2) {
+                double es = 0.0;
+                for (int i = i0; i < i0 + m; ++i) es += T ? s.w * se[i] : ss[i].w * se[i];
+                acc -= es;
+            }
+        }
         __syncthreads();
     }
     if (live) part[(long)blockIdx.y * nr + r] = acc;
@@ -195,11 +386,11 @@ __global__ __launch_bounds__(256) void k_roughness(const double *b, long bs, int
     }
 }
 
+// Coarse nodes per slice: about 1024 blocks, a multiple of the tile (at most
+// kSmallCoarseMax / kCoarseTile = 128 slices, and up to 9 for the band).
 int product_chunk(int nr, int n) {
-    // about 1500 blocks, chunks of a multiple of the stage
-    const int ob = cdiv(nr, 256);
-    int c = cdiv(n, std::max(1, cdiv(1500, ob)));
-    return std::max(1, cdiv(c, kCoarseStage)) * kCoarseStage;
+    const int c = cdiv(n, std::max(1, cdiv(2048, cdiv(nr, 256))));
+    return std::max(1, cdiv(c, kCoarseTile)) * kCoarseTile;
 }
 
 }  // namespace
@@ -211,7 +402,7 @@ void launch_coarse_map(const Coarse &C, int *map, double *fac, hipStream_t st) {
 void launch_assemble_coarse(const Nodes &N, const double *hrow, int mode, const int *map,
                             const double *fac, int n, int corr, double *out, long ld,
                             hipStream_t st) {
-    const dim3 grid(cdiv(ld, 64), cdiv(n, 4));
+    const dim3 grid(cdiv(ld, 64), cdiv(n, 4 * kCoarseRows));
     switch (mode) {
     case kCoarseA: hipLaunchKernelGGL(k_assemble_coarse<kCoarseA>, grid, dim3(256), 0, st, N, hrow, map, fac, n, corr, out, ld); break;
     case kCoarseAT: hipLaunchKernelGGL(k_assemble_coarse<kCoarseAT>, grid, dim3(256), 0, st, N, hrow, map, fac, n, corr, out, ld); break;
@@ -226,19 +417,21 @@ void launch_assemble_interp(const Nodes &N, const int *map, const double *fac, i
                        dim3(256), 0, st, N, map, fac, N.n, n, corr, out, ld);
 }
 
-int coarse_slices(int nr, int n) { return cdiv(n, product_chunk(nr, n)); }
-
-void launch_coarse_correct(const Nodes &N, const double *hrow, int mode, const int *map,
-                           const double *fac, int n, int corr, const double *e, int r0, int nr,
-                           int flip, double inv_d, const double *r, double *x, bool add,
+void launch_coarse_correct(const Nodes &N, const Coarse &C, const double *hrow, int mode,
+                           const int *map, const double *fac, int corr, const double *e, int r0,
+                           int nr, int flip, double inv_d, const double *r, double *x, bool add,
                            double *part, hipStream_t st) {
-    const int chunk = product_chunk(nr, n), ns = cdiv(n, chunk);
+    // at most four of the band's nodes per lane and slice
+    int least = C.c[0];
+    for (int k = 1; k < C.nb; ++k) least = std::min(least, C.c[k]);
+    const int bands = cdiv(2 * kNearBand / least + 1, 4);
+    const int chunk = product_chunk(nr, C.n), ns = cdiv(C.n, chunk) + bands;
     const dim3 grid(cdiv(nr, 256), ns);
     switch (mode) {
-    case kCoarseA: hipLaunchKernelGGL(k_coarse_product<kCoarseA>, grid, dim3(256), 0, st, N, hrow, map, fac, n, r0, nr, chunk, corr, e, part); break;
-    case kCoarseAT: hipLaunchKernelGGL(k_coarse_product<kCoarseAT>, grid, dim3(256), 0, st, N, hrow, map, fac, n, r0, nr, chunk, corr, e, part); break;
-    case kCoarseGt: hipLaunchKernelGGL(k_coarse_product<kCoarseGt>, grid, dim3(256), 0, st, N, hrow, map, fac, n, r0, nr, chunk, corr, e, part); break;
-    default: hipLaunchKernelGGL(k_coarse_product<kCoarseWall>, grid, dim3(256), 0, st, N, hrow, map, fac, n, r0, nr, chunk, corr, e, part); break;
+    case kCoarseA: hipLaunchKernelGGL(k_coarse_product<kCoarseA>, grid, dim3(256), 0, st, N, C, hrow, map, fac, r0, nr, chunk, bands, corr, e, part); break;
+    case kCoarseAT: hipLaunchKernelGGL(k_coarse_product<kCoarseAT>, grid, dim3(256), 0, st, N, C, hrow, map, fac, r0, nr, chunk, bands, corr, e, part); break;
+    case kCoarseGt: hipLaunchKernelGGL(k_coarse_product<kCoarseGt>, grid, dim3(256), 0, st, N, C, hrow, map, fac, r0, nr, chunk, bands, corr, e, part); break;
+    default: hipLaunchKernelGGL(k_coarse_product<kCoarseWall>, grid, dim3(256), 0, st, N, C, hrow, map, fac, r0, nr, chunk, bands, corr, e, part); break;
     }
     hipLaunchKernelGGL(k_coarse_finish, dim3(cdiv(nr, 64)), dim3(64 * kSliceWaves), 0, st, nr,
                        part, ns, flip, inv_d, r, x, add ? 1 : 0);

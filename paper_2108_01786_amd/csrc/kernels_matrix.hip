@@ -22,11 +22,6 @@ inline int asm_rows(int rows, long ld) {
     return r;
 }
 
-// Kinds of a far entry of A when the target and source boundaries are
-// uniform: the real part of the source-flavour term (surface row and wall
-// column), its negative (wall row and surface column), or the imaginary part.
-enum { kFastReNeg = 0, kFastRePos = 1, kFastIm = 2 };
-
 // ---------------------------------------------------------------------------
 // assembly: one thread per column (coalesced row writes), a tile of rows per
 // block with the target data staged in LDS (read as broadcasts).
@@ -422,17 +417,6 @@ __global__ __launch_bounds__(256) void k_near_band(Nodes N, const double *hrow, 
     if (i < nout && g == 0) out[i] = acc;
 }
 
-// Smallest distance between two discs of E values (centre, radius) against
-// the cut |E| / f of the larger |E| (a relative margin covers the rounding of
-// the discs): false when no pair of the two cells is closer than the cut.
-__device__ __forceinline__ bool discs_within(const double *a, const double *b, double f) {
-    const double gx = a[0] - b[0], gy = a[1] - b[1];
-    return (sqrt(gx * gx + gy * gy) - a[2] - b[2]) * f < 1.001 * max(a[3], b[3]);
-}
-__device__ __forceinline__ bool discs_may_be_near(const double *a, const double *b) {
-    return discs_within(a, b, kNearCut);
-}
-
 // True when every pair of target nodes [pa, pb] and source nodes [qa, qb] is
 // at least |E_p| / 4 apart in E (tested on the 64-node cells' discs).  The far
 // tiles of A then form E_q - E_p from the leading parts of E alone: its
@@ -453,20 +437,6 @@ __device__ __forceinline__ bool cells_far(const Nodes &N, int pa, int pb, int qa
 // the FP32 estimate refined twice, and E's trailing parts only where the
 // discs come within |E| / 4 (cells_far).  Every other wave takes a_val64,
 // the full entry (band, near pairs, diagonal limits).
-template <int KIND, bool LO>
-__device__ __forceinline__ double a_fast64(const Tgt &t, const Src &s, double fa, double fb,
-                                           double ec) {
-    const double dr = LO ? (s.ex - t.ex) + (s.exl - t.exl) : s.ex - t.ex;
-    const double di = LO ? (s.ey - t.ey) + (s.eyl - t.eyl) : s.ey - t.ey;
-    const double nr = s.ex + t.ex, ni = s.ey + t.ey;
-    const double inv = recip64_from32(dr * dr + di * di);
-    const double pr = nr * dr + ni * di;
-    const double pi = ni * dr - nr * di;
-    if (KIND == kFastReNeg) return -(fa * pi + fb * pr) * inv;
-    if (KIND == kFastRePos) return (fa * pi + fb * pr) * inv;
-    return (fa * pr - fb * pi) * inv - ec;
-}
-
 template <int KIND, bool LO>
 __device__ __forceinline__ void asm64_tile(const Tgt *tg, int rend, const Src &s, double fa,
                                            double fb, double ec, bool live, double *o, long ld) {
