@@ -236,6 +236,12 @@ struct Ctx {
     // one-launch solve; false when it could not run (solve by gmres())
     bool gmres_small(const Op &op, const double *b, double *x, bool x_zero, double tol,
                      int restart, int max_iter, SolveStats &st, int &status);
+    // its halves: the launch (false when it is not available), and the wait
+    // and the result (false when the launch gave up, x then undefined)
+    bool queue_small(const Op &op, const double *b, double *x, bool x_zero, double tol,
+                     int restart, int max_iter);
+    bool small_result(SolveStats &st, int &status);
+    int small_rc = 0;
     // words and results for nsys one-launch solves; false when out of memory
     bool ensure_small(int nsys);
     int ensure_coarse(int n, int nsys = 1);
