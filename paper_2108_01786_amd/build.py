@@ -19,7 +19,7 @@ BUILD_DIR = os.path.join(ROOT, "_build")
 
 SOURCES = ["api.hip", "kernels_geom.hip", "kernels_matrix.hip", "kernels_gemv.hip",
            "kernels_reduce.hip", "kernels_gmres.hip", "kernels_small.hip", "kernels_coarse.hip",
-           "kernels_adjoint.hip", "kernels_multi.hip",
+           "kernels_adjoint.hip", "kernels_multi.hip", "kernels_cells.hip",
            "kernels_evolve.hip", "kernels_interior.hip", "noalloc.hip"]
 
 HIPCC_FLAGS = [

@@ -295,7 +295,7 @@ void Ctx::apply(const Op &op, const double *x, const float *x32, const double *c
     case OP_W_O64: {
         const int o1 = L.off[1], nw = L.n - o1;
         launch_rflavour(L, N, hrow, 3, 0, o1, nw, o1, nw, x, part, active, stream);
-        launch_reduce_partials(nw, part, rflavour_nsplit(N, nw, nw, 0), c, 1.0, y, active,
+        launch_reduce_partials(nw, part, rflavour_nsplit(N, 3, nw, nw, 0), c, 1.0, y, active,
                                stream, op.flip);
         break;
     }
@@ -304,7 +304,7 @@ void Ctx::apply(const Op &op, const double *x, const float *x32, const double *c
         break;
     case OP_GT_O64:
         launch_rflavour(L, N, hrow, 8, 0, 0, L.n, 0, L.n, x, part, active, stream);
-        launch_reduce_partials(L.n, part, rflavour_nsplit(N, L.n, L.n, 0), c, 1.0, y, active,
+        launch_reduce_partials(L.n, part, rflavour_nsplit(N, 8, L.n, L.n, 0), c, 1.0, y, active,
                                stream, op.flip);
         break;
     }
@@ -1065,7 +1065,7 @@ void Ctx::eval_U_from_gamma(const double *gamma, double *U) {
     launch_circulant_apply(L, rowH, gamma, hg, 1.0, 0.0, 0, 0, stream);
     launch_umv(N, F, 0, n0, um, stream);
     launch_rflavour(L, N, hrow, 2, 0, 0, n0, 0, L.n, gamma, part, nullptr, stream);
-    launch_U_finalize(n0, s, um, hg, part, rflavour_nsplit(N, n0, L.n, 0), U, stream);
+    launch_U_finalize(n0, s, um, hg, part, rflavour_nsplit(N, 2, n0, L.n, 0), U, stream);
 }
 
 void Ctx::gamma_from_omega(const double *omega, double *gamma) {
@@ -1726,7 +1726,7 @@ int wwbi_solve_gamma(wwbi_ctx *ctx, const wwbi_geom *g, const double *gamma0, co
     // wall right-hand side: -G_0k^dagger gamma_0 - s dphi_mv/dn on every wall
     launch_umv(c->N, c->F, n0, nw, um, c->stream);
     launch_rflavour(c->L, c->N, c->hrow, 2, 0, n0, nw, 0, n0, gamma0, c->part, nullptr, c->stream);
-    launch_wall_rhs_finalize(nw, um, c->part, rflavour_nsplit(c->N, nw, n0, 0), rhs, c->stream);
+    launch_wall_rhs_finalize(nw, um, c->part, rflavour_nsplit(c->N, 2, nw, n0, 0), rhs, c->stream);
     hipEventRecord(c->ev[1], c->stream);
     // the wall operator: GMRES in FP64 (stored or on the fly), or (stored,
     // FP32_REFINED) FP32 products inside FP64 refinement with on-the-fly FP64
@@ -1790,7 +1790,7 @@ int wwbi_tangential_energy(wwbi_ctx *ctx, const wwbi_geom *g, const double *phi,
             launch_circulant_apply(c->L, c->rowH, gam, hg, 1.0, 0.0, 1, c->L.nb - 1, sm);
         launch_rflavour(c->L, c->N, c->hrow, 5, 0, 0, n, 0, n, gam, c->part, nullptr, sm);
         launch_tangential_finalize(n, n0, c->s, tm, gam, hg, c->part,
-                                   rflavour_nsplit(c->N, n, n, 0), dphids, sm);
+                                   rflavour_nsplit(c->N, 5, n, n, 0), dphids, sm);
     }
     hipEventRecord(c->ev[3], sm);
     if (energy) {
@@ -1800,7 +1800,7 @@ int wwbi_tangential_energy(wwbi_ctx *ctx, const wwbi_geom *g, const double *phi,
         launch_circulant_apply(c->L, c->rowD, phi, dphi, 1.0, 0.0, 0, 0, sm);
         launch_block_means(c->L, omega, means, sm);
         launch_rflavour(c->L, c->N, c->hrow, 4, 0, 0, n0, 0, n, omega, c->part, nullptr, sm);
-        launch_energy(n0, c->N, c->F, tau, grav, hw, c->part, rflavour_nsplit(c->N, n0, n, 0),
+        launch_energy(n0, c->N, c->F, tau, grav, hw, c->part, rflavour_nsplit(c->N, 4, n0, n, 0),
                       dphi, tm, means, e, E, sm);
         if (hipMemcpyAsync(c->hst, E, sizeof(double), hipMemcpyDeviceToHost, sm) != hipSuccess)
             return WWBI_EHIP;
@@ -1861,22 +1861,25 @@ int wwbi_solve_gamma_t(wwbi_ctx *ctx, const wwbi_geom *g, const double *phi, con
     c->gamma_from_omega(om, gam);
     launch_tmv(c->N, c->F, 0, n0, tm, sm);
     launch_rflavour(L, c->N, c->hrow, 5, 0, 0, n0, 0, n, gam, c->part, nullptr, sm);
-    launch_reduce_partials(n0, c->part, rflavour_nsplit(c->N, n0, n, 0), nullptr, 1.0, qg,
+    launch_reduce_partials(n0, c->part, rflavour_nsplit(c->N, 5, n0, n, 0), nullptr, 1.0, qg,
                            nullptr, sm);
     launch_gt_vectors(n0, V, u0, gam, c->s, fV, fU, sm);
     launch_circulant_apply(L, c->rowH, fU, hfu, 1.0, 0.0, 0, 0, sm);
-    const int nss = rflavour_nsplit(c->N, n0, n0, 0), nsw = rflavour_nsplit(c->N, nw, n0, 0);
     launch_rflavour(L, c->N, c->hrow, 6, 0, 0, n0, 0, n0, fV, c->part, nullptr, sm);
-    launch_reduce_partials(n0, c->part, nss, nullptr, 1.0, kfv, nullptr, sm);
+    launch_reduce_partials(n0, c->part, rflavour_nsplit(c->N, 6, n0, n0, 0), nullptr, 1.0, kfv,
+                           nullptr, sm);
     launch_rflavour(L, c->N, c->hrow, 7, 0, 0, n0, 0, n0, fU, c->part, nullptr, sm);
-    launch_reduce_partials(n0, c->part, nss, nullptr, 1.0, gfu, nullptr, sm);
+    launch_reduce_partials(n0, c->part, rflavour_nsplit(c->N, 7, n0, n0, 0), nullptr, 1.0, gfu,
+                           nullptr, sm);
     launch_gt_surface(n0, c->N, tau, grav, V, u0, gam, tm, qg, 1, hfu, kfv, gfu, e, sm);
     if (nw > 0) {
         // wall k: -F_k0 gamma_0 = KS fU - GS fV
         launch_rflavour(L, c->N, c->hrow, 6, 0, n0, nw, 0, n0, fU, c->part, nullptr, sm);
-        launch_reduce_partials(nw, c->part, nsw, nullptr, 1.0, e + n0, nullptr, sm);
+        launch_reduce_partials(nw, c->part, rflavour_nsplit(c->N, 6, nw, n0, 0), nullptr, 1.0,
+                               e + n0, nullptr, sm);
         launch_rflavour(L, c->N, c->hrow, 7, 0, n0, nw, 0, n0, fV, c->part, nullptr, sm);
-        launch_reduce_partials(nw, c->part, nsw, e + n0, 1.0, e + n0, nullptr, sm);
+        launch_reduce_partials(nw, c->part, rflavour_nsplit(c->N, 7, nw, n0, 0), e + n0, 1.0,
+                               e + n0, nullptr, sm);
     }
     // D e, the surface rows negated as the solve takes them
     launch_circulant_apply2(L, c->rowD, e, b, -1.0, 1.0, 0.0, 0, L.nb - 1, sm);
@@ -2106,7 +2109,7 @@ static void boundary_derivs(Ctx *c, const double *omega, double *sds, double *sd
     launch_circulant_apply(L, c->rowH, gam, hg, 1.0, 0.0, 0, L.nb - 1, sm);
     launch_tmv(c->N, c->F, 0, n, tm, sm);
     launch_umv(c->N, c->F, 0, n, um, sm);
-    const int ns = rflavour_nsplit(c->N, n, n, 0);
+    const int ns = rflavour_nsplit(c->N, 5, n, n, 0);   // and of mode 2
     launch_rflavour(L, c->N, c->hrow, 5, 0, 0, n, 0, n, gam, c->part, nullptr, sm);
     launch_tangential_finalize(n, n0, nullptr, tm, gam, hg, c->part, ns, sds, sm);
     launch_rflavour(L, c->N, c->hrow, 2, 0, 0, n, 0, n, gam, c->part, nullptr, sm);
@@ -2264,15 +2267,15 @@ int wwbi_pressure(wwbi_ctx *ctx, const wwbi_geom *g, const double *phi, double t
     launch_circulant_apply(L, c->rowH, x, hw, 1.0, 0.0, 0, L.nb - 1, sm);
     launch_block_means(L, x, means, sm);
     launch_rflavour(L, c->N, c->hrow, 4, 0, 0, n0, 0, n, x, c->part, nullptr, sm);
-    launch_reduce_partials(n0, c->part, rflavour_nsplit(c->N, n0, n, 0), nullptr, 1.0, ps,
+    launch_reduce_partials(n0, c->part, rflavour_nsplit(c->N, 4, n0, n, 0), nullptr, 1.0, ps,
                            nullptr, sm);
     if (nw > 0) {
         launch_rflavour(L, c->N, c->hrow, 6, 0, n0, nw, 0, n0, x, c->part, nullptr, sm);
-        launch_reduce_partials(nw, c->part, rflavour_nsplit(c->N, nw, n0, 0), nullptr, 1.0, rw,
+        launch_reduce_partials(nw, c->part, rflavour_nsplit(c->N, 6, nw, n0, 0), nullptr, 1.0, rw,
                                nullptr,
                                sm);
         launch_rflavour(L, c->N, c->hrow, 7, 0, n0, nw, n0, nw, x + n0, c->part, nullptr, sm);
-        launch_reduce_partials(nw, c->part, rflavour_nsplit(c->N, nw, nw, 0), rw, -1.0, rw,
+        launch_reduce_partials(nw, c->part, rflavour_nsplit(c->N, 7, nw, nw, 0), rw, -1.0, rw,
                                nullptr, sm);
     }
     launch_phi_aux_values(n, n0, b, ps, rw, hw, c->bid, means, fr, fi, sm);
@@ -2356,7 +2359,7 @@ int wwbi_adjoint_phi(wwbi_ctx *ctx, const wwbi_geom *g, const double *omega, con
     // c = Ubar / s;  gammabar = T^T c - H c / 2 (surface block);  mu = Gamma^T gammabar
     launch_adj_c(n0, dJdU, c->s, cv, sm);
     launch_rflavour(c->L, c->N, c->hrow, 2, 1, 0, n0, 0, n, cv, c->part, nullptr, sm);
-    launch_reduce_partials(n, c->part, rflavour_nsplit(c->N, n0, n, 1), nullptr, 1.0, gbar,
+    launch_reduce_partials(n, c->part, rflavour_nsplit(c->N, 2, n0, n, 1), nullptr, 1.0, gbar,
                            nullptr, sm);
     launch_circulant_apply(c->L, c->rowH, cv, gbar, -0.5, 1.0, 0, 0, sm);
     // (its surface rows negated, as the solve takes them)
@@ -2470,7 +2473,7 @@ int wwbi_tangent_phi(wwbi_ctx *ctx, const wwbi_geom *g, const double *omega, int
             launch_tlm_finalize(n0, nd, c->s, um, hgs, tgs, dU, sm);
         } else {
             // no room for T: its on-the-fly product, one direction at a time
-            const int nsu = rflavour_nsplit(c->N, n0, n, 0);
+            const int nsu = rflavour_nsplit(c->N, 2, n0, n, 0);
             for (int i = 0; i < nd; ++i) {
                 launch_rflavour(c->L, c->N, c->hrow, 2, 0, 0, n0, 0, n, dG + (long)i * ldv,
                                 c->part, nullptr, sm);

@@ -325,7 +325,7 @@ void launch_rflavour(const Layout &L, const Nodes &N, const double *hrow, int mo
 // partial slices (far chunks + the near band) of a product over nr rows and
 // nc columns, forward or transposed; at most 257, each of length nr
 // (forward) or nc (transposed)
-int rflavour_nsplit(const Nodes &N, int nr, int nc, int transpose);
+int rflavour_nsplit(const Nodes &N, int mode, int nr, int nc, int transpose);
 void launch_reduce_partials(int n, const double *part, int nsplit, const double *c, double scale,
                             double *y, const int *active, hipStream_t st, int flip = 0);
 int otf_chunk(int n);
@@ -400,6 +400,17 @@ struct SmallArgs {
 long small_exchange_words();
 // nsys systems with the same matrix; WWBI_OK when queued
 int launch_small_gmres(SmallArgs a, int nsys, hipStream_t st);
+
+// ---- kernels_cells.hip -------------------------------------------------------
+// Far part (all but the same-boundary band) of an on-the-fly FP64 product of a
+// mode, outputs [o0, o0 + no), summed nodes [s0, s0 + ns): cell_slices(no, ns)
+// slices of no values in part; mom: cell_moments_size(N.n) doubles.
+constexpr long kCellPairs = 24000000, kCellPairsH = 36000000;
+int cell_slices(int no, int ns);
+long cell_moments_size(int n);
+void launch_cell_far(const Nodes &N, const double *hrow, int mode, bool cols, int o0, int no,
+                     int s0, int ns, int corr, const double *x, double *part, double *mom,
+                     const int *active, hipStream_t st);
 
 // ---- kernels_coarse.hip ------------------------------------------------------
 // A coarse subset of the nodes: every c[k]-th node of boundary k from node

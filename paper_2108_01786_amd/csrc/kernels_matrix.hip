@@ -1232,10 +1232,26 @@ static int split_chunk(int nout, int nsum, int per_block) {
 static int rows_chunk(int nr, int nc) { return split_chunk(nr, nc, 256 * kTPT); }
 static int cols_chunk(int nr, int nc) { return split_chunk(nc, nr, 256); }
 
+// Where the far part of the FP64 products (rows of every mode, and the
+// columns of A) goes through the cells' moments (kernels_cells.hip): two
+// launches that take 23 to 31 us however small the product.  Without h, pair
+// by pair takes 28 us at 21 million pairs, 34 at 25, 44 at 36 and 88 at 105
+// (moments: 29, 32, 33, 43); with h, 29 to 50 at 18 and 41 at 42 (moments: 37
+// to 43, and 36).
+static bool use_cells(int mode, int nr, int nc) {
+    const bool h = mode == 2 || mode == 4 || mode == 5 || mode == 7;
+    return (long)nr * nc >= (h ? kCellPairsH : kCellPairs);
+}
+// the moments' place behind the slices of `part`, which holds 258 vectors
+static double *cell_moments(const Nodes &N, double *part) {
+    return part + 256L * ((N.n + 63) / 64 * 64);
+}
+
 // Partial slices of an on-the-fly product of modes 2..8: the far chunks, the
 // near band and, when the geometry has near pairs, the near-pair fix.
-int rflavour_nsplit(const Nodes &N, int nr, int nc, int transpose) {
+int rflavour_nsplit(const Nodes &N, int mode, int nr, int nc, int transpose) {
     const int fix = N.near ? 2 : 1;
+    if (!transpose && use_cells(mode, nr, nc)) return cell_slices(nr, nc) + fix;
     return transpose ? cdiv(nr, cols_chunk(nr, nc)) + fix : cdiv(nc, rows_chunk(nr, nc)) + fix;
 }
 
@@ -1345,8 +1361,9 @@ void launch_otf_matvec(const Layout &L, const Nodes &N, int flags, int fp32, int
                        const int *active, hipStream_t st, int flip) {
     const double *hrow = nullptr;
     const int n = L.n;
+    const bool cells = !fp32 && near_width(band) == kNearBand && use_cells(0, n, n);
     const int chunk = transpose ? cols_chunk(n, n) : rows_chunk(n, n);
-    const int ns = cdiv(n, chunk);
+    const int ns = cells ? cell_slices(n, n) : cdiv(n, chunk);
     const int nb = near_width(band);
     const int corr = (flags & WWBI_FLAG_NO_CORRECTION) ? 0 : 1;
     dim3 grid(cdiv(n, 256), ns);
@@ -1355,6 +1372,9 @@ void launch_otf_matvec(const Layout &L, const Nodes &N, int flags, int fp32, int
     const dim3 gfix(fix_blocks(0, n));
     double *near = part + (long)ns * n;
     double *fix = near + n;
+    if (cells)
+        launch_cell_far(N, hrow, 0, transpose != 0, 0, n, 0, n, corr, x, part,
+                        cell_moments(N, part), active, st);
     if (!transpose) {
         if (fp32) {
             hipLaunchKernelGGL((k_otf_rows<1, true>), gridr, dim3(256), 0, st, N, hrow, 0, n, 0, n,
@@ -1362,8 +1382,9 @@ void launch_otf_matvec(const Layout &L, const Nodes &N, int flags, int fp32, int
             hipLaunchKernelGGL((k_near_band<1, false>), gnear, dim3(256), 0, st, N,
                                hrow, 0, n, 0, n, corr, band, nb, x, near, active);
         } else {
-            hipLaunchKernelGGL((k_otf_rows<0, false>), gridr, dim3(256), 0, st, N, hrow, 0, n, 0, n,
-                               chunk, corr, nb, x, part, active);
+            if (!cells)
+                hipLaunchKernelGGL((k_otf_rows<0, false>), gridr, dim3(256), 0, st, N, hrow, 0, n,
+                                   0, n, chunk, corr, nb, x, part, active);
             hipLaunchKernelGGL((k_near_band<0, false>), gnear, dim3(256), 0, st, N,
                                hrow, 0, n, 0, n, corr, band, nb, x, near, active);
             if (N.near)
@@ -1377,8 +1398,9 @@ void launch_otf_matvec(const Layout &L, const Nodes &N, int flags, int fp32, int
             hipLaunchKernelGGL((k_near_band<1, true>), gnear, dim3(256), 0, st, N,
                                hrow, 0, n, 0, n, corr, band, nb, x, near, active);
         } else {
-            hipLaunchKernelGGL((k_otf_cols<0, false>), grid, dim3(256), 0, st, N, hrow, 0, n, 0, n,
-                               chunk, corr, nb, x, part, active);
+            if (!cells)
+                hipLaunchKernelGGL((k_otf_cols<0, false>), grid, dim3(256), 0, st, N, hrow, 0, n,
+                                   0, n, chunk, corr, nb, x, part, active);
             hipLaunchKernelGGL((k_near_band<0, true>), gnear, dim3(256), 0, st, N,
                                hrow, 0, n, 0, n, corr, band, nb, x, near, active);
             if (N.near)
@@ -1399,11 +1421,16 @@ static void rflavour_mode(const Nodes &N, const double *hrow, int transpose, int
                           hipStream_t st) {
     const int nb = kNearBand;
     if (!transpose) {
+        const bool cells = use_cells(MODE, nr, nc);
         const int chunk = rows_chunk(nr, nc);
-        const int ns = cdiv(nc, chunk);
+        const int ns = cells ? cell_slices(nr, nc) : cdiv(nc, chunk);
         dim3 grid(cdiv(nr, 256 * kTPT), ns);
-        hipLaunchKernelGGL((k_otf_rows<MODE, false>), grid, dim3(256), 0, st, N, hrow, r0, nr, c0,
-                           nc, chunk, 1, nb, x, part, active);
+        if (cells)
+            launch_cell_far(N, hrow, MODE, false, r0, nr, c0, nc, 1, x, part,
+                            cell_moments(N, part), active, st);
+        else
+            hipLaunchKernelGGL((k_otf_rows<MODE, false>), grid, dim3(256), 0, st, N, hrow, r0, nr,
+                               c0, nc, chunk, 1, nb, x, part, active);
         hipLaunchKernelGGL((k_near_band<MODE, false>), dim3(cdiv(nr, kNearPerBlock)), dim3(256), 0,
                            st, N, hrow, r0, nr, c0, nc, 1, 0, nb, x, part + (long)ns * nr,
                            active);

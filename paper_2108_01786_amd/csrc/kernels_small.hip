@@ -25,6 +25,7 @@
 // solves by the multi-kernel loop.  That can only happen when the blocks of
 // one launch are kept from running together for that long, by other work
 // filling the device.
+#include "entries.h"
 #include "internal.h"
 
 namespace wwbi {
@@ -44,31 +45,6 @@ __device__ __forceinline__ void put_word(u64 *p, u64 v) {
 }
 __device__ __forceinline__ u64 get_word(const u64 *p) {
     return __hip_atomic_load(const_cast<u64 *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// v of the lane that DPP control CTRL names (every lane has a source)
-template <int CTRL>
-__device__ __forceinline__ double dpp_move(double v) {
-    const u64 u = (u64)__double_as_longlong(v);
-    const int lo = __builtin_amdgcn_mov_dpp((int)(u & 0xffffffffu), CTRL, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_mov_dpp((int)(u >> 32), CTRL, 0xf, 0xf, true);
-    return __longlong_as_double((long long)(((u64)(unsigned)hi << 32) | (unsigned)lo));
-}
-__device__ __forceinline__ double lane_value(double v, int lane) {
-    const u64 u = (u64)__double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)(u & 0xffffffffu), lane);
-    const int hi = __builtin_amdgcn_readlane((int)(u >> 32), lane);
-    return __longlong_as_double((long long)(((u64)(unsigned)hi << 32) | (unsigned)lo));
-}
-
-// Sum over the wave, the same value in every lane: neighbours, quads, half
-// rows and rows of 16 by DPP moves (no LDS round trip), then the four rows.
-__device__ __forceinline__ double wave_total(double v) {
-    v += dpp_move<0xB1>(v);      // quad_perm [1,0,3,2]
-    v += dpp_move<0x4E>(v);      // quad_perm [2,3,0,1]
-    v += dpp_move<0x141>(v);     // row_half_mirror
-    v += dpp_move<0x140>(v);     // row_mirror
-    return ((lane_value(v, 0) + lane_value(v, 16)) + lane_value(v, 32)) + lane_value(v, 48);
 }
 
 template <int CPL, int RW>
