@@ -2322,7 +2322,7 @@ int wwbi_adjoint_phi(wwbi_ctx *ctx, const wwbi_geom *g, const double *omega, con
     }
     const int n = rc ? 0 : c->L.n, n0 = rc ? 0 : c->L.off[1];
     if (!rc) {
-        const int ns = adjoint_nsplit(n);
+        const int ns = adjoint_nsplit(n, n0);
         rc = grow(c->apart, c->capapart, (size_t)12 * ns * n0 + 64);
     }
     if (rc) {
@@ -2379,12 +2379,12 @@ int wwbi_adjoint_phi(wwbi_ctx *ctx, const wwbi_geom *g, const double *omega, con
     hipEventRecord(c->ev[3], sm);
     if (status < 0) { c->finish_report(rep, status, st, bytes); return status; }
     // derivative contractions and the final combination
-    const int ns = adjoint_nsplit(n);
+    const int ns = adjoint_nsplit(n, n0);
     double *prow = c->apart, *pcol = c->apart + (size_t)6 * ns * n0;
     launch_adj_rows(c->N, c->hrow, n0, n, omega, gam, prow, sm);
     launch_adj_cols(c->N, n0, n, lam, cv, pcol, sm);
-    launch_adj_finalize(c->N, c->F, n0, dJdU, U, omega, gam, lam, prow, ns, pcol, ns, g_phi, g_x,
-                        g_y, g_dx, g_dy, g_ddx, g_ddy, sm);
+    launch_adj_finalize(c->N, c->F, n0, n, dJdU, U, omega, gam, lam, prow, pcol, g_phi, g_x, g_y, g_dx,
+                        g_dy, g_ddx, g_ddy, sm);
     hipEventRecord(c->ev[4], sm);
     c->finish_report(rep, status, st, bytes);
     if (hipGetLastError() != hipSuccess) return WWBI_EHIP;
@@ -2412,7 +2412,7 @@ int wwbi_tangent_phi(wwbi_ctx *ctx, const wwbi_geom *g, const double *omega, int
         rc = c->setup(g, dirs, (int)(7L * nd * g->M[0]), false);
     }
     const int n = rc ? 0 : c->L.n, n0 = rc ? 0 : c->L.off[1];
-    const int nsr = rc ? 0 : adjoint_nsplit(n), nsc = rc ? 0 : tlm_nsplit(n, n0);
+    const int nsr = rc ? 0 : adjoint_nsplit(n, n0), nsc = rc ? 0 : tlm_nsplit(n, n0);
     if (!rc) rc = c->ensure_multi(n, nd, o->restart);
     if (!rc)
         rc = grow(c->apart, c->capapart,
@@ -2585,13 +2585,13 @@ int wwbi_surface_fill(wwbi_ctx *ctx, int32_t n, const double *xt, const double *
     int rc = c->ensure(n, c->restart_cap);
     if (rc) return rc;
     hipStream_t st = c->stream;
-    launch_circ_row1(n, WWBI_OP_D, c->rowD, st);
-    launch_surface_base(n, xt, yt, x, y, st);
-    launch_circ_apply1(n, c->rowD, xt, dx, 1.0, 0.0, st);
-    launch_circ_apply1(n, c->rowD, dx, ddx, 1.0, 0.0, st);
-    launch_add_scalar(n, dx, 1.0, st);
-    launch_circ_apply1(n, c->rowD, yt, dy, 1.0, 0.0, st);
-    launch_circ_apply1(n, c->rowD, dy, ddy, 1.0, 0.0, st);
+    // (x, y) side by side: three launches of 3 to 9 us
+    double *tmp = c->vec[VTMP];
+    launch_surface_base(n, xt, yt, x, y, c->rowD, st);
+    launch_circ_pair(n, c->rowD, {xt, dx, nullptr, tmp, 1.0}, {yt, dy, nullptr, nullptr, 0.0}, 0.0,
+                     st);
+    launch_circ_pair(n, c->rowD, {tmp, ddx, nullptr, nullptr, 0.0}, {dy, ddy, nullptr, nullptr, 0.0},
+                     0.0, st);
     if (hipStreamSynchronize(st) != hipSuccess) return WWBI_EHIP;
     return hip_ok(hipGetLastError());
 }
@@ -2607,17 +2607,13 @@ int wwbi_surface_fill_adjoint(wwbi_ctx *ctx, int32_t n, const double *g_x, const
     int rc = c->ensure(n, c->restart_cap);
     if (rc) return rc;
     hipStream_t st = c->stream;
-    double *tmp = c->vec[VTMP];
+    double *tx = c->vec[VTMP], *ty = c->vec[VTMP2];
     launch_circ_row1(n, WWBI_OP_D, c->rowD, st);
-    // g_xt = g_x - D g_dx + D (D g_ddx)   (D^T = -D, (D2)^T = D2)
-    launch_copy(g_xt, g_x, n, st);
-    launch_circ_apply1(n, c->rowD, g_dx, g_xt, -1.0, 1.0, st);
-    launch_circ_apply1(n, c->rowD, g_ddx, tmp, 1.0, 0.0, st);
-    launch_circ_apply1(n, c->rowD, tmp, g_xt, 1.0, 1.0, st);
-    launch_copy(g_yt, g_y, n, st);
-    launch_circ_apply1(n, c->rowD, g_dy, g_yt, -1.0, 1.0, st);
-    launch_circ_apply1(n, c->rowD, g_ddy, tmp, 1.0, 0.0, st);
-    launch_circ_apply1(n, c->rowD, tmp, g_yt, 1.0, 1.0, st);
+    // g_xt = g_x + D (D g_ddx - g_dx)   (D^T = -D, (D2)^T = D2)
+    launch_circ_pair(n, c->rowD, {g_ddx, tx, g_dx, nullptr, 0.0}, {g_ddy, ty, g_dy, nullptr, 0.0},
+                     -1.0, st);
+    launch_circ_pair(n, c->rowD, {tx, g_xt, g_x, nullptr, 0.0}, {ty, g_yt, g_y, nullptr, 0.0}, 1.0,
+                     st);
     if (hipStreamSynchronize(st) != hipSuccess) return WWBI_EHIP;
     return hip_ok(hipGetLastError());
 }

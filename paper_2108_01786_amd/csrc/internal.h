@@ -205,8 +205,18 @@ void launch_U_finalize(int n0, const double *s, const double *umv, const double 
 void launch_wall_rhs_finalize(int nw, const double *umv_w, const double *part, int nsplit,
                               double *rhs, hipStream_t st);
 void launch_surface_base(int n, const double *xt, const double *yt, double *x, double *y,
-                         hipStream_t st);
-void launch_add_scalar(int n, double *v, double c, hipStream_t st);
+                         double *row, hipStream_t st);
+// out = (circulant row) f + c add + shift, raw the same without the shift, for
+// two vectors side by side; add and raw may be null
+struct CircVec {
+    const double *f;
+    double *out;
+    const double *add;
+    double *raw;
+    double shift;
+};
+void launch_circ_pair(int M, const double *row, const CircVec &a, const CircVec &b, double c,
+                      hipStream_t st);
 
 // ---- kernels_evolve.hip ------------------------------------------------------
 constexpr int kMaxStages = 16;   // Runge-Kutta stages per step
@@ -328,11 +338,9 @@ void launch_rflavour(const Layout &L, const Nodes &N, const double *hrow, int mo
 int rflavour_nsplit(const Nodes &N, int mode, int nr, int nc, int transpose);
 void launch_reduce_partials(int n, const double *part, int nsplit, const double *c, double scale,
                             double *y, const int *active, hipStream_t st, int flip = 0);
-int otf_chunk(int n);
-int otf_nsplit(int n);
 
 // ---- kernels_adjoint.hip -----------------------------------------------------
-int adjoint_nsplit(int n);
+int adjoint_nsplit(int n, int n0);
 // Tangent-linear model of the velocity-potential solve (up to 32 directions
 // at once; dirs 7 x nd x M_0): the source-moving parts of dA omega (pA, n per
 // direction and slice) and of dT gamma (pT, M_0), from the weights W
@@ -354,11 +362,11 @@ void launch_adj_rows(const Nodes &N, const double *hrow, int n0, int n, const do
                      const double *gamma, double *part, hipStream_t st);
 void launch_adj_cols(const Nodes &N, int n0, int n, const double *lam, const double *cvec,
                      double *part, hipStream_t st);
-void launch_adj_finalize(const Nodes &N, const Flow &F, int n0, const double *Ubar,
+void launch_adj_finalize(const Nodes &N, const Flow &F, int n0, int n, const double *Ubar,
                          const double *U, const double *omega, const double *gamma,
-                         const double *lam, const double *prow, int nsr, const double *pcol,
-                         int nsc, double *g_phi, double *g_x, double *g_y, double *g_dx,
-                         double *g_dy, double *g_ddx, double *g_ddy, hipStream_t st);
+                         const double *lam, const double *prow, const double *pcol, double *g_phi,
+                         double *g_x, double *g_y, double *g_dx, double *g_dy, double *g_ddx,
+                         double *g_ddy, hipStream_t st);
 
 // ---- kernels_small.hip -------------------------------------------------------
 // Restarted GMRES of a small system in one launch: whole systems of up to

@@ -20,7 +20,6 @@ namespace wwbi {
 namespace {
 
 inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
-constexpr int kStage = 256;
 constexpr int kTlmMax = 32;      // directions of one tangent-linear launch
 constexpr int kTlmWaves = 4608;  // waves the column pass's source split aims at
 
@@ -86,120 +85,176 @@ __device__ __forceinline__ void store6(double *part, long st, long off, const do
 }
 
 // Far part of both passes: every pair except the surface pairs within nb
-// grid steps of r (diagonal included), with kappa from E alone.  Chunk
-// blockIdx.y of the other index, written as slice blockIdx.y of `part`
-// (component stride st).  A staged tile that holds no near-band pair for the
-// wave skips the per-pair test (CHECK = false).
-template <bool CHECK>
-__device__ __forceinline__ void adj_rows_tile(const Tgt &t, const Src *ss, const double *sw,
-                                              const double *sg, int m, int nb, double (&a)[6]) {
-    for (int i = 0; i < m; ++i) {
-        const Src &s = ss[i];
-        if (CHECK && in_band(t, s, nb)) continue;
-        double cr, ci;
-        kappa64_far(t, s, cr, ci);
-        row_terms(t, s, cr, ci, sw[i], sg[i], a);
+// grid steps of r (diagonal included), with kappa from E alone.  A block takes
+// 64 nodes r, a lane each, and a chunk of the other index, staged in LDS and
+// shared by its waves: slice blockIdx.y of `part` (component stride st).  What
+// a pair contributes is linear in a few sums over 1 + kappa^2 and kappa, so
+// the loops form those (35 operations a pair instead of 75) and the factors of
+// node r follow once.  With a node per thread of 256, a wave went through 256
+// pairs on its own and the launch had half a wave per SIMD: 95 us for the rows
+// and 86 for the columns at 2048 x 4608 nodes; now 19 and 18.
+constexpr int kAdjWaves = 4;
+constexpr int kAdjStage = 64 * kAdjWaves;
+
+// A staged node: E, complex weight a (of 1 + kappa^2) and real weight g.
+struct AdjNode {
+    double ex, ey, exl, eyl, ar, ai, g;
+    int loc;
+};
+
+// Sums over nodes [i0, i1): A = sum a (1 + kappa^2), Q = sum g (1 + kappa^2),
+// K = sum g kappa; kappa of (source, target) = (node, own) or, with OWN_SRC,
+// (own, node).  CHECK: nodes within nb steps of the own are left out.
+struct AdjSums {
+    Cx A, Q, K;
+};
+template <bool OWN_SRC, bool CHECK>
+__device__ __forceinline__ void adj_sums(const AdjNode *f, int i0, int i1, double ox, double oy,
+                                         double oxl, double oyl, int loc, int M, int nb,
+                                         AdjSums &o) {
+    for (int i = i0; i < i1; ++i) {
+        const AdjNode &c = f[i];
+        double dr = (c.ex - ox) + (c.exl - oxl), di = (c.ey - oy) + (c.eyl - oyl);
+        if (OWN_SRC) {
+            dr = -dr;
+            di = -di;
+        }
+        const double nr = c.ex + ox, ni = c.ey + oy;
+        const double inv = recip64(dr * dr + di * di);
+        double cr = -(ni * dr - nr * di) * inv, ci = (nr * dr + ni * di) * inv;
+        double ar = c.ar, ai = c.ai, g = c.g;
+        if (CHECK && cyc_dist(c.loc, loc, M) <= nb) cr = ci = ar = ai = g = 0.0;
+        const double qr = 1.0 + cr * cr - ci * ci, qi = 2.0 * cr * ci;
+        o.A.re += ar * qr - ai * qi;
+        o.A.im += ar * qi + ai * qr;
+        o.Q.re += g * qr;
+        o.Q.im += g * qi;
+        o.K.re += g * cr;
+        o.K.im += g * ci;
     }
 }
 
-template <bool CHECK>
-__device__ __forceinline__ void adj_cols_tile(const Src &s, const Tgt *ts, const double *sl,
-                                              const double *sc, int m, int nb, double (&a)[6]) {
-    for (int i = 0; i < m; ++i) {
-        const Tgt &t = ts[i];
-        if (CHECK && in_band(t, s, nb)) continue;
-        double cr, ci;
-        kappa64_far(t, s, cr, ci);
-        col_terms(t, s, cr, ci, sl[i], sc[i], a);
+// The chunk's sums over the surface's nodes (S) and the walls' (W) for the
+// wave's share of every stage.
+template <bool OWN_SRC, class Load>
+__device__ __forceinline__ void adj_chunk(const Nodes &N, AdjNode *f, int r0, int n0, int b0,
+                                          int e0, int nb, double ox, double oy, double oxl,
+                                          double oyl, Load load, AdjSums &S, AdjSums &W) {
+    const int wv = threadIdx.x >> 6, r = r0 + (threadIdx.x & 63);
+    for (int b = b0; b < e0; b += kAdjStage) {
+        const int m = min(kAdjStage, e0 - b);
+        if (b > b0) __syncthreads();
+        if ((int)threadIdx.x < m) f[threadIdx.x] = load(b + threadIdx.x);
+        __syncthreads();
+        const int share = (m + kAdjWaves - 1) / kAdjWaves;
+        const int i0 = min(m, share * wv), i1 = min(m, i0 + share);
+        const int ms = min(max(n0 - b, i0), i1);       // surface nodes come first
+        if (ms > i0) {
+            const int ra = r0, rb = min(r0 + 63, n0 - 1);
+            if (ranges_apart(N, ra, rb, b + i0, b + ms - 1, nb))
+                adj_sums<OWN_SRC, false>(f, i0, ms, ox, oy, oxl, oyl, r, n0, nb, S);
+            else
+                adj_sums<OWN_SRC, true>(f, i0, ms, ox, oy, oxl, oyl, r, n0, nb, S);
+        }
+        adj_sums<OWN_SRC, false>(f, ms, i1, ox, oy, oxl, oyl, r, n0, nb, W);
     }
 }
 
-__global__ __launch_bounds__(256) void k_adj_rows(Nodes N, int n0, int n, int chunk, int nb,
-                                                  const double *__restrict__ omega,
-                                                  const double *__restrict__ gamma,
-                                                  double *__restrict__ part, long st) {
-    __shared__ Src ss[kStage];
-    __shared__ double sw[kStage], sg[kStage];
-    const int wb = wave_base();
-    const int r = blockIdx.x * 256 + threadIdx.x;
-    const bool live = r < n0;
-    Tgt t;
-    if (live) t = load_tgt(N, r);
+// The waves' six values of a node added in wave order into the slice.
+__device__ __forceinline__ void adj_store(double (*red)[6][64], const double (&a)[6], int r0,
+                                          int n0, double *part, long st, long slice) {
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) red[wv][k][lane] = a[k];
+    __syncthreads();
+    for (int k = wv; k < 6; k += kAdjWaves) {
+        double v = red[0][k][lane];
+        for (int w = 1; w < kAdjWaves; ++w) v += red[w][k][lane];
+        if (r0 + lane < n0) part[k * st + slice * n0 + r0 + lane] = v;
+    }
+}
+
+__global__ __launch_bounds__(kAdjStage) void k_adj_rows(Nodes N, int n0, int n, int chunk, int nb,
+                                                        const double *__restrict__ omega,
+                                                        const double *__restrict__ gamma,
+                                                        double *__restrict__ part, long st) {
+    __shared__ AdjNode f[kAdjStage];
+    __shared__ double red[kAdjWaves][6][64];
+    const int r0 = blockIdx.x * 64, r = min(r0 + (int)(threadIdx.x & 63), n0 - 1);
     const int qb = blockIdx.y * chunk, qe = min(n, qb + chunk);
-    double a[6] = {0, 0, 0, 0, 0, 0};
-    for (int qq = qb; qq < qe; qq += kStage) {
-        const int q = qq + threadIdx.x;
-        if (q < qe) {
-            ss[threadIdx.x] = load_src(N, q);
-            sw[threadIdx.x] = omega[q];
-            sg[threadIdx.x] = gamma[q];
-        }
-        __syncthreads();
-        const int m = min(kStage, qe - qq);
-        const bool apart = wave_apart<false>(N, 0, blockIdx.x * 256 + wb, n0, qq, m, nb);
-        if (live) {
-            if (apart)
-                adj_rows_tile<false>(t, ss, sw, sg, m, nb, a);
-            else
-                adj_rows_tile<true>(t, ss, sw, sg, m, nb, a);
-        }
-        __syncthreads();
-    }
-    if (live) store6(part, st, (long)blockIdx.y * n0 + r, a);
+    AdjSums S{}, W{};
+    // dS/dz_r = d_q Q / 4 with the weight w omega, the R terms with w gamma
+    adj_chunk<false>(N, f, r0, n0, qb, qe, nb, N.ex[r], N.ey[r], N.exl[r], N.eyl[r],
+                     [&](int q) {
+                         const double w = N.w[q], a = 0.25 * w * omega[q];
+                         return AdjNode{N.ex[q], N.ey[q], N.exl[q], N.eyl[q],
+                                        a * N.dx[q], a * N.dy[q], w * gamma[q], N.loc[q]};
+                     },
+                     S, W);
+    const Cx d{N.dx[r], N.dy[r]};
+    // dR/dz_r = -d_r Q / 4, dR/dd_r = -kappa / 2; a surface source takes Im S
+    // and Re R, a wall source Re S and Im R
+    const Cx R0 = cscale(cmul(d, S.Q), -0.25), R1 = cscale(cmul(d, W.Q), -0.25);
+    const double a[6] = {S.A.im + W.A.re,        S.A.re - W.A.im,
+                         R0.re + R1.im,          -R0.im + R1.re,
+                         -0.5 * (S.K.re + W.K.im), 0.5 * (S.K.im - W.K.re)};
+    adj_store(red, a, r0, n0, part, st, blockIdx.y);
 }
 
-__global__ __launch_bounds__(256) void k_adj_cols(Nodes N, int n0, int n, int chunk, int nb,
-                                                  const double *__restrict__ lam,
-                                                  const double *__restrict__ cvec,
-                                                  double *__restrict__ part, long st) {
-    __shared__ Tgt ts[kStage];
-    __shared__ double sl[kStage], sc[kStage];
-    const int wb = wave_base();
-    const int r = blockIdx.x * 256 + threadIdx.x;
-    const bool live = r < n0;
-    Src s;
-    if (live) s = load_src(N, r);
+__global__ __launch_bounds__(kAdjStage) void k_adj_cols(Nodes N, int n0, int n, int chunk, int nb,
+                                                        const double *__restrict__ lam,
+                                                        const double *__restrict__ cvec,
+                                                        double *__restrict__ part, long st) {
+    __shared__ AdjNode f[kAdjStage];
+    __shared__ double red[kAdjWaves][6][64];
+    const int r0 = blockIdx.x * 64, r = min(r0 + (int)(threadIdx.x & 63), n0 - 1);
     const int pb = blockIdx.y * chunk, pe = min(n, pb + chunk);
-    double a[6] = {0, 0, 0, 0, 0, 0};
-    for (int pp = pb; pp < pe; pp += kStage) {
-        const int p = pp + threadIdx.x;
-        if (p < pe) {
-            ts[threadIdx.x] = load_tgt(N, p);
-            sl[threadIdx.x] = lam[p];
-            sc[threadIdx.x] = p < n0 ? cvec[p] : 0.0;
-        }
-        __syncthreads();
-        const int m = min(kStage, pe - pp);
-        const bool apart = wave_apart<true>(N, 0, blockIdx.x * 256 + wb, n0, pp, m, nb);
-        if (live) {
-            if (apart)
-                adj_cols_tile<false>(s, ts, sl, sc, m, nb, a);
-            else
-                adj_cols_tile<true>(s, ts, sl, sc, m, nb, a);
-        }
-        __syncthreads();
-    }
-    if (live) store6(part, st, (long)blockIdx.y * n0 + r, a);
+    AdjSums S{}, W{};
+    // the S terms with the weight lambda, dR/dz_r = d_p Q / 4 with c (surface
+    // targets only)
+    adj_chunk<true>(N, f, r0, n0, pb, pe, nb, N.ex[r], N.ey[r], N.exl[r], N.eyl[r],
+                    [&](int p) {
+                        const double c = p < n0 ? 0.25 * cvec[p] : 0.0;
+                        return AdjNode{N.ex[p], N.ey[p], N.exl[p], N.eyl[p],
+                                       c * N.dx[p], c * N.dy[p], lam[p], N.loc[p]};
+                    },
+                    S, W);
+    const double w = N.w[r];
+    const Cx d{N.dx[r], N.dy[r]};
+    // dS/dz_r = -d_r Q / 4, dS/dd_r = kappa / 2; a surface row takes Im S, a
+    // wall row -Re S
+    const Cx S0 = cscale(cmul(d, S.Q), -0.25 * w), S1 = cscale(cmul(d, W.Q), -0.25 * w);
+    const double a[6] = {S0.im - S1.re,
+                         S0.re + S1.im,
+                         0.5 * w * (S.K.im - W.K.re),
+                         0.5 * w * (S.K.re + W.K.im),
+                         w * S.A.re,
+                         -w * S.A.im};
+    adj_store(red, a, r0, n0, part, st, blockIdx.y);
 }
 
 // Near part of both passes: the surface partners of r within nb grid steps
 // (the whole surface when it has at most 2 nb + 1 nodes), diagonal excluded,
 // with the exact-difference kappa; written as slice `slice`.
+// kAdjNearLanes lanes share a node and add their sums in a fixed butterfly order.
+constexpr int kAdjNearLanes = 8;
+
 template <bool COLS>
 __global__ __launch_bounds__(256) void k_adj_near(Nodes N, int n0, int nb,
                                                   const double *__restrict__ v1,
                                                   const double *__restrict__ v2,
                                                   double *__restrict__ part, long st, int slice) {
-    const int r = blockIdx.x * 256 + threadIdx.x;
-    if (r >= n0) return;
+    const int g = threadIdx.x % kAdjNearLanes;
+    const int r = blockIdx.x * (256 / kAdjNearLanes) + threadIdx.x / kAdjNearLanes;
+    const int rr = min(r, n0 - 1);
     const bool whole = 2 * nb + 1 >= n0;
-    const int d0 = whole ? -r : -nb, d1 = whole ? n0 - 1 - r : nb;
+    const int d0 = whole ? -rr : -nb, d1 = whole ? n0 - 1 - rr : nb;
     double a[6] = {0, 0, 0, 0, 0, 0};
-    const Tgt tr = load_tgt(N, r);
-    const Src sr = load_src(N, r);
-    for (int d = d0; d <= d1; ++d) {
+    const Tgt tr = load_tgt(N, rr);
+    const Src sr = load_src(N, rr);
+    for (int d = d0 + g; d <= d1; d += kAdjNearLanes) {
         if (d == 0) continue;
-        int l = r + d;
+        int l = rr + d;
         if (l < 0) l += n0;
         if (l >= n0) l -= n0;
         double cr, ci;
@@ -213,7 +268,21 @@ __global__ __launch_bounds__(256) void k_adj_near(Nodes N, int n0, int nb,
             col_terms(t, sr, cr, ci, v1[l], v2[l], a);
         }
     }
-    store6(part, st, (long)slice * n0 + r, a);
+#pragma unroll
+    for (int k = 0; k < 6; ++k)
+#pragma unroll
+        for (int o = kAdjNearLanes / 2; o > 0; o >>= 1) a[k] += __shfl_xor(a[k], o, 64);
+    if (g == 0 && r < n0) store6(part, st, (long)slice * n0 + r, a);
+}
+
+// The ns slices of component blockIdx.y summed into its first.
+__global__ __launch_bounds__(64 * kSliceWaves) void k_adj_sum(int n0, int ns, double *part,
+                                                              long st) {
+    __shared__ double red[kSliceWaves][64];
+    const int r = blockIdx.x * 64 + (threadIdx.x & 63);
+    double *p = part + blockIdx.y * st;
+    const double v = sum_slices_waves<kSliceWaves>(p, ns, n0, r, r < n0, red);
+    if (threadIdx.x < 64 && r < n0) p[r] = v;
 }
 
 // Derivatives of u_mv = -(V1 + sum a / 2) y' + sum_j a_j Re{cot((z - z_j)/2) z' / 2}
@@ -255,17 +324,16 @@ __device__ __forceinline__ void diag_limit_derivs(double dx, double dy, double e
 __global__ void k_adj_finalize(Nodes N, Flow F, int n0, const double *__restrict__ Ubar,
                                const double *__restrict__ U, const double *__restrict__ omega,
                                const double *__restrict__ gamma, const double *__restrict__ lam,
-                               const double *__restrict__ prow, int nsr,
-                               const double *__restrict__ pcol, int nsc, double *g_phi,
+                               const double *__restrict__ prow,
+                               const double *__restrict__ pcol, long st, double *g_phi,
                                double *g_x, double *g_y, double *g_dx, double *g_dy, double *g_ddx,
                                double *g_ddy) {
     const int r = blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= n0) return;
-    double R[6] = {0, 0, 0, 0, 0, 0}, Cc[6] = {0, 0, 0, 0, 0, 0};
-    const long sr = (long)nsr * n0, sc = (long)nsc * n0;
+    double R[6], Cc[6];
     for (int k = 0; k < 6; ++k) {
-        for (int b = 0; b < nsr; ++b) R[k] += prow[k * sr + (long)b * n0 + r];
-        for (int b = 0; b < nsc; ++b) Cc[k] += pcol[k * sc + (long)b * n0 + r];
+        R[k] = prow[k * st + r];
+        Cc[k] = pcol[k * st + r];
     }
     const double x = N.x[r], y = N.y[r], dx = N.dx[r], dy = N.dy[r];
     const double ex = N.ddx[r], ey = N.ddy[r];
@@ -421,7 +489,7 @@ __global__ __launch_bounds__(256) void k_tlm_cols(Nodes N, int n0, int n, int nd
 // plus the diagonal limits' derivatives.
 __global__ void k_tlm_rhs(Nodes N, Flow F, int n0, int n, int nd, const double *__restrict__ dirs,
                           const double *__restrict__ omega, const double *__restrict__ gamma,
-                          const double *__restrict__ U, const double *__restrict__ prow, int nsr,
+                          const double *__restrict__ U, const double *__restrict__ prow, long st,
                           const double *__restrict__ pA, const double *__restrict__ pT, int nsc,
                           double *rhs, long ldb, double *um) {
     const int r = blockIdx.x * blockDim.x + threadIdx.x;
@@ -433,10 +501,8 @@ __global__ void k_tlm_rhs(Nodes N, Flow F, int n0, int n, int nd, const double *
         rhs[i * ldb + r] = -colA;
         return;
     }
-    double R[6] = {0, 0, 0, 0, 0, 0};
-    const long sr = (long)nsr * n0;
-    for (int k = 0; k < 6; ++k)
-        for (int b = 0; b < nsr; ++b) R[k] += prow[k * sr + (long)b * n0 + r];
+    double R[6];
+    for (int k = 0; k < 6; ++k) R[k] = prow[k * st + r];
     double colT = 0.0;
     for (int b = 0; b < nsc; ++b) colT += pT[((long)b * nd + i) * n0 + r];
     double d[7];
@@ -476,8 +542,14 @@ __global__ void k_adj_c(int n0, const double *Ubar, const double *s, double *c) 
 
 }  // namespace
 
+// Nodes per far slice: about 1024 blocks, a multiple of 64.
+static int adj_chunk_nodes(int n, int n0) {
+    const int c = cdiv(n, std::max(1, cdiv(1024, cdiv(n0, 64))));
+    return cdiv(c, 64) * 64;
+}
+
 // partial slices per component: far chunks plus the near slice
-int adjoint_nsplit(int n) { return cdiv(n, otf_chunk(n)) + 1; }
+int adjoint_nsplit(int n, int n0) { return cdiv(n, adj_chunk_nodes(n, n0)) + 1; }
 
 // slices of the tangent-linear column pass over the M_0 surface sources:
 // about kTlmWaves waves for n targets in tiles of 16, chunks of a multiple of
@@ -505,7 +577,7 @@ void launch_tlm_rhs(const Nodes &N, const Flow &F, int n0, int n, int nd, const 
                     const double *prow, const double *pA, const double *pT, double *rhs, long ldb,
                     double *um, hipStream_t st) {
     hipLaunchKernelGGL(k_tlm_rhs, dim3(cdiv(n, 256), nd), dim3(256), 0, st, N, F, n0, n, nd, dirs,
-                       omega, gamma, U, prow, adjoint_nsplit(n), pA, pT, tlm_nsplit(n, n0), rhs, ldb,
+                       omega, gamma, U, prow, (long)adjoint_nsplit(n, n0) * n0, pA, pT, tlm_nsplit(n, n0), rhs, ldb,
                        um);
 }
 
@@ -522,34 +594,36 @@ void launch_adj_c(int n0, const double *Ubar, const double *s, double *c, hipStr
 void launch_adj_rows(const Nodes &N, const double *hrow, int n0, int n, const double *omega,
                      const double *gamma, double *part, hipStream_t st) {
     (void)hrow;
-    const int chunk = otf_chunk(n);
-    const int ns = cdiv(n, chunk);
+    const int chunk = adj_chunk_nodes(n, n0), ns = cdiv(n, chunk);
     const long cs = (long)(ns + 1) * n0;
-    hipLaunchKernelGGL(k_adj_rows, dim3(cdiv(n0, 256), ns), dim3(256), 0, st, N, n0, n, chunk,
+    hipLaunchKernelGGL(k_adj_rows, dim3(cdiv(n0, 64), ns), dim3(kAdjStage), 0, st, N, n0, n, chunk,
                        kNearBand, omega, gamma, part, cs);
-    hipLaunchKernelGGL((k_adj_near<false>), dim3(cdiv(n0, 256)), dim3(256), 0, st, N, n0,
-                       kNearBand, omega, gamma, part, cs, ns);
+    hipLaunchKernelGGL((k_adj_near<false>), dim3(cdiv(n0, 256 / kAdjNearLanes)), dim3(256), 0, st,
+                       N, n0, kNearBand, omega, gamma, part, cs, ns);
+    hipLaunchKernelGGL(k_adj_sum, dim3(cdiv(n0, 64), 6), dim3(64 * kSliceWaves), 0, st, n0, ns + 1,
+                       part, cs);
 }
 
 void launch_adj_cols(const Nodes &N, int n0, int n, const double *lam, const double *cvec,
                      double *part, hipStream_t st) {
-    const int chunk = otf_chunk(n);
-    const int ns = cdiv(n, chunk);
+    const int chunk = adj_chunk_nodes(n, n0), ns = cdiv(n, chunk);
     const long cs = (long)(ns + 1) * n0;
-    hipLaunchKernelGGL(k_adj_cols, dim3(cdiv(n0, 256), ns), dim3(256), 0, st, N, n0, n, chunk,
+    hipLaunchKernelGGL(k_adj_cols, dim3(cdiv(n0, 64), ns), dim3(kAdjStage), 0, st, N, n0, n, chunk,
                        kNearBand, lam, cvec, part, cs);
-    hipLaunchKernelGGL((k_adj_near<true>), dim3(cdiv(n0, 256)), dim3(256), 0, st, N, n0,
-                       kNearBand, lam, cvec, part, cs, ns);
+    hipLaunchKernelGGL((k_adj_near<true>), dim3(cdiv(n0, 256 / kAdjNearLanes)), dim3(256), 0, st, N,
+                       n0, kNearBand, lam, cvec, part, cs, ns);
+    hipLaunchKernelGGL(k_adj_sum, dim3(cdiv(n0, 64), 6), dim3(64 * kSliceWaves), 0, st, n0, ns + 1,
+                       part, cs);
 }
 
-void launch_adj_finalize(const Nodes &N, const Flow &F, int n0, const double *Ubar,
+void launch_adj_finalize(const Nodes &N, const Flow &F, int n0, int n, const double *Ubar,
                          const double *U, const double *omega, const double *gamma,
-                         const double *lam, const double *prow, int nsr, const double *pcol,
-                         int nsc, double *g_phi, double *g_x, double *g_y, double *g_dx,
-                         double *g_dy, double *g_ddx, double *g_ddy, hipStream_t st) {
-    hipLaunchKernelGGL(k_adj_finalize, dim3(cdiv(n0, 256)), dim3(256), 0, st, N, F, n0, Ubar, U,
-                       omega, gamma, lam, prow, nsr, pcol, nsc, g_phi, g_x, g_y, g_dx, g_dy,
-                       g_ddx, g_ddy);
+                         const double *lam, const double *prow, const double *pcol, double *g_phi,
+                         double *g_x, double *g_y, double *g_dx, double *g_dy, double *g_ddx,
+                         double *g_ddy, hipStream_t st) {
+    hipLaunchKernelGGL(k_adj_finalize, dim3(cdiv(n0, 64)), dim3(64), 0, st, N, F, n0, Ubar, U,
+                       omega, gamma, lam, prow, pcol, (long)adjoint_nsplit(n, n0) * n0, g_phi, g_x,
+                       g_y, g_dx, g_dy, g_ddx, g_ddy);
 }
 
 }  // namespace wwbi

@@ -250,10 +250,11 @@ __device__ __forceinline__ int wrap_index(int d, int M) {
     return d < 0 ? d + M : d;
 }
 
-// out[m0 .. m0+63] of one boundary of M nodes (see above).
-__device__ __forceinline__ void circ_tile(int M, int m0, const double *__restrict__ row,
-                                          const double *__restrict__ f, double *out,
-                                          double alpha, double beta) {
+// The sums of outputs m0 .. m0+63 of one boundary of M nodes (see above):
+// put(m, sum) in the lanes of wave 0.
+template <class Put>
+__device__ __forceinline__ void circ_sums(int M, int m0, const double *__restrict__ row,
+                                          const double *__restrict__ f, Put put) {
     __shared__ double fs[kCW][kCT];
     __shared__ double rs[kCW][2 * kCT];
     __shared__ double red[kCW][kCT];
@@ -294,8 +295,16 @@ __device__ __forceinline__ void circ_tile(int M, int m0, const double *__restric
         double s = 0.0;
         for (int w = 0; w < kCW; ++w) s += red[w][lane];
         const int m = m0 + lane;
-        if (m < M) out[m] = alpha * s + (beta != 0.0 ? beta * out[m] : 0.0);
+        if (m < M) put(m, s);
     }
+}
+
+__device__ __forceinline__ void circ_tile(int M, int m0, const double *__restrict__ row,
+                                          const double *__restrict__ f, double *out,
+                                          double alpha, double beta) {
+    circ_sums(M, m0, row, f, [&](int m, double s) {
+        out[m] = alpha * s + (beta != 0.0 ? beta * out[m] : 0.0);
+    });
 }
 
 __global__ __launch_bounds__(kCT * kCW) void k_circ_tile(int M, const double *__restrict__ row,
@@ -303,6 +312,18 @@ __global__ __launch_bounds__(kCT * kCW) void k_circ_tile(int M, const double *__
                                                          double *out, double alpha,
                                                          double beta) {
     circ_tile(M, blockIdx.x * kCT, row, f, out, alpha, beta);
+}
+
+// Two vectors of one grid (blockIdx.y): out = sums + c add + shift, raw (may be
+// null) the same without the shift.
+__global__ __launch_bounds__(kCT * kCW) void k_circ_pair(int M, const double *__restrict__ row,
+                                                         CircVec a, CircVec b, double c) {
+    const CircVec v = blockIdx.y ? b : a;
+    circ_sums(M, blockIdx.x * kCT, row, v.f, [&](int m, double s) {
+        const double t = v.add ? s + c * v.add[m] : s;
+        if (v.raw) v.raw[m] = t;
+        v.out[m] = t + v.shift;
+    });
 }
 
 // The same for boundaries first..last of a layout in one launch (their tiles
@@ -540,16 +561,15 @@ __global__ void k_energy_final(int n0, const double *e, Flow F, const double *ps
     }
 }
 
-__global__ void k_surface_base(int n, const double *xt, const double *yt, double *x, double *y) {
+// The row of D, and the surface alpha + xt + i yt.
+__global__ void k_surface_base(int n, const double *xt, const double *yt, double *x, double *y,
+                               double *row) {
     const int m = blockIdx.x * blockDim.x + threadIdx.x;
     if (m >= n) return;
+    double h, half;
+    circ_entry(m, n, row[m], h, half);
     x[m] = 2.0 * M_PI * (double)m / (double)n + xt[m];
     y[m] = yt[m];
-}
-
-__global__ void k_add_scalar(int n, double *v, double c) {
-    const int m = blockIdx.x * blockDim.x + threadIdx.x;
-    if (m < n) v[m] += c;
 }
 
 }  // namespace
@@ -677,12 +697,13 @@ void launch_wall_rhs_finalize(int nw, const double *umv_w, const double *part, i
 }
 
 void launch_surface_base(int n, const double *xt, const double *yt, double *x, double *y,
-                         hipStream_t st) {
-    hipLaunchKernelGGL(k_surface_base, dim3(cdiv(n, 256)), dim3(256), 0, st, n, xt, yt, x, y);
+                         double *row, hipStream_t st) {
+    hipLaunchKernelGGL(k_surface_base, dim3(cdiv(n, 128)), dim3(128), 0, st, n, xt, yt, x, y, row);
 }
 
-void launch_add_scalar(int n, double *v, double c, hipStream_t st) {
-    hipLaunchKernelGGL(k_add_scalar, dim3(cdiv(n, 256)), dim3(256), 0, st, n, v, c);
+void launch_circ_pair(int M, const double *row, const CircVec &a, const CircVec &b, double c,
+                      hipStream_t st) {
+    hipLaunchKernelGGL(k_circ_pair, dim3(cdiv(M, kCT), 2), dim3(kCT * kCW), 0, st, M, row, a, b, c);
 }
 
 }  // namespace wwbi

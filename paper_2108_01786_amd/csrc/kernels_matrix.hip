@@ -323,7 +323,6 @@ __global__ __launch_bounds__(256) void k_assemble32_band(Nodes N, int n, int cor
 // 4 = stream-function map P on the surface, 5 = tangential map Q,
 // 6 / 7 = source-flavour maps KS / GS of the F operators, 8 = gamma_t operator.
 // ---------------------------------------------------------------------------
-constexpr int kStage = 256;          // chunk granularity of otf_chunk (adjoint contractions)
 // Sources (targets) staged per pass of the forward (transpose) product: 128
 // keeps a block's LDS near 13 KB, so that LDS does not limit the resident
 // blocks below the wave limit.
@@ -1209,13 +1208,6 @@ __global__ __launch_bounds__(256) void k_otf_cols(Nodes N, const double *hrow, i
 inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
 
 }  // namespace
-
-int otf_chunk(int n) {
-    int c = cdiv(n, 64);
-    c = cdiv(c, kStage) * kStage;
-    return c < kStage ? kStage : c;
-}
-int otf_nsplit(int n) { return cdiv(n, otf_chunk(n)); }
 
 // Chunk of the summed index for an on-the-fly product with `nout` outputs
 // (`per_block` of them per block) and `nsum` summed indices: enough chunks
