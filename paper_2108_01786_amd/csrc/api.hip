@@ -686,8 +686,7 @@ int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, co
     if (ensure_coarse(L.n)) return kTwoGridNone;
     const int corr = (o.flags & WWBI_FLAG_NO_CORRECTION) ? 0 : 1;
     const double inv_d = mode == kCoarseGt || mode == kCoarseWall ? -2.0 : 2.0;
-    const int G = gmres_nblocks(n);
-    double *r = vec[VRR], *Pn = norm_partials();    // 128 doubles
+    double *r = vec[VRR];
     const double *h = (const double *)hst;
     launch_coarse_map(C, cmap, cfac, stream);
     launch_assemble_coarse(N, hrow, mode, cmap, cfac, nc, corr, cA, ldc, stream);
@@ -695,11 +694,8 @@ int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, co
     const double *rr = b;
     bool have_x = false;
     if (check_rough) {
-        launch_roughness(b, 0, n, 1, part, stream);
-        if (hipMemcpyAsync(hst, part, 128 * sizeof(double), hipMemcpyDeviceToHost, stream) !=
-                hipSuccess ||
-            hipStreamSynchronize(stream) != hipSuccess)
-            return WWBI_EHIP;
+        launch_roughness(b, 0, n, 1, hstd, stream);
+        if (hipStreamSynchronize(stream) != hipSuccess) return WWBI_EHIP;
         double s2 = 0.0, d2 = 0.0;
         for (int i = 0; i < 64; ++i) { s2 += h[i]; d2 += h[64 + i]; }
         if (!std::isfinite(s2) || s2 == 0.0) return kTwoGridNone;
@@ -747,20 +743,18 @@ int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, co
         const bool had_x = have_x;
         have_x = true;
         apply(op, x, nullptr, b, r, nullptr);
-        launch_norm_partial(r, n, Pn, G, stream);
-        if (bn < 0.0) launch_norm_partial(b, n, Pn + 64, G, stream);
-        if (hipMemcpyAsync(hst, Pn, sizeof(double) * 128, hipMemcpyDeviceToHost, stream) !=
-                hipSuccess ||
-            hipStreamSynchronize(stream) != hipSuccess || hipGetLastError() != hipSuccess)
+        // the sums go to the host's memory: no copy between them and the wait
+        launch_norms(r, bn < 0.0 ? b : nullptr, n, hstd, stream);
+        if (hipStreamSynchronize(stream) != hipSuccess || hipGetLastError() != hipSuccess)
             return WWBI_EHIP;
         if (hsmall->status == kSmallAborted || hsmall->aborted)
             return had_x ? kTwoGridPart : kTwoGridNone;
         double s2 = 0.0;
-        for (int i = 0; i < G; ++i) s2 += h[i];
+        for (int i = 0; i < 64; ++i) s2 += h[i];
         const double rn = std::sqrt(s2);
         if (bn < 0.0) {
             double t2 = 0.0;
-            for (int i = 0; i < G; ++i) t2 += h[64 + i];
+            for (int i = 0; i < 64; ++i) t2 += h[64 + i];
             bn = std::sqrt(t2);
         }
         if (!std::isfinite(rn)) return kTwoGridNone;
@@ -805,11 +799,8 @@ int Ctx::two_grid_multi(const double *A64, long ld, double *K, size_t kcap, cons
     launch_coarse_map(C, cmap, cfac, stream);
     launch_assemble_coarse(N, hrow, kCoarseA, cmap, cfac, nc, 1, cA, ldc, stream);
     launch_assemble_interp(N, cmap, cfac, nc, 1, K, ldc, stream);
-    launch_roughness(B, ldv, n, nr, m.part, stream);
-    if (hipMemcpyAsync(hst, m.part, (size_t)nr * 128 * sizeof(double), hipMemcpyDeviceToHost,
-                       stream) != hipSuccess ||
-        hipStreamSynchronize(stream) != hipSuccess)
-        return WWBI_EHIP;
+    launch_roughness(B, ldv, n, nr, hstd, stream);
+    if (hipStreamSynchronize(stream) != hipSuccess) return WWBI_EHIP;
     std::vector<double> bn(nr), rn(nr);
     bool rough = false;
     for (int s = 0; s < nr; ++s) {
@@ -861,10 +852,8 @@ int Ctx::two_grid_multi(const double *A64, long ld, double *K, size_t kcap, cons
             launch_axpy(X, m.d, (int)(nr * ldv), 2.0, stream);
         residual();
         R = m.rr;
-        launch_norm_partial(m.rr, n, m.nrm, G, stream, bt);
-        if (hipMemcpyAsync(hst, m.nrm, sizeof(double) * 64 * nr, hipMemcpyDeviceToHost, stream) !=
-                hipSuccess ||
-            hipStreamSynchronize(stream) != hipSuccess || hipGetLastError() != hipSuccess)
+        launch_norm_partial(m.rr, n, hstd, G, stream, bt);
+        if (hipStreamSynchronize(stream) != hipSuccess || hipGetLastError() != hipSuccess)
             return WWBI_EHIP;
         double worst = 0.0;
         int its = 0;
@@ -1504,7 +1493,11 @@ int wwbi_create(wwbi_ctx **out, int32_t device, void *stream) {
     scratch_init(device);
     int rc = WWBI_OK;
     if (hipMalloc((void **)&c->gs, sizeof(GState)) != hipSuccess) rc = WWBI_ECAPACITY;
-    if (!rc && hipHostMalloc(&c->hst, kHostStaging) != hipSuccess) rc = WWBI_ECAPACITY;
+    if (!rc && hipHostMalloc(&c->hst, kHostStaging, hipHostMallocMapped | hipHostMallocCoherent) !=
+                   hipSuccess)
+        rc = WWBI_ECAPACITY;
+    if (!rc && hipHostGetDevicePointer((void **)&c->hstd, c->hst, 0) != hipSuccess)
+        rc = WWBI_EHIP;
     if (!rc && hipHostMalloc((void **)&c->hmir, sizeof(GState),
                              hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess)
         rc = WWBI_ECAPACITY;
@@ -1643,16 +1636,10 @@ int solve_phi_impl(Ctx *c, const wwbi_geom *g, const double *phi, const wwbi_opt
         c->gamma_from_omega(x, gam);
         c->eval_U_from_gamma(gam, U);
         if (omega) launch_copy(omega, x, n, c->stream);
-        if (psi_k && c->L.nb > 2) {
-            double *means = c->vec[VTMP];
-            launch_block_means(c->L, x, means, c->stream);
-            hipMemcpyAsync(c->hst, means, sizeof(double) * (c->L.nb - 2), hipMemcpyDeviceToHost,
-                           c->stream);
-        }
+        // both into the host's memory: a copy behind each was 2 us and its gap
+        if (psi_k) launch_block_means(c->L, x, c->hstd, c->stream);
         // resolution check: the Fourier tail of omega on every boundary
-        launch_tail_monitor(c->L, x, c->part, c->val, c->stream);
-        hipMemcpyAsync(tails, c->val, sizeof(double) * 2 * c->L.nb, hipMemcpyDeviceToHost,
-                       c->stream);
+        launch_tail_monitor(c->L, x, c->part, c->hstd + kTailOffset / sizeof(double), c->stream);
         hipEventRecord(c->ev[4], c->stream);
     };
     double bytes = 0.0;

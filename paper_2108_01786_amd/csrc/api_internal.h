@@ -167,6 +167,7 @@ struct Ctx {
     MultiWS mw;
     GState *gs = nullptr;
     void *hst = nullptr;    // pinned host staging (4 KiB)
+    double *hstd = nullptr;     // its address on the device
     // host-mapped coherent copy of the single-solve cycle state, written by
     // the device kernels (hmir on the host, dmir its device address)
     GState *hmir = nullptr;

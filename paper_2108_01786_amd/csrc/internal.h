@@ -446,6 +446,8 @@ void launch_scale_copy(int n, const double *b, double a, double *x, hipStream_t 
 // out[0..63] and out[64..127]: partial sums of b^2 and of its squared
 // differences; 128 per system, the right-hand sides bs apart
 void launch_roughness(const double *b, long bs, int n, int nsys, double *out, hipStream_t st);
+// out[0..63]: partial sums of r^2, out[64..127]: of b^2 (unless b is null)
+void launch_norms(const double *r, const double *b, int n, double *out, hipStream_t st);
 
 // ---- kernels_multi.hip -------------------------------------------------------
 // Y_s = c_s - S A X_s (or S A X_s when c is null), S negating rows [0, flip),

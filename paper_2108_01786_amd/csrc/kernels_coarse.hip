@@ -386,6 +386,18 @@ __global__ __launch_bounds__(256) void k_roughness(const double *b, long bs, int
     }
 }
 
+__global__ __launch_bounds__(256) void k_norms(const double *r, const double *b, int n,
+                                               double *out) {
+    __shared__ double sh[4];
+    const double *v = blockIdx.y ? b : r;
+    double s = 0.0;
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < n; i += gridDim.x * 256) s += v[i] * v[i];
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) out[blockIdx.y * 64 + blockIdx.x] = ((sh[0] + sh[1]) + sh[2]) + sh[3];
+}
+
 // Coarse nodes per slice: about 1024 blocks, a multiple of the tile (at most
 // kSmallCoarseMax / kCoarseTile = 128 slices, and up to 9 for the band).
 int product_chunk(int nr, int n) {
@@ -443,6 +455,10 @@ void launch_scale_copy(int n, const double *b, double a, double *x, hipStream_t 
 
 void launch_roughness(const double *b, long bs, int n, int nsys, double *out, hipStream_t st) {
     hipLaunchKernelGGL(k_roughness, dim3(64, nsys), dim3(256), 0, st, b, bs, n, out);
+}
+
+void launch_norms(const double *r, const double *b, int n, double *out, hipStream_t st) {
+    hipLaunchKernelGGL(k_norms, dim3(64, b ? 2 : 1), dim3(256), 0, st, r, b, n, out);
 }
 
 }  // namespace wwbi
