@@ -625,7 +625,7 @@ bool Ctx::small_result(SolveStats &st, int &status) {
     return true;
 }
 
-// The most accurate grid whose one-launch solve keeps 27 steps in a
+// The most accurate grid whose one-launch solve keeps 28 steps in a
 // cycle (kSmallFullCycle nodes: the solve then ends in one, at M = 10240 512
 // nodes and 0.62 ms a solve where 1024 in cycles of 17 took 0.82), else the
 // most accurate that fits at all.  A coarser grid costs passes, a finer one

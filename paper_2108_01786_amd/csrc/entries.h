@@ -66,12 +66,12 @@ __device__ __forceinline__ void cot_half64(double u, double v, double &cr, doubl
     ci = -sh * ch * r;
 }
 
-// v of the lane that DPP control CTRL names (every lane has a source)
-template <int CTRL>
+// v of the lane that DPP control CTRL names, in the rows of MASK; zero elsewhere
+template <int CTRL, int MASK>
 __device__ __forceinline__ double dpp_move(double v) {
     const unsigned long long u = (unsigned long long)__double_as_longlong(v);
-    const int lo = __builtin_amdgcn_mov_dpp((int)(u & 0xffffffffu), CTRL, 0xf, 0xf, true);
-    const int hi = __builtin_amdgcn_mov_dpp((int)(u >> 32), CTRL, 0xf, 0xf, true);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(u & 0xffffffffu), CTRL, MASK, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(u >> 32), CTRL, MASK, 0xf, false);
     return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
 __device__ __forceinline__ double lane_value(double v, int lane) {
@@ -81,15 +81,19 @@ __device__ __forceinline__ double lane_value(double v, int lane) {
     return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
 
-// Sum over the wave, the same value in every lane: neighbours, quads, half
-// rows and rows of 16 by DPP moves (no LDS round trip), then the four rows.
-__device__ __forceinline__ double wave_total(double v) {
-    v += dpp_move<0xB1>(v);      // quad_perm [1,0,3,2]
-    v += dpp_move<0x4E>(v);      // quad_perm [2,3,0,1]
-    v += dpp_move<0x141>(v);     // row_half_mirror
-    v += dpp_move<0x140>(v);     // row_mirror
-    return ((lane_value(v, 0) + lane_value(v, 16)) + lane_value(v, 32)) + lane_value(v, 48);
+// Sum over the wave, in lane 63: neighbours, quads, half rows and rows of 16
+// by DPP moves (no LDS round trip), then rows 0 and 1, 2 and 3, and both
+// pairs by row broadcasts.
+__device__ __forceinline__ double wave_sum63(double v) {
+    v += dpp_move<0xB1, 0xf>(v);      // quad_perm [1,0,3,2]
+    v += dpp_move<0x4E, 0xf>(v);      // quad_perm [2,3,0,1]
+    v += dpp_move<0x141, 0xf>(v);     // row_half_mirror
+    v += dpp_move<0x140, 0xf>(v);     // row_mirror
+    v += dpp_move<0x142, 0xa>(v);     // row_bcast:15 into rows 1 and 3
+    v += dpp_move<0x143, 0xc>(v);     // row_bcast:31 into rows 2 and 3
+    return v;
 }
+__device__ __forceinline__ double wave_total(double v) { return lane_value(wave_sum63(v), 63); }
 
 // 1/x from the hardware reciprocal estimate refined by two Newton steps
 // (each step doubles the correct bits; the result is within an ulp of 1/x).

@@ -374,7 +374,7 @@ void launch_adj_finalize(const Nodes &N, const Flow &F, int n0, int n, const dou
 // coarse systems of up to kSmallCoarseMax, in shorter cycles.
 constexpr int kSmallMax = 1024;
 constexpr int kSmallCoarseMax = 2048;
-constexpr int kSmallFullCycle = 640;   // the basis of 27 steps fits
+constexpr int kSmallFullCycle = 640;   // the basis of 28 steps fits
 constexpr int kSmallAborted = -100;
 struct SmallRes {
     int status;            // WWBI_OK, WWBI_NOT_CONVERGED, WWBI_STAGNATED or kSmallAborted

@@ -34,8 +34,8 @@ namespace {
 
 constexpr int kTS = 512;                   // threads per block
 constexpr int kWS = kTS / 64;
-constexpr int kSmallSteps = 48;            // at most this many steps per cycle
-constexpr int kLdsBytes = 144 * 1024;      // for the basis (160 KB less the static part)
+constexpr int kSmallSteps = 32;            // at most this many steps per cycle
+constexpr int kLdsBytes = 145 * 1024;      // for the basis (160 KB less the static part)
 constexpr long kSpinTicks = 20000000;      // 0.2 s at 100 MHz
 
 typedef unsigned long long u64;
@@ -47,14 +47,20 @@ __device__ __forceinline__ u64 get_word(const u64 *p) {
     return __hip_atomic_load(const_cast<u64 *>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+template <int W> struct Width { static constexpr int value = W; };
+
 template <int CPL, int RW>
 __global__ __launch_bounds__(kTS, 2) void k_small_gmres(SmallArgs a) {
     extern __shared__ double basis[];      // slot i: v_i, NP doubles (zero past n)
     constexpr int NP = 64 * CPL;
     constexpr int NE = (NP + kTS - 1) / kTS;
+    // the shapes of many systems side by side, each block with many rows
+    constexpr bool kMany = RW >= 8;
     __shared__ double h1[kSmallSteps + 2], h2[kSmallSteps + 2];
     __shared__ double R[kSmallSteps * (kSmallSteps + 1) / 2];
-    __shared__ double cs[kSmallSteps], sn[kSmallSteps], g[kSmallSteps + 1], yv[kSmallSteps];
+    constexpr int kQ = kSmallSteps + 1;    // Q[k * kQ + i]: the rotations' product, entry (i, k)
+    __shared__ double Q[kQ * kQ];
+    __shared__ double g[kSmallSteps + 1], yv[kSmallSteps];
     __shared__ int stop;                   // 1: the cycle ends, 2: a poll gave up
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int sys = blockIdx.y, n = a.n;
@@ -81,7 +87,8 @@ __global__ __launch_bounds__(kTS, 2) void k_small_gmres(SmallArgs a) {
 
     // w = S A v for the vector in LDS slot `from`, received whole into we
     // (element t + kTS e of thread t); false when a poll gave up
-    auto product = [&](const double *v, double (&we)[NE]) __attribute__((always_inline)) {
+    auto product = [&](const double *v, double (&we)[NE], auto meanwhile)
+                       __attribute__((always_inline)) {
         double acc[RW];
 #pragma unroll
         for (int r = 0; r < RW; ++r) acc[r] = 0.0;
@@ -91,88 +98,140 @@ __global__ __launch_bounds__(kTS, 2) void k_small_gmres(SmallArgs a) {
 #pragma unroll
             for (int r = 0; r < RW; ++r) acc[r] += m[r][k] * vk;
         }
-        u64 *buf = xch + (long)(tag & 1u) * 2 * NP;
+        u64 *blo = xch + (long)(tag & 1u) * 2 * NP, *bhi = blo + NP;   // low and high halves
         const u64 tg = (u64)tag << 32;
+#pragma unroll
+        for (int r = 0; r < RW; ++r) acc[r] = wave_sum63(acc[r]);
+        // lanes 2 r and 2 r + 1 write row r's words, all in one store (a store
+        // each by the lane that holds the sums took 25 of 137 us of a solve
+        // with 2 rows, n = 580)
         double mine = 0.0;
 #pragma unroll
         for (int r = 0; r < RW; ++r) {
-            const double s = wave_total(acc[r]);
-            if (lane == r) mine = s;
+            const double s = lane_value(acc[r], 63);
+            if (lane >> 1 == r) mine = s;
         }
-        if (lane < RW && row0 + lane < n) {
+        if (lane < 2 * RW && row0 + (lane >> 1) < n) {
             const u64 u = (u64)__double_as_longlong(mine);
-            put_word(buf + 2 * (row0 + lane), tg | (u & 0xffffffffu));
-            put_word(buf + 2 * (row0 + lane) + 1, tg | (u >> 32));
+            put_word((lane & 1 ? bhi : blo) + row0 + (lane >> 1),
+                     tg | (lane & 1 ? u >> 32 : u & 0xffffffffu));
         }
+        meanwhile();
         const long t0 = wall_clock64();
         int quit = 0;
+        u64 lo[NE], hi[NE];
 #pragma unroll
-        for (int e = 0; e < NE; ++e) {
-            const int i = t + kTS * e;
-            u64 lo = 0, hi = 0;
-            if (i < n) {
-                for (int spin = 1;; ++spin) {
-                    lo = get_word(buf + 2 * i);
-                    hi = get_word(buf + 2 * i + 1);
-                    if ((unsigned)(lo >> 32) == tag && (unsigned)(hi >> 32) == tag) break;
-                    if ((spin & 63) == 0 &&
-                        (wall_clock64() - t0 > kSpinTicks ||
-                         __hip_atomic_load(a.abort_tag, __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT) == a.tag)) {
-                        quit = 1;
-                        break;
-                    }
+        for (int e = 0; e < NE; ++e) lo[e] = hi[e] = tg;     // elements past n need no word
+        for (int spin = 1;; ++spin) {
+            bool all = true;
+#pragma unroll
+            for (int e = 0; e < NE; ++e) {
+                const int i = t + kTS * e;
+                if (i < n) {
+                    lo[e] = get_word(blo + i);
+                    hi[e] = get_word(bhi + i);
                 }
             }
-            we[e] = i < n ? __longlong_as_double((long long)((lo & 0xffffffffu) | (hi << 32))) : 0.0;
+#pragma unroll
+            for (int e = 0; e < NE; ++e)
+                all = all && (unsigned)(lo[e] >> 32) == tag && (unsigned)(hi[e] >> 32) == tag;
+            if (all) break;
+            if ((spin & 63) == 0 &&
+                (wall_clock64() - t0 > kSpinTicks ||
+                 __hip_atomic_load(a.abort_tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
+                     a.tag)) {
+                quit = 1;
+                break;
+            }
         }
+#pragma unroll
+        for (int e = 0; e < NE; ++e)
+            we[e] = t + kTS * e < n
+                        ? __longlong_as_double((long long)((lo[e] & 0xffffffffu) | (hi[e] << 32)))
+                        : 0.0;
         if (quit) {
             stop = 2;
-            a.out[sys].aborted = 1;        // whatever block 0 reports
             __hip_atomic_store(a.abort_tag, a.tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            a.out[sys].aborted = 1;        // whatever block 0 reports
         }
         ++tag;
     };
     // h[i] = <slot i, slot q> for i <= last, wave wv taking i = wv, wv + kWS, ...
     auto dots = [&](int q, int last, double *h) __attribute__((always_inline)) {
         double wl[CPL];
-        const double *wq = basis + (long)q * NP;
+        const double *wq = basis + (long)q * NP + lane;
 #pragma unroll
-        for (int k = 0; k < CPL; ++k) wl[k] = wq[lane + 64 * k];
-        for (int i = wv; i <= last; i += 2 * kWS) {
-            const bool two = i + kWS <= last;
-            const double *v0 = basis + (long)i * NP, *v1 = two ? v0 + (long)kWS * NP : v0;
-            double s0 = 0.0, s1 = 0.0;
+        for (int k = 0; k < CPL; ++k) wl[k] = wq[64 * k];
+        int i = wv;
+        for (; i + kWS <= last; i += 2 * kWS) {
+            const double *v0 = basis + (long)i * NP + lane;
+            double s0 = 0.0, s1 = 0.0, u0 = 0.0, u1 = 0.0;
 #pragma unroll
-            for (int k = 0; k < CPL; ++k) {
-                s0 += v0[lane + 64 * k] * wl[k];
-                s1 += v1[lane + 64 * k] * wl[k];
+            for (int k = 0; k + 1 < CPL; k += 2) {
+                s0 += v0[64 * k] * wl[k];
+                s1 += v0[kWS * NP + 64 * k] * wl[k];
+                u0 += v0[64 * k + 64] * wl[k + 1];
+                u1 += v0[kWS * NP + 64 * k + 64] * wl[k + 1];
             }
-            s0 = wave_total(s0);
-            s1 = wave_total(s1);
-            if (lane == 0) {
+            s0 = wave_sum63(s0 + u0);
+            s1 = wave_sum63(s1 + u1);
+            if (lane == 63) {
                 h[i] = s0;
-                if (two) h[i + kWS] = s1;
+                h[i + kWS] = s1;
             }
+        }
+        if (i <= last) {
+            const double *v0 = basis + (long)i * NP + lane;
+            double s0 = 0.0, u0 = 0.0;
+#pragma unroll
+            for (int k = 0; k + 1 < CPL; k += 2) {
+                s0 += v0[64 * k] * wl[k];
+                u0 += v0[64 * k + 64] * wl[k + 1];
+            }
+            s0 = wave_sum63(s0 + u0);
+            if (lane == 63) h[i] = s0;
         }
     };
-    // we -= sum_{i <= j} h_i v_i on the thread's elements
-    auto project = [&](int j, const double *h, double (&we)[NE]) __attribute__((always_inline)) {
+    // we -= sum_{i < k} h_i v_i on the thread's elements, in groups of eight,
+    // four, two and one so that each group's reads are in flight together
+    auto project = [&](int k, const double *h, double (&we)[NE]) __attribute__((always_inline)) {
+        const double *v[NE];
+        double s0[NE], s1[NE];
 #pragma unroll
         for (int e = 0; e < NE; ++e) {
-            const int i = t + kTS * e;
-            if (i < NP) {
-                const double *v = basis + i;
-                double s0 = 0.0, s1 = 0.0;
-                int q = 0;
-                for (; q + 1 <= j; q += 2) {
-                    s0 += h[q] * v[(long)q * NP];
-                    s1 += h[q + 1] * v[(long)(q + 1) * NP];
-                }
-                if (q <= j) s0 += h[q] * v[(long)q * NP];
-                we[e] -= s0 + s1;
-            }
+            // threads past the padded length repeat an element they drop
+            v[e] = basis + (t + kTS * e < NP ? t + kTS * e : 0);
+            s0[e] = s1[e] = 0.0;
         }
+        int q = 0;
+        auto group = [&](auto width) __attribute__((always_inline)) {
+            constexpr int W = decltype(width)::value;
+            double u[NE][W], hq[W];
+#pragma unroll
+            for (int c = 0; c < W; ++c) {
+                hq[c] = h[q + c];
+#pragma unroll
+                for (int e = 0; e < NE; ++e) u[e][c] = v[e][(long)(q + c) * NP];
+            }
+#pragma unroll
+            for (int c = 0; c < W; ++c)
+#pragma unroll
+                for (int e = 0; e < NE; ++e) {
+                    if (c & 1) s1[e] += hq[c] * u[e][c];
+                    else s0[e] += hq[c] * u[e][c];
+                }
+            q += W;
+        };
+        if constexpr (NE <= 2 && !kMany) {
+            while (q + 8 <= k) group(Width<8>{});
+            if (k & 4) group(Width<4>{});
+        } else {
+            while (q + 4 <= k) group(Width<4>{});       // eight would spill
+        }
+        if (k & 2) group(Width<2>{});
+        if (k & 1) group(Width<1>{});
+#pragma unroll
+        for (int e = 0; e < NE; ++e) we[e] -= s0[e] + s1[e];
     };
     auto store_slot = [&](int q, const double (&we)[NE], double sc) __attribute__((always_inline)) {
 #pragma unroll
@@ -190,6 +249,49 @@ __global__ __launch_bounds__(kTS, 2) void k_small_gmres(SmallArgs a) {
         return sqrt(wave_total(s));
     };
 
+    double tol_abs = 0.0;
+    // Column j of the Hessenberg matrix, its rotation and the residual
+    // estimate, by wave 0; sets stop when the cycle ends with step j.
+    auto rotate = [&](int j, int len, double nrm) __attribute__((always_inline)) {
+        if (wv != 0) return;
+        // The Hessenberg column through the previous rotations, whose
+        // product is kept as a matrix: lane i forms entry i from
+        // independent reads, where applying them one by one is a chain.
+        const double hj = lane <= j ? h1[lane] + h2[lane] : 0.0;
+        double r0 = 0.0, r1 = 0.0;
+        const double *Qi = Q + (lane <= j ? lane : 0);
+        int k = 0;
+        for (; k + 1 <= j; k += 2) {
+            r0 += lane_value(hj, k) * Qi[k * kQ];
+            r1 += lane_value(hj, k + 1) * Qi[(k + 1) * kQ];
+        }
+        if (k <= j) r0 += lane_value(hj, k) * Qi[k * kQ];
+        r0 += r1;
+        double *col = R + j * (j + 1) / 2;
+        const double c = lane_value(r0, j);
+        const double r = sqrt(c * c + nrm * nrm);
+        const double ir = r > 0.0 ? 1.0 / r : 0.0;
+        const double cj = r > 0.0 ? c * ir : 1.0, sj = nrm * ir;
+        if (lane <= j) {
+            col[lane] = lane < j ? r0 : r;
+            // rows j and j + 1 of the product, (Q_j, e_{j+1}) rotated
+            const double qj = Q[lane * kQ + j];
+            Q[lane * kQ + j] = cj * qj;
+            Q[lane * kQ + j + 1] = -sj * qj;
+        }
+        if (lane < j) Q[(j + 1) * kQ + lane] = 0.0;
+        if (lane == j + 1) {
+            Q[lane * kQ + j] = sj;
+            Q[lane * kQ + j + 1] = cj;
+        }
+        if (lane == 0) {
+            const double gj = g[j];
+            g[j] = cj * gj;
+            g[j + 1] = -sj * gj;
+            if (fabs(sj * gj) <= tol_abs || !(nrm > 0.0) || j + 1 >= len) stop = 1;
+        }
+    };
+
     double xe[NE], re[NE];                 // solution and residual, thread t's elements
 #pragma unroll
     for (int e = 0; e < NE; ++e) {
@@ -200,7 +302,7 @@ __global__ __launch_bounds__(kTS, 2) void k_small_gmres(SmallArgs a) {
     store_slot(0, re, 1.0);
     __syncthreads();
     const double bnorm = slot_norm(0);
-    const double tol_abs = a.tol * bnorm;
+    tol_abs = a.tol * bnorm;
     double beta = bnorm, prev = HUGE_VAL;
     bool aborted = false;
     // the residual of the solution in xe (through slot 0): re, its norm beta
@@ -209,7 +311,7 @@ __global__ __launch_bounds__(kTS, 2) void k_small_gmres(SmallArgs a) {
         store_slot(0, xe, 1.0);
         __syncthreads();
         double we[NE];
-        product(basis, we);
+        product(basis, we, [] {});
 #pragma unroll
         for (int e = 0; e < NE; ++e) {
             const int i = t + kTS * e;
@@ -244,55 +346,53 @@ __global__ __launch_bounds__(kTS, 2) void k_small_gmres(SmallArgs a) {
         prev = beta;
         __syncthreads();                   // slot 0 has been read by every wave
         store_slot(0, re, 1.0 / beta);
-        if (t == 0) g[0] = beta;
+        if (t == 0) {
+            g[0] = beta;
+            Q[0] = 1.0;
+        }
         __syncthreads();
         const int len = min(a.steps, a.max_iter - its);
-        int j = 0;
-        for (;; ++j) {
+        // The rotation of step j runs while the rows of step j + 1 travel; the
+        // step that ends a cycle is therefore known one product late (but for
+        // the last the basis has room for), and that product is dropped.
+        // (With many systems a product costs more than the wait.)
+        int k = 0;                         // steps done
+        double nrm = 0.0;
+        for (int j = 0;; ++j) {
             double we[NE];
-            product(basis + (long)j * NP, we);
+            product(basis + (long)j * NP, we, [&] {
+                if (!kMany && j > 0) rotate(j - 1, len, nrm);
+            });
             store_slot(j + 1, we, 1.0);
             __syncthreads();
             if (stop == 2) { aborted = true; break; }
+            if (stop) break;
             dots(j + 1, j, h1);
             __syncthreads();
-            project(j, h1, we);
+            project(j + 1, h1, we);
             store_slot(j + 1, we, 1.0);
             __syncthreads();
             dots(j + 1, j + 1, h2);        // h2[j + 1] = ||w'||^2
             __syncthreads();
-            // ||w''||^2 = ||w'||^2 - ||h2||^2: h2 is at rounding level
-            double s2 = 0.0;
-            for (int i = 0; i <= j; ++i) s2 += h2[i] * h2[i];
-            const double q = h2[j + 1] - s2;
-            const double nrm = q > 0.0 ? sqrt(q) : 0.0;
-            if (t == 0) {
-                // the Hessenberg column through the previous rotations, the
-                // new rotation and the residual estimate
-                double *col = R + j * (j + 1) / 2;
-                double c = h1[0] + h2[0];
-                for (int i = 0; i < j; ++i) {
-                    const double d = h1[i + 1] + h2[i + 1];
-                    col[i] = cs[i] * c + sn[i] * d;
-                    c = cs[i] * d - sn[i] * c;
-                }
-                const double r = sqrt(c * c + nrm * nrm);
-                const double cj = r > 0.0 ? c / r : 1.0, sj = r > 0.0 ? nrm / r : 0.0;
-                cs[j] = cj;
-                sn[j] = sj;
-                col[j] = r;
-                const double gj = g[j];
-                g[j] = cj * gj;
-                g[j + 1] = -sj * gj;
-                if (fabs(g[j + 1]) <= tol_abs || !(nrm > 0.0) || j + 1 >= len) stop = 1;
-            }
-            project(j, h2, we);
+            // ||w''||^2 = ||w'||^2 - ||h2||^2: h2 is at rounding level.  Lane i
+            // of every wave holds h2_i (j < 64).
+            const double hl = lane <= j ? h2[lane] : 0.0;
+            const double ww = h2[j + 1];
+            const double q = ww - wave_total(hl * hl);
+            nrm = q > 0.0 ? sqrt(q) : 0.0;
+            if (kMany) rotate(j, len, nrm);
+            project(j + 1, h2, we);
             store_slot(j + 1, we, nrm > 0.0 ? 1.0 / nrm : 0.0);
+            k = j + 1;
             __syncthreads();
-            if (stop) break;
+            if (kMany && stop) break;
+            if (!kMany && k >= len) {
+                rotate(j, len, nrm);
+                __syncthreads();
+                break;
+            }
         }
         if (aborted) break;
-        const int k = j + 1;
         its += k;
         cycles += 1;
         // y = R^{-1} g, one wave: lane i carries g_i (k <= 64)
@@ -360,9 +460,7 @@ int launch_cpl(SmallArgs a, int nsys, hipStream_t st) {
 long small_exchange_words() { return 2L * 2 * kSmallCoarseMax; }
 
 int launch_small_gmres(SmallArgs a, int nsys, hipStream_t st) {
-    // columns per lane in steps of two; the rows per wave keep the matrix
-    // within 144 registers a lane and a launch within 32 blocks (of whole
-    // systems; 128 at the largest coarse one)
+    // columns per lane in steps of two
     const int cpl = (cdiv(a.n, 64) + 1) / 2 * 2;
     // A block's basis fills the LDS of its CU.  Where many systems would not
     // all be resident, more rows per wave run more of them at once (32 of 512
@@ -376,16 +474,21 @@ int launch_small_gmres(SmallArgs a, int nsys, hipStream_t st) {
         default: return launch_cpl<10, 10>(a, nsys, st);
         }
     }
+    // Else two rows per wave, for a short product: at most 64 blocks a system
+    // up to 1024 unknowns, so that the solves of four queues are resident
+    // together.  Solves of 384, 448, 580 and 864 unknowns to rounding take 64,
+    // 108, 112 and 150 us; with 3 rows 66, 111, 120 and 154, with 4 a little
+    // more, with 1 (448) 128.
     switch (cpl) {
     case 2: return launch_cpl<2, 2>(a, nsys, st);
     case 4: return launch_cpl<4, 2>(a, nsys, st);
     case 6: return launch_cpl<6, 2>(a, nsys, st);
     case 8: return launch_cpl<8, 2>(a, nsys, st);
-    case 10: return launch_cpl<10, 3>(a, nsys, st);
-    case 12: return launch_cpl<12, 4>(a, nsys, st);
-    case 14: return launch_cpl<14, 4>(a, nsys, st);
-    case 16: return launch_cpl<16, 4>(a, nsys, st);
-    case 18: case 20: return launch_cpl<20, 3>(a, nsys, st);
+    case 10: return launch_cpl<10, 2>(a, nsys, st);
+    case 12: return launch_cpl<12, 2>(a, nsys, st);
+    case 14: return launch_cpl<14, 2>(a, nsys, st);
+    case 16: return launch_cpl<16, 2>(a, nsys, st);
+    case 18: case 20: return launch_cpl<20, 2>(a, nsys, st);
     case 22: case 24: return launch_cpl<24, 2>(a, nsys, st);
     case 26: case 28: return launch_cpl<28, 2>(a, nsys, st);
     case 30: case 32: return launch_cpl<32, 2>(a, nsys, st);
