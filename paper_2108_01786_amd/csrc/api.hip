@@ -2153,8 +2153,9 @@ int wwbi_interior_eval(wwbi_ctx *ctx, const wwbi_geom *g, const double *f_re,
     if (!f_re || !f_im || !out_re || !out_im) return WWBI_EINVAL_NULL;
     int rc = interior_common(c, g, npts, zx, zy);
     if (rc) return rc;
-    launch_helsing_ojala(c->N, c->L.n, c->L.off[1], npts, zx, zy, f_re, f_im, c->hop, c->hoi,
-                         false, out_re, out_im, c->stream);
+    launch_helsing_ojala(c->N, c->L.n, c->L.off[1], npts, zx, zy,
+                         HoValues{{f_re}, {f_im}, {out_re}, {out_im}}, 1, c->hop, c->hoi, false,
+                         c->stream);
     if (hipStreamSynchronize(c->stream) != hipSuccess) return WWBI_EHIP;
     return hip_ok(hipGetLastError());
 }
@@ -2170,8 +2171,8 @@ int wwbi_interior_velocity(wwbi_ctx *ctx, const wwbi_geom *g, const double *omeg
     double *sds = c->vec[VE], *sdn = c->vec[VQG], *fr = c->vec[VFV], *fi = c->vec[VFU];
     boundary_derivs(c, omega, sds, sdn);
     launch_boundary_velocity(c->L.n, g->dx, g->dy, sds, sdn, true, fr, fi, c->stream);
-    launch_helsing_ojala(c->N, c->L.n, c->L.off[1], npts, zx, zy, fr, fi, c->hop, c->hoi, true,
-                         u, v, c->stream);
+    launch_helsing_ojala(c->N, c->L.n, c->L.off[1], npts, zx, zy,
+                         HoValues{{fr}, {fi}, {u}, {v}}, 1, c->hop, c->hoi, true, c->stream);
     if (hipStreamSynchronize(c->stream) != hipSuccess) return WWBI_EHIP;
     return hip_ok(hipGetLastError());
 }
@@ -2201,7 +2202,7 @@ int wwbi_pressure(wwbi_ctx *ctx, const wwbi_geom *g, const double *phi, double t
     }
     if (!rc) {
         const size_t ns = (size_t)ho_slices(npts, (int)nsum);
-        rc = grow(c->hop, c->caphop, 4 * ns * npts + 3 * (size_t)npts + 64);
+        rc = grow(c->hop, c->caphop, 6 * ns * npts + 4 * (size_t)npts + 64);
         if (!rc) rc = grow(c->hoi, c->caphoi, ns * npts + 64);
     }
     if (!rc) {
@@ -2274,11 +2275,12 @@ int wwbi_pressure(wwbi_ctx *ctx, const wwbi_geom *g, const double *phi, double t
     launch_phi_aux_values(n, n0, b, ps, rw, hw, c->bid, means, fr, fi, sm);
     // 5. phi_t - C and u - i v inside the fluid, then the pressure
     const size_t ns = (size_t)ho_slices(npts, n);
-    double *phit = c->hop + 4 * ns * npts, *wr = phit + npts, *wi = wr + npts;
-    launch_helsing_ojala(c->N, n, n0, npts, zx, zy, fr, fi, c->hop, c->hoi, false, phit, wi, sm);
+    double *phit = c->hop + 6 * ns * npts, *wr = phit + npts, *wi = wr + npts, *pim = wi + npts;
     double *vr = c->vec[VKF], *vi = c->vec[VGF];
     launch_boundary_velocity(n, g->dx, g->dy, sds, sdn, true, vr, vi, sm);
-    launch_helsing_ojala(c->N, n, n0, npts, zx, zy, vr, vi, c->hop, c->hoi, false, wr, wi, sm);
+    launch_helsing_ojala(c->N, n, n0, npts, zx, zy,
+                         HoValues{{fr, vr}, {fi, vi}, {phit, wr}, {pim, wi}}, 2, c->hop, c->hoi,
+                         false, sm);
     launch_pressure_final(npts, phit, wr, wi, zy, grav, p, sm);
     const bool ok = hipStreamSynchronize(sm) == hipSuccess && hipGetLastError() == hipSuccess;
     if (rep) {

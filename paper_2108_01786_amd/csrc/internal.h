@@ -252,16 +252,21 @@ void launch_rk_combine(int M, const double *base, const double *K, long ld, cons
                        double *out, hipStream_t st);
 
 // ---- kernels_interior.hip ----------------------------------------------------
-// Helsing-Ojala rule at P points from boundary values f (partial slices in
-// part: 4 * ho_slices * P doubles; hit: ho_slices * P ints)
+// Helsing-Ojala rule at P points from the boundary values of nf = 1 or 2
+// functions (partial slices in part: (2 + 2 nf) * ho_slices * P doubles; hit:
+// ho_slices * P ints)
+struct HoValues {
+    const double *fr[2], *fi[2];
+    double *outr[2], *outi[2];
+};
 int ho_slices(int P, int n);
 // out[0] = points with a non-finite coordinate, out[1] = finite points with
 // |y| > kMaxAbsY (2 doubles, device)
 void launch_check_points(int P, const double *zx, const double *zy, double *out,
                          hipStream_t st);
 void launch_helsing_ojala(const Nodes &N, int n, int n0, int P, const double *zx,
-                          const double *zy, const double *fr, const double *fi, double *part,
-                          int *hit, bool neg_im, double *outr, double *outi, hipStream_t st);
+                          const double *zy, const HoValues &F, int nf, double *part, int *hit,
+                          bool neg_im, hipStream_t st);
 void launch_boundary_velocity(int n, const double *dx, const double *dy, const double *sds,
                               const double *sdn, bool phi_prime, double *u, double *v,
                               hipStream_t st);

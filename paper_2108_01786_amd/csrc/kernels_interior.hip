@@ -20,22 +20,24 @@ inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
 
 constexpr int kHoStage = 256;
 
-struct HoNode {
-    double ex, ey, exl, eyl, x, y, dx, dy, w, fr, fi;
-    int neg;   // free-surface node (sigma = -1)
+// A staged node: E, sigma w zeta' / 2 and the values of NF functions.
+template <int NF> struct HoNode {
+    double ex, ey, exl, eyl, a, b, f[2 * NF];
 };
 
 // Partial sums over chunk blockIdx.y of the nodes, one point per thread:
-// part[c][s][p] for c = Re num, Im num, Re den, Im den; hit[s][p] = the first
-// node of the chunk that coincides with the point, or -1.
+// part[c][s][p] for c = Re den, Im den, then Re and Im of each function's num;
+// hit[s][p] = the first node of the chunk that coincides with the point, or
+// -1.  The weights are most of a pair (30 operations of 34): two functions at
+// the same points share them (6000 x 6000: 83 us a function alone, 78 for
+// two).
+template <int NF>
 __global__ __launch_bounds__(256) void k_ho_partial(Nodes N, int n, int n0, int P,
                                                     const double *__restrict__ zx,
-                                                    const double *__restrict__ zy,
-                                                    const double *__restrict__ fr,
-                                                    const double *__restrict__ fi, int chunk,
-                                                    double *__restrict__ part,
+                                                    const double *__restrict__ zy, HoValues F,
+                                                    int chunk, double *__restrict__ part,
                                                     int *__restrict__ hit) {
-    __shared__ HoNode sn[kHoStage];
+    __shared__ HoNode<NF> sn[kHoStage];
     const int p = blockIdx.x * 256 + threadIdx.x;
     const bool live = p < P;
     const double x = live ? zx[p] : 0.0, y = live ? zy[p] : 0.0;
@@ -44,57 +46,62 @@ __global__ __launch_bounds__(256) void k_ho_partial(Nodes N, int n, int n0, int 
     DD ezr, ezi;
     dd_expi(x, y, ezr, ezi);
     const double er = ezr.hi, ei = ezi.hi, erl = ezr.lo, eil = ezi.lo;
-    const double ee = er * er + ei * ei;
-    double nr = 0.0, ni = 0.0, dr = 0.0, di = 0.0;
+    const double cut = (er * er + ei * ei) * (1.0 / 4096.0);
+    double dr = 0.0, di = 0.0, nr[NF], ni[NF];
+#pragma unroll
+    for (int c = 0; c < NF; ++c) nr[c] = ni[c] = 0.0;
     int h = -1;
     const int qb = blockIdx.y * chunk, qe = min(n, qb + chunk);
     for (int qq = qb; qq < qe; qq += kHoStage) {
         const int q = qq + threadIdx.x;
         if (q < qe) {
-            HoNode v;
-            v.ex = N.ex[q]; v.ey = N.ey[q]; v.exl = N.exl[q]; v.eyl = N.eyl[q];
-            v.x = N.x[q]; v.y = N.y[q];
-            v.dx = N.dx[q]; v.dy = N.dy[q]; v.w = N.w[q]; v.fr = fr[q]; v.fi = fi[q];
-            v.neg = q < n0 ? 1 : 0;
+            HoNode<NF> v;
+            v.ex = N.ex[q];
+            v.ey = N.ey[q];
+            v.exl = N.exl[q];
+            v.eyl = N.eyl[q];
+            const double sw = (q < n0 ? -0.5 : 0.5) * N.w[q];
+            v.a = sw * N.dx[q];
+            v.b = sw * N.dy[q];
+#pragma unroll
+            for (int c = 0; c < NF; ++c) {
+                v.f[2 * c] = F.fr[c][q];
+                v.f[2 * c + 1] = F.fi[c][q];
+            }
             sn[threadIdx.x] = v;
         }
         __syncthreads();
-        const int m = min(kHoStage, qe - qq);
-        if (live) {
-            for (int i = 0; i < m; ++i) {
-                const HoNode &v = sn[i];
-                const double ddr = (v.ex - er) + (v.exl - erl);
-                const double ddi = (v.ey - ei) + (v.eyl - eil);
-                const double den = ddr * ddr + ddi * ddi;
-                double kr, ki;
-                if (den == 0.0) {       // the point is this node (or a period image)
+        const int m = live ? min(kHoStage, qe - qq) : 0;
+        for (int i = 0; i < m; ++i) {
+            const HoNode<NF> &v = sn[i];
+            const double ddr = (v.ex - er) + (v.exl - erl);
+            const double ddi = (v.ey - ei) + (v.eyl - eil);
+            const double den = ddr * ddr + ddi * ddi;
+            double kr, ki;
+            if (den < cut) {
+                const double u = N.x[qq + i] - x, w = N.y[qq + i] - y;
+                // the point is this node (or a period image)
+                if (den == 0.0 || (u == 0.0 && w == 0.0)) {
                     if (h < 0) h = qq + i;
                     continue;
                 }
-                if (den * 4096.0 < ee) {
-                    const double u = v.x - x, w = v.y - y;
-                    if (u == 0.0 && w == 0.0) {   // the node itself
-                        if (h < 0) h = qq + i;
-                        continue;
-                    }
-                    cot_half64(u, w, kr, ki);
-                } else {
-                    // cot((zeta - z)/2) = i (E_zeta + E_z) / (E_zeta - E_z)
-                    const double sr = v.ex + er, si = v.ey + ei;
-                    const double inv = 1.0 / den;
-                    const double pr = (sr * ddr + si * ddi) * inv;
-                    const double pi = (si * ddr - sr * ddi) * inv;
-                    kr = -pi;
-                    ki = pr;
-                }
-                // lam = sigma w (1/2) kappa zeta'
-                const double sw = (v.neg ? -0.5 : 0.5) * v.w;
-                const double lr = sw * (kr * v.dx - ki * v.dy);
-                const double li = sw * (kr * v.dy + ki * v.dx);
-                nr += lr * v.fr - li * v.fi;
-                ni += lr * v.fi + li * v.fr;
-                dr += lr;
-                di += li;
+                cot_half64(u, w, kr, ki);
+            } else {
+                // cot((zeta - z)/2) = i (E_zeta + E_z) / (E_zeta - E_z)
+                const double sr = v.ex + er, si = v.ey + ei;
+                const double inv = recip64(den);
+                kr = -(si * ddr - sr * ddi) * inv;
+                ki = (sr * ddr + si * ddi) * inv;
+            }
+            // lam = sigma w (1/2) kappa zeta'
+            const double lr = kr * v.a - ki * v.b;
+            const double li = kr * v.b + ki * v.a;
+            dr += lr;
+            di += li;
+#pragma unroll
+            for (int c = 0; c < NF; ++c) {
+                nr[c] += lr * v.f[2 * c] - li * v.f[2 * c + 1];
+                ni[c] += lr * v.f[2 * c + 1] + li * v.f[2 * c];
             }
         }
         __syncthreads();
@@ -102,36 +109,54 @@ __global__ __launch_bounds__(256) void k_ho_partial(Nodes N, int n, int n0, int 
     if (live) {
         const long st = (long)gridDim.y * P;
         const long o = (long)blockIdx.y * P + p;
-        part[o] = nr;
-        part[st + o] = ni;
-        part[2 * st + o] = dr;
-        part[3 * st + o] = di;
+        part[o] = dr;
+        part[st + o] = di;
+#pragma unroll
+        for (int c = 0; c < NF; ++c) {
+            part[(2 + 2 * c) * st + o] = nr[c];
+            part[(3 + 2 * c) * st + o] = ni[c];
+        }
         hit[o] = h;
     }
 }
 
-// f(z) = num / den, or the coinciding node's value; neg_im stores -Im f
-__global__ void k_ho_finalize(int P, int ns, const double *__restrict__ part,
-                              const int *__restrict__ hit, const double *__restrict__ fr,
-                              const double *__restrict__ fi, int neg_im,
-                              double *__restrict__ outr, double *__restrict__ outi) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= P) return;
+// f(z) = num / den, or the coinciding node's value; neg_im stores -Im f.  64
+// points per block, the slices shared by kSliceWaves waves (a thread per point
+// went through them in 35 us at 6000 points and 64 slices).
+template <int NF>
+__global__ __launch_bounds__(64 * kSliceWaves) void k_ho_finalize(
+    int P, int ns, const double *__restrict__ part, const int *__restrict__ hit, HoValues F,
+    int neg_im) {
+    __shared__ double red[kSliceWaves][64];
+    __shared__ int first[kSliceWaves][64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int p = blockIdx.x * 64 + lane;
+    const bool live = p < P;
     int h = -1;
-    for (int s = 0; s < ns && h < 0; ++s) h = hit[(long)s * P + p];
-    const double sg = neg_im ? -1.0 : 1.0;
-    if (h >= 0) {
-        outr[p] = fr[h];
-        outi[p] = sg * fi[h];
-        return;
+    const int k0 = (int)((long)ns * wv / kSliceWaves), k1 = (int)((long)ns * (wv + 1) / kSliceWaves);
+    for (int s = k1 - 1; live && s >= k0; --s) {
+        const int v = hit[(long)s * P + p];
+        h = v >= 0 ? v : h;
     }
+    first[wv][lane] = h;
     const long st = (long)ns * P;
-    const double nr = sum_slices(part, ns, P, p), ni = sum_slices(part + st, ns, P, p);
-    const double dr = sum_slices(part + 2 * st, ns, P, p);
-    const double di = sum_slices(part + 3 * st, ns, P, p);
-    const double inv = 1.0 / (dr * dr + di * di);
-    outr[p] = (nr * dr + ni * di) * inv;
-    outi[p] = sg * (ni * dr - nr * di) * inv;
+    double v[2 + 2 * NF];
+#pragma unroll
+    for (int c = 0; c < 2 + 2 * NF; ++c) {
+        v[c] = sum_slices_waves<kSliceWaves>(part + c * st, ns, P, p, live, red);
+        __syncthreads();
+    }
+    if (wv != 0 || !live) return;
+    h = -1;
+    for (int w = kSliceWaves - 1; w >= 0; --w) h = first[w][lane] >= 0 ? first[w][lane] : h;
+    const double sg = neg_im ? -1.0 : 1.0;
+    const double inv = 1.0 / (v[0] * v[0] + v[1] * v[1]);
+#pragma unroll
+    for (int c = 0; c < NF; ++c) {
+        const double nr = v[2 + 2 * c], ni = v[3 + 2 * c];
+        F.outr[c][p] = h >= 0 ? F.fr[c][h] : (nr * v[0] + ni * v[1]) * inv;
+        F.outi[c][p] = sg * (h >= 0 ? F.fi[c][h] : (ni * v[0] - nr * v[1]) * inv);
+    }
 }
 
 // u - i v on every node from s dphi/ds and s dphi/dn:
@@ -275,14 +300,22 @@ void launch_check_points(int P, const double *zx, const double *zy, double *out,
 }
 
 void launch_helsing_ojala(const Nodes &N, int n, int n0, int P, const double *zx,
-                          const double *zy, const double *fr, const double *fi, double *part,
-                          int *hit, bool neg_im, double *outr, double *outi, hipStream_t st) {
+                          const double *zy, const HoValues &F, int nf, double *part, int *hit,
+                          bool neg_im, hipStream_t st) {
     const int chunk = ho_chunk(P, n);
     const int ns = cdiv(n, chunk);
-    hipLaunchKernelGGL(k_ho_partial, dim3(cdiv(P, 256), ns), dim3(256), 0, st, N, n, n0, P, zx, zy,
-                       fr, fi, chunk, part, hit);
-    hipLaunchKernelGGL(k_ho_finalize, dim3(cdiv(P, 64)), dim3(64), 0, st, P, ns, part, hit, fr, fi,
-                       neg_im ? 1 : 0, outr, outi);
+    const dim3 grid(cdiv(P, 256), ns), fin(cdiv(P, 64));
+    if (nf == 2) {
+        hipLaunchKernelGGL(k_ho_partial<2>, grid, dim3(256), 0, st, N, n, n0, P, zx, zy, F, chunk,
+                           part, hit);
+        hipLaunchKernelGGL(k_ho_finalize<2>, fin, dim3(64 * kSliceWaves), 0, st, P, ns, part, hit, F,
+                           neg_im ? 1 : 0);
+    } else {
+        hipLaunchKernelGGL(k_ho_partial<1>, grid, dim3(256), 0, st, N, n, n0, P, zx, zy, F, chunk,
+                           part, hit);
+        hipLaunchKernelGGL(k_ho_finalize<1>, fin, dim3(64 * kSliceWaves), 0, st, P, ns, part, hit, F,
+                           neg_im ? 1 : 0);
+    }
 }
 
 void launch_boundary_velocity(int n, const double *dx, const double *dy, const double *sds,
