@@ -638,10 +638,11 @@ __device__ void strip_block(const Layout &L, const Nodes &N, int stride, int cou
 // pairs (p in a, any q) added into *count.  A cell that straddles two
 // boundaries has a disc that meets nearly every other: testing all pairs of
 // up to 80 cells, one cell after the other, took 32 us at 580 nodes, 105 at
-// 2208 and 144 at 5002.  So the listed cells are first cut down, one per
-// thread, to those whose disc comes near a node of a, and then only the nodes
-// of either cell that come near the other's disc are tested, in shares of the
-// block's waves, the next cell's nodes in flight: 16, 16 and 17 us.
+// 2208 and 144 at 5002.  So the listed cells are first cut down, eight threads
+// to a cell, to those whose disc comes near a node of a (4 us of 16 with one
+// thread each), and then only the nodes of either cell that come near the
+// other's disc are tested, in shares of the block's waves, the next cell's
+// nodes in flight: 12, 14 and 14 us.
 // The blocks after them measure the strips (12 us for both at 10240 nodes; the
 // strips alone took 56 with a wave per source and a square root and a
 // division per pair, which are now one of each per node).
@@ -686,22 +687,30 @@ __global__ __launch_bounds__(64 * kNearWaves) void k_near_cells(Layout L, Nodes 
         __syncthreads();
         int nl = list_disc_cells<kNearWaves>(N, da, c0, min(kMaxScanCells, ncell - c0), list, wcnt);
         if (nl > 8) {
-            // in place: a round writes at most as far as it has read
+            // in place: a round writes at most as far as it has read.  Eight
+            // threads share a cell, a thread every eighth node of a.
             int kept = 0;
-            for (int j0 = 0; j0 < nl; j0 += 64 * kNearWaves) {
-                const int j = j0 + (int)threadIdx.x, b = j < nl ? list[j] : 0;
+            for (int j0 = 0; j0 < nl; j0 += 8 * kNearWaves) {
+                const int j = j0 + (int)threadIdx.x / 8, b = j < nl ? list[j] : 0;
                 bool f = false;
                 if (j < nl) {
                     const double d[4] = {N.cell[4 * b], N.cell[4 * b + 1], N.cell[4 * b + 2],
                                          N.cell[4 * b + 3]};
-                    for (int i = 0; i < kCellNodes; ++i) f = f || node_near(sx[i], sy[i], sr[i], d);
+                    for (int i = threadIdx.x % 8; i < kCellNodes; i += 8)
+                        f = f || node_near(sx[i], sy[i], sr[i], d);
                 }
-                const unsigned long long bal = __ballot(f);
+                // bit 8 c: any of the eight threads of the wave's cell c
+                unsigned long long bal = __ballot(f);
+                bal |= bal >> 4;
+                bal |= bal >> 2;
+                bal |= bal >> 1;
+                bal &= 0x0101010101010101ull;
                 if (lane == 0) wcnt[wv] = __popcll(bal);
                 __syncthreads();
                 int before = kept;
                 for (int w = 0; w < wv; ++w) before += wcnt[w];
-                if (f) list[before + __popcll(bal & ((1ull << lane) - 1ull))] = b;
+                if (lane % 8 == 0 && (bal >> lane & 1ull))
+                    list[before + __popcll(bal & ((1ull << lane) - 1ull))] = b;
                 for (int w = 0; w < kNearWaves; ++w) kept += wcnt[w];
                 __syncthreads();
             }
