@@ -1056,11 +1056,10 @@ int Ctx::refine(const Op &op32, const Op &op64, const double *b, double *x, bool
 // Sec. 4.1): U = (u_mv + H gamma_0 / 2 + T gamma) / s.
 void Ctx::eval_U_from_gamma(const double *gamma, double *U) {
     const int n0 = L.off[1];
-    double *hg = vec[VHG], *um = vec[VUM];
+    double *hg = vec[VHG];
     launch_circulant_apply(L, rowH, gamma, hg, 1.0, 0.0, 0, 0, stream);
-    launch_umv(N, F, 0, n0, um, stream);
     launch_rflavour(L, N, hrow, 2, 0, 0, n0, 0, L.n, gamma, part, nullptr, stream);
-    launch_U_finalize(n0, s, um, hg, part, rflavour_nsplit(N, 2, n0, L.n, 0), U, stream);
+    launch_U_finalize(n0, N, F, nullptr, hg, part, rflavour_nsplit(N, 2, n0, L.n, 0), U, stream);
 }
 
 void Ctx::gamma_from_omega(const double *omega, double *gamma) {
@@ -1635,11 +1634,11 @@ int solve_phi_impl(Ctx *c, const wwbi_geom *g, const double *phi, const wwbi_opt
         double *gam = c->vec[VG];
         c->gamma_from_omega(x, gam);
         c->eval_U_from_gamma(gam, U);
-        if (omega) launch_copy(omega, x, n, c->stream);
-        // both into the host's memory: a copy behind each was 2 us and its gap
-        if (psi_k) launch_block_means(c->L, x, c->hstd, c->stream);
-        // resolution check: the Fourier tail of omega on every boundary
-        launch_tail_monitor(c->L, x, c->part, c->hstd + kTailOffset / sizeof(double), c->stream);
+        // the resolution check, the Fourier tail of omega on every boundary, with
+        // omega's copy and means (4 us each on their own): the host's numbers
+        // into its memory, where a copy behind each was 2 us and its gap
+        launch_tail_monitor(c->L, x, c->part, c->hstd + kTailOffset / sizeof(double),
+                            psi_k ? c->hstd : nullptr, omega, c->stream);
         hipEventRecord(c->ev[4], c->stream);
     };
     double bytes = 0.0;
@@ -2472,7 +2471,7 @@ int wwbi_tangent_phi(wwbi_ctx *ctx, const wwbi_geom *g, const double *omega, int
             for (int i = 0; i < nd; ++i) {
                 launch_rflavour(c->L, c->N, c->hrow, 2, 0, 0, n0, 0, n, dG + (long)i * ldv,
                                 c->part, nullptr, sm);
-                launch_U_finalize(n0, c->s, um + (long)i * n0, hgs + (long)i * n0, c->part, nsu,
+                launch_U_finalize(n0, c->N, c->F, um + (long)i * n0, hgs + (long)i * n0, c->part, nsu,
                                   dU + (long)i * n0, sm);
             }
         }

@@ -182,8 +182,10 @@ void launch_energy(int n0, const Nodes &N, const Flow &F, double tau, double gra
 // out[2k] = energy in the modes ceil(3 M_k / 8) .. M_k / 2 (both signs),
 // out[2k+1] = total energy; modes holds tail_modes_total(L) doubles.
 int tail_modes_total(const Layout &L);
+// means (may be null): the mean of f on every boundary k >= 2, at k - 2; copy
+// (may be null): f once more
 void launch_tail_monitor(const Layout &L, const double *f, double *modes, double *out,
-                         hipStream_t st);
+                         double *means, double *copy, hipStream_t st);
 // out = alpha C_k f + beta out on boundaries first..last (one launch);
 // launch_circulant_apply2 scales boundary 0 by alpha0 and the others by alpha
 void launch_circulant_apply(const Layout &L, const double *rows, const double *f, double *out,
@@ -200,7 +202,8 @@ void launch_circ_row1(int M, int op, double *row, hipStream_t st);
 void launch_circ_apply1(int M, const double *row, const double *f, double *out, double alpha,
                         double beta, hipStream_t st);
 void launch_block_means(const Layout &L, const double *v, double *out, hipStream_t st);
-void launch_U_finalize(int n0, const double *s, const double *umv, const double *hg,
+// umv null: u_mv is formed with the rest
+void launch_U_finalize(int n0, const Nodes &N, const Flow &F, const double *umv, const double *hg,
                        const double *part, int nsplit, double *U, hipStream_t st);
 void launch_wall_rhs_finalize(int nw, const double *umv_w, const double *part, int nsplit,
                               double *rhs, hipStream_t st);

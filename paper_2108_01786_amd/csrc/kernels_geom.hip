@@ -98,7 +98,7 @@ __device__ __forceinline__ double block_sum(double v, double *sh) {
 // the data.
 __device__ void validate_block(const Layout &L, const Nodes &N, const double *phi, int nphi,
                                int pb, int k, double *out) {
-    __shared__ double sh[16];
+    __shared__ double sh[16], sums[4][16];
     if (k >= L.nb) {
         // the data array: block b of pb counts its share (grid-stride) into
         // out[4 nb + 2 + b], for the host to add
@@ -125,15 +125,16 @@ __device__ void validate_block(const Layout &L, const Nodes &N, const double *ph
         area += 0.5 * (v[0] * v[3] - v[1] * v[2]) * (2.0 * M_PI / M);
         mdx += v[2] / M;
     }
-    bad = block_sum(bad, sh);
-    area = block_sum(area, sh);
-    mdx = block_sum(mdx, sh);
-    far = block_sum(far, sh);
-    if (threadIdx.x == 0) {
-        out[4 * k + 0] = bad;
-        out[4 * k + 1] = area;
-        out[4 * k + 2] = mdx;
-        out[4 * k + 3] = far;
+    double v[4] = {bad, area, mdx, far};
+    for (int o = 32; o > 0; o >>= 1)
+        for (int i = 0; i < 4; ++i) v[i] += __shfl_xor(v[i], o, 64);
+    if ((threadIdx.x & 63) == 0)
+        for (int i = 0; i < 4; ++i) sums[i][threadIdx.x >> 6] = v[i];
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        double t = 0.0;
+        for (int w = 0; w < (int)(blockDim.x >> 6); ++w) t += sums[threadIdx.x][w];
+        out[4 * k + threadIdx.x] = t;
     }
 }
 
@@ -202,20 +203,26 @@ __global__ void k_rhs_phi(Layout L, Nodes N, Flow F, const double *phi, const do
 }
 
 // s dphi_mv/dn = -(V1 + sum a_j / 2) y' + sum_j a_j Re{(1/2) cot((z - z_j)/2) z'}  (Sec. 3.4)
-__global__ void k_umv(Nodes N, Flow F, int first, int count, double *out) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= count) return;
-    const int p = first + i;
+// Share `w` of W of it: the obstacles w, w + W, ..., share 0 the rest too.
+__device__ __forceinline__ double umv_share(const Nodes &N, const Flow &F, int p, int w, int W) {
     const double dx = N.dx[p], dy = N.dy[p];
-    double asum = 0.0;
-    for (int j = 0; j < F.nobs; ++j) asum += F.a[j];
-    double v = -(F.V1 + 0.5 * asum) * dy;
-    for (int j = 0; j < F.nobs; ++j) {
+    double v = 0.0;
+    if (w == 0) {
+        double asum = 0.0;
+        for (int j = 0; j < F.nobs; ++j) asum += F.a[j];
+        v = -(F.V1 + 0.5 * asum) * dy;
+    }
+    for (int j = w; j < F.nobs; j += W) {
         double cr, ci;
         cot_half64(N.x[p] - F.zx[j], N.y[p] - F.zy[j], cr, ci);
         v += F.a[j] * 0.5 * (cr * dx - ci * dy);
     }
-    out[i] = v;
+    return v;
+}
+
+__global__ void k_umv(Nodes N, Flow F, int first, int count, double *out) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < count) out[i] = umv_share(N, F, first + i, 0, 1);
 }
 
 __global__ void k_circ_row1(int M, int op, double *row) {
@@ -423,7 +430,8 @@ __global__ __launch_bounds__(64 * kTailWaves) void k_tail_modes(Layout L, int to
 // One block per boundary: out[2k] = tail energy, out[2k+1] = total energy.
 __global__ __launch_bounds__(256) void k_tail_finish(Layout L, const double *__restrict__ f,
                                                      const double *__restrict__ modes,
-                                                     double *__restrict__ out) {
+                                                     double *__restrict__ out, double *means,
+                                                     double *copy) {
     __shared__ double sh[8];
     const int k = blockIdx.x;
     int m0 = 0;
@@ -432,31 +440,41 @@ __global__ __launch_bounds__(256) void k_tail_finish(Layout L, const double *__r
     const int cnt = tail_count(M);
     double t = 0.0;
     for (int i = threadIdx.x; i < cnt; i += blockDim.x) t += modes[m0 + i];
-    double e = 0.0;
-    for (int m = threadIdx.x; m < M; m += blockDim.x) e += f[L.off[k] + m] * f[L.off[k] + m];
+    double e = 0.0, a = 0.0;
+    for (int m = threadIdx.x; m < M; m += blockDim.x) {
+        const double v = f[L.off[k] + m];
+        e += v * v;
+        a += v;
+        if (copy) copy[L.off[k] + m] = v;
+    }
     t = block_sum(t, sh);
     e = block_sum(e, sh);
+    if (means && k >= 2) a = block_sum(a, sh);
     if (threadIdx.x == 0) {
         out[2 * k] = t;
         out[2 * k + 1] = (double)M * e;
+        if (means && k >= 2) means[k - 2] = a / (double)M;
     }
 }
 
 // U_m = (u_mv + (1/2) H gamma_0 + sum over split partials of T gamma) / s_m
-// (64 targets per block, the slices shared by kSliceWaves waves)
-__global__ __launch_bounds__(64 * kSliceWaves) void k_U_finalize(int n0, const double *s,
+// (64 targets per block, the slices and, without umv, the obstacles' terms of
+// u_mv shared by kSliceWaves waves)
+__global__ __launch_bounds__(64 * kSliceWaves) void k_U_finalize(int n0, Nodes N, Flow F,
                                                                  const double *umv,
                                                                  const double *hg,
                                                                  const double *part, int nsplit,
                                                                  double *U) {
-    __shared__ double red[kSliceWaves][64];
-    const int m = blockIdx.x * 64 + (threadIdx.x & 63);
+    __shared__ double red[kSliceWaves][64], um[kSliceWaves][64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, m = blockIdx.x * 64 + lane;
+    if (!umv) um[wv][lane] = m < n0 ? umv_share(N, F, m, wv, kSliceWaves) : 0.0;
     const double acc = sum_slices_waves<kSliceWaves>(part, nsplit, n0, m, m < n0, red);
     if (threadIdx.x >= 64 || m >= n0) return;
-    U[m] = (umv[m] + 0.5 * hg[m] + acc) / s[m];
+    double u = umv ? umv[m] : um[0][lane];
+    for (int w = 1; !umv && w < kSliceWaves; ++w) u += um[w][lane];
+    U[m] = (u + 0.5 * hg[m] + acc) / N.s[m];
 }
 
-// wall rhs = -(sum of G_0k^dagger gamma_0 partials) - s dphi_mv/dn
 __global__ __launch_bounds__(64 * kSliceWaves) void k_wall_rhs_finalize(int nw,
                                                                         const double *umv_w,
                                                                         const double *part,
@@ -672,11 +690,11 @@ int tail_modes_total(const Layout &L) {
 }
 
 void launch_tail_monitor(const Layout &L, const double *f, double *modes, double *out,
-                         hipStream_t st) {
+                         double *means, double *copy, hipStream_t st) {
     const int total = tail_modes_total(L);
     hipLaunchKernelGGL(k_tail_modes, dim3((total + kTailWaves - 1) / kTailWaves),
                        dim3(64 * kTailWaves), 0, st, L, total, f, modes);
-    hipLaunchKernelGGL(k_tail_finish, dim3(L.nb), dim3(256), 0, st, L, f, modes, out);
+    hipLaunchKernelGGL(k_tail_finish, dim3(L.nb), dim3(256), 0, st, L, f, modes, out, means, copy);
 }
 
 void launch_block_means(const Layout &L, const double *v, double *out, hipStream_t st) {
@@ -684,9 +702,9 @@ void launch_block_means(const Layout &L, const double *v, double *out, hipStream
     hipLaunchKernelGGL(k_block_means, dim3(L.nb - 2), dim3(256), 0, st, L, v, out);
 }
 
-void launch_U_finalize(int n0, const double *s, const double *umv, const double *hg,
+void launch_U_finalize(int n0, const Nodes &N, const Flow &F, const double *umv, const double *hg,
                        const double *part, int nsplit, double *U, hipStream_t st) {
-    hipLaunchKernelGGL(k_U_finalize, dim3(cdiv(n0, 64)), dim3(64 * kSliceWaves), 0, st, n0, s,
+    hipLaunchKernelGGL(k_U_finalize, dim3(cdiv(n0, 64)), dim3(64 * kSliceWaves), 0, st, n0, N, F,
                        umv, hg, part, nsplit, U);
 }
 
