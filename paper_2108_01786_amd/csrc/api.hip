@@ -1957,17 +1957,19 @@ static int stage_impl(Ctx *c, const wwbi_geom *g, int mode, const double *q, con
     if (mode == WWBI_SURF_GRAPH) {
         // zeta = alpha + i eta (Sec. 2.1)
         launch_graph_base(M0, q, x, y, dx, ddx, st);
-        launch_circ_apply1(M0, rD, q, dy, 1.0, 0.0, st);
+        launch_circ_pair(M0, rD, {q, dy, nullptr, nullptr, 0.0}, {phi, dphi, nullptr, nullptr, 0.0},
+                         0.0, st);
         launch_circ_apply1(M0, rD, dy, ddy, 1.0, 0.0, st);
     } else {
         // the curve from P theta (Sec. 2.2)
         launch_mean_cs(M0, q, sc, st);
         launch_hls_slope(M0, q, sc, dx, dy, t1, st);
-        launch_circ_apply1(M0, rI, t1, t2, 1.0, 0.0, st);      // xi^aux
-        launch_circ_apply1(M0, rI, dy, t3, 1.0, 0.0, st);      // eta^aux
+        launch_circ_pair(M0, rI, {t1, t2, nullptr, nullptr, 0.0}, {dy, t3, nullptr, nullptr, 0.0}, 0.0,
+                         st);                                  // xi^aux, eta^aux
         launch_mean_prod(M0, t3, dx, sc + 2, st);
         launch_hls_xy(M0, t2, t3, sc + 2, x, y, st);
-        launch_circ_apply1(M0, rD, q, t4, 1.0, 0.0, st);       // theta_alpha
+        launch_circ_pair(M0, rD, {q, t4, nullptr, nullptr, 0.0}, {phi, dphi, nullptr, nullptr, 0.0},
+                         0.0, st);                             // theta_alpha, phi_alpha
         launch_hls_curv(M0, t4, dx, dy, ddx, ddy, st);
     }
     wwbi_report r{};
@@ -1986,7 +1988,6 @@ static int stage_impl(Ctx *c, const wwbi_geom *g, int mode, const double *q, con
         launch_mean_prod(M0, t1, nullptr, sc + 3, st);
         launch_sub_mean(M0, t1, sc + 3, qt, st);
     }
-    launch_circ_apply1(M0, rD, phi, dphi, 1.0, 0.0, st);
     launch_phit(M0, c->N, c->F, dphi, U, V, tau, grav, phit, st);
     if (Uout) launch_copy(Uout, U, M0, st);
     if (Vout) launch_copy(Vout, V, M0, st);
@@ -2046,8 +2047,7 @@ int wwbi_rk_step(wwbi_ctx *ctx, const wwbi_geom *g, int32_t mode, int32_t nstage
         co.ns = i;
         co.h = h;
         for (int j = 0; j < i; ++j) co.c[j] = A[i * nstage + j];
-        launch_rk_combine(M0, q, Kq, (long)M, co, qi, st);
-        launch_rk_combine(M0, phi, Kp, (long)M, co, pi, st);
+        launch_rk_combine(M0, {q, Kq, qi}, {phi, Kp, pi}, (long)M, co, st);
         wwbi_report r{};
         const int s = stage_impl(c, g, mode, qi, pi, tau, grav, o, Kq + i * M, Kp + i * M,
                                  nullptr, nullptr, &r);
@@ -2066,13 +2066,12 @@ int wwbi_rk_step(wwbi_ctx *ctx, const wwbi_geom *g, int32_t mode, int32_t nstage
         co.ns = nstage;
         co.h = h;
         for (int j = 0; j < nstage; ++j) co.c[j] = b[j];
-        launch_rk_combine(M0, q, Kq, (long)M, co, qi, st);
-        launch_rk_combine(M0, phi, Kp, (long)M, co, pi, st);
+        launch_rk_combine(M0, {q, Kq, qi}, {phi, Kp, pi}, (long)M, co, st);
         if (filter) {
             // the 36th-order filter at the end of the step (Sec. 5)
             const double *rF = c->evrow + 2 * M;
-            launch_circ_apply1(M0, rF, qi, q, 1.0, 0.0, st);
-            launch_circ_apply1(M0, rF, pi, phi, 1.0, 0.0, st);
+            launch_circ_pair(M0, rF, {qi, q, nullptr, nullptr, 0.0}, {pi, phi, nullptr, nullptr, 0.0},
+                             0.0, st);
         } else {
             launch_copy(q, qi, M0, st);
             launch_copy(phi, pi, M0, st);

@@ -251,8 +251,12 @@ void launch_hls_f(int M, const double *dU, const double *V, const double *ta, co
 void launch_sub_mean(int M, const double *f, const double *mean, double *out, hipStream_t st);
 void launch_phit(int M, const Nodes &N, const Flow &F, const double *dphi, const double *U,
                  const double *V, double tau, double grav, double *out, hipStream_t st);
-void launch_rk_combine(int M, const double *base, const double *K, long ld, const RkCoef &co,
-                       double *out, hipStream_t st);
+struct RkState {
+    const double *base, *K;
+    double *out;
+};
+void launch_rk_combine(int M, const RkState &q, const RkState &phi, long ld, const RkCoef &co,
+                       hipStream_t st);
 
 // ---- kernels_interior.hip ----------------------------------------------------
 // Helsing-Ojala rule at P points from the boundary values of nf = 1 or 2

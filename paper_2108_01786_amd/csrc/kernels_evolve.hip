@@ -186,15 +186,16 @@ __global__ void k_phit(int M, Nodes N, Flow F, const double *dphi, const double 
              tau * 2.0 * N.lim[m] / s;
 }
 
-// out = base + h sum_j c_j K_j, K_j = K + j ld, the sum in increasing j
-__global__ void k_rk_combine(int M, const double *base, const double *K, long ld, RkCoef co,
-                             double *out) {
+// out = base + h sum_j c_j K_j, K_j = K + j ld, the sum in increasing j, for
+// the surface's state and the potential (blockIdx.y)
+__global__ void k_rk_combine(int M, RkState q, RkState phi, long ld, RkCoef co) {
     const int m = blockIdx.x * blockDim.x + threadIdx.x;
     if (m >= M) return;
+    const RkState s = blockIdx.y ? phi : q;
     double acc = 0.0;
     for (int j = 0; j < co.ns; ++j)
-        if (co.c[j] != 0.0) acc += co.c[j] * K[(long)j * ld + m];
-    out[m] = base[m] + co.h * acc;
+        if (co.c[j] != 0.0) acc += co.c[j] * s.K[(long)j * ld + m];
+    s.out[m] = s.base[m] + co.h * acc;
 }
 
 }  // namespace
@@ -261,10 +262,9 @@ void launch_phit(int M, const Nodes &N, const Flow &F, const double *dphi, const
                        grav, out);
 }
 
-void launch_rk_combine(int M, const double *base, const double *K, long ld, const RkCoef &co,
-                       double *out, hipStream_t st) {
-    hipLaunchKernelGGL(k_rk_combine, dim3(cdiv(M, 256)), dim3(256), 0, st, M, base, K, ld, co,
-                       out);
+void launch_rk_combine(int M, const RkState &q, const RkState &phi, long ld, const RkCoef &co,
+                       hipStream_t st) {
+    hipLaunchKernelGGL(k_rk_combine, dim3(cdiv(M, 256), 2), dim3(256), 0, st, M, q, phi, ld, co);
 }
 
 }  // namespace wwbi
