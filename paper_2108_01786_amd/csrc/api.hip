@@ -669,8 +669,10 @@ int Ctx::ensure_coarse(int n, int nsys) {
 
 // Where the passes stop: at 0.2 of the tolerance, at tight tolerances 0.4 (up to
 // 4e-15, a few times the rounding of the residual itself, which a pass more
-// would take to rounding at 0.1 ms or more: 2208 unknowns refined to 1e-14 leave
-// 2.4e-15 after one).
+// would take to rounding: 2208 unknowns refined to 1e-14 leave 2.4e-15 after one,
+// 399 us with the second pass, 350 us without).  Errors of that solve against 64
+// bits, over those of GMRES on all unknowns to the tolerance itself, on six
+// random right-hand sides: 0.88 to 1.05, geometric mean 0.97.
 constexpr double kTwoGridMargin = 0.2;
 double two_grid_target(double tol) {
     return std::max(kTwoGridMargin * tol, std::min(2.0 * kTwoGridMargin * tol, 4e-15));
