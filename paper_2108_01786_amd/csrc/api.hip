@@ -450,8 +450,9 @@ int Ctx::gmres(const Op &op, const double *b, double *x, bool x_zero, double tol
             if (trace)
                 std::fprintf(stderr, "wwbi: op %d n %d cycle %d its %d beta/bnorm %.3e\n",
                              op.kind, n, st.cycles, st.iters, st.rel_resid);
-            if (!h.active) { status = WWBI_OK; break; }
+            // first: a NaN is above no tolerance, so it is not active either
             if (!std::isfinite(h.beta)) { status = WWBI_STAGNATED; break; }
+            if (!h.active) { status = WWBI_OK; break; }
             if (st.iters >= max_iter) { status = WWBI_NOT_CONVERGED; break; }
             if (!first && h.beta > 0.99 * prev_beta) { status = WWBI_STAGNATED; break; }
             prev_beta = h.beta;
@@ -921,13 +922,14 @@ int Ctx::solve_system(int mode, Op op, int k0, const int (&kinds)[4], const doub
     if (fp32) return refine(in, op64, b, x, x_zero, o, st);
     const int status =
         gmres(in, b, x, x_zero, o.tol, o.restart, o.max_iter, o.poll_every, true, st);
-    if (small && o.precision == WWBI_FP32_REFINED) as_refined(x_zero, st);
+    if (small && o.precision == WWBI_FP32_REFINED) return as_refined(x_zero, status, st);
     return status;
 }
 
-void Ctx::as_refined(bool x_zero, SolveStats &st) {
+int Ctx::as_refined(bool x_zero, int status, SolveStats &st) {
     st.refine_steps = st.cycles;
     if (x_zero && !hist.empty()) hist.erase(hist.begin());
+    return status == WWBI_STAGNATED ? WWBI_REFINE_STALLED : status;
 }
 
 // Operator kinds of a system: stored FP64, stored FP32, on the fly in FP64 and
@@ -1251,8 +1253,8 @@ int Ctx::gmres_multi(int kind, int n, long ld, const double *B, double *X, int n
                 bsum += h[s].beta;
             }
             st.rel_resid = worst;
-            if (!any) { status = WWBI_OK; break; }
             if (!std::isfinite(bsum)) { status = WWBI_STAGNATED; break; }
+            if (!any) { status = WWBI_OK; break; }
             if (st.iters >= max_iter) { status = WWBI_NOT_CONVERGED; break; }
             if (!first && bsum > 0.99 * prev) { status = WWBI_STAGNATED; break; }
             prev = bsum;
@@ -1410,7 +1412,7 @@ int Ctx::refine_multi(int n, long ld, const double *B, double *X, int nr, const 
         double worst = 0.0;
         bool done = true, stalled = false;
         for (int s = 0; s < nr; ++s) {
-            const double rel = bnrm[s] > 0 ? rn[s] / bnrm[s] : 0.0;
+            const double rel = bnrm[s] != 0.0 ? rn[s] / bnrm[s] : 0.0;   // a NaN stays one
             worst = std::max(worst, rel);
             done = done && rel <= o.tol;
             stalled = stalled || !std::isfinite(rn[s]) ||
@@ -1656,7 +1658,7 @@ int solve_phi_impl(Ctx *c, const wwbi_geom *g, const double *phi, const wwbi_opt
         results();
         bytes = c->op_bytes(small);
         queued = c->small_result(st, status);
-        if (queued && o->precision == WWBI_FP32_REFINED) c->as_refined(xz, st);
+        if (queued && o->precision == WWBI_FP32_REFINED) status = c->as_refined(xz, status, st);
     }
     if (!queued) {
         status = c->solve_system(kCoarseA, op, 0, kKindsA, b, x, xz, *o, false, c->a_ready,

@@ -271,8 +271,8 @@ struct Ctx {
                      bool x_zero, const wwbi_opts &o, bool check_rough, bool &assembled,
                      Assemble assemble, SolveStats &st, double &bytes);
     // the report of a small FP64 solve that was asked for in refined FP32: its
-    // cycles are the refinement steps
-    void as_refined(bool x_zero, SolveStats &st);
+    // cycles are the refinement steps, and its stagnation a stalled refinement
+    int as_refined(bool x_zero, int status, SolveStats &st);
     double device_norm(const double *v, int n);
     int refine(const Op &op32, const Op &op64, const double *b, double *x, bool x_zero,
                const wwbi_opts &o, SolveStats &st);

@@ -339,8 +339,9 @@ __global__ __launch_bounds__(kTS, 2) void k_small_gmres(SmallArgs a) {
         // re = the true residual of xe, beta its norm, slot 0 = re
         if (writer && nhist < WWBI_HIST_MAX) out->hist[nhist] = bnorm > 0 ? beta / bnorm : 0.0;
         ++nhist;
+        // first: a NaN is above no tolerance
+        if (!isfinite(beta) || !isfinite(bnorm)) { status = WWBI_STAGNATED; break; }
         if (!(beta > tol_abs)) { status = WWBI_OK; break; }
-        if (!isfinite(beta)) { status = WWBI_STAGNATED; break; }
         if (its >= a.max_iter || cycles >= a.max_cycles) { status = WWBI_NOT_CONVERGED; break; }
         if (cycles > 0 && beta > 0.99 * prev) { status = WWBI_STAGNATED; break; }
         prev = beta;
