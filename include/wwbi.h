@@ -69,8 +69,9 @@ extern "C" {
 #define WWBI_FP64                 0  /* FP64 matrix and matvecs                          */
 #define WWBI_FP32_REFINED         1  /* FP32 matrix/matvec (FP64 accumulation) inside
                                         FP64 iterative refinement.  A system of at most
-                                        1024 unknowns is solved in FP64 either way, in
-                                        one launch (its cycles count as the steps)     */
+                                        1024 unknowns is solved in FP64 either way, by
+                                        restarted GMRES (its cycles count as the steps,
+                                        and max_refine does not limit them)            */
 #define WWBI_MATVEC_AUTO          0  /* the fastest: above 1024 unknowns, from a cold
                                         start and where the grid has nodes to spare,
                                         a two-grid iteration (a coarse subset of the
@@ -141,7 +142,8 @@ typedef struct {
 typedef struct {
     int32_t status;
     int32_t iters;         /* Arnoldi steps taken (all cycles, refinement steps and
-                              coarse solves)                                              */
+                              coarse solves) by the solve that ended the call: an
+                              attempt that handed its system on is not counted            */
     int32_t restarts;      /* restart cycles and two-grid passes                          */
     int32_t refine_steps;  /* FP32_REFINED: inner solves and two-grid passes              */
     double rel_resid;      /* final ||b - A x|| / ||b|| with the FP64 operator            */

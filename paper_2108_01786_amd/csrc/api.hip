@@ -385,10 +385,13 @@ void Ctx::prof_end() {
 int Ctx::gmres(const Op &op, const double *b, double *x, bool x_zero, double tol, int restart,
                int max_iter, int poll, bool verify, SolveStats &st, int kc) {
     const int n = op.n;
-    if (verify && n <= kSmallMax && stored_fp64(op.kind) && !fixed_ws && !profiling) {
+    if (verify && n <= kSmallMax && stored_fp64(op.kind) && !fixed_ws && !profiling && !handed_on) {
         int status;
-        if (gmres_small(op, b, x, x_zero, tol, restart, max_iter, st, status)) return status;
+        if (queue_small(op, b, x, x_zero, tol, restart, max_iter) &&
+            small_result(st, status, x_zero))
+            return status;
     }
+    handed_on = false;
     const int G = gmres_nblocks(n);
     const int ldp = restart + 1 + vpre;    // rows of Gram-Schmidt partials (recycled ones too)
     const long ldv = round_up(n, 64);
@@ -446,6 +449,7 @@ int Ctx::gmres(const Op &op, const double *b, double *x, bool x_zero, double tol
             its_seen = h.its;
             st.iters = its0 + h.its;
             st.rel_resid = h.bnorm > 0 ? h.beta / h.bnorm : 0.0;
+            if (first) cold_hist = !x_set;
             note_resid(st.rel_resid);
             if (trace)
                 std::fprintf(stderr, "wwbi: op %d n %d cycle %d its %d beta/bnorm %.3e\n",
@@ -541,7 +545,6 @@ int Ctx::gmres(const Op &op, const double *b, double *x, bool x_zero, double tol
 }
 
 bool Ctx::small_system(int n, const wwbi_opts &o) {
-    cycle_cap = o.precision == WWBI_FP32_REFINED ? o.max_refine : INT_MAX;
     return n <= kSmallMax && o.matvec != WWBI_MATVEC_ON_THE_FLY && !fixed_ws && !profiling;
 }
 
@@ -578,17 +581,27 @@ bool Ctx::take_tags(long need, unsigned &first) {
     return true;
 }
 
-bool Ctx::gmres_small(const Op &op, const double *b, double *x, bool x_zero, double tol,
-                      int restart, int max_iter, SolveStats &st, int &status) {
-    return queue_small(op, b, x, x_zero, tol, restart, max_iter) && small_result(st, status);
-}
+// The LDS holds cycles of 17 (1024 unknowns) to 32 steps, whatever restart
+// says.  A system that needs more restarts there, and where the cycles gain
+// little it is handed on, from the iterate reached, to the multi-kernel loop,
+// whose cycles are as long as asked for: 896 unknowns with an ellipse of half
+// length 2.6 in a layer of 0.2 take 101 steps in cycles of 100 and stagnate in
+// cycles of 19.  A cycle has to gain a decade: 19 steps take about 90 us, and a
+// decade of a system on which they gain less takes 5 to 7 steps of 20 us there.
+constexpr double kCutCycleStall = 0.1, kCycleStall = 0.99;
 
 bool Ctx::queue_small(const Op &op, const double *b, double *x, bool x_zero, double tol,
                       int restart, int max_iter) {
     if (!ensure_small(1)) return false;
-    // an exchange takes a tag: one a step and one a cycle
     SmallArgs a{};
-    if (!take_tags(2L * max_iter + 8, a.tag)) return false;
+    a.max_iter = std::min(max_iter, 1 << 20);
+    // an exchange takes a tag: one a step and at most two more a cycle (the
+    // product dropped at its end and the residual), of a step at least
+    if (!take_tags(3L * a.max_iter + 8, a.tag)) return false;
+    const int most = small_cycle_steps(op.n);
+    const bool cut = restart > most && max_iter > most;
+    small_cut = cut || a.max_iter < max_iter;
+    small_cold = x_zero;
     a.A = (const double *)A;
     a.ld = op.ld;
     a.n = op.n;
@@ -598,8 +611,8 @@ bool Ctx::queue_small(const Op &op, const double *b, double *x, bool x_zero, dou
     a.x0 = x_zero ? nullptr : x;
     a.tol = tol;
     a.steps = restart;
-    a.max_iter = max_iter;
-    a.max_cycles = cycle_cap;
+    a.max_cycles = INT_MAX;
+    a.stall = cut ? kCutCycleStall : kCycleStall;
     a.verify = 1;
     a.xch = xch + 8;
     a.abort_tag = reinterpret_cast<unsigned *>(xch);
@@ -610,14 +623,26 @@ bool Ctx::queue_small(const Op &op, const double *b, double *x, bool x_zero, dou
     return true;
 }
 
-bool Ctx::small_result(SolveStats &st, int &status) {
+bool Ctx::small_result(SolveStats &st, int &status, bool &x_zero) {
     if (small_rc != WWBI_OK || hipGetLastError() != hipSuccess ||
         hipStreamSynchronize(stream) != hipSuccess) {
         status = WWBI_EHIP;
         return true;
     }
     const SmallRes &r = *hsmall;
-    if (r.status == kSmallAborted || r.aborted) return false;
+    if (r.status == kSmallAborted || r.aborted) {
+        handed_on = true;
+        return false;
+    }
+    if (r.status != WWBI_OK && small_cut && std::isfinite(r.resid)) {
+        if (trace)
+            std::fprintf(stderr, "wwbi: one-launch solve its %d cycles %d handed on at %.3e\n", r.its,
+                         r.cycles, r.resid / r.bnorm);
+        handed_on = true;
+        x_zero = false;
+        return false;
+    }
+    cold_hist = small_cold;
     st.iters += r.its;
     st.cycles += r.cycles;
     for (int i = 0; i < r.nhist; ++i) note_resid(r.hist[i]);
@@ -742,6 +767,7 @@ int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, co
         // replaces; where the LDS holds only a short cycle, several with it
         a.verify = nc > kSmallMax ? 1 : 0;
         a.max_cycles = a.verify ? 16 : 1;
+        a.stall = kCycleStall;
         a.xch = xch + 8;
         a.abort_tag = reinterpret_cast<unsigned *>(xch);
         a.out = dsmall;
@@ -848,6 +874,7 @@ int Ctx::two_grid_multi(const double *A64, long ld, double *K, size_t kcap, cons
         a.max_iter = 512;
         a.verify = nc > kSmallMax ? 1 : 0;
         a.max_cycles = a.verify ? 16 : 1;
+        a.stall = kCycleStall;
         a.xch = xch + 8;
         a.xchs = small_exchange_words();
         a.abort_tag = reinterpret_cast<unsigned *>(xch);
@@ -922,13 +949,13 @@ int Ctx::solve_system(int mode, Op op, int k0, const int (&kinds)[4], const doub
     if (fp32) return refine(in, op64, b, x, x_zero, o, st);
     const int status =
         gmres(in, b, x, x_zero, o.tol, o.restart, o.max_iter, o.poll_every, true, st);
-    if (small && o.precision == WWBI_FP32_REFINED) return as_refined(x_zero, status, st);
+    if (small && o.precision == WWBI_FP32_REFINED) return as_refined(status, st);
     return status;
 }
 
-int Ctx::as_refined(bool x_zero, int status, SolveStats &st) {
+int Ctx::as_refined(int status, SolveStats &st) {
     st.refine_steps = st.cycles;
-    if (x_zero && !hist.empty()) hist.erase(hist.begin());
+    if (cold_hist && !hist.empty()) hist.erase(hist.begin());
     return status == WWBI_STAGNATED ? WWBI_REFINE_STALLED : status;
 }
 
@@ -1092,6 +1119,7 @@ int Ctx::check_opts(const wwbi_opts *o) {
 
 void Ctx::begin_report(bool prof) {
     profiling = prof;
+    handed_on = false;
     nprof = 0;
     cyc_done.clear();
     hist.clear();
@@ -1619,7 +1647,7 @@ int solve_phi_impl(Ctx *c, const wwbi_geom *g, const double *phi, const wwbi_opt
         c->a_ready = true;
     }
     hipEventRecord(c->ev[2], c->stream);
-    const bool xz = o->x0 == nullptr;
+    bool xz = o->x0 == nullptr;
     if (!xz) launch_copy(x, o->x0, n, c->stream);
     const Op op{OP_A_O64, n, ld, o->flags, o->band, n0};
     // A one-launch solve is queued with all that follows it before anything
@@ -1657,8 +1685,8 @@ int solve_phi_impl(Ctx *c, const wwbi_geom *g, const double *phi, const wwbi_opt
     if (queued) {
         results();
         bytes = c->op_bytes(small);
-        queued = c->small_result(st, status);
-        if (queued && o->precision == WWBI_FP32_REFINED) status = c->as_refined(xz, status, st);
+        queued = c->small_result(st, status, xz);
+        if (queued && o->precision == WWBI_FP32_REFINED) status = c->as_refined(status, st);
     }
     if (!queued) {
         status = c->solve_system(kCoarseA, op, 0, kKindsA, b, x, xz, *o, false, c->a_ready,

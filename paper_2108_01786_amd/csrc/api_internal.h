@@ -126,7 +126,10 @@ struct Ctx {
     unsigned long long *xch = nullptr; size_t capxch = 0;
     SmallRes *hsmall = nullptr, *dsmall = nullptr;
     unsigned xtag = 1;
-    int cycle_cap = 0;
+    bool small_cold = false;    // the queued one started from zero
+    bool small_cut = false;     // and may stop short of what was asked for
+    bool handed_on = false;     // it did: gmres() goes on with its own loop
+    bool cold_hist = false;     // hist begins with the residual of a zero start
     // two-grid iteration: the coarse matrix, the coarse nodes' fine indices and
     // weight factors, and the coarse solution
     double *cA = nullptr;   size_t capcA = 0;
@@ -232,16 +235,13 @@ struct Ctx {
               int max_iter, int poll, bool verify, SolveStats &st, int kc = 0);
     // whether a system of n unknowns is solved in one launch (in FP64, whichever
     // precision was asked for); not for profiled calls, which time the products.
-    // Sets the cycle budget of such a solve: max_refine when FP32 was asked for.
     bool small_system(int n, const wwbi_opts &o);
-    // one-launch solve; false when it could not run (solve by gmres())
-    bool gmres_small(const Op &op, const double *b, double *x, bool x_zero, double tol,
-                     int restart, int max_iter, SolveStats &st, int &status);
-    // its halves: the launch (false when it is not available), and the wait
-    // and the result (false when the launch gave up, x then undefined)
+    // one-launch solve: the launch (false when it is not available), and the
+    // wait and the result (false when gmres() has to solve, from x unless
+    // x_zero)
     bool queue_small(const Op &op, const double *b, double *x, bool x_zero, double tol,
                      int restart, int max_iter);
-    bool small_result(SolveStats &st, int &status);
+    bool small_result(SolveStats &st, int &status, bool &x_zero);
     int small_rc = 0;
     // words and results for nsys one-launch solves; false when out of memory
     bool ensure_small(int nsys);
@@ -272,7 +272,7 @@ struct Ctx {
                      Assemble assemble, SolveStats &st, double &bytes);
     // the report of a small FP64 solve that was asked for in refined FP32: its
     // cycles are the refinement steps, and its stagnation a stalled refinement
-    int as_refined(bool x_zero, int status, SolveStats &st);
+    int as_refined(int status, SolveStats &st);
     double device_norm(const double *v, int n);
     int refine(const Op &op32, const Op &op64, const double *b, double *x, bool x_zero,
                const wwbi_opts &o, SolveStats &st);

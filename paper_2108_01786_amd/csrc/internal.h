@@ -410,6 +410,7 @@ struct SmallArgs {
     double tol;
     int steps;             // Arnoldi steps per cycle (cut to what the LDS holds)
     int max_iter, max_cycles;
+    double stall;          // a cycle that leaves more of the residual than this ends the solve
     int verify;            // 0: one cycle, no true residual
     unsigned long long *xch;   // small_exchange_words() per system, zero at first
     long xchs;
@@ -418,6 +419,8 @@ struct SmallArgs {
     SmallRes *out;         // one per system
 };
 long small_exchange_words();
+// steps of a cycle that the LDS holds at n unknowns
+int small_cycle_steps(int n);
 // nsys systems with the same matrix; WWBI_OK when queued
 int launch_small_gmres(SmallArgs a, int nsys, hipStream_t st);
 

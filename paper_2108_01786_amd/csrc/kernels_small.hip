@@ -343,7 +343,7 @@ __global__ __launch_bounds__(kTS, 2) void k_small_gmres(SmallArgs a) {
         if (!isfinite(beta) || !isfinite(bnorm)) { status = WWBI_STAGNATED; break; }
         if (!(beta > tol_abs)) { status = WWBI_OK; break; }
         if (its >= a.max_iter || cycles >= a.max_cycles) { status = WWBI_NOT_CONVERGED; break; }
-        if (cycles > 0 && beta > 0.99 * prev) { status = WWBI_STAGNATED; break; }
+        if (cycles > 0 && beta > a.stall * prev) { status = WWBI_STAGNATED; break; }
         prev = beta;
         __syncthreads();                   // slot 0 has been read by every wave
         store_slot(0, re, 1.0 / beta);
@@ -439,11 +439,20 @@ __global__ __launch_bounds__(kTS, 2) void k_small_gmres(SmallArgs a) {
 
 inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
 
+// Columns per lane: in steps of two, above 16 of four.
+inline int columns(int n) {
+    const int c = (cdiv(n, 64) + 1) / 2 * 2;
+    return c <= 16 ? c : (c + 3) / 4 * 4;
+}
+inline int cycle_steps(int cpl) {
+    const int slots = kLdsBytes / (64 * cpl * 8);
+    return slots - 1 < kSmallSteps ? slots - 1 : kSmallSteps;
+}
+
 template <int CPL, int RW>
 int launch_cpl(SmallArgs a, int nsys, hipStream_t st) {
-    const int slots = kLdsBytes / (64 * CPL * 8);
-    a.steps = a.steps < slots - 1 ? a.steps : slots - 1;
-    a.steps = a.steps < kSmallSteps ? a.steps : kSmallSteps;
+    const int most = cycle_steps(CPL);
+    a.steps = a.steps < most ? a.steps : most;
     const size_t lds = (size_t)(a.steps + 1) * 64 * CPL * 8;
     static_assert(RW <= 64 && CPL * 8 * 64 * 2 <= kLdsBytes, "shape");
     const hipError_t e = hipFuncSetAttribute(
@@ -460,9 +469,10 @@ int launch_cpl(SmallArgs a, int nsys, hipStream_t st) {
 // Words of one system's exchange buffers (two parities, two words per value).
 long small_exchange_words() { return 2L * 2 * kSmallCoarseMax; }
 
+int small_cycle_steps(int n) { return cycle_steps(columns(n)); }
+
 int launch_small_gmres(SmallArgs a, int nsys, hipStream_t st) {
-    // columns per lane in steps of two
-    const int cpl = (cdiv(a.n, 64) + 1) / 2 * 2;
+    const int cpl = columns(a.n);
     // A block's basis fills the LDS of its CU.  Where many systems would not
     // all be resident, more rows per wave run more of them at once (32 of 512
     // unknowns: 8 blocks each, one round of 256 blocks instead of four).
@@ -489,10 +499,10 @@ int launch_small_gmres(SmallArgs a, int nsys, hipStream_t st) {
     case 12: return launch_cpl<12, 2>(a, nsys, st);
     case 14: return launch_cpl<14, 2>(a, nsys, st);
     case 16: return launch_cpl<16, 2>(a, nsys, st);
-    case 18: case 20: return launch_cpl<20, 2>(a, nsys, st);
-    case 22: case 24: return launch_cpl<24, 2>(a, nsys, st);
-    case 26: case 28: return launch_cpl<28, 2>(a, nsys, st);
-    case 30: case 32: return launch_cpl<32, 2>(a, nsys, st);
+    case 20: return launch_cpl<20, 2>(a, nsys, st);
+    case 24: return launch_cpl<24, 2>(a, nsys, st);
+    case 28: return launch_cpl<28, 2>(a, nsys, st);
+    case 32: return launch_cpl<32, 2>(a, nsys, st);
     default: return WWBI_EINVAL_SIZE;
     }
 }

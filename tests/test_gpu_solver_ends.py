@@ -79,3 +79,67 @@ def test_not_finite_is_no_solution(ww, ctx, M0, M1, Mo, prec, mode):
     # the context is as good as before
     _, again, _, r = ctx.solve_phi(dg0, p, **kw)
     assert r.status in (ww.OK, ww.WARN_UNDERRESOLVED) and torch.equal(again, omega)
+
+
+def thin_cell(depth, half):
+    """A flat-bottomed layer with one long flat ellipse in its middle."""
+    zc = np.pi - 0.5j * depth
+    curves = [fourier_surface(384, 0.02 * depth, []), graph_bottom(256, -depth),
+              ellipse(256, zc.real, zc.imag, half, 0.25 * depth, 0.0)]
+    return Geometry(curves, np.array([zc]), np.array([0.5]), 1.0)
+
+
+def norm_rel(a, b):
+    a, b = a.cpu().numpy(), b.numpy()
+    return float(np.linalg.norm(a - b) / np.linalg.norm(b))
+
+
+# one cycle of 100 steps, at most two, where cycles of 19 take 9 or more or stagnate
+@pytest.mark.parametrize("depth,half", [(0.6, 2.6), (0.4, 1.8), (0.4, 2.6), (0.3, 2.6), (0.2, 2.6)])
+@pytest.mark.parametrize("prec", ["fp64", "refined"])
+@pytest.mark.parametrize("mode", ["auto", "stored"])
+def test_small_cells_that_need_long_cycles(ww, ctx, depth, half, prec, mode):
+    geom = thin_cell(depth, half)
+    phi = torch.as_tensor(trig_potential(384, [0.1, 0.05], [0.05, 0.02]))
+    print(f"case thin layer {depth} {half} {prec} {mode}", flush=True)
+    og = O.OGeom.from_synth(geom)
+    ref = O.solve_phi(og, phi)
+    cond = float(np.linalg.cond(O.assemble_A(og).numpy()))
+    dg = ww.DeviceGeometry.from_synth(geom, DEV)
+    kw = options(ww, prec, tol=1e-14,
+                 matvec=ww.MATVEC_AUTO if mode == "auto" else ww.MATVEC_STORED)
+    U, om, _, r = ctx.solve_phi(dg, phi.to(DEV), **kw)
+    assert r.status in (ww.OK, ww.WARN_UNDERRESOLVED) and r.rel_resid <= 1e-14
+    # the solve's residual and the oracle's (a few units of rounding)
+    assert norm_rel(om, ref["omega"]) <= 2 * cond * 1e-14
+    assert (r.refine_steps > 0) == (prec == "refined") and r.history()[-1] == r.rel_resid
+    # from another start, and the transpose
+    U2, om2, _, r2 = ctx.solve_phi(dg, phi.to(DEV), x0=torch.ones_like(om), **kw)
+    assert r2.status == r.status and norm_rel(om2, ref["omega"]) <= 2 * cond * 1e-14
+    g, ra = ctx.adjoint_phi(dg, om, torch.ones_like(U), **kw)
+    assert ra.status == ww.OK and ra.rel_resid <= 1e-14
+
+
+@pytest.mark.parametrize("max_refine", [2, 3])
+def test_small_refined_within_its_refinement_steps(ww, ctx, max_refine):
+    """Five ellipses at 1024 unknowns: two refinement steps of the FP32 matrix,
+    five cycles of the one-launch solve."""
+    zc = np.array([(2 * j + 1) * np.pi / 5 - 0.5j for j in range(5)])
+    geom = Geometry([fourier_surface(384, 0.03, []), graph_bottom(120, -1.0)] +
+                    [ellipse(104, z.real, z.imag, 0.6, 0.35, 0.0) for z in zc],
+                    zc, np.linspace(-0.5, 0.5, 5), 1.0)
+    print(f"case five ellipses max_refine={max_refine}", flush=True)
+    phi = torch.as_tensor(trig_potential(384, [0.1, 0.05], [0.05, 0.02]), device=DEV)
+    dg = ww.DeviceGeometry.from_synth(geom, DEV)
+    r = ctx.solve_phi(dg, phi, **options(ww, "refined", tol=1e-14, max_refine=max_refine))[3]
+    assert r.status in (ww.OK, ww.WARN_UNDERRESOLVED) and r.rel_resid <= 1e-14
+
+
+@pytest.mark.parametrize("steps", [1, 5, 17, 18, 40])
+def test_small_solves_keep_to_their_budget(ww, ctx, steps):
+    geom = thin_cell(0.2, 2.6)
+    print(f"case budget of {steps} steps", flush=True)
+    phi = torch.as_tensor(trig_potential(384, [0.1, 0.05], [0.05, 0.02]), device=DEV)
+    r = ctx.solve_phi(ww.DeviceGeometry.from_synth(geom, DEV), phi,
+                      **options(ww, "fp64", tol=1e-14, max_iter=steps))[3]
+    assert r.status == ww.NOT_CONVERGED and r.iters <= steps and r.rel_resid < 1.0
