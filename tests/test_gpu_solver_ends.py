@@ -81,11 +81,11 @@ def test_not_finite_is_no_solution(ww, ctx, M0, M1, Mo, prec, mode):
     assert r.status in (ww.OK, ww.WARN_UNDERRESOLVED) and torch.equal(again, omega)
 
 
-def thin_cell(depth, half):
+def thin_cell(depth, half, M=(384, 256, 256)):
     """A flat-bottomed layer with one long flat ellipse in its middle."""
     zc = np.pi - 0.5j * depth
-    curves = [fourier_surface(384, 0.02 * depth, []), graph_bottom(256, -depth),
-              ellipse(256, zc.real, zc.imag, half, 0.25 * depth, 0.0)]
+    curves = [fourier_surface(M[0], 0.02 * depth, []), graph_bottom(M[1], -depth),
+              ellipse(M[2], zc.real, zc.imag, half, 0.25 * depth, 0.0)]
     return Geometry(curves, np.array([zc]), np.array([0.5]), 1.0)
 
 
@@ -143,3 +143,31 @@ def test_small_solves_keep_to_their_budget(ww, ctx, steps):
     r = ctx.solve_phi(ww.DeviceGeometry.from_synth(geom, DEV), phi,
                       **options(ww, "fp64", tol=1e-14, max_iter=steps))[3]
     assert r.status == ww.NOT_CONVERGED and r.iters <= steps and r.rel_resid < 1.0
+
+
+# cells on which the two-grid iteration stops early and the stored matrix takes over
+@pytest.mark.parametrize("M,depth,entry", [((1536, 512, 512), 0.4, "phi"), ((768, 384, 384), 0.2, "adjoint"),
+                                           ((3000, 1500, 1500), 0.2, "gamma")])
+@pytest.mark.parametrize("prec", ["fp64", "refined"])
+def test_systems_the_two_grid_iteration_hands_on(ww, ctx, M, depth, entry, prec):
+    geom = thin_cell(depth, 2.6, M)
+    print(f"case handed on {entry} n={geom.Mtot} {prec}", flush=True)
+    dg = ww.DeviceGeometry.from_synth(geom, DEV)
+    phi = torch.as_tensor(trig_potential(M[0], [0.1, 0.05], [0.05, 0.02]), device=DEV)
+    tol = 1e-13 if prec == "fp64" else 1e-14
+    out = []
+    for mode in (ww.MATVEC_AUTO, ww.MATVEC_STORED):
+        kw = options(ww, prec, tol=tol, matvec=mode)
+        if entry == "phi":
+            U, v, _, r = ctx.solve_phi(dg, phi, **kw)
+        elif entry == "gamma":
+            U, v, r = ctx.solve_gamma(dg, phi, **kw)
+        else:
+            _, om, _, _ = ctx.solve_phi(dg, phi, **kw)
+            w = torch.as_tensor(np.random.default_rng(0).uniform(0, 1, M[0]), device=DEV)
+            g, r = ctx.adjoint_phi(dg, om, w, **kw)
+            v = g["phi"]
+        assert r.status in (ww.OK, ww.WARN_UNDERRESOLVED) and r.rel_resid <= tol
+        out.append(v)
+    # two residuals of tol and condition numbers of up to 1e4
+    assert rel(*out) <= 2e4 * tol
