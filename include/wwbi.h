@@ -129,7 +129,7 @@ typedef struct {
     int32_t precision;   /* WWBI_FP64 or WWBI_FP32_REFINED                                 */
     int32_t matvec;      /* WWBI_MATVEC_*                                                  */
     int32_t poll_every;  /* Arnoldi steps between host checks for the end of a cycle      */
-    int32_t max_refine;  /* FP32_REFINED: maximum refinement steps                         */
+    int32_t max_refine;  /* FP32_REFINED: maximum refinement steps, or two-grid passes     */
     int32_t band;        /* FP32: same-boundary pairs with cyclic |l-m| <= band are
                             evaluated in FP64 and rounded (near-singular kernel)          */
     int32_t flags;       /* WWBI_FLAG_*                                                    */

@@ -710,8 +710,16 @@ double two_grid_target(double tol) {
 // over 6.6.
 constexpr double kTwoGridGain = 0.3;
 
+// Passes of one call: within the budgets of refinement steps and, by the steps
+// of the coarse solves, of Arnoldi steps.  A system handed on has both whole
+// again: its steps are charged to the call by the solve that ends it alone.
+int two_grid_passes(const wwbi_opts &o) {
+    return o.precision == WWBI_FP32_REFINED ? std::min(6, o.max_refine) : 6;
+}
+constexpr int kCoarseIters = 512;        // at most, of one pass
+
 int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, const wwbi_opts &o,
-                  bool check_rough, SolveStats &st) {
+                  bool check_rough, SolveStats &out) {
     Coarse C;
     // a budget too small for the coarse solves is left to GMRES, which counts
     // steps of the whole system
@@ -743,8 +751,10 @@ int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, co
             have_x = true;
         }
     }
-    int status = kTwoGridPart;
-    for (int pass = 0; pass < 6; ++pass) {
+    int status = kTwoGridPart, left = o.max_iter;
+    SolveStats st{};
+    const size_t hist0 = hist.size();
+    for (int pass = 0; pass < two_grid_passes(o) && left > 0; ++pass) {
         SmallArgs a{};
         if (!take_tags(1024, a.tag)) break;
         a.A = cA;
@@ -762,7 +772,7 @@ int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, co
                     : std::min(0.1, 0.1 * o.tol * bn / prev);
         a.tol = std::max(a.tol, 5e-16);
         a.steps = 1024;
-        a.max_iter = 512;
+        a.max_iter = std::min(kCoarseIters, left);
         // one cycle without its true residual, which the whole system's
         // replaces; where the LDS holds only a short cycle, several with it
         a.verify = nc > kSmallMax ? 1 : 0;
@@ -783,8 +793,10 @@ int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, co
         launch_norms(r, bn < 0.0 ? b : nullptr, n, hstd, stream);
         if (hipStreamSynchronize(stream) != hipSuccess || hipGetLastError() != hipSuccess)
             return WWBI_EHIP;
-        if (hsmall->status == kSmallAborted || hsmall->aborted)
-            return had_x ? kTwoGridPart : kTwoGridNone;
+        if (hsmall->status == kSmallAborted || hsmall->aborted) {
+            status = had_x ? kTwoGridPart : kTwoGridNone;
+            break;
+        }
         double s2 = 0.0;
         for (int i = 0; i < 64; ++i) s2 += h[i];
         const double rn = std::sqrt(s2);
@@ -793,8 +805,9 @@ int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, co
             for (int i = 0; i < 64; ++i) t2 += h[64 + i];
             bn = std::sqrt(t2);
         }
-        if (!std::isfinite(rn)) return kTwoGridNone;
+        if (!std::isfinite(rn)) { status = kTwoGridNone; break; }
         st.iters += hsmall->its;
+        left -= hsmall->its;
         st.cycles += 1;
         if (o.precision == WWBI_FP32_REFINED) st.refine_steps += 1;
         else if (pass == 0) note_resid(1.0);
@@ -813,7 +826,9 @@ int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, co
         prev = rn;
         rr = r;
     }
-    return status;
+    if (status == WWBI_OK) out = st;
+    else hist.resize(hist0);
+    return status == kTwoGridPart && !have_x ? kTwoGridNone : status;
 }
 
 // The right-hand sides share the coarse matrix (one launch solves all their
@@ -857,7 +872,8 @@ int Ctx::two_grid_multi(const double *A64, long ld, double *K, size_t kcap, cons
     }
     int status = kTwoGridPart;
     double gain = 0.03 * o.tol, prev = HUGE_VAL;
-    for (int pass = 0; pass < 6; ++pass) {
+    int left = o.max_iter;
+    for (int pass = 0; pass < two_grid_passes(o) && left > 0; ++pass) {
         SmallArgs a{};
         if (!take_tags(1024, a.tag)) break;
         a.A = cA;
@@ -871,7 +887,7 @@ int Ctx::two_grid_multi(const double *A64, long ld, double *K, size_t kcap, cons
         a.xs = ldc;
         a.tol = std::max(gain, 5e-16);
         a.steps = 1024;
-        a.max_iter = 512;
+        a.max_iter = std::min(kCoarseIters, left);
         a.verify = nc > kSmallMax ? 1 : 0;
         a.max_cycles = a.verify ? 16 : 1;
         a.stall = kCycleStall;
@@ -906,6 +922,7 @@ int Ctx::two_grid_multi(const double *A64, long ld, double *K, size_t kcap, cons
             its = std::max(its, hsmall[s].its);
         }
         st.iters += its;
+        left -= its;
         st.cycles += 1;
         if (o.precision == WWBI_FP32_REFINED) {
             st.refine_steps += 1;

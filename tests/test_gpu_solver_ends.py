@@ -171,3 +171,24 @@ def test_systems_the_two_grid_iteration_hands_on(ww, ctx, M, depth, entry, prec)
         out.append(v)
     # two residuals of tol and condition numbers of up to 1e4
     assert rel(*out) <= 2e4 * tol
+
+
+@pytest.mark.parametrize("depth", [0.6, 0.4, 0.2])
+@pytest.mark.parametrize("prec", ["fp64", "refined"])
+def test_budgets_of_the_two_grid_iteration(ww, ctx, depth, prec):
+    """The coarse solves take 130 to 180 steps a pass here, the stored matrix
+    in FP64 51, 64 and 100 in all."""
+    geom = thin_cell(depth, 2.6, (2048, 1024, 1024))
+    print(f"case budgets layer {depth} {prec}", flush=True)
+    dg = ww.DeviceGeometry.from_synth(geom, DEV)
+    phi = torch.as_tensor(trig_potential(2048, [0.1, 0.05], [0.05, 0.02]), device=DEV)
+    done = (ww.OK, ww.WARN_UNDERRESOLVED)
+    kw = options(ww, prec, tol=1e-14, max_iter=200 if prec == "fp64" else 300)
+    r = ctx.solve_phi(dg, phi, **kw)[3]
+    assert r.status in done and r.rel_resid <= 1e-14 and r.iters <= kw["max_iter"]
+    rhs = torch.as_tensor(np.random.default_rng(3).standard_normal((2, geom.Mtot)), device=DEV)
+    rm = ctx.solve_phi_multi(dg, rhs, **dict(kw, max_iter=600))[1]
+    assert rm.iters <= 600
+    if prec == "refined":
+        r = ctx.solve_phi(dg, phi, **dict(kw, max_refine=3))[3]
+        assert r.status in done and r.rel_resid <= 1e-14 and r.refine_steps <= 3
