@@ -88,6 +88,8 @@ int Ctx::ws_plan(int n, int restart, WsItem *it, bool recycle) {
 
 int Ctx::ensure(int n, int restart) {
     trace = std::getenv("WWBI_TRACE") != nullptr;
+    const char *from = std::getenv("WWBI_GIVE_UP");
+    give_up_from = from ? std::atoi(from) : INT_MAX;
     WsItem it[kMaxWsItems];
     // a carved workspace (the allocation-free entry point) has no room for a
     // recycled space
@@ -590,6 +592,15 @@ bool Ctx::take_tags(long need, unsigned &first) {
 // decade of a system on which they gain less takes 5 to 7 steps of 20 us there.
 constexpr double kCutCycleStall = 0.1, kCycleStall = 0.99;
 
+int Ctx::launch_small(SmallArgs &a, int nsys) {
+    a.give_up = launches++ >= give_up_from;
+    for (int s = 0; s < nsys; ++s) {
+        hsmall[s].status = kSmallAborted;
+        hsmall[s].aborted = 0;
+    }
+    return launch_small_gmres(a, nsys, stream);
+}
+
 bool Ctx::queue_small(const Op &op, const double *b, double *x, bool x_zero, double tol,
                       int restart, int max_iter) {
     if (!ensure_small(1)) return false;
@@ -617,9 +628,7 @@ bool Ctx::queue_small(const Op &op, const double *b, double *x, bool x_zero, dou
     a.xch = xch + 8;
     a.abort_tag = reinterpret_cast<unsigned *>(xch);
     a.out = dsmall;
-    hsmall->status = kSmallAborted;
-    hsmall->aborted = 0;
-    small_rc = launch_small_gmres(a, 1, stream);
+    small_rc = launch_small(a, 1);
     return true;
 }
 
@@ -781,22 +790,17 @@ int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, co
         a.xch = xch + 8;
         a.abort_tag = reinterpret_cast<unsigned *>(xch);
         a.out = dsmall;
-        hsmall->status = kSmallAborted;
-        hsmall->aborted = 0;
-        if (launch_small_gmres(a, 1, stream) != WWBI_OK) return WWBI_EHIP;
+        if (launch_small(a, 1) != WWBI_OK) return WWBI_EHIP;
         launch_coarse_correct(N, C, hrow, mode, cmap, cfac, corr, ce, r0, n, op.flip, inv_d, rr, x,
                               have_x, part, stream);
-        const bool had_x = have_x;
         have_x = true;
         apply(op, x, nullptr, b, r, nullptr);
         // the sums go to the host's memory: no copy between them and the wait
         launch_norms(r, bn < 0.0 ? b : nullptr, n, hstd, stream);
         if (hipStreamSynchronize(stream) != hipSuccess || hipGetLastError() != hipSuccess)
             return WWBI_EHIP;
-        if (hsmall->status == kSmallAborted || hsmall->aborted) {
-            status = had_x ? kTwoGridPart : kTwoGridNone;
-            break;
-        }
+        // the correction is in x already, of a coarse solution that is none
+        if (hsmall->status == kSmallAborted || hsmall->aborted) { status = kTwoGridNone; break; }
         double s2 = 0.0;
         for (int i = 0; i < 64; ++i) s2 += h[i];
         const double rn = std::sqrt(s2);
@@ -828,7 +832,8 @@ int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, co
     }
     if (status == WWBI_OK) out = st;
     else hist.resize(hist0);
-    return status == kTwoGridPart && !have_x ? kTwoGridNone : status;
+    // an iterate worse than zero is none either
+    return status == kTwoGridPart && !(st.cycles > 0 && st.rel_resid < 1.0) ? kTwoGridNone : status;
 }
 
 // The right-hand sides share the coarse matrix (one launch solves all their
@@ -895,8 +900,7 @@ int Ctx::two_grid_multi(const double *A64, long ld, double *K, size_t kcap, cons
         a.xchs = small_exchange_words();
         a.abort_tag = reinterpret_cast<unsigned *>(xch);
         a.out = dsmall;
-        for (int s = 0; s < nr; ++s) { hsmall[s].status = kSmallAborted; hsmall[s].aborted = 0; }
-        if (launch_small_gmres(a, nr, stream) != WWBI_OK) return WWBI_EHIP;
+        if (launch_small(a, nr) != WWBI_OK) return WWBI_EHIP;
         // x (+)= 2 (r - S K e)
         launch_mfma_rect64(K, ldc, n, nc, ce, ldc, nr, m.d, ldv, m.part, stream, R, ldv, n0);
         if (R == B)
@@ -1143,6 +1147,7 @@ int Ctx::check_opts(const wwbi_opts *o) {
 void Ctx::begin_report(bool prof) {
     profiling = prof;
     handed_on = false;
+    launches = 0;
     nprof = 0;
     cyc_done.clear();
     hist.clear();

@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <climits>
 #include <cstddef>
 #include <vector>
 
@@ -126,6 +127,8 @@ struct Ctx {
     unsigned long long *xch = nullptr; size_t capxch = 0;
     SmallRes *hsmall = nullptr, *dsmall = nullptr;
     unsigned xtag = 1;
+    int launches = 0;           // of the call so far,
+    int give_up_from = INT_MAX; // and the first that gives up at once (WWBI_GIVE_UP: tests)
     bool small_cold = false;    // the queued one started from zero
     bool small_cut = false;     // and may stop short of what was asked for
     bool handed_on = false;     // it did: gmres() goes on with its own loop
@@ -243,6 +246,8 @@ struct Ctx {
                      int restart, int max_iter);
     bool small_result(SolveStats &st, int &status, bool &x_zero);
     int small_rc = 0;
+    // the launch, with its results marked as missing
+    int launch_small(SmallArgs &a, int nsys);
     // words and results for nsys one-launch solves; false when out of memory
     bool ensure_small(int nsys);
     int ensure_coarse(int n, int nsys = 1);
@@ -253,8 +258,9 @@ struct Ctx {
     bool choose_coarse(int k0, Coarse &C) const;
     // Two-grid iteration (kernels_coarse.hip) for the operator of `mode`, op
     // its on-the-fly FP64 form, from a zero start: kTwoGridNone when it does
-    // not apply (x untouched), kTwoGridPart when x holds an unconverged
-    // iterate, WWBI_OK when ||b - op x|| <= tol ||b||, or an error (< 0)
+    // not apply or was given up (x is of no use then), kTwoGridPart when x holds
+    // an unconverged iterate, WWBI_OK when ||b - op x|| <= tol ||b||, or an
+    // error (< 0)
     int two_grid(int mode, const Op &op, int k0, const double *b, double *x, const wwbi_opts &o,
                  bool check_rough, SolveStats &st);
     // The same for nr systems with A and stored matrices: A64 (row stride ld)

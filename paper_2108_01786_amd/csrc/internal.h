@@ -416,6 +416,7 @@ struct SmallArgs {
     long xchs;
     unsigned tag;          // first tag of this launch (each exchange takes the next)
     unsigned *abort_tag;   // tag of the last launch that gave up
+    int give_up;           // give up at once
     SmallRes *out;         // one per system
 };
 long small_exchange_words();

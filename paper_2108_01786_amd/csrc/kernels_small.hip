@@ -304,7 +304,7 @@ __global__ __launch_bounds__(kTS, 2) void k_small_gmres(SmallArgs a) {
     const double bnorm = slot_norm(0);
     tol_abs = a.tol * bnorm;
     double beta = bnorm, prev = HUGE_VAL;
-    bool aborted = false;
+    bool aborted = a.give_up != 0;
     // the residual of the solution in xe (through slot 0): re, its norm beta
     auto residual = [&]() __attribute__((always_inline)) {
         __syncthreads();
@@ -323,7 +323,7 @@ __global__ __launch_bounds__(kTS, 2) void k_small_gmres(SmallArgs a) {
         __syncthreads();
         beta = slot_norm(0);
     };
-    if (a.x0) {
+    if (a.x0 && !aborted) {
         const double *x0 = a.x0 + (long)sys * a.xs;
 #pragma unroll
         for (int e = 0; e < NE; ++e) {

@@ -192,3 +192,61 @@ def test_budgets_of_the_two_grid_iteration(ww, ctx, depth, prec):
     if prec == "refined":
         r = ctx.solve_phi(dg, phi, **dict(kw, max_refine=3))[3]
         assert r.status in done and r.rel_resid <= 1e-14 and r.refine_steps <= 3
+
+
+@pytest.fixture
+def giving_up():
+    """The one-launch solves of a call from its k-th on give up, as if other work
+    kept their blocks from running together."""
+    def set_from(k):
+        os.environ["WWBI_GIVE_UP"] = str(k)
+    yield set_from
+    os.environ.pop("WWBI_GIVE_UP", None)
+
+
+# a whole system in one launch, first and later passes of the two-grid
+# iteration, its rough right-hand sides (the transpose) and many at once
+@pytest.mark.parametrize("M,first", [((256, 128, 64), 0), ((1024, 512, 512), 0), ((1024, 512, 512), 1),
+                                     ((2048, 1024, 1024), 1)])
+@pytest.mark.parametrize("prec", ["fp64", "refined"])
+def test_a_launch_that_gives_up_leaves_nothing(ww, ctx, giving_up, M, first, prec):
+    """Then the stored matrix solves from the call's own start, to the bit as
+    where it is asked for."""
+    geom, M0 = thin_cell(0.9, 0.6, M), M[0]
+    phi = trig_potential(M0, [0.1, 0.05], [0.05, 0.02])
+    n = geom.Mtot
+    print(f"case giving up n={n} from {first} {prec}", flush=True)
+    dg = ww.DeviceGeometry.from_synth(geom, DEV)
+    p = torch.as_tensor(phi, device=DEV)
+    rng = np.random.default_rng(5)
+    w = torch.as_tensor(rng.uniform(0, 1, M0), device=DEV)
+    rhs = torch.as_tensor(rng.standard_normal((5, n)), device=DEV)
+    kw = options(ww, prec, tol=1e-14)
+    x0 = torch.as_tensor(rng.standard_normal(n), device=DEV)
+    _, before, _, _ = ctx.solve_phi(dg, p, **kw)
+
+    def calls(k, mode):
+        if k is not None:
+            giving_up(k)
+        m = dict(kw, matvec=mode)
+        U, om, _, r = ctx.solve_phi(dg, p, **m)
+        g, ra = ctx.adjoint_phi(dg, before, w, **m)
+        X, rm = ctx.solve_phi_multi(dg, rhs, **m)
+        xw, rx = ctx.solve_phi(dg, p, x0=x0, **m)[1::2]
+        gw, rw = ctx.solve_gamma(dg, p, **m)[1:]
+        os.environ.pop("WWBI_GIVE_UP", None)
+        for q in (r, ra, rm, rx, rw):
+            assert q.status in (ww.OK, ww.WARN_UNDERRESOLVED) and q.rel_resid <= 1e-14
+        return [((U, om), r), ((g["phi"], g["x"]), ra), ((X,), rm), ((xw,), rx), ((gw,), rw)]
+
+    plain = calls(None, ww.MATVEC_AUTO)
+    stored = calls(0, ww.MATVEC_STORED)
+    reached = 0
+    for (got, _), (a, r), (b, _) in zip(calls(first, ww.MATVEC_AUTO), plain, stored):
+        # a call of fewer launches than that does not notice
+        late = r.restarts <= first
+        reached += not late
+        for v, x in zip(got, a if late else b):
+            assert torch.equal(v, x)
+    assert reached >= 1
+    assert torch.equal(ctx.solve_phi(dg, p, **kw)[1], before)
