@@ -763,6 +763,8 @@ int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, co
     int status = kTwoGridPart, left = o.max_iter;
     SolveStats st{};
     const size_t hist0 = hist.size();
+    // the last iterate within the tolerance, while a further pass runs
+    double *kept = vec[VD], kept_resid = -1.0;
     for (int pass = 0; pass < two_grid_passes(o) && left > 0; ++pass) {
         SmallArgs a{};
         if (!take_tags(1024, a.tag)) break;
@@ -827,8 +829,19 @@ int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, co
         status = rn <= o.tol * bn ? WWBI_OK : kTwoGridPart;
         if (rn <= two_grid_target(o.tol) * bn && status == WWBI_OK) break;
         if (pass > 0 && !(rn < kTwoGridGain * prev)) break;
+        if (status == WWBI_OK) {
+            launch_copy(kept, x, n, stream);
+            kept_resid = st.rel_resid;
+        }
         prev = rn;
         rr = r;
+    }
+    if (status != WWBI_OK && status >= 0 && kept_resid >= 0.0) {
+        // the further pass lost it (the rounding of the residual, or given up)
+        launch_copy(x, kept, n, stream);
+        st.rel_resid = kept_resid;
+        if (!hist.empty() && hist.back() != kept_resid) hist.pop_back();
+        status = WWBI_OK;
     }
     if (status == WWBI_OK) out = st;
     else hist.resize(hist0);
@@ -877,6 +890,7 @@ int Ctx::two_grid_multi(const double *A64, long ld, double *K, size_t kcap, cons
     }
     int status = kTwoGridPart;
     double gain = 0.03 * o.tol, prev = HUGE_VAL;
+    double *kept = m.r, kept_resid = -1.0;     // as for one system
     int left = o.max_iter;
     for (int pass = 0; pass < two_grid_passes(o) && left > 0; ++pass) {
         SmallArgs a{};
@@ -914,17 +928,19 @@ int Ctx::two_grid_multi(const double *A64, long ld, double *K, size_t kcap, cons
             return WWBI_EHIP;
         double worst = 0.0;
         int its = 0;
+        bool lost = false;
         gain = 0.1;
         for (int s = 0; s < nr; ++s) {
-            if (hsmall[s].status == kSmallAborted || hsmall[s].aborted) return kTwoGridNone;
+            if (hsmall[s].status == kSmallAborted || hsmall[s].aborted) lost = true;
             double s2 = 0.0;
             for (int i = 0; i < G; ++i) s2 += h[s * 64 + i];
             rn[s] = std::sqrt(s2);
-            if (!std::isfinite(rn[s])) return kTwoGridNone;
+            if (!std::isfinite(rn[s])) lost = true;
             if (bn[s] > 0.0) worst = std::max(worst, rn[s] / bn[s]);
             if (rn[s] > 0.0) gain = std::min(gain, 0.1 * o.tol * bn[s] / rn[s]);
             its = std::max(its, hsmall[s].its);
         }
+        if (lost) { status = kTwoGridNone; break; }
         st.iters += its;
         left -= its;
         st.cycles += 1;
@@ -940,7 +956,17 @@ int Ctx::two_grid_multi(const double *A64, long ld, double *K, size_t kcap, cons
         status = worst <= o.tol ? WWBI_OK : kTwoGridPart;
         if (status == WWBI_OK && worst <= two_grid_target(o.tol)) break;
         if (pass > 0 && !(worst < kTwoGridGain * prev)) break;
+        if (status == WWBI_OK) {
+            launch_copy(kept, X, (int)(nr * ldv), stream);
+            kept_resid = worst;
+        }
         prev = worst;
+    }
+    if (status != WWBI_OK && kept_resid >= 0.0) {
+        launch_copy(X, kept, (int)(nr * ldv), stream);
+        st.rel_resid = kept_resid;
+        if (!hist.empty() && hist.back() != kept_resid) hist.pop_back();
+        status = WWBI_OK;
     }
     return status;
 }
