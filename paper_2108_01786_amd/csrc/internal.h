@@ -417,9 +417,12 @@ struct SmallArgs {
     unsigned tag;          // first tag of this launch (each exchange takes the next)
     unsigned *abort_tag;   // tag of the last launch that gave up
     int give_up;           // give up at once
+    long wait;             // clock ticks to wait in the first exchange
     SmallRes *out;         // one per system
 };
 long small_exchange_words();
+// blocks of a launch over the blocks resident at once, rounded up
+int small_rounds(int n, int nsys);
 // steps of a cycle that the LDS holds at n unknowns
 int small_cycle_steps(int n);
 // nsys systems with the same matrix; WWBI_OK when queued

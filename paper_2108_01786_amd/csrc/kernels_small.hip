@@ -20,11 +20,17 @@
 // writes after reading all of step s.  Tags are new for every launch (the
 // caller's counter), so nothing has to be cleared.
 //
-// A poll gives up after kSpinTicks of the constant-rate clock or when another
+// A poll gives up after a limit on the constant-rate clock or when another
 // block has given up; the result is then marked as aborted and the caller
 // solves by the multi-kernel loop.  That can only happen when the blocks of
 // one launch are kept from running together for that long, by other work
-// filling the device.
+// filling the device.  In the first exchange the limit is kStartTicks, longer
+// than most kernels that the blocks may have to wait for: those that wait hold a
+// CU each, and launches of 128 of them (2048 unknowns) on three streams could
+// each hold part of the device and wait for the rest (not seen in 48 solves on
+// four streams).  The first to give up would let the others run.  Once all blocks
+// have met they stay resident, and the later limit only ends a launch whose queue
+// was set aside.
 #include "entries.h"
 #include "internal.h"
 
@@ -36,7 +42,9 @@ constexpr int kTS = 512;                   // threads per block
 constexpr int kWS = kTS / 64;
 constexpr int kSmallSteps = 32;            // at most this many steps per cycle
 constexpr int kLdsBytes = 145 * 1024;      // for the basis (160 KB less the static part)
-constexpr long kSpinTicks = 20000000;      // 0.2 s at 100 MHz
+constexpr long kStartTicks = 2000000;      // 20 ms at 100 MHz
+constexpr long kSpinTicks = 20000000;      // 0.2 s
+constexpr int kResident = 256;             // blocks, one to a CU
 
 typedef unsigned long long u64;
 
@@ -117,7 +125,7 @@ __global__ __launch_bounds__(kTS, 2) void k_small_gmres(SmallArgs a) {
                      tg | (lane & 1 ? u >> 32 : u & 0xffffffffu));
         }
         meanwhile();
-        const long t0 = wall_clock64();
+        const long t0 = wall_clock64(), limit = tag == a.tag ? a.wait : kSpinTicks;
         int quit = 0;
         u64 lo[NE], hi[NE];
 #pragma unroll
@@ -137,7 +145,7 @@ __global__ __launch_bounds__(kTS, 2) void k_small_gmres(SmallArgs a) {
                 all = all && (unsigned)(lo[e] >> 32) == tag && (unsigned)(hi[e] >> 32) == tag;
             if (all) break;
             if ((spin & 63) == 0 &&
-                (wall_clock64() - t0 > kSpinTicks ||
+                (wall_clock64() - t0 > limit ||
                  __hip_atomic_load(a.abort_tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
                      a.tag)) {
                 quit = 1;
@@ -471,12 +479,27 @@ long small_exchange_words() { return 2L * 2 * kSmallCoarseMax; }
 
 int small_cycle_steps(int n) { return cycle_steps(columns(n)); }
 
+namespace {
+
+// A block's basis fills the LDS of its CU.  Where many systems would not
+// all be resident, more rows per wave run more of them at once (32 of 512
+// unknowns: 8 blocks each, one round of 256 blocks instead of four).
+bool many_rows(int n, int nsys) {
+    return nsys > 1 && columns(n) <= 10 && (long)nsys * cdiv(n, 2 * kWS) > kResident;
+}
+
+}  // namespace
+
+int small_rounds(int n, int nsys) {
+    const int rows = !many_rows(n, nsys) ? 2 : columns(n) == 10 ? 10 : 8;
+    return cdiv((long)nsys * cdiv(n, rows * kWS), kResident);
+}
+
 int launch_small_gmres(SmallArgs a, int nsys, hipStream_t st) {
     const int cpl = columns(a.n);
-    // A block's basis fills the LDS of its CU.  Where many systems would not
-    // all be resident, more rows per wave run more of them at once (32 of 512
-    // unknowns: 8 blocks each, one round of 256 blocks instead of four).
-    if (nsys > 1 && cpl <= 10 && (long)nsys * cdiv(a.n, 2 * kWS) > 256) {
+    // a system's blocks may wait for those of the systems before it
+    a.wait = kStartTicks * small_rounds(a.n, nsys);
+    if (many_rows(a.n, nsys)) {
         switch (cpl) {
         case 2: return launch_cpl<2, 8>(a, nsys, st);
         case 4: return launch_cpl<4, 8>(a, nsys, st);
