@@ -233,9 +233,10 @@ struct Ctx {
     void prof_begin();
     void prof_end();
     // kc > 0: deflate the kc recycled vectors in front of the basis (one
-    // cycle, no verification, x = the solution from zero)
+    // cycle, no verification, x = the solution from zero); twice: two
+    // Gram-Schmidt passes a step, which verify implies
     int gmres(const Op &op, const double *b, double *x, bool x_zero, double tol, int restart,
-              int max_iter, int poll, bool verify, SolveStats &st, int kc = 0);
+              int max_iter, int poll, bool verify, SolveStats &st, int kc = 0, bool twice = false);
     // whether a system of n unknowns is solved in one launch (in FP64, whichever
     // precision was asked for); not for profiled calls, which time the products.
     bool small_system(int n, const wwbi_opts &o);
