@@ -385,7 +385,7 @@ void Ctx::prof_end() {
 // memory: the host sees the end without a queued copy, and steps enqueued
 // after it return at once on the device flag.
 int Ctx::gmres(const Op &op, const double *b, double *x, bool x_zero, double tol, int restart,
-               int max_iter, int poll, bool verify, SolveStats &st, int kc, bool twice) {
+               int max_iter, int poll, bool verify, SolveStats &st, int kc) {
     const int n = op.n;
     if (verify && n <= kSmallMax && stored_fp64(op.kind) && !fixed_ws && !profiling && !handed_on) {
         int status;
@@ -408,12 +408,12 @@ int Ctx::gmres(const Op &op, const double *b, double *x, bool x_zero, double tol
     // by the kernel that forms the vector
     float *x32 = stored_fp32(op.kind) ? v32 : nullptr;
     // the inner solves of the refinement (the only callers without the
-    // true-residual check) orthogonalise once, at first; every other solve twice
-    const bool single_pass = !verify && !twice;
+    // true-residual check) orthogonalise once; every other solve twice
+    const bool single_pass = !verify;
     if (kc > 0) {
         // deflated solve: r0 = b - C C^T b starts the (only) cycle; the
         // tolerance is relative to ||b||
-        if (!single_pass || !x_zero || kc > vpre) return WWBI_EINVAL_OPTS;
+        if (verify || !x_zero || kc > vpre) return WWBI_EINVAL_OPTS;
         restart = std::min(restart, WWBI_MAX_RESTART - kc);
         launch_recycle_dots(Cb, ldv, b, n, kc, P1, P3, G, stream);
         launch_set_tol(P3, G, tol, gs, stream);
@@ -1054,25 +1054,14 @@ double Ctx::device_norm(const double *v, int n) {
 // (C orthonormal, A32 U = C; up to kRecycleMax vectors) and every later inner
 // solve deflates it: the residuals of the later steps are dominated by the
 // same slowly converging directions, which the first solve has already found.
-//
-// One Gram-Schmidt pass is enough for most: its loss of orthogonality is about
-// 1e-16 over the square of what the inner solve gains, times how much of the
-// first product it cancels.  With the sign of the surface rows A is half the
-// identity and smooth kernels, and of a rough right-hand side (the weights of
-// an adjoint) it cancels nearly all: on hard cells an inner solve then ends
-// "converged" with nothing gained (adjoint of 1536 unknowns in a layer of 0.2:
-// 7e-8 where the tolerance is 1e-14).  The step is taken back if it lost, and the
-// solves after it orthogonalise twice (1.3 times the time of a step).
 int Ctx::refine(const Op &op32, const Op &op64, const double *b, double *x, bool x_zero,
                 const wwbi_opts &o, SolveStats &st) {
     const int n = op64.n;
     const int G = gmres_nblocks(n);
     const long ldv = round_up(n, 64);
     double *r = vec[VRR], *d = vec[VD];
-    bool recycle = !(o.flags & WWBI_FLAG_NO_RECYCLE) && vpre > 0 && op32.n == n &&
-                   stored_fp32(op32.kind);
-    bool twice = false;        // inner solves orthogonalise twice
-    bool x_is_d = false;       // x holds the first inner solve's result alone
+    const bool recycle = !(o.flags & WWBI_FLAG_NO_RECYCLE) && vpre > 0 && op32.n == n &&
+                         stored_fp32(op32.kind);
     int kc = 0;                // recycled vectors the later inner solves deflate
     bool first_inner = true;   // the pending inner solve is the first one
     double *Pn = norm_partials() + 64;   // norm partials (64 doubles)
@@ -1134,20 +1123,8 @@ int Ctx::refine(const Op &op32, const Op &op64, const double *b, double *x, bool
                              st.iters, st.rel_resid);
             if (rn <= o.tol * bn) { status = WWBI_OK; break; }
             if (!std::isfinite(rn) || (k > 0 && rn > 0.5 * prev)) {
-                if (twice || !std::isfinite(rn)) {
-                    status = WWBI_REFINE_STALLED;
-                    break;
-                }
-                twice = true;
-                recycle = false;
-                kc = 0;
-                if (rn > prev) {
-                    // without the step that lost
-                    if (x_is_d) launch_fill(x, 0.0, n, stream);
-                    else launch_axpy(x, d, n, -1.0, stream);
-                    apply(op64, x, nullptr, b, r, nullptr);
-                    rn = prev;
-                }
+                status = WWBI_REFINE_STALLED;
+                break;
             }
         }
         if (k >= o.max_refine || st.iters >= o.max_iter) { status = WWBI_NOT_CONVERGED; break; }
@@ -1156,9 +1133,8 @@ int Ctx::refine(const Op &op32, const Op &op64, const double *b, double *x, bool
         // for the cold step rn = ||b||, where the inner tolerance does not depend on ||b||
         const double itol = cold ? inner_tolerance(o, 1.0, 1.0) : inner_tolerance(o, bn, rn);
         const int rc = gmres(op32, cold ? b : r, cold ? x : d, true, itol, o.restart,
-                             o.max_iter - st.iters, o.poll_every, false, in, kc, twice);
+                             o.max_iter - st.iters, o.poll_every, false, in, kc);
         if (rc < 0) return rc;
-        x_is_d = cold;
         inner_pending = true;
         st.cycles += in.cycles;
         st.refine_steps += 1;

@@ -233,10 +233,9 @@ struct Ctx {
     void prof_begin();
     void prof_end();
     // kc > 0: deflate the kc recycled vectors in front of the basis (one
-    // cycle, no verification, x = the solution from zero); twice: two
-    // Gram-Schmidt passes a step, which verify implies
+    // cycle, no verification, x = the solution from zero)
     int gmres(const Op &op, const double *b, double *x, bool x_zero, double tol, int restart,
-              int max_iter, int poll, bool verify, SolveStats &st, int kc = 0, bool twice = false);
+              int max_iter, int poll, bool verify, SolveStats &st, int kc = 0);
     // whether a system of n unknowns is solved in one launch (in FP64, whichever
     // precision was asked for); not for profiled calls, which time the products.
     bool small_system(int n, const wwbi_opts &o);
