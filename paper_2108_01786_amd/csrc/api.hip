@@ -410,6 +410,7 @@ int Ctx::gmres(const Op &op, const double *b, double *x, bool x_zero, double tol
     // the inner solves of the refinement (the only callers without the
     // true-residual check) orthogonalise once; every other solve twice
     const bool single_pass = !verify;
+    const double shift = single_pass ? identity_part(op.kind) : 0.0;
     if (kc > 0) {
         // deflated solve: r0 = b - C C^T b starts the (only) cycle; the
         // tolerance is relative to ||b||
@@ -483,7 +484,7 @@ int Ctx::gmres(const Op &op, const double *b, double *x, bool x_zero, double tol
                 prof_begin();
                 if (fuse32)
                     launch_gemv32_dots((const float *)A, op.ld, n, x32, w, op.flip, &gs->active,
-                                       Cb, ldv, kc + j, pw, pw + 64L * NB, stream);
+                                       Cb, ldv, kc + j, pw, pw + 64L * NB, stream, shift);
                 else if (fuse64)
                     launch_gemv64_dots((const double *)A, op.ld, n, vj, w, op.flip, &gs->active,
                                        Vb, ldv, j, pw, pw + 64L * NB, stream);
@@ -495,7 +496,7 @@ int Ctx::gmres(const Op &op, const double *b, double *x, bool x_zero, double tol
                     launch_reduce_rows(pw, NB, pw + 64L * NB, kc + j + 2, hsum, gs, stream);
                     launch_cgs_final(Cb, ldv, w, n, j, pw, pw + 64L * NB, G, x32, H, restart + 1,
                                      false, cs, sn, gv, jmax, gs, cid, dmir, stream, kSingle, NB,
-                                     kc, Bm, kRecycleMax, hsum);
+                                     kc, Bm, kRecycleMax, hsum, shift);
                     continue;
                 }
                 if (fuse64) {
@@ -506,11 +507,12 @@ int Ctx::gmres(const Op &op, const double *b, double *x, bool x_zero, double tol
                                      sn, gv, jmax, gs, cid, dmir, stream);
                     continue;
                 }
-                launch_cgs_dot(Cb, ldv, w, n, kc + j, P1, P3, G, gs, stream);
+                launch_cgs_dot(Cb, ldv, w, n, kc + j, P1, P3, G, gs, stream, kSingle, nullptr, 0,
+                               0, 0, shift);
                 if (single_pass) {
                     launch_cgs_final(Cb, ldv, w, n, j, P1, P3, G, x32, H, restart + 1, false, cs,
                                      sn, gv, jmax, gs, cid, dmir, stream, kSingle, 0, kc, Bm,
-                                     kRecycleMax);
+                                     kRecycleMax, nullptr, shift);
                 } else {
                     launch_cgs_first(Vb, ldv, w, n, j, P1, P2, P3, G, H, restart + 1, gs, stream);
                     launch_cgs_final(Vb, ldv, w, n, j, P2, P3, G, x32, H, restart + 1, true, cs,
@@ -1304,6 +1306,7 @@ int Ctx::gmres_multi(int kind, int n, long ld, const double *B, double *X, int n
                  (long)restart + 2};
     double *P1 = m.P, *P2 = m.P + 64 * ldp, *P3 = m.P + 2 * 64 * ldp;
     float *x32 = kind == OP_A_S32 ? m.v32 : nullptr;
+    const double shift = x32 ? identity_part(kind) : 0.0;
     launch_fill(X, 0.0, (int)(nr * ldv), stream);
     launch_norm_partial(B, n, P3, G, stream, bt);
     launch_set_tol(P3, G, tol, m.gs, stream, bt);
@@ -1357,11 +1360,12 @@ int Ctx::gmres_multi(int kind, int n, long ld, const double *B, double *X, int n
                                               stream);
                 prof_end();
                 launch_cgs_dot(m.V, ldv, m.w, n, j, P1, P3, G, m.gs, stream, bt, m.part, ks, nr,
-                               L.off[1]);
+                               L.off[1], shift);
                 if (x32) {
                     // FP32 inner solves: one Gram-Schmidt pass, as for one system
                     launch_cgs_final(m.V, ldv, m.w, n, j, P1, P3, G, x32, m.H, ldp, false, m.cs,
-                                     m.sn, m.g, jmax, m.gs, 0, nullptr, stream, bt);
+                                     m.sn, m.g, jmax, m.gs, 0, nullptr, stream, bt, 0, 0,
+                                     nullptr, 0, nullptr, shift);
                 } else {
                     launch_cgs_first(m.V, ldv, m.w, n, j, P1, P2, P3, G, m.H, ldp, m.gs, stream,
                                      bt);

@@ -39,6 +39,13 @@ inline bool stored_fp32(int kind) {
     return kind == OP_A_S32 || kind == OP_GT_S32 || kind == OP_W_S32;
 }
 
+// The multiple of the identity in S times the operator (S: Op::flip).
+inline double identity_part(int kind) {
+    const bool half = kind == OP_W_S64 || kind == OP_W_O64 || kind == OP_W_S32 || kind == OP_GT_S64 ||
+                      kind == OP_GT_O64 || kind == OP_GT_S32;
+    return half ? -0.5 : 0.5;
+}
+
 struct Op {
     int kind;
     int n;          // operator size

@@ -327,9 +327,10 @@ int gemv_partials(int n);
 // y = S A x (FP32 matrix and x, FP64 accumulation) fused with the first
 // Gram-Schmidt dots: P[i * gemv_partials(n) + b] (i <= j < 64) and the squared
 // norm partials P3[b] of y, per block b, summed later in a fixed order.
+// shift: y = S A x - shift x instead (x = V_j)
 void launch_gemv32_dots(const float *A, long ld, int n, const float *x, double *y,
                         int flip, const int *active, const double *V, long ldv, int j, double *P,
-                        double *P3, hipStream_t st);
+                        double *P3, hipStream_t st, double shift);
 // the same for an FP64 matrix
 void launch_gemv64_dots(const double *A, long ld, int n, const double *x, double *y,
                         int flip, const int *active, const double *V, long ldv, int j, double *P,
@@ -511,10 +512,12 @@ void launch_cycle_start(const double *r, int n, const double *P, int G, double *
                         const Bat &bt = kSingle);
 // partial dots of w with V_0..V_j into P, partial |w|^2 into P3
 // With part (ks slices of nr systems, as launch_mfma_parts* leave them), w is
-// first written as their sum in slice order.
+// first written as their sum in slice order; with a shift, w - shift V_j takes
+// w's place.
 void launch_cgs_dot(const double *V, long ldv, double *w, int n, int j, double *P,
                     double *P3, int G, const GState *gs, hipStream_t st, const Bat &bt = kSingle,
-                    const double *part = nullptr, int ks = 0, int nr = 0, int flip = 0);
+                    const double *part = nullptr, int ks = 0, int nr = 0, int flip = 0,
+                    double shift = 0.0);
 // first Gram-Schmidt pass (w -= V h; dots of V with w into P2, |w|^2 into P3)
 // GP: the number of partials in P1 (0: G, the chunk count)
 // hred (may be null): the coefficients already summed (launch_reduce_rows)
@@ -531,12 +534,13 @@ void launch_reduce_rows(const double *P, int GP, const double *Px, int nrows, do
 // GP: the number of partials in P2 and P3 (0: G, the chunk count)
 // kc > 0: V points at kc recycled vectors in front of the Arnoldi basis, whose
 // coefficients go to column j of B (ld ldb)
+// shift: what was taken from the diagonal of the operator (launch_cgs_dot)
 void launch_cgs_final(const double *V, long ldv, const double *w, int n, int j,
                       const double *P2, const double *P3, int G, float *v32, double *H, int ldh,
                       bool add, double *cs, double *sn, double *g, int restart_len, GState *gs,
                       int cyc, GState *mirror, hipStream_t st, const Bat &bt = kSingle,
                       int GP = 0, int kc = 0, double *B = nullptr, int ldb = 0,
-                      const double *hred = nullptr);
+                      const double *hred = nullptr, double shift = 0.0);
 // Recycling of an inner solve's Krylov space (k steps, basis V, rotated
 // Hessenberg H, rotations cs/sn): C (k rows, orthonormal) and U with A U = C
 void launch_recycle_build(const double *V, long ldv, int n, int k, const double *H, int ldh,

@@ -57,6 +57,7 @@ struct GemvDots {
     long ldv;
     int j;              // last basis vector (j < 64)
     double *P, *P3;
+    double shift;
 };
 
 // y = c - S A x (or S A x), S negating rows [0, flip): each wave owns R rows and walks them in steps of
@@ -137,10 +138,12 @@ __global__ __launch_bounds__(64 * WPB) void k_gemv(const TA *__restrict__ A, lon
         if (!DOTS) {
             if (lane == 0 && r0 + r < n) y[r0 + r] = c ? c[r0 + r] - v : v;
         } else if (r0 + r < n) {
-            // the fused step is an Arnoldi product: y = A x (no c)
-            if (lane == 0) y[r0 + r] = v;
-            pd += vr[r] * v;
-            nn += v * v;
+            // the fused step is an Arnoldi product: y = A x - shift x (no c),
+            // x = V_j, whose row lane j holds
+            const double u = v - d.shift * __shfl(vr[r], d.j, 64);
+            if (lane == 0) y[r0 + r] = u;
+            pd += vr[r] * u;
+            nn += u * u;
         }
     }
     if (DOTS) {
@@ -185,10 +188,10 @@ int gemv_partials(int n) { return cdiv(cdiv(n, kGemvR), kDotsWaves); }
 
 void launch_gemv32_dots(const float *A, long ld, int n, const float *x, double *y,
                         int flip, const int *active, const double *V, long ldv, int j, double *P,
-                        double *P3, hipStream_t st) {
+                        double *P3, hipStream_t st, double shift) {
     hipLaunchKernelGGL((k_gemv<float, float, double, kGemvR, kGemvU, true, kDotsWaves>),
                        dim3(gemv_partials(n)), dim3(64 * kDotsWaves), 0, st, A, ld, n, x, nullptr,
-                       y, flip, active, GemvDots{V, ldv, j, P, P3});
+                       y, flip, active, GemvDots{V, ldv, j, P, P3, shift});
 }
 
 void launch_gemv64_dots(const double *A, long ld, int n, const double *x, double *y,
@@ -196,7 +199,7 @@ void launch_gemv64_dots(const double *A, long ld, int n, const double *x, double
                         double *P3, hipStream_t st) {
     hipLaunchKernelGGL((k_gemv<double, double, double, kGemvR, kGemvU, true, kDotsWaves>),
                        dim3(gemv_partials(n)), dim3(64 * kDotsWaves), 0, st, A, ld, n, x,
-                       nullptr, y, flip, active, GemvDots{V, ldv, j, P, P3});
+                       nullptr, y, flip, active, GemvDots{V, ldv, j, P, P3, 0.0});
 }
 
 void launch_gemv32(const float *A, long ld, int n, const float *x, const double *c, double *y,

@@ -259,7 +259,7 @@ __global__ __launch_bounds__(kT) void k_reduce_rows(const double *P, int GP, con
 __global__ __launch_bounds__(kT) void k_cgs_dot(const double *V, long ldv, double *w, int n,
                                                 int j, double *P, double *P3, int G,
                                                 const GState *gs, Bat bt, const double *part,
-                                                int ks, int nr, int flip) {
+                                                int ks, int nr, int flip, double shift) {
     const int s = sys();
     gs += s;
     if (gs->active == 0) return;
@@ -271,13 +271,20 @@ __global__ __launch_bounds__(kT) void k_cgs_dot(const double *V, long ldv, doubl
     int c0, c1;
     chunk_of(n, G, blockIdx.x, c0, c1);
     double nn = 0.0;
-    if (part) {
+    if (part || shift != 0.0) {
         // w = the product's slices summed in order, on this block's chunk
-        // (negated in rows [0, flip))
+        // (negated in rows [0, flip)), less the shift
+        const double *vj = V + (long)j * ldv;
         for (int m = c0 + threadIdx.x; m < c1; m += kT) {
             double a = 0.0;
-            for (int k = 0; k < ks; ++k) a += part[((long)k * nr + s) * n + m];
-            w[m] = m < flip ? -a : a;
+            if (part) {
+                for (int k = 0; k < ks; ++k) a += part[((long)k * nr + s) * n + m];
+                a = m < flip ? -a : a;
+            } else {
+                a = w[m];
+            }
+            if (shift != 0.0) a -= shift * vj[m];
+            w[m] = a;
             nn += a * a;
         }
         __syncthreads();    // the chunk's w, written by this block, read below
@@ -336,6 +343,12 @@ __global__ __launch_bounds__(kT) void k_cgs_first(const double *V, long ldv, dou
 // rounding level, so the difference loses nothing; as the only pass (add = 0)
 // the difference is exact to about eps (||w|| / ||w''||)^2, ample for the
 // inner solves of the refinement, whose outer FP64 residual corrects them.
+// The operators are a multiple `shift` of the identity and smooth kernels,
+// and the one pass would cancel that part of A v_j: its rounding, over the little
+// that is left of w, costs the basis its orthogonality (2 to 6 digits a solve; of
+// rough data all of it, and the solve ends with nothing gained).  So w comes
+// without it (w = A v_j - shift v_j spans the same space) and the column takes
+// it back: V^T V - I stays within 1e-12 where it was 1e-2.
 //
 // Blocks 0..G-1 form V_{j+1} on their chunks.  Block G, beside them, adds h
 // to (add = 1) or stores it into (add = 0) column j of H, applies the
@@ -355,7 +368,7 @@ __global__ __launch_bounds__(kT) void k_cgs_final(const double *V_, long ldv, co
                                                   double *sn, double *g, int restart_len,
                                                   GState *gs, int cyc, GState *mirror,
                                                   Bat bt, int kc, double *B, int ldb,
-                                                  const double *hred) {
+                                                  const double *hred, double shift) {
     gs += sys();
     if (!step_runs(gs, j)) return;
     P2 += sys() * bt.p;
@@ -398,7 +411,8 @@ __global__ __launch_bounds__(kT) void k_cgs_final(const double *V_, long ldv, co
     g += sys() * bt.rot;
     __shared__ double col[WWBI_MAX_RESTART + 2], lc[WWBI_MAX_RESTART], ls[WWBI_MAX_RESTART];
     double *hc = H + (long)j * ldh;
-    for (int i = threadIdx.x; i <= j; i += kT) col[i] = (add ? hc[i] : 0.0) + h[kc + i];
+    for (int i = threadIdx.x; i <= j; i += kT)
+        col[i] = (add ? hc[i] : 0.0) + h[kc + i] + (i == j ? shift : 0.0);
     for (int i = threadIdx.x; i < j; i += kT) { lc[i] = cs[i]; ls[i] = sn[i]; }
     if (kc > 0) {
         double *bc = B + (long)j * ldb;
@@ -676,9 +690,9 @@ void launch_cycle_start(const double *r, int n, const double *P, int G, double *
 }
 void launch_cgs_dot(const double *V, long ldv, double *w, int n, int j, double *P,
                     double *P3, int G, const GState *gs, hipStream_t st, const Bat &bt,
-                    const double *part, int ks, int nr, int flip) {
+                    const double *part, int ks, int nr, int flip, double shift) {
     hipLaunchKernelGGL(k_cgs_dot, dim3(G, bt.nsys), dim3(kT), 0, st, V, ldv, w, n, j, P, P3, G,
-                       gs, bt, part, ks, nr, flip);
+                       gs, bt, part, ks, nr, flip, shift);
 }
 void launch_cgs_first(const double *V, long ldv, double *w, int n, int j, const double *P1,
                       double *P2, double *P3, int G, double *H, int ldh, const GState *gs,
@@ -694,12 +708,12 @@ void launch_cgs_final(const double *V, long ldv, const double *w, int n, int j,
                       const double *P2, const double *P3, int G, float *v32, double *H, int ldh,
                       bool add, double *cs, double *sn, double *g, int restart_len, GState *gs,
                       int cyc, GState *mirror, hipStream_t st, const Bat &bt, int GP, int kc,
-                      double *B, int ldb, const double *hred) {
+                      double *B, int ldb, const double *hred, double shift) {
     // G vector blocks and one Hessenberg block
     hipLaunchKernelGGL(k_cgs_final, dim3(G + 1, bt.nsys), dim3(kT), 0, st, V, ldv, w, n, j, P2,
                        P3, G,
                        GP > 0 ? GP : G, v32, H, ldh, add ? 1 : 0, cs, sn, g, restart_len, gs,
-                       cyc, mirror, bt, kc, B, ldb, hred);
+                       cyc, mirror, bt, kc, B, ldb, hred, shift);
 }
 void launch_recycle_build(const double *V, long ldv, int n, int k, const double *H, int ldh,
                           const double *cs, const double *sn, double *C, double *U,

@@ -173,6 +173,25 @@ def test_systems_the_two_grid_iteration_hands_on(ww, ctx, M, depth, entry, prec)
     assert rel(*out) <= 2e4 * tol
 
 
+# rough data (an adjoint's weights) on hard cells: the stored matrix alone
+@pytest.mark.parametrize("M,depth", [((768, 384, 384), 0.2), ((1280, 768, 512), 0.4),
+                                     ((2048, 1024, 1024), 0.4), ((4096, 2048, 2048), 0.2)])
+@pytest.mark.parametrize("mode", ["stored", "auto"])
+def test_refined_adjoints_of_hard_cells(ww, ctx, M, depth, mode):
+    geom = thin_cell(depth, 2.6, M)
+    print(f"case adjoint layer {depth} n={geom.Mtot} {mode}", flush=True)
+    dg = ww.DeviceGeometry.from_synth(geom, DEV)
+    phi = torch.as_tensor(trig_potential(M[0], [0.1, 0.05], [0.05, 0.02]), device=DEV)
+    om = ctx.solve_phi(dg, phi, **options(ww, "fp64", tol=1e-13))[1]
+    w = torch.as_tensor(np.random.default_rng(0).uniform(0, 1, M[0]), device=DEV)
+    m = ww.MATVEC_STORED if mode == "stored" else ww.MATVEC_AUTO
+    g, r = ctx.adjoint_phi(dg, om, w, **options(ww, "refined", tol=1e-14, matvec=m))
+    ref, _ = ctx.adjoint_phi(dg, om, w, **options(ww, "fp64", tol=1e-14, matvec=ww.MATVEC_STORED))
+    assert r.status == ww.OK and r.rel_resid <= 1e-14
+    assert r.history()[-1] == r.rel_resid
+    assert rel(g["phi"], ref["phi"]) <= 1e4 * 2e-14
+
+
 @pytest.mark.parametrize("depth", [0.6, 0.4, 0.2])
 @pytest.mark.parametrize("prec", ["fp64", "refined"])
 def test_budgets_of_the_two_grid_iteration(ww, ctx, depth, prec):
