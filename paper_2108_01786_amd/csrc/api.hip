@@ -988,13 +988,7 @@ int Ctx::solve_system(int mode, Op op, int k0, const int (&kinds)[4], const doub
     if (o.matvec == WWBI_MATVEC_AUTO && x_zero && have_strips && !small) {
         const int s = two_grid(mode, op64, k0, b, x, o, check_rough, st);
         if (s == WWBI_OK || s < 0) return s;
-        // GMRES goes on from the iterate.  A refinement starts anew: what the
-        // passes leave is rough, which the identity part alone takes to itself, so
-        // that one Gram-Schmidt pass of an inner solve cancels nearly all of A r
-        // and its basis loses orthogonality (2560 unknowns in a layer of 0.4: the
-        // first inner solve ended "converged" with the residual grown from 2.1e-7 to
-        // 2.7e-7).  From zero it takes no more steps than from such an iterate.
-        if (s == kTwoGridPart) x_zero = fp32;
+        if (s == kTwoGridPart) x_zero = false;
     }
     if (stored && !assembled) {
         const int rc = assemble(fp32);
