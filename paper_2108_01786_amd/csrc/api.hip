@@ -714,12 +714,12 @@ constexpr double kTwoGridMargin = 0.2;
 double two_grid_target(double tol) {
     return std::max(kTwoGridMargin * tol, std::min(2.0 * kTwoGridMargin * tol, 4e-15));
 }
-// A pass that leaves more than this ends the iteration.  On the coarsest grids
+// A pass that gains less (decades) ends the iteration.  On the coarsest grids
 // one may gain a digit only, where it turns what no coarse node sees into the
 // smooth error that the next removes: at M = 40960 on 1664 nodes 1.3e-12,
 // 1.6e-13, then rounding; a further pass is 0.4 ms, the stored solve that takes
 // over 6.6.
-constexpr double kTwoGridGain = 0.3;
+constexpr double kTwoGridGain = 0.5;
 
 // Passes of one call: within the budgets of refinement steps and, by the steps
 // of the coarse solves, of Arnoldi steps.  A system handed on has both whole
@@ -728,6 +728,53 @@ int two_grid_passes(const wwbi_opts &o) {
     return o.precision == WWBI_FP32_REFINED ? std::min(6, o.max_refine) : 6;
 }
 constexpr int kCoarseIters = 512;        // at most, of one pass
+
+// Whether the iteration pays.  Its passes cost coarse steps, the stored matrix
+// steps of its own; us of either, fitted to timed solves of 2048 to 16384
+// unknowns and of 16 systems of 2048 to 8192.
+double stored_step_us(int n, bool fp32, int nr) {
+    const double bytes = (double)n * n * (fp32 ? 4 : 8);
+    if (nr > 1) return 45.0 + bytes / 4.6e6;
+    return fp32 ? 12.0 + bytes / 4.7e6 : 25.0 + bytes / 5.2e6;
+}
+double coarse_step_us(int nc, int nr) {
+    return (nc > kSmallMax ? 9.0 : 5.0) * small_rounds(nc, nr);
+}
+// A cell that takes the matrix few steps (2 a decade) converges in a pass or two,
+// for which this is never close.  On a hard one (a long ellipse in a thin layer,
+// 4 to 7 a decade) a short coarse cycle gains a fraction of a decade, and passes
+// that went on as long as they gained anything took 1.6 times what the matrix
+// takes (4096 unknowns in a layer of 0.4, refined: 4969 us, now 2330), for 16
+// systems, whose coarse solves run in up to eight rounds, six times (40.4 ms, now
+// 5.0).
+constexpr double kStepsPerDecade = 4.5;
+// The least part of the residual a cycle of a coarse solve may leave: the matrix
+// gains as much in the same time.
+double coarse_stall(int nc, int nr, double step_us) {
+    const double cycle_us = small_cycle_steps(nc) * coarse_step_us(nc, nr);
+    return std::min(kCycleStall, std::pow(10.0, -cycle_us / (kStepsPerDecade * step_us)));
+}
+// Decades that a coarse solve took.
+double decades(const SmallRes &r) {
+    return r.resid > 0.0 ? std::max(0.1, std::log10(r.bnorm / r.resid)) : 16.0;
+}
+// After a pass that gained `gain` decades, its coarse solve `took` of them in
+// coarse_us, and base_us the rest of it: whether the passes to gain `left` more
+// cost less than `lenient` times the matrix, assembled and for `anew` decades.
+// Of 432 calls on easy and hard cells of 1100 to 8192 unknowns 1.5 times made 9
+// slower than the matrix alone by more than 2%, 1 time 7 and 2.5 times 17, and the
+// whole least.
+bool pass_pays(double gain, double left, double took, double coarse_us, double base_us, double anew,
+               int n, double step_us, double lenient) {
+    const double pass_us = base_us + coarse_us * std::min(1.0, (left + 1.0) / took);
+    const double matrix_us = 100.0 + 8.0 * n * n / 4e6 + kStepsPerDecade * anew * step_us;
+    return gain > kTwoGridGain && std::ceil(left / gain) * pass_us <= lenient * matrix_us;
+}
+// What a later pass gains at most, of what the first one's coarse solve took
+// (measured 0.45 to 0.55 where that is one cycle, 0.6 to 1 where it is several):
+// the first pass of a smooth right-hand side itself gains more than any other,
+// and of a rough one less.
+double later_gain(double took, int nc) { return (nc > kSmallMax ? 0.7 : 0.5) * took; }
 
 int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, const wwbi_opts &o,
                   bool check_rough, SolveStats &out) {
@@ -744,6 +791,8 @@ int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, co
     const double *h = (const double *)hst;
     launch_coarse_map(C, cmap, cfac, stream);
     launch_assemble_coarse(N, hrow, mode, cmap, cfac, nc, corr, cA, ldc, stream);
+    const bool refined = o.precision == WWBI_FP32_REFINED;
+    const double step_us = stored_step_us(n, refined, 1);
     double bn = -1.0, prev = HUGE_VAL;
     const double *rr = b;
     bool have_x = false;
@@ -790,7 +839,7 @@ int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, co
         // replaces; where the LDS holds only a short cycle, several with it
         a.verify = nc > kSmallMax ? 1 : 0;
         a.max_cycles = a.verify ? 16 : 1;
-        a.stall = kCycleStall;
+        a.stall = coarse_stall(nc, 1, step_us);
         a.xch = xch + 8;
         a.abort_tag = reinterpret_cast<unsigned *>(xch);
         a.out = dsmall;
@@ -817,7 +866,7 @@ int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, co
         st.iters += hsmall->its;
         left -= hsmall->its;
         st.cycles += 1;
-        if (o.precision == WWBI_FP32_REFINED) st.refine_steps += 1;
+        if (refined) st.refine_steps += 1;
         else if (pass == 0) note_resid(1.0);
         st.rel_resid = bn > 0 ? rn / bn : 0.0;
         note_resid(st.rel_resid);
@@ -830,10 +879,19 @@ int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, co
         // rough right-hand side)
         status = rn <= o.tol * bn ? WWBI_OK : kTwoGridPart;
         if (rn <= two_grid_target(o.tol) * bn && status == WWBI_OK) break;
-        if (pass > 0 && !(rn < kTwoGridGain * prev)) break;
+        const bool rough = pass == 0 && rr != b;
+        double gain = rough ? 8.0 : std::log10((pass == 0 ? bn : prev) / rn);
         if (status == WWBI_OK) {
+            if (pass > 0 && !(gain > kTwoGridGain)) break;
             launch_copy(kept, x, n, stream);
             kept_resid = st.rel_resid;
+        } else {
+            const double took = decades(*hsmall), left = std::log10(st.rel_resid / o.tol);
+            if (pass == 0) gain = std::min(gain, later_gain(took, nc));
+            // (the walls' systems take fewer steps a decade)
+            if (!pass_pays(gain, left, took, hsmall->its * coarse_step_us(nc, 1), 60.0 + 1.5e-7 * n * n,
+                           left, n, step_us, mode == kCoarseWall ? 1.0 : 1.5))
+                break;
         }
         prev = rn;
         rr = r;
@@ -862,6 +920,11 @@ int Ctx::two_grid_multi(const double *A64, long ld, double *K, size_t kcap, cons
     if ((size_t)n * ldc > kcap || ensure_coarse(n, nr) ||
         grow(mw.part, mw.cpart, (size_t)multi_part_size_rect64(n, nc, nr) + 64))
         return kTwoGridNone;
+    // two passes of a few dozen coarse steps against as many of the matrix
+    const double step_us = stored_step_us(n, o.precision == WWBI_FP32_REFINED, nr);
+    const double base_us = 100.0 + ((double)n * n + (double)n * nc) * 8.0 / 4.6e6;
+    const int likely = nc > kSmallMax ? 30 : std::min(24, small_cycle_steps(nc));
+    if (2.0 * (base_us + likely * coarse_step_us(nc, nr)) > 28.0 * step_us) return kTwoGridNone;
     const int G = gmres_nblocks(n);
     MultiWS &m = mw;
     const Bat bt{nr, 0, 0, ldv, 64, 0, 0};
@@ -911,7 +974,7 @@ int Ctx::two_grid_multi(const double *A64, long ld, double *K, size_t kcap, cons
         a.max_iter = std::min(kCoarseIters, left);
         a.verify = nc > kSmallMax ? 1 : 0;
         a.max_cycles = a.verify ? 16 : 1;
-        a.stall = kCycleStall;
+        a.stall = coarse_stall(nc, nr, step_us);
         a.xch = xch + 8;
         a.xchs = small_exchange_words();
         a.abort_tag = reinterpret_cast<unsigned *>(xch);
@@ -931,6 +994,7 @@ int Ctx::two_grid_multi(const double *A64, long ld, double *K, size_t kcap, cons
         double worst = 0.0;
         int its = 0;
         bool lost = false;
+        double took = 16.0;
         gain = 0.1;
         for (int s = 0; s < nr; ++s) {
             if (hsmall[s].status == kSmallAborted || hsmall[s].aborted) lost = true;
@@ -941,6 +1005,7 @@ int Ctx::two_grid_multi(const double *A64, long ld, double *K, size_t kcap, cons
             if (bn[s] > 0.0) worst = std::max(worst, rn[s] / bn[s]);
             if (rn[s] > 0.0) gain = std::min(gain, 0.1 * o.tol * bn[s] / rn[s]);
             its = std::max(its, hsmall[s].its);
+            if (hsmall[s].its > 0) took = std::min(took, decades(hsmall[s]));
         }
         if (lost) { status = kTwoGridNone; break; }
         st.iters += its;
@@ -957,8 +1022,14 @@ int Ctx::two_grid_multi(const double *A64, long ld, double *K, size_t kcap, cons
                          nr, n, nc, pass, its, worst);
         status = worst <= o.tol ? WWBI_OK : kTwoGridPart;
         if (status == WWBI_OK && worst <= two_grid_target(o.tol)) break;
-        if (pass > 0 && !(worst < kTwoGridGain * prev)) break;
-        if (status == WWBI_OK) {
+        double gain = std::log10((pass == 0 ? 1.0 : prev) / worst);
+        if (status != WWBI_OK) {
+            if (pass == 0) gain = rough ? later_gain(took, nc) : std::min(gain, later_gain(took, nc));
+            if (!pass_pays(gain, std::log10(worst / o.tol), took, its * coarse_step_us(nc, nr),
+                           base_us, -std::log10(o.tol), n, step_us, 1.0))
+                break;
+        } else {
+            if (pass > 0 && !(gain > kTwoGridGain)) break;
             launch_copy(kept, X, (int)(nr * ldv), stream);
             kept_resid = worst;
         }

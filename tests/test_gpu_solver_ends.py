@@ -366,3 +366,47 @@ def test_large_coarse_solves_on_several_streams(ww):
     # one solve alone takes 2 ms, one on the stored matrix 8; four that wait for
     # each other end within four limits of 20 ms
     assert took[-1] <= 0.15
+
+
+def coarse_steps(lines):
+    """The steps of the coarse solves, and whether the stored matrix took part."""
+    its = [int(s.split("its")[1].split()[0]) for s in lines if "two-grid" in s]
+    return its, any("cycle" in s or "refine step" in s for s in lines)
+
+
+# (how it looks to the trace) easy cells end on the coarse grid, with no matrix
+@pytest.mark.parametrize("M", [(1024, 512, 512), (2048, 1024, 1024), (4096, 2048, 2048)])
+@pytest.mark.parametrize("prec", ["fp64", "refined"])
+def test_easy_cells_take_the_two_grid_iteration(ww, ctx, traced, M, prec):
+    geom = thin_cell(0.9, 0.6, M)
+    print(f"case easy n={geom.Mtot} {prec}", flush=True)
+    dg = ww.DeviceGeometry.from_synth(geom, DEV)
+    phi = torch.as_tensor(trig_potential(M[0], [0.1, 0.05], [0.05, 0.02]), device=DEV)
+    rhs = torch.as_tensor(np.random.default_rng(0).standard_normal((16, geom.Mtot)), device=DEV)
+    kw = options(ww, prec, tol=1e-13 if prec == "fp64" else 1e-14)
+    om = ctx.solve_phi(dg, phi, **kw)[1]
+    its, matrix = coarse_steps(traced())
+    assert its and not matrix
+    for call in (lambda: ctx.adjoint_phi(dg, om, phi, **kw), lambda: ctx.solve_phi_multi(dg, rhs, **kw),
+                 lambda: ctx.solve_gamma_t(dg, phi, 0.1 * phi, tau=0.1, **kw)):
+        call()
+        its, matrix = coarse_steps(traced())
+        assert its and not matrix
+
+
+# hard cells: before the passes were weighed against the matrix, 439 and 512
+# steps of coarse solves of 2048 unknowns, the latter for 16 systems in 8 rounds
+@pytest.mark.parametrize("depth", [0.4, 0.2])
+def test_hard_cells_leave_the_two_grid_iteration_soon(ww, ctx, traced, depth):
+    geom = thin_cell(depth, 2.6, (2048, 1024, 1024))
+    print(f"case hard n={geom.Mtot} {depth}", flush=True)
+    dg = ww.DeviceGeometry.from_synth(geom, DEV)
+    phi = torch.as_tensor(trig_potential(2048, [0.1, 0.05], [0.05, 0.02]), device=DEV)
+    rhs = torch.as_tensor(np.random.default_rng(0).standard_normal((16, geom.Mtot)), device=DEV)
+    r = ctx.solve_phi(dg, phi, **options(ww, "refined", tol=1e-14))[3]
+    its, matrix = coarse_steps(traced())
+    assert r.status in (ww.OK, ww.WARN_UNDERRESOLVED) and matrix and sum(its) <= 64
+    for prec in ("fp64", "refined"):
+        ctx.solve_phi_multi(dg, rhs, **options(ww, prec, tol=1e-13))
+        its, _ = coarse_steps(traced())
+        assert not its
