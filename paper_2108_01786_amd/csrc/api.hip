@@ -704,16 +704,10 @@ int Ctx::ensure_coarse(int n, int nsys) {
     return rc;
 }
 
-// Where the passes stop: at 0.2 of the tolerance, at tight tolerances 0.4 (up to
-// 4e-15, a few times the rounding of the residual itself, which a pass more
-// would take to rounding: 2208 unknowns refined to 1e-14 leave 2.4e-15 after one,
-// 399 us with the second pass, 350 us without).  Errors of that solve against 64
-// bits, over those of GMRES on all unknowns to the tolerance itself, on six
-// random right-hand sides: 0.88 to 1.05, geometric mean 0.97.
+// Where the passes stop: below the tolerance, while they gain.  What a coarse grid
+// leaves is smooth, but holds more of the modes that U amplifies than what an
+// Arnoldi cycle leaves.
 constexpr double kTwoGridMargin = 0.2;
-double two_grid_target(double tol) {
-    return std::max(kTwoGridMargin * tol, std::min(2.0 * kTwoGridMargin * tol, 4e-15));
-}
 // A pass that gains less (decades) ends the iteration.  On the coarsest grids
 // one may gain a digit only, where it turns what no coarse node sees into the
 // smooth error that the next removes: at M = 40960 on 1664 nodes 1.3e-12,
@@ -873,12 +867,8 @@ int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, co
         if (trace)
             std::fprintf(stderr, "wwbi: two-grid mode %d n %d coarse %d pass %d its %d rel_resid %.3e\n",
                          mode, n, nc, pass, hsmall->its, st.rel_resid);
-        // what a coarse grid leaves is smooth, but holds more of the modes that U
-        // amplifies than what an Arnoldi cycle leaves: aim below the tolerance
-        // while the passes gain (several decades each, but for the first of a
-        // rough right-hand side)
         status = rn <= o.tol * bn ? WWBI_OK : kTwoGridPart;
-        if (rn <= two_grid_target(o.tol) * bn && status == WWBI_OK) break;
+        if (rn <= kTwoGridMargin * o.tol * bn && status == WWBI_OK) break;
         const bool rough = pass == 0 && rr != b;
         double gain = rough ? 8.0 : std::log10((pass == 0 ? bn : prev) / rn);
         if (status == WWBI_OK) {
@@ -1021,7 +1011,7 @@ int Ctx::two_grid_multi(const double *A64, long ld, double *K, size_t kcap, cons
             std::fprintf(stderr, "wwbi: two-grid %d systems n %d coarse %d pass %d its %d rel_resid %.3e\n",
                          nr, n, nc, pass, its, worst);
         status = worst <= o.tol ? WWBI_OK : kTwoGridPart;
-        if (status == WWBI_OK && worst <= two_grid_target(o.tol)) break;
+        if (status == WWBI_OK && worst <= kTwoGridMargin * o.tol) break;
         double gain = std::log10((pass == 0 ? 1.0 : prev) / worst);
         if (status != WWBI_OK) {
             if (pass == 0) gain = rough ? later_gain(took, nc) : std::min(gain, later_gain(took, nc));

@@ -410,3 +410,15 @@ def test_hard_cells_leave_the_two_grid_iteration_soon(ww, ctx, traced, depth):
         ctx.solve_phi_multi(dg, rhs, **options(ww, prec, tol=1e-13))
         its, _ = coarse_steps(traced())
         assert not its
+
+
+@pytest.mark.parametrize("tol", [1e-13, 1e-14])
+def test_passes_stop_below_the_tolerance(ww, ctx, tol):
+    """At a fifth of it, at any tolerance: the passes gain decades here."""
+    rng = np.random.default_rng(2208)
+    for seed in range(8):
+        geom, phi = cell(1728, 96, (128, 128, 128), rng.uniform(0.25, 0.4), seed)
+        print(f"case margin {tol} seed {seed}", flush=True)
+        dg = ww.DeviceGeometry.from_synth(geom, DEV)
+        r = ctx.solve_phi(dg, torch.as_tensor(phi, device=DEV), **options(ww, "refined", tol=tol))[3]
+        assert r.rel_resid <= 0.2 * tol
