@@ -133,7 +133,10 @@ typedef struct {
     int32_t band;        /* FP32: same-boundary pairs with cyclic |l-m| <= band are
                             evaluated in FP64 and rounded (near-singular kernel)          */
     int32_t flags;       /* WWBI_FLAG_*                                                    */
-    const double *x0;    /* (device) sum(M) warm start for omega, or NULL for zero        */
+    const double *x0;    /* (device) sum(M) warm start for omega, or NULL for zero.  It
+                            excludes the two-grid iteration: above 1024 unknowns a
+                            start that is not within a digit or two of the tolerance
+                            takes several times a cold start                       */
 } wwbi_opts;
 
 #define WWBI_MAX_RESTART 256

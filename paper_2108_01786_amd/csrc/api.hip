@@ -63,7 +63,7 @@ int Ctx::ws_plan(int n, int restart, WsItem *it, bool recycle) {
         D(Urec, capUrec, pre * nn);
         D(Brec, capBrec, pre * (rr + 2));
     }
-    D(part, cappart, 258 * nn + 64);   // up to 256 far slices + the near-band and near-fix slices
+    D(part, cappart, kPartVecs * nn + 64);   // up to 256 far slices + the near-band and near-fix slices
     D(pw, cappw, 65 * (size_t)gemv_partials(nn) + 64);   // 64 dot rows + the norms
     D(hsum, caphsum, 128);
     I(bid, capbid, nn);

@@ -16,7 +16,7 @@ inline long round_up(long a, long b) { return (a + b - 1) / b * b; }
 // Linear operators GMRES can run on.
 enum OpKind {
     OP_A_S64 = 0,   // velocity-potential A, stored FP64
-    OP_A_S32,       // stored FP32 (FP32 accumulation)
+    OP_A_S32,       // stored FP32 (FP64 accumulation)
     OP_A_O64,       // on the fly FP64
     OP_A_O32,       // on the fly FP32 (FP64 band and limits)
     OP_AT_O64,      // transposes on the fly (a stored transpose is assembled as
@@ -25,7 +25,7 @@ enum OpKind {
     OP_W_O64,       // on the fly FP64
     OP_GT_S64,      // gamma_t operator (Sec. 4.2), stored FP64
     OP_GT_O64,      // on the fly FP64
-    OP_GT_S32,      // stored FP32 (FP32 accumulation), inside FP64 refinement
+    OP_GT_S32,      // stored FP32 (FP64 accumulation), inside FP64 refinement
     OP_W_S32,       // wall operator, stored FP32, inside FP64 refinement
 };
 

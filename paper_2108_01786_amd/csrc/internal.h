@@ -129,9 +129,6 @@ struct Bat {
 };
 constexpr Bat kSingle{1, 0, 0, 0, 0, 0, 0};
 
-// circulant row (1/2) cot(pi n / M) of the Hilbert regulariser h (n != 0)
-constexpr int kOpHalfCot = 100;
-
 struct Ctx;   // host context (api.hip)
 
 // ---- kernels_geom.hip --------------------------------------------------------
@@ -198,6 +195,7 @@ void launch_circulant_apply2(const Layout &L, const double *rows, const double *
 void launch_circulant_batched(const Layout &L, const double *rows, const double *f, long fs,
                               double *out, long os, int nv, double alpha0, double alpha,
                               double beta, int first_block, int last_block, hipStream_t st);
+// the row of D or H
 void launch_circ_row1(int M, int op, double *row, hipStream_t st);
 void launch_circ_apply1(int M, const double *row, const double *f, double *out, double alpha,
                         double beta, hipStream_t st);
@@ -432,10 +430,12 @@ int launch_small_gmres(SmallArgs a, int nsys, hipStream_t st);
 // ---- kernels_cells.hip -------------------------------------------------------
 // Far part (all but the same-boundary band) of an on-the-fly FP64 product of a
 // mode, outputs [o0, o0 + no), summed nodes [s0, s0 + ns): cell_slices(no, ns)
-// slices of no values in part; mom: cell_moments_size(N.n) doubles.
+// slices of no values in part; mom: kCellMomentVecs vectors of the nodes, rounded
+// up to whole cells.
 constexpr long kCellPairs = 24000000, kCellPairsH = 36000000;
+constexpr int kCellMomentVecs = 2;
+constexpr int kPartVecs = 258;           // vectors of Ctx::part
 int cell_slices(int no, int ns);
-long cell_moments_size(int n);
 void launch_cell_far(const Nodes &N, const double *hrow, int mode, bool cols, int o0, int no,
                      int s0, int ns, int corr, const double *x, double *part, double *mom,
                      const int *active, hipStream_t st);

@@ -44,6 +44,7 @@ inline int cdiv(long a, long b) { return (int)((a + b - 1) / b); }
 constexpr int kMom = 28;
 constexpr int kRecHead = 8;
 constexpr int kRecE = kRecHead + 2 * kMom, kRecH = kRecE + 2 * kMom;
+static_assert(kRecH <= kCellMomentVecs * kCellNodes, "the records' place behind the slices");
 
 // Modes as of the on-the-fly products: weights w x zeta' / 2 (the source
 // flavours), or w x (the target flavours), or x alone (outputs are sources).
@@ -419,7 +420,7 @@ __global__ __launch_bounds__(64 * kCellWaves, 4) void k_cell_far(
 
 int out_cells(int o0, int no) { return (o0 + no - 1) / kCellNodes - o0 / kCellNodes + 1; }
 
-// Cells of summed nodes per slice: about 1024 blocks, at most 128 slices.
+// Cells of summed nodes per slice: up to about 4096 blocks, at most 128 slices.
 int cell_chunk(int no, int ns) {
     const int oc = cdiv(no, kCellNodes) + 1, sc = cdiv(ns, kCellNodes) + 1;
     const int slices = std::max(1, std::min(128, 4096 / oc));
@@ -443,8 +444,6 @@ int cell_slices(int no, int ns) {
     // the summed range may overlap one more cell than ns / 64
     return cdiv(cdiv(ns, kCellNodes) + 1, cell_chunk(no, ns));
 }
-
-long cell_moments_size(int n) { return (long)cdiv(n, kCellNodes) * kRecH; }
 
 void launch_cell_far(const Nodes &N, const double *hrow, int mode, bool cols, int o0, int no,
                      int s0, int ns, int corr, const double *x, double *part, double *mom,

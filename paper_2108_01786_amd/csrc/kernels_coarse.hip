@@ -398,7 +398,7 @@ __global__ __launch_bounds__(256) void k_norms(const double *r, const double *b,
     if (threadIdx.x == 0) out[blockIdx.y * 64 + blockIdx.x] = ((sh[0] + sh[1]) + sh[2]) + sh[3];
 }
 
-// Coarse nodes per slice: about 1024 blocks, a multiple of the tile (at most
+// Coarse nodes per slice: about 2048 blocks, a multiple of the tile (at most
 // kSmallCoarseMax / kCoarseTile = 128 slices, and up to 9 for the band).
 int product_chunk(int nr, int n) {
     const int c = cdiv(n, std::max(1, cdiv(2048, cdiv(nr, 256))));

@@ -230,7 +230,7 @@ __global__ void k_circ_row1(int M, int op, double *row) {
     if (nn >= M) return;
     double d, h, half;
     circ_entry(nn, M, d, h, half);
-    row[nn] = op == kOpHalfCot ? half : op == WWBI_OP_D ? d : h;
+    row[nn] = op == WWBI_OP_D ? d : h;
 }
 
 // Circulant product on one periodic grid of M points:
@@ -475,6 +475,7 @@ __global__ __launch_bounds__(64 * kSliceWaves) void k_U_finalize(int n0, Nodes N
     U[m] = (u + 0.5 * hg[m] + acc) / N.s[m];
 }
 
+// wall rhs = -(sum of G_0k^dagger gamma_0 partials) - s dphi_mv/dn
 __global__ __launch_bounds__(64 * kSliceWaves) void k_wall_rhs_finalize(int nw,
                                                                         const double *umv_w,
                                                                         const double *part,

@@ -428,8 +428,8 @@ __device__ __forceinline__ bool cells_far(const Nodes &N, int pa, int pb, int qa
     return true;
 }
 
-// FP64 assembly of A.  One column per thread and asm_rows() rows per block, as in the FP32 far pass.  A wave whose live columns lie on one
-// boundary, in a block whose rows lie on one boundary, clear of the
+// FP64 assembly of A.  One column per thread and asm_rows() rows per block, as
+// in the FP32 far pass.  A wave whose live columns lie on one boundary, in a block whose rows lie on one boundary, clear of the
 // same-boundary band and, by the 64-node cells' E discs, of every near pair,
 // takes the E quotient with one entry formula for the whole tile: the source
 // data pre-scaled (a = w dx / 2, b = w dy / 2), the reciprocal of |D|^2 from
@@ -508,14 +508,6 @@ __global__ __launch_bounds__(256) void k_assemble64(Nodes N, int n, int corr, do
 // (k_near_fix), visiting only the listed cells.
 constexpr int kMaxScanCells = 1024;        // cells tested per pass of the full scan
 
-// v of lane jj (the same jj in every lane)
-__device__ __forceinline__ double lane_bcast(double v, int jj) {
-    const unsigned long long u = (unsigned long long)__double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)(u & 0xffffffffu), jj);
-    const int hi = __builtin_amdgcn_readlane((int)(u >> 32), jj);
-    return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-
 // The pair test shared by the list build and the fix: outside the band of
 // `nb` steps (by index: me's boundary starts at mbase, has mM nodes, me is
 // node mloc of it) and inside the near cut.
@@ -550,20 +542,6 @@ __device__ int list_disc_cells(const Nodes &N, const double *d, int c0, int cn, 
         __syncthreads();
     }
     return nl;
-}
-
-// Stage the E values of cell b's nodes in LDS (threads 0..63; clamped to the
-// last node).  Every thread of the block calls it.
-__device__ __forceinline__ void stage_cell(const Nodes &N, int b, double (*se)[kCellNodes]) {
-    __syncthreads();
-    if (threadIdx.x < kCellNodes) {
-        const int q = min(b * kCellNodes + (int)threadIdx.x, N.n - 1);
-        se[0][threadIdx.x] = N.ex[q];
-        se[1][threadIdx.x] = N.ey[q];
-        se[2][threadIdx.x] = N.exl[q];
-        se[3][threadIdx.x] = N.eyl[q];
-    }
-    __syncthreads();
 }
 
 // Half-width of the strip of analyticity, per boundary (the grid rule of the
@@ -743,8 +721,8 @@ __global__ __launch_bounds__(64 * kNearWaves) void k_near_cells(Layout L, Nodes 
                 for (qs &= share; qs; qs &= qs - 1) {
                     const int jj = __builtin_ctzll(qs);
                     mine += near_pair(q0 + jj, mbase, mloc, mM, nb, ex, ey, exl, eyl,
-                                      lane_bcast(qx, jj), lane_bcast(qy, jj), lane_bcast(qxl, jj),
-                                      lane_bcast(qyl, jj)) ? 1 : 0;
+                                      lane_value(qx, jj), lane_value(qy, jj), lane_value(qxl, jj),
+                                      lane_value(qyl, jj)) ? 1 : 0;
                 }
                 if (!live) mine = 0;
             } else {
@@ -752,8 +730,8 @@ __global__ __launch_bounds__(64 * kNearWaves) void k_near_cells(Layout L, Nodes 
                     const int jj = __builtin_ctzll(ps);
                     mine += near_pair(q0 + lane, __builtin_amdgcn_readlane(mbase, jj),
                                       __builtin_amdgcn_readlane(mloc, jj),
-                                      __builtin_amdgcn_readlane(mM, jj), nb, lane_bcast(ex, jj),
-                                      lane_bcast(ey, jj), lane_bcast(exl, jj), lane_bcast(eyl, jj),
+                                      __builtin_amdgcn_readlane(mM, jj), nb, lane_value(ex, jj),
+                                      lane_value(ey, jj), lane_value(exl, jj), lane_value(eyl, jj),
                                       qx, qy, qxl, qyl) ? 1 : 0;
                 }
                 if (!qlive) mine = 0;
@@ -1243,9 +1221,10 @@ static bool use_cells(int mode, int nr, int nc) {
     const bool h = mode == 2 || mode == 4 || mode == 5 || mode == 7;
     return (long)nr * nc >= (h ? kCellPairsH : kCellPairs);
 }
-// the moments' place behind the slices of `part`, which holds 258 vectors
+// the moments' place behind the slices of `part` (at most 128 and two more then)
 static double *cell_moments(const Nodes &N, double *part) {
-    return part + 256L * ((N.n + 63) / 64 * 64);
+    static_assert(kCellNodes == 64 && kPartVecs - kCellMomentVecs >= 130, "room for both");
+    return part + (long)(kPartVecs - kCellMomentVecs) * ((N.n + 63) / 64 * 64);
 }
 
 // Partial slices of an on-the-fly product of modes 2..8: the far chunks, the

@@ -422,3 +422,41 @@ def test_passes_stop_below_the_tolerance(ww, ctx, tol):
         dg = ww.DeviceGeometry.from_synth(geom, DEV)
         r = ctx.solve_phi(dg, torch.as_tensor(phi, device=DEV), **options(ww, "refined", tol=tol))[3]
         assert r.rel_resid <= 0.2 * tol
+
+
+@pytest.mark.parametrize("M", [(384, 256, 256), (2048, 1024, 1024)])
+@pytest.mark.parametrize("prec", ["fp64", "refined"])
+def test_a_reserved_context_allocates_nothing(ww, M, prec):
+    """One-launch and two-grid solves after wwbi_reserve."""
+    geom = thin_cell(0.9, 0.6, M)
+    print(f"case reserved n={geom.Mtot} {prec}", flush=True)
+    dg = ww.DeviceGeometry.from_synth(geom, DEV)
+    phi = torch.as_tensor(trig_potential(M[0], [0.1, 0.05], [0.05, 0.02]), device=DEV)
+    kw = options(ww, prec, tol=1e-13)
+    first, c = ww.Context(0), ww.Context(0)
+    U, om, _, _ = first.solve_phi(dg, phi, **kw)         # torch's own pool
+    del U
+    c.reserve(geom.Mtot, 100, kw["precision"])
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    _, om2, _, r = c.solve_phi(dg, phi, **kw)
+    torch.cuda.synchronize()
+    assert torch.cuda.mem_get_info()[0] >= free
+    assert r.rel_resid <= 1e-13 and torch.equal(om, om2)
+    first.close()
+    c.close()
+
+
+@pytest.mark.parametrize("band", [0, 16, 17, 40])
+def test_moments_and_the_width_of_the_band(ww, ctx, band):
+    """Products of 27 million pairs: through the moments up to the library's own
+    band, pair by pair above it, with the same sums."""
+    geom, phi = cell(3072, 1024, (544, 560), 0.2, 1)
+    print(f"case band {band} n={geom.Mtot}", flush=True)
+    dg = ww.DeviceGeometry.from_synth(geom, DEV)
+    x = torch.as_tensor(np.random.default_rng(0).standard_normal(geom.Mtot), device=DEV)
+    for t in (False, True):
+        y, _ = ctx.matvec(dg, x, mode=ww.MATVEC_ON_THE_FLY, transpose=t, band=band)
+        ref, _ = ctx.matvec(dg, x, mode=ww.MATVEC_STORED, transpose=t)
+        # sums of n rounded terms of about 1/2 in all: n^(1/2) units of rounding
+        assert float((y - ref).abs().max()) <= 80 * 2.0 ** -53 * float(x.abs().max())
