@@ -726,9 +726,9 @@ constexpr int kCoarseIters = 512;        // at most, of one pass
 // Whether the iteration pays.  Its passes cost coarse steps, the stored matrix
 // steps of its own; us of either, fitted to timed solves of 2048 to 16384
 // unknowns and of 16 systems of 2048 to 8192.
-double stored_step_us(int n, bool fp32, int nr) {
+double stored_step_us(int n, bool fp32, bool many) {
     const double bytes = (double)n * n * (fp32 ? 4 : 8);
-    if (nr > 1) return 45.0 + bytes / 4.6e6;
+    if (many) return 45.0 + bytes / 4.6e6;
     return fp32 ? 12.0 + bytes / 4.7e6 : 25.0 + bytes / 5.2e6;
 }
 double coarse_step_us(int nc, int nr) {
@@ -755,9 +755,10 @@ double decades(const SmallRes &r) {
 // After a pass that gained `gain` decades, its coarse solve `took` of them in
 // coarse_us, and base_us the rest of it: whether the passes to gain `left` more
 // cost less than `lenient` times the matrix, assembled and for `anew` decades.
-// Of 432 calls on easy and hard cells of 1100 to 8192 unknowns 1.5 times made 9
-// slower than the matrix alone by more than 2%, 1 time 7 and 2.5 times 17, and the
-// whole least.
+// Of 432 calls on easy and hard cells of 1100 to 8192 unknowns 6 are slower than
+// without the iteration by more than 5% (59 before there was an estimate), and of
+// 1500 random ones 5 slower than with passes that go on while they gain, by at
+// most 25%; stricter (1.0) 5 and 12.
 bool pass_pays(double gain, double left, double took, double coarse_us, double base_us, double anew,
                int n, double step_us, double lenient) {
     const double pass_us = base_us + coarse_us * std::min(1.0, (left + 1.0) / took);
@@ -765,10 +766,13 @@ bool pass_pays(double gain, double left, double took, double coarse_us, double b
     return gain > kTwoGridGain && std::ceil(left / gain) * pass_us <= lenient * matrix_us;
 }
 // What a later pass gains at most, of what the first one's coarse solve took
-// (measured 0.45 to 0.55 where that is one cycle, 0.6 to 1 where it is several):
-// the first pass of a smooth right-hand side itself gains more than any other,
-// and of a rough one less.
-double later_gain(double took, int nc) { return (nc > kSmallMax ? 0.7 : 0.5) * took; }
+// (median 0.6 of smooth right-hand sides and 0.8 of rough ones over 550 passes):
+// the first pass of a smooth one itself gains more than any other, and of a rough
+// one less.
+constexpr double kLaterGain = 0.7;
+// A caller who restarts sooner leaves the matrix's steps no such estimate: then
+// the passes go on while they gain.
+constexpr int kWeighedRestart = 30;
 
 int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, const wwbi_opts &o,
                   bool check_rough, SolveStats &out) {
@@ -786,7 +790,8 @@ int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, co
     launch_coarse_map(C, cmap, cfac, stream);
     launch_assemble_coarse(N, hrow, mode, cmap, cfac, nc, corr, cA, ldc, stream);
     const bool refined = o.precision == WWBI_FP32_REFINED;
-    const double step_us = stored_step_us(n, refined, 1);
+    const double step_us = stored_step_us(n, refined, false);
+    const bool weighed = o.restart >= kWeighedRestart;
     double bn = -1.0, prev = HUGE_VAL;
     const double *rr = b;
     bool have_x = false;
@@ -833,7 +838,7 @@ int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, co
         // replaces; where the LDS holds only a short cycle, several with it
         a.verify = nc > kSmallMax ? 1 : 0;
         a.max_cycles = a.verify ? 16 : 1;
-        a.stall = coarse_stall(nc, 1, step_us);
+        a.stall = weighed ? coarse_stall(nc, 1, step_us) : kCycleStall;
         a.xch = xch + 8;
         a.abort_tag = reinterpret_cast<unsigned *>(xch);
         a.out = dsmall;
@@ -877,10 +882,10 @@ int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, co
             kept_resid = st.rel_resid;
         } else {
             const double took = decades(*hsmall), left = std::log10(st.rel_resid / o.tol);
-            if (pass == 0) gain = std::min(gain, later_gain(took, nc));
+            if (pass == 0) gain = std::min(gain, kLaterGain * took);
             // (the walls' systems take fewer steps a decade)
             if (!pass_pays(gain, left, took, hsmall->its * coarse_step_us(nc, 1), 60.0 + 1.5e-7 * n * n,
-                           left, n, step_us, mode == kCoarseWall ? 1.0 : 1.5))
+                           left, n, step_us, !weighed ? HUGE_VAL : mode == kCoarseWall ? 1.0 : 1.5))
                 break;
         }
         prev = rn;
@@ -911,10 +916,12 @@ int Ctx::two_grid_multi(const double *A64, long ld, double *K, size_t kcap, cons
         grow(mw.part, mw.cpart, (size_t)multi_part_size_rect64(n, nc, nr) + 64))
         return kTwoGridNone;
     // two passes of a few dozen coarse steps against as many of the matrix
-    const double step_us = stored_step_us(n, o.precision == WWBI_FP32_REFINED, nr);
+    const double step_us = stored_step_us(n, o.precision == WWBI_FP32_REFINED, true);
     const double base_us = 100.0 + ((double)n * n + (double)n * nc) * 8.0 / 4.6e6;
     const int likely = nc > kSmallMax ? 30 : std::min(24, small_cycle_steps(nc));
-    if (2.0 * (base_us + likely * coarse_step_us(nc, nr)) > 28.0 * step_us) return kTwoGridNone;
+    const bool weighed = o.restart >= kWeighedRestart;
+    if (weighed && 2.0 * (base_us + likely * coarse_step_us(nc, nr)) > 28.0 * step_us)
+        return kTwoGridNone;
     const int G = gmres_nblocks(n);
     MultiWS &m = mw;
     const Bat bt{nr, 0, 0, ldv, 64, 0, 0};
@@ -964,7 +971,7 @@ int Ctx::two_grid_multi(const double *A64, long ld, double *K, size_t kcap, cons
         a.max_iter = std::min(kCoarseIters, left);
         a.verify = nc > kSmallMax ? 1 : 0;
         a.max_cycles = a.verify ? 16 : 1;
-        a.stall = coarse_stall(nc, nr, step_us);
+        a.stall = weighed ? coarse_stall(nc, nr, step_us) : kCycleStall;
         a.xch = xch + 8;
         a.xchs = small_exchange_words();
         a.abort_tag = reinterpret_cast<unsigned *>(xch);
@@ -1014,9 +1021,9 @@ int Ctx::two_grid_multi(const double *A64, long ld, double *K, size_t kcap, cons
         if (status == WWBI_OK && worst <= kTwoGridMargin * o.tol) break;
         double gain = std::log10((pass == 0 ? 1.0 : prev) / worst);
         if (status != WWBI_OK) {
-            if (pass == 0) gain = rough ? later_gain(took, nc) : std::min(gain, later_gain(took, nc));
+            if (pass == 0) gain = rough ? kLaterGain * took : std::min(gain, kLaterGain * took);
             if (!pass_pays(gain, std::log10(worst / o.tol), took, its * coarse_step_us(nc, nr),
-                           base_us, -std::log10(o.tol), n, step_us, 1.0))
+                           base_us, -std::log10(o.tol), n, step_us, weighed ? 1.2 : HUGE_VAL))
                 break;
         } else {
             if (pass > 0 && !(gain > kTwoGridGain)) break;
