@@ -590,9 +590,9 @@ bool Ctx::take_tags(long need, unsigned &first) {
 // little it is handed on, from the iterate reached, to the multi-kernel loop,
 // whose cycles are as long as asked for: 896 unknowns with an ellipse of half
 // length 2.6 in a layer of 0.2 take 101 steps in cycles of 100 and stagnate in
-// cycles of 19.  A cycle has to gain a decade: 19 steps take about 90 us, and a
-// decade of a system on which they gain less takes 5 to 7 steps of 20 us there.
-constexpr double kCutCycleStall = 0.1, kCycleStall = 0.99;
+// cycles of 19.  A cycle takes about 90 us; there a step takes 20 us, a decade of a
+// system on which cycles gain less than one 5 to 7 steps, and the first step 300 us.
+constexpr float kCutCycleSpare = 3.3f, kCutCycleRate = 1.2f;
 
 int Ctx::launch_small(SmallArgs &a, int nsys) {
     a.give_up = launches++ >= give_up_from;
@@ -625,7 +625,8 @@ bool Ctx::queue_small(const Op &op, const double *b, double *x, bool x_zero, dou
     a.tol = tol;
     a.steps = restart;
     a.max_cycles = INT_MAX;
-    a.stall = cut ? kCutCycleStall : kCycleStall;
+    a.spare = kCutCycleSpare;
+    a.rate = cut ? kCutCycleRate : HUGE_VALF;
     a.verify = 1;
     a.xch = xch + 8;
     a.abort_tag = reinterpret_cast<unsigned *>(xch);
@@ -742,11 +743,9 @@ double coarse_step_us(int nc, int nr) {
 // systems, whose coarse solves run in up to eight rounds, six times (40.4 ms, now
 // 5.0).
 constexpr double kStepsPerDecade = 4.5;
-// The least part of the residual a cycle of a coarse solve may leave: the matrix
-// gains as much in the same time.
-double coarse_stall(int nc, int nr, double step_us) {
-    const double cycle_us = small_cycle_steps(nc) * coarse_step_us(nc, nr);
-    return std::min(kCycleStall, std::pow(10.0, -cycle_us / (kStepsPerDecade * step_us)));
+// Cycles of a coarse solve in which the matrix gains a decade.
+float coarse_rate(int nc, int nr, double step_us) {
+    return (float)(kStepsPerDecade * step_us / (small_cycle_steps(nc) * coarse_step_us(nc, nr)));
 }
 // Decades that a coarse solve took.
 double decades(const SmallRes &r) {
@@ -838,7 +837,7 @@ int Ctx::two_grid(int mode, const Op &op, int k0, const double *b, double *x, co
         // replaces; where the LDS holds only a short cycle, several with it
         a.verify = nc > kSmallMax ? 1 : 0;
         a.max_cycles = a.verify ? 16 : 1;
-        a.stall = weighed ? coarse_stall(nc, 1, step_us) : kCycleStall;
+        a.rate = weighed ? coarse_rate(nc, 1, step_us) : HUGE_VALF;
         a.xch = xch + 8;
         a.abort_tag = reinterpret_cast<unsigned *>(xch);
         a.out = dsmall;
@@ -971,7 +970,7 @@ int Ctx::two_grid_multi(const double *A64, long ld, double *K, size_t kcap, cons
         a.max_iter = std::min(kCoarseIters, left);
         a.verify = nc > kSmallMax ? 1 : 0;
         a.max_cycles = a.verify ? 16 : 1;
-        a.stall = weighed ? coarse_stall(nc, nr, step_us) : kCycleStall;
+        a.rate = weighed ? coarse_rate(nc, nr, step_us) : HUGE_VALF;
         a.xch = xch + 8;
         a.xchs = small_exchange_words();
         a.abort_tag = reinterpret_cast<unsigned *>(xch);

@@ -409,7 +409,9 @@ struct SmallArgs {
     double tol;
     int steps;             // Arnoldi steps per cycle (cut to what the LDS holds)
     int max_iter, max_cycles;
-    double stall;          // a cycle that leaves more of the residual than this ends the solve
+    // The solve ends where the cycles left, at what the last one gained, are more
+    // than spare + rate * (decades left): another solver's cost in cycles
+    float spare, rate;
     int verify;            // 0: one cycle, no true residual
     unsigned long long *xch;   // small_exchange_words() per system, zero at first
     long xchs;

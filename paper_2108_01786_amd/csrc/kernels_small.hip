@@ -351,7 +351,13 @@ __global__ __launch_bounds__(kTS, 2) void k_small_gmres(SmallArgs a) {
         if (!isfinite(beta) || !isfinite(bnorm)) { status = WWBI_STAGNATED; break; }
         if (!(beta > tol_abs)) { status = WWBI_OK; break; }
         if (its >= a.max_iter || cycles >= a.max_cycles) { status = WWBI_NOT_CONVERGED; break; }
-        if (cycles > 0 && beta > a.stall * prev) { status = WWBI_STAGNATED; break; }
+        if (cycles > 0) {
+            const float left = __log10f((float)(beta / tol_abs)), gain = __log10f((float)(prev / beta));
+            if (!(beta <= 0.99 * prev) || left > (a.spare + a.rate * left) * gain) {
+                status = WWBI_STAGNATED;
+                break;
+            }
+        }
         prev = beta;
         __syncthreads();                   // slot 0 has been read by every wave
         store_slot(0, re, 1.0 / beta);

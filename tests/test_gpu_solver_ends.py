@@ -412,6 +412,62 @@ def test_hard_cells_leave_the_two_grid_iteration_soon(ww, ctx, traced, depth):
         assert not its
 
 
+@pytest.mark.parametrize("prec", ["fp64", "refined"])
+def test_one_system_of_a_batch_takes_the_two_grid_iteration(ww, ctx, traced, prec):
+    """The call for many systems, with one."""
+    geom = thin_cell(0.9, 0.6, (1024, 512, 512))
+    print(f"case one of a batch {prec}", flush=True)
+    dg = ww.DeviceGeometry.from_synth(geom, DEV)
+    t = 2 * np.pi * np.arange(geom.Mtot) / geom.Mtot
+    rhs = torch.as_tensor(np.exp(np.sin(t))[None], device=DEV)
+    kw = options(ww, prec, tol=1e-13)
+    x, r = ctx.solve_phi_multi(dg, rhs, **kw)
+    lines = traced()
+    assert r.status == ww.OK and lines and all("two-grid" in s for s in lines)
+    ref, rr = ctx.solve_phi_multi(dg, rhs, **dict(kw, matvec=ww.MATVEC_STORED, precision=ww.FP64, tol=1e-14))
+    assert rr.status == ww.OK
+    assert rel(x.cpu().numpy(), ref.cpu().numpy()) < 1e-12
+
+
+@pytest.mark.parametrize("depth,half", [(0.6, 1.8), (0.4, 2.6)])
+@pytest.mark.parametrize("prec", ["fp64", "refined"])
+@pytest.mark.parametrize("nr", [0, 8])
+def test_short_restarts_keep_the_two_grid_iteration(ww, ctx, traced, depth, half, prec, nr):
+    """Cycles of five steps hardly converge on the matrix: the passes go on."""
+    geom = thin_cell(depth, half, (600, 300, 200))
+    print(f"case short restarts {depth} {prec} {nr}", flush=True)
+    dg = ww.DeviceGeometry.from_synth(geom, DEV)
+    t = 2 * np.pi * np.arange(geom.Mtot) / geom.Mtot
+    rhs = torch.as_tensor(np.stack([np.exp(np.sin(t + j)) for j in range(max(nr, 1))]), device=DEV)
+    phi = torch.as_tensor(trig_potential(600, [0.1, 0.05], [0.05, 0.02]), device=DEV)
+
+    def solve(**kw):
+        if nr:
+            return ctx.solve_phi_multi(dg, rhs, **kw)
+        return ctx.solve_phi(dg, phi, **kw)[1::2]
+
+    kw = options(ww, prec, tol=1e-12, restart=5)
+    x, r = solve(**kw)
+    lines = traced()
+    assert r.status in (ww.OK, ww.WARN_UNDERRESOLVED)
+    assert lines and all("two-grid" in s for s in lines)
+    ref, rr = solve(**options(ww, "fp64", tol=1e-14, matvec=ww.MATVEC_STORED))
+    assert rr.status in (ww.OK, ww.WARN_UNDERRESOLVED)
+    assert rel(x.cpu().numpy(), ref.cpu().numpy()) < 1e-10
+
+
+@pytest.mark.parametrize("depth,half", [(0.4, 2.6)])
+def test_short_cycles_that_gain_are_not_handed_on(ww, ctx, depth, half):
+    """896 unknowns, cycles of 19 that gain just under a decade each: fifteen of
+    them take less than the matrix and its first step."""
+    geom = thin_cell(depth, half)
+    print(f"case cut cycles {depth}", flush=True)
+    dg = ww.DeviceGeometry.from_synth(geom, DEV)
+    phi = torch.as_tensor(trig_potential(384, [0.1, 0.05], [0.05, 0.02]), device=DEV)
+    r = ctx.solve_phi(dg, phi, tol=1e-13)[3]
+    assert r.status in (ww.OK, ww.WARN_UNDERRESOLVED) and r.restarts > 5
+
+
 @pytest.mark.parametrize("tol", [1e-13, 1e-14])
 def test_passes_stop_below_the_tolerance(ww, ctx, tol):
     """At a fifth of it, at any tolerance: the passes gain decades here."""
