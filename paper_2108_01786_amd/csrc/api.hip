@@ -739,9 +739,9 @@ double coarse_step_us(int nc, int nr) {
 // for which this is never close.  On a hard one (a long ellipse in a thin layer,
 // 4 to 7 a decade) a short coarse cycle gains a fraction of a decade, and passes
 // that went on as long as they gained anything took 1.6 times what the matrix
-// takes (4096 unknowns in a layer of 0.4, refined: 4969 us, now 2330), for 16
-// systems, whose coarse solves run in up to eight rounds, six times (40.4 ms, now
-// 5.0).
+// takes (4096 unknowns in a layer of 0.4, refined: 4940 us, now 2350), for 16
+// systems, whose coarse solves run in up to eight rounds, six times (40.3 ms, now
+// 4.5).
 constexpr double kStepsPerDecade = 4.5;
 // Cycles of a coarse solve in which the matrix gains a decade.
 float coarse_rate(int nc, int nr, double step_us) {
@@ -754,7 +754,7 @@ double decades(const SmallRes &r) {
 // After a pass that gained `gain` decades, its coarse solve `took` of them in
 // coarse_us, and base_us the rest of it: whether the passes to gain `left` more
 // cost less than `lenient` times the matrix, assembled and for `anew` decades.
-// Of 432 calls on easy and hard cells of 1100 to 8192 unknowns 6 are slower than
+// Of 432 calls on easy and hard cells of 1100 to 8192 unknowns 7 are slower than
 // without the iteration by more than 5% (59 before there was an estimate), and of
 // 1500 random ones 5 slower than with passes that go on while they gain, by at
 // most 25%; stricter (1.0) 5 and 12.

@@ -4,6 +4,7 @@
 // Stored matrices are row-major with a leading dimension padded to a multiple
 // of 64 elements; padding columns hold zeros.  Every product that can be
 // skipped after GMRES convergence takes `active` (device flag, may be null).
+#include "entries.h"
 #include "internal.h"
 
 namespace wwbi {
@@ -139,8 +140,10 @@ __global__ __launch_bounds__(64 * WPB) void k_gemv(const TA *__restrict__ A, lon
             if (lane == 0 && r0 + r < n) y[r0 + r] = c ? c[r0 + r] - v : v;
         } else if (r0 + r < n) {
             // the fused step is an Arnoldi product: y = A x - shift x (no c),
-            // x = V_j, whose row lane j holds
-            const double u = v - d.shift * __shfl(vr[r], d.j, 64);
+            // x = V_j, whose row lane j holds (a readlane: a shuffle made it 112
+            // registers of 86, four waves of five and 5% of the kernel; FP64
+            // products have no shift)
+            const double u = sizeof(TA) == 4 ? v - d.shift * lane_value(vr[r], d.j) : v;
             if (lane == 0) y[r0 + r] = u;
             pd += vr[r] * u;
             nn += u * u;
